@@ -44,6 +44,7 @@
 #include <vector>
 
 #include "nnqp_internal.hpp"
+#include "rows.hpp"
 
 // 1: chunks of global steps replayed as captured graphs; 0: launched one by one
 #ifndef NNQP_BATCH_GRAPH
@@ -152,6 +153,12 @@ __device__ __forceinline__ double bcomb(int op, double a, double b)
     return op == OP_SUM ? a + b : (op == OP_MIN ? fmin(a, b) : fmax(a, b));
 }
 
+// combination of one value over the wavefront (every lane active)
+__device__ __forceinline__ double bwave(int op, double a)
+{
+    return op == OP_SUM ? wave_sum(a) : (op == OP_MIN ? wave_min(a) : wave_max(a));
+}
+
 __device__ __forceinline__ double bident(int op)
 {
     return op == OP_SUM ? 0.0 : (op == OP_MIN ? INFINITY : -INFINITY);
@@ -187,9 +194,7 @@ __device__ __forceinline__ void for_bslices(const BDev &B, const int (&ops)[NV],
             body(p, s, s * kSlice + lane, il, il < B.nrow[p], a);
         }
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1)
-#pragma unroll
-            for (int k = 0; k < NV; k++) a[k] = bcomb(ops[k], a[k], __shfl_xor(a[k], o, 64));
+        for (int k = 0; k < NV; k++) a[k] = bwave(ops[k], a[k]);
         if (lane == 0)
 #pragma unroll
             for (int k = 0; k < NV; k++) B.part[(size_t)s * kBNV + k] = a[k];
@@ -744,9 +749,7 @@ __device__ __forceinline__ bool member_reduce(const BDev &B, int p, const int (&
 #pragma unroll
         for (int k = 0; k < NV; k++) a[k] = bcomb(ops[k], a[k], B.part[(size_t)s * kBNV + k]);
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
-#pragma unroll
-        for (int k = 0; k < NV; k++) a[k] = bcomb(ops[k], a[k], __shfl_xor(a[k], o, 64));
+    for (int k = 0; k < NV; k++) a[k] = bwave(ops[k], a[k]);
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (lane == 0)
 #pragma unroll
@@ -905,22 +908,15 @@ __global__ void kb_rows(BDev B, const VT *__restrict__ gvals, BVec<VV> V)
         // wave combination (the phase is uniform in the wave): only the
         // values the phase reports
         const int nv = ph == PH_GRAD ? 5 : (ph == PH_CG ? 1 : 3);
-        if (nv == 1) {
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) a[0] += __shfl_xor(a[0], o, 64);
-        } else if (nv == 3) {
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1)
-#pragma unroll
-                for (int v = 0; v < 3; v++) a[v] += __shfl_xor(a[v], o, 64);
-        } else {
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) {
-                a[0] += __shfl_xor(a[0], o, 64);
-                a[1] += __shfl_xor(a[1], o, 64);
-                a[2] = fmax(a[2], __shfl_xor(a[2], o, 64));
-                a[3] = fmin(a[3], __shfl_xor(a[3], o, 64));
-                a[4] += __shfl_xor(a[4], o, 64);
+        a[0] = wave_sum(a[0]);
+        if (nv >= 3) {
+            a[1] = wave_sum(a[1]);
+            if (nv == 3) {
+                a[2] = wave_sum(a[2]);
+            } else {
+                a[2] = wave_max(a[2]);
+                a[3] = wave_min(a[3]);
+                a[4] = wave_sum(a[4]);
             }
         }
         if (lane == 0)
@@ -1171,13 +1167,12 @@ __global__ void kb_vec(BDev B, BVec<VV> V)
             if (row) c[i] = projb(B, c[i] + S.ts * (double)V.w[i]);
             continue;
         }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-#pragma unroll
-            for (int v = 0; v < 4; v++) {
-                const double other = __shfl_xor(a[v], o, 64);
-                a[v] = (vop == VO_BREAK && v == 0) ? fmin(a[v], other) : a[v] + other;
-            }
+        // (an update reports two values, a breakpoint three)
+        a[0] = vop == VO_BREAK ? wave_min(a[0]) : wave_sum(a[0]);
+        a[1] = wave_sum(a[1]);
+        if (vop != VO_UPDATE) {
+            a[2] = wave_sum(a[2]);
+            a[3] = wave_sum(a[3]);
         }
         if (lane == 0)
 #pragma unroll

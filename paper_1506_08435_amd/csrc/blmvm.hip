@@ -85,9 +85,7 @@ __device__ __forceinline__ void block_sums(double (&a)[NV], double *part)
     __shared__ double sh[kWaves][NV];
     const int lane = threadIdx.x & 63, wid = wave_id();
 #pragma unroll
-    for (int k = 0; k < NV; k++)
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) a[k] += __shfl_xor(a[k], o, 64);
+    for (int k = 0; k < NV; k++) a[k] = wave_sum(a[k]);
     if (lane == 0)
 #pragma unroll
         for (int k = 0; k < NV; k++) sh[wid][k] = a[k];
@@ -198,8 +196,7 @@ __global__ __launch_bounds__(64) void kl_coef(int nb, LmState *st, const double 
         }
 #pragma unroll
         for (int k = 0; k < NV; k++) {
-            double v = acc[k];
-            for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+            const double v = wave_sum(acc[k]);
             if (lane == 0) t[k] = v;
         }
     }
@@ -295,12 +292,10 @@ __global__ __launch_bounds__(64) void kl_summary(int nb, LmState *st, double *pa
         gs += h[b];
         sks += h[kMaxBlocks + b];
     }
-    for (int o = 32; o >= 1; o >>= 1) {
-        bm = fmin(bm, __shfl_xor(bm, o, 64));
-        gd += __shfl_xor(gd, o, 64);
-        gs += __shfl_xor(gs, o, 64);
-        sks += __shfl_xor(sks, o, 64);
-    }
+    bm = wave_min(bm);
+    gd = wave_sum(gd);
+    gs = wave_sum(gs);
+    sks = wave_sum(sks);
     if (threadIdx.x == 0) {
         st->bmin = bm;
         st->gd = gd;

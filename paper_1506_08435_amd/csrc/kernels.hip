@@ -314,22 +314,26 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(Part P, const int *__restric
                                                     int max_it, double rtol2)
 {
     if (S->done) return;
-    double u[4];
-    combine_partials<kOpsU, 4>(slot_ptr(partials, (j & 1) ? SLOT_U1 : SLOT_U0), P.nb, u);
+    // r.z and r.r; the set-up's face counts only before the first iteration
+    // (four values at once hold 66 VGPRs, seven waves per SIMD)
+    const double *slot = slot_ptr(partials, (j & 1) ? SLOT_U1 : SLOT_U0);
+    double u[2], cnt[2] = {0.0, 0.0};
+    combine_partials<0u, 2>(slot, P.nb, u);
+    if (j == 0) combine_partials<0u, 2>(slot + 2 * kMaxBlocks, P.nb, cnt);
     const double rz = u[0], rr2 = u[1];
     const double rr_stop = j == 0 ? rtol2 * rr2 : S->rr_stop;
     int done = 0;
     if (TR && j > 0 && S->tr_hit) done = 2;
     else if (!isfinite(rz) || !isfinite(rr2)) done = 4;
-    else if ((j == 0 && (rr2 == 0.0 || u[2] == 0.0)) || (j > 0 && rr2 <= rr_stop) ||
+    else if ((j == 0 && (rr2 == 0.0 || cnt[0] == 0.0)) || (j > 0 && rr2 <= rr_stop) ||
              j >= max_it || !(rz > 0.0))
         done = 1;
     const double beta = j == 0 ? 0.0 : rz / S->rzh[(j - 1) & 1];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (j == 0) {
             S->rr_stop = rr_stop;
-            S->n_free = u[2];
-            S->nnz_free = u[3];
+            S->n_free = cnt[0];
+            S->nnz_free = cnt[1];
         }
         S->rzh[j & 1] = rz;
         if (done) {

@@ -11,6 +11,13 @@
 
 namespace nnqp {
 
+// Index of the calling wavefront in its block.  It is uniform in the
+// wavefront; readfirstlane states that to the compiler, so the slice index,
+// the slice offsets and width and the loop bounds derived from it live in
+// scalar registers (the row passes of the batched solver dropped from 54 to
+// 43 VGPRs with it).
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
 // ---------------------------------------------------------------- reductions
 template <uint32_t OPS>
 __device__ __forceinline__ constexpr int op_of(int k)
@@ -38,39 +45,74 @@ __device__ __forceinline__ void red_init(double (&a)[NV])
     }
 }
 
+// A value of the lanes l ^ O moved to lane l, O = 8, 4, 2, 1, and the pair a
+// lane forms with lane l ^ 32 or l ^ 16, without LDS.  The butterfly of
+// __shfl_xor is two ds_bpermute_b32 per double and level, twelve LDS trips of
+// latency in a row; the lane swaps of gfx950 (v_permlane32_swap,
+// v_permlane16_swap) and the row rotations and quad permutations of DPP do
+// the same exchange in the vector pipeline.  After the level O = 8 every
+// 16-lane row holds its sums with period 8, so a rotation by 4 brings lane
+// l ^ 4 (or a lane that holds the same bits).
+template <int O>
+__device__ __forceinline__ int dpp_xor(int x)
+{
+    static_assert(O == 8 || O == 4 || O == 2 || O == 1, "exchange within a 16-lane row");
+    constexpr int ctrl = O == 8 ? 0x128 : (O == 4 ? 0x124 : (O == 2 ? 0x4e : 0xb1));
+    return __builtin_amdgcn_mov_dpp(x, ctrl, 0xf, 0xf, false);
+}
+
+template <int O, class F>
+__device__ __forceinline__ double wave_level(double a, F comb)
+{
+    const int lo = __double2loint(a), hi = __double2hiint(a);
+    if constexpr (O == 32 || O == 16) {
+        if constexpr (O == 32) {
+            const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+            const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+            return comb(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+        } else {
+            const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+            const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+            return comb(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+        }
+    } else {
+        return comb(a, __hiloint2double(dpp_xor<O>(hi), dpp_xor<O>(lo)));
+    }
+}
+
+// Combination over the wavefront (levels 32, 16, 8, 4, 2, 1), the same bits
+// in every lane; every lane must be active.
+template <class F>
+__device__ __forceinline__ double wave_all(double a, F comb)
+{
+    a = wave_level<32>(a, comb);
+    a = wave_level<16>(a, comb);
+    a = wave_level<8>(a, comb);
+    a = wave_level<4>(a, comb);
+    a = wave_level<2>(a, comb);
+    return wave_level<1>(a, comb);
+}
+__device__ __forceinline__ double wave_sum(double a)
+{
+    return wave_all(a, [](double x, double y) { return x + y; });
+}
+__device__ __forceinline__ double wave_min(double a)
+{
+    return wave_all(a, [](double x, double y) { return fmin(x, y); });
+}
+__device__ __forceinline__ double wave_max(double a)
+{
+    return wave_all(a, [](double x, double y) { return fmax(x, y); });
+}
+
 template <uint32_t OPS, int NV>
 __device__ __forceinline__ void wave_red(double (&a)[NV])
 {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1)
-#pragma unroll
-        for (int k = 0; k < NV; k++) a[k] = red_comb(op_of<OPS>(k), a[k], __shfl_xor(a[k], o, 64));
-}
-
-// Block-wide combination (waves in order) of a[]; every thread gets the block
-// total.  Thread k combines value k across the waves, so the combine costs a
-// handful of registers instead of one per wave and value.
-template <uint32_t OPS, int NV>
-__device__ __forceinline__ void block_red(double (&a)[NV], double (*sh)[NV + 1])
-{
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    wave_red<OPS, NV>(a);
-    __syncthreads();
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < NV; k++) sh[wid][k] = a[k];
-    __syncthreads();
-    if (threadIdx.x < NV) {
-        const int k = threadIdx.x;
-        const int op = (int)((OPS >> (2 * k)) & 3u);
-        double v = sh[0][k];
-#pragma nounroll
-        for (int w = 1; w < kWaves; w++) v = red_comb(op, v, sh[w][k]);
-        sh[kWaves][k] = v;
+    for (int k = 0; k < NV; k++) {
+        const int op = op_of<OPS>(k);
+        a[k] = op == OP_SUM ? wave_sum(a[k]) : (op == OP_MIN ? wave_min(a[k]) : wave_max(a[k]));
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NV; k++) a[k] = sh[kWaves][k];
 }
 
 __host__ __device__ __forceinline__ double *slot_ptr(double *partials, int s)
@@ -78,36 +120,73 @@ __host__ __device__ __forceinline__ double *slot_ptr(double *partials, int s)
     return partials + (size_t)s * kMaxRed * kMaxBlocks;
 }
 
+// v[0], v[1], ..., v[N - 1] of the lanes' values combined in lane order (the
+// same bits in every lane): lane reads through scalar registers, so the chain
+// holds no vector registers beyond its sum.
+template <int N>
+__device__ __forceinline__ double lanes_in_order(int op, double x)
+{
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    double v = __hiloint2double(__builtin_amdgcn_readlane(hi, 0), __builtin_amdgcn_readlane(lo, 0));
+#pragma unroll
+    for (int w = 1; w < N; w++)
+        v = red_comb(op, v, __hiloint2double(__builtin_amdgcn_readlane(hi, w),
+                                             __builtin_amdgcn_readlane(lo, w)));
+    return v;
+}
+
 // Store this block's total of a[] as its partial: slot[k * kMaxBlocks + block].
+// The wavefronts' totals meet in LDS once (one barrier); the first wavefront
+// reads them one per lane and combines them in wavefront order.
 template <uint32_t OPS, int NV>
 __device__ __forceinline__ void block_partial(double (&a)[NV], double *slot)
 {
-    __shared__ double sh[kWaves + 1][NV + 1];
-    block_red<OPS, NV>(a, sh);
-    if (threadIdx.x == 0)
+    __shared__ double sh[NV][kWaves];
+    const int lane = threadIdx.x & 63, wid = wave_id();
+    wave_red<OPS, NV>(a);
+    if (lane == 0)
 #pragma unroll
-        for (int k = 0; k < NV; k++) slot[k * kMaxBlocks + blockIdx.x] = a[k];
+        for (int k = 0; k < NV; k++) sh[k][wid] = a[k];
+    __syncthreads();
+    if (wid == 0) {
+#pragma unroll
+        for (int k = 0; k < NV; k++) {
+            const double v = lanes_in_order<kWaves>(op_of<OPS>(k), sh[k][lane & (kWaves - 1)]);
+            if (lane == 0) slot[k * kMaxBlocks + blockIdx.x] = v;
+        }
+    }
 }
 
 // Combine the partials of `nb` blocks left in `slot` by the previous kernel:
 // every block runs the same fixed-order combination and gets the same bits.
+// Wavefront w combines the partials 64 w .. 64 w + 63, and every thread adds
+// the wavefronts' values in order: one barrier, and only the first
+// kMaxBlocks / 64 wavefronts hold partials.
+constexpr int kPartWaves = kMaxBlocks / 64;
+static_assert(kMaxBlocks % 64 == 0 && kPartWaves <= kWaves, "one partial per thread");
+
 template <uint32_t OPS, int NV>
 __device__ __forceinline__ void combine_partials(const double *slot, int nb, double (&a)[NV])
 {
-    __shared__ double sh[kWaves + 1][NV + 1];
+    __shared__ double sh[NV][kPartWaves];
+    __syncthreads();   // a second combination reuses sh
     red_init<OPS, NV>(a);
-    for (int b = threadIdx.x; b < nb; b += kBlock)
+    const int b = threadIdx.x;
+    if (b < nb)
 #pragma unroll
         for (int k = 0; k < NV; k++) a[k] = red_comb(op_of<OPS>(k), a[k], slot[k * kMaxBlocks + b]);
-    block_red<OPS, NV>(a, sh);
+    const int lane = threadIdx.x & 63, wid = wave_id();
+    if (wid < kPartWaves) {
+        wave_red<OPS, NV>(a);
+        if (lane == 0)
+#pragma unroll
+            for (int k = 0; k < NV; k++) sh[k][wid] = a[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NV; k++)
+        a[k] = lanes_in_order<kPartWaves>(op_of<OPS>(k), sh[k][lane & (kPartWaves - 1)]);
 }
-
-// Index of the calling wavefront in its block.  It is uniform in the
-// wavefront; readfirstlane states that to the compiler, so the slice index,
-// the slice offsets and width and the loop bounds derived from it live in
-// scalar registers (the row passes of the batched solver dropped from 54 to
-// 43 VGPRs with it).
-__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // ---------------------------------------------------------------- slice walkers
 // Calls body(i, act) for the row i = 64 s + lane of every slice s this
