@@ -189,60 +189,100 @@ void prof_collect(nn_ctx *ctx)
 
 namespace nnqp {
 
-// Copies of K that the single-problem passes read: with f64, the paired
-// int16 offsets and float64 values; when the float32 values exist, the quad
-// int16 offsets and float32 values.
+// Copies of K that the single-problem passes read.  Where the pattern has a
+// diagonal layout (diag.hip) they hold its arrays; else, when the int16
+// offsets exist, float64 values in pairs and float32 values in quads.
 #ifndef NNQP_PAIR_F64
 #define NNQP_PAIR_F64 1   // float64 solves read the paired layout when it exists
 #endif
 
-// The paired int16 offsets (nn_matrix::d16p) that every float64 paired copy
-// is read with.
-static nn_status ensure_d16p(nn_ctx *ctx, nn_matrix *K)
+// The index copy of one precision (d16p for float64, d16q for float32): the
+// diagonal layout's tables, or the paired or quad int16 offsets; none when the
+// pattern has neither.
+static nn_status ensure_index(nn_ctx *ctx, nn_matrix *K, bool f32)
 {
-    if (K->d16p || !K->sl_d16 || K->n == 0) return NN_OK;
+    short *&idx = f32 ? K->d16q : K->d16p;
+    bool &ready = f32 ? K->d16q_ready : K->d16p_ready;
+    if (ready || K->n == 0) return NN_OK;
+    if (K->diag_tried && !K->diag_plan && !K->sl_d16) return NN_OK;
     const size_t m = (size_t)std::max<int64_t>(K->nsell, 1);
-    if (dev_malloc(K->al, &K->d16p, sizeof(short) * m) != hipSuccess)
-        return fail(ctx, NN_EOOM, "paired offsets allocation");
-    launch_pair_d16(ctx, K, K->sl_d16, K->d16p);
+    if (!idx && dev_malloc(K->al, &idx, sizeof(short) * m) != hipSuccess)
+        return fail(ctx, NN_EOOM, "index copy allocation");
+    nn_status st = diag_find(ctx, K, idx);
+    if (st != NN_OK) return st;
+    if (K->diag_plan) {
+        if ((st = diag_upload(ctx, K, idx)) != NN_OK) return st;
+    } else if (K->sl_d16) {
+        if (f32) launch_quad_d16(ctx, K, K->sl_d16, idx);
+        else launch_pair_d16(ctx, K, K->sl_d16, idx);
+    } else {
+        dev_free(K->al, idx);
+        idx = nullptr;
+        return NN_OK;
+    }
+    NN_HIP_TRY(ctx, hipGetLastError());
+    ready = true;
+    return NN_OK;
+}
+
+// src in the layout of the index copy
+static nn_status fill_copy(nn_ctx *ctx, nn_matrix *K, const double *src, double *dst)
+{
+    if (K->diag_plan) return diag_fill(ctx, K, K->d16p, src, dst);
+    launch_pair_f64(ctx, K, src, dst);
+    return NN_OK;
+}
+static nn_status fill_copy(nn_ctx *ctx, nn_matrix *K, const float *src, float *dst)
+{
+    if (K->diag_plan) return diag_fill(ctx, K, K->d16q, src, dst);
+    launch_quad_f32(ctx, K, src, dst);
     return NN_OK;
 }
 
 nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64)
 {
-    if (!K->sl_d16 || K->n == 0) return NN_OK;
+    if (K->n == 0) return NN_OK;
     const size_t m = (size_t)std::max<int64_t>(K->nsell, 1);
-    if (f64 && ensure_d16p(ctx, K) != NN_OK) return NN_EOOM;
+    nn_status st = NN_OK;
     if (K->val32 && !K->val32q) {
-        if (!K->d16q) {
-            if (dev_malloc(K->al, &K->d16q, sizeof(short) * m) != hipSuccess)
-                return fail(ctx, NN_EOOM, "quad offsets allocation");
-            launch_quad_d16(ctx, K, K->sl_d16, K->d16q);
+        if ((st = ensure_index(ctx, K, true)) != NN_OK) return st;
+        if (K->d16q) {
+            float *v = nullptr;
+            if (dev_malloc(K->al, &v, sizeof(float) * m) != hipSuccess)
+                return fail(ctx, NN_EOOM, "float32 copy allocation");
+            K->val32q = v;
+            if ((st = fill_copy(ctx, K, K->val32, v)) != NN_OK) return st;
         }
-        if (dev_malloc(K->al, &K->val32q, sizeof(float) * m) != hipSuccess)
-            return fail(ctx, NN_EOOM, "quad float32 allocation");
-        launch_quad_f32(ctx, K, K->val32, K->val32q);
     }
     if (f64 && !K->val64p) {
-        if (dev_malloc(K->al, &K->val64p, sizeof(double) * m) != hipSuccess)
-            return fail(ctx, NN_EOOM, "paired float64 allocation");
-        launch_pair_f64(ctx, K, K->val, K->val64p);
+        if ((st = ensure_index(ctx, K, false)) != NN_OK) return st;
+        if (K->d16p) {
+            double *v = nullptr;
+            if (dev_malloc(K->al, &v, sizeof(double) * m) != hipSuccess)
+                return fail(ctx, NN_EOOM, "float64 copy allocation");
+            K->val64p = v;
+            if ((st = fill_copy(ctx, K, K->val, v)) != NN_OK) return st;
+        }
     }
     NN_HIP_TRY(ctx, hipGetLastError());
     return NN_OK;
 }
 
 // M/dt + K values for a backward-Euler step (formed once per dt, kept with K).
-// `paired`: the single-problem solver will read the paired copy for this
-// precision (the batched solver reads the column-major values only).  Every
-// copy that exists is re-formed when dt changes.
+// `paired`: the single-problem solver will read the copy for this precision
+// (the batched solver reads the column-major values only).  Every copy that
+// exists is re-formed when dt changes.
 nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, bool paired)
 {
     const int64_t n = K->n;
     if (n == 0) return NN_OK;
     const size_t m = (size_t)std::max<int64_t>(K->nsell, 1);
-    const bool want32q = paired && mixed && K->sl_d16;
-    const bool want64p = paired && !mixed && NNQP_PAIR_F64 && K->sl_d16;
+    bool want32q = paired && mixed;
+    bool want64p = paired && !mixed && NNQP_PAIR_F64;
+    nn_status st = NN_OK;
+    if ((want32q || want64p) && (st = ensure_index(ctx, K, mixed)) != NN_OK) return st;
+    want32q = want32q && K->d16q;
+    want64p = want64p && K->d16p;
     const bool fresh = K->kt && K->kt_dt == dt;
     if (fresh && (!mixed || K->kt32) && (!want32q || K->kt32q) && (!want64p || K->kt64p))
         return NN_OK;
@@ -255,21 +295,15 @@ nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, boo
         return fail(ctx, NN_EOOM, "transient diagonal allocation");
     if (mixed && !K->kt32 && dev_malloc(K->al, &K->kt32, sizeof(float) * m) != hipSuccess)
         return fail(ctx, NN_EOOM, "transient float32 allocation");
-    if (want64p && ensure_d16p(ctx, K) != NN_OK) return NN_EOOM;
-    if (want32q && !K->d16q) {
-        if (dev_malloc(K->al, &K->d16q, sizeof(short) * m) != hipSuccess)
-            return fail(ctx, NN_EOOM, "quad offsets allocation");
-        launch_quad_d16(ctx, K, K->sl_d16, K->d16q);
-    }
     if (want32q && !K->kt32q && dev_malloc(K->al, &K->kt32q, sizeof(float) * m) != hipSuccess)
         return fail(ctx, NN_EOOM, "transient float32 allocation");
     if (want64p && !K->kt64p && dev_malloc(K->al, &K->kt64p, sizeof(double) * m) != hipSuccess)
-        return fail(ctx, NN_EOOM, "transient paired float64 allocation");
+        return fail(ctx, NN_EOOM, "transient float64 copy allocation");
     launch_axpby_vals(ctx, K->nsell, K->mval, dt, K->val, K->kt);
     launch_diag(ctx, K, K->kt, K->kt_diag);
     if (K->kt32) launch_to_f32(ctx, K->nsell, K->kt, K->kt32);
-    if (K->kt32 && K->kt32q) launch_quad_f32(ctx, K, K->kt32, K->kt32q);
-    if (K->kt64p) launch_pair_f64(ctx, K, K->kt, K->kt64p);
+    if (K->kt32 && K->kt32q && (st = fill_copy(ctx, K, K->kt32, K->kt32q)) != NN_OK) return st;
+    if (K->kt64p && (st = fill_copy(ctx, K, K->kt, K->kt64p)) != NN_OK) return st;
     NN_HIP_TRY(ctx, hipGetLastError());
     K->kt_dt = dt;
     return NN_OK;
@@ -606,6 +640,7 @@ void nn_matrix_free(nn_ctx *ctx, nn_matrix *A)
     float *fv[] = {A->val32, A->kt32, A->val32q, A->kt32q};
     for (float *p : fv)
         dev_free(A->al, p);
+    diag_free(A);
     delete A;
 }
 
@@ -643,8 +678,10 @@ nn_status nn_solve_nonneg(nn_ctx *ctx, nn_matrix *K, const double *f_dev,
     if (!K || (K->n > 0 && (!f_dev || !c_dev))) return fail(ctx, NN_EINVAL, "null argument");
     nn_status st = check_opts(ctx, opts);
     if (st != NN_OK) return st;
-    if (opts->method == NN_BLMVM)
-        return blmvm_impl(ctx, K, K->val, f_dev, opts, c_dev, active_dev, stats);
+    if (opts->method == NN_BLMVM) {
+        if ((st = ensure_paired(ctx, K, true)) != NN_OK) return st;
+        return blmvm_impl(ctx, K, K->val, K->val64p, f_dev, opts, c_dev, active_dev, stats);
+    }
     if ((st = choose_solo(ctx, K, opts)) == NN_OK)
         return solo_solve_impl(ctx, K, K->val, K->diag, f_dev, opts, c_dev, active_dev, stats);
     if (st != NN_EMAXIT) return st;   // (NN_EMAXIT: the multi-block passes)
@@ -658,7 +695,7 @@ nn_status nn_solve_nonneg(nn_ctx *ctx, nn_matrix *K, const double *f_dev,
         }
         v32 = K->val32;
     }
-    // paired copies for the CG and search passes (when the int16 offsets exist)
+    // the copies the CG and search passes read
     const bool pair64 = NNQP_PAIR_F64 && v32 == nullptr;
     if ((v32 || pair64) && (st = ensure_paired(ctx, K, pair64)) != NN_OK) return st;
     return solve_impl(ctx, K, K->val, v32, v32 ? K->val32q : nullptr, v32 ? nullptr : K->val64p,
@@ -674,6 +711,7 @@ nn_status nn_solve_galerkin(nn_ctx *ctx, nn_matrix *K, const double *f_dev, cons
     if (st != NN_OK) return st;
     if (opts->precision != NN_FP64)
         return fail(ctx, NN_EINVAL, "the Galerkin solve runs in float64 only");
+    if ((st = ensure_paired(ctx, K, true)) != NN_OK) return st;
     return galerkin_impl(ctx, K, f_dev, opts, c_dev, stats);
 }
 
@@ -696,7 +734,7 @@ nn_status nn_step_transient(nn_ctx *ctx, nn_matrix *K, double dt, const double *
     launch_transient_rhs(ctx, K, c_dev, f_dev, dt, ctx->ws.ft);
     nn_opts o = *opts;
     o.c0_mode = 1;   // warm start from c^(n)
-    if (o.method == NN_BLMVM) return blmvm_impl(ctx, K, K->kt, ctx->ws.ft, &o, c_dev, active_dev, stats);
+    if (o.method == NN_BLMVM) return blmvm_impl(ctx, K, K->kt, K->kt64p, ctx->ws.ft, &o, c_dev, active_dev, stats);
     if ((st = choose_solo(ctx, K, &o)) == NN_OK)
         return solo_solve_impl(ctx, K, K->kt, K->kt_diag, ctx->ws.ft, &o, c_dev, active_dev, stats);
     if (st != NN_EMAXIT) return st;

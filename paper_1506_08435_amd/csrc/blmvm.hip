@@ -39,7 +39,7 @@
 #include <cstring>
 
 #include "nnqp_internal.hpp"
-#include "rows.hpp"
+#include "diag.hpp"
 
 namespace nnqp {
 
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(kBlock) void kl_dir(Part P, const double *__restric
 // 4. trial: gathers c(t) = P(c + t d), writes gn = K c(t) - f; g.s, s.(gn - g), s.s
 // with s = c(t) - c
 template <int WMAX, class Cols>
-__global__ __launch_bounds__(kBlock) void kl_trial(Part P, const int *__restrict__ so, Cols cols,
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void kl_trial(Part P, const int *__restrict__ so, Cols cols,
                                                    const double *__restrict__ v,
                                                    const double *__restrict__ c,
                                                    const double *__restrict__ d, double t,
@@ -370,12 +370,12 @@ __global__ __launch_bounds__(kBlock) void kl_trial(Part P, const int *__restrict
                                                    double *__restrict__ gn, Box B,
                                                    double *partials)
 {
-    auto ct = [&](int j) { return proj_box(c[j] + t * d[j], B); };
+    auto ct = [&](int ub, int l) { return proj_box((c + ub)[l] + t * (d + ub)[l], B); };
     constexpr uint32_t kOps = OPS3(OP_SUM, OP_SUM, OP_SUM);
     double a[3];
     red_init<kOps, 3>(a);
-    sell_rows<WMAX>(P, so, cols, v, AllRows(),
-                    [&](int i) { return Three{ct(i) - c[i], f[i], g[i]}; }, ct,
+    walk_rows<WMAX, 5>(P, so, cols, v, AllRows(),
+                    [&](int i) { return Three{ct(0, i) - c[i], f[i], g[i]}; }, ct,
                     [&](int i, double kc, Three x) {
                         const double gni = kc - x.b;
                         gn[i] = gni;
@@ -492,8 +492,8 @@ void lm_release(nn_ctx *ctx)
     L = LmWork();
 }
 
-nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const double *f,
-                     const nn_opts *o, double *c, uint8_t *active, nn_stats *st)
+nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const double *vals64p,
+                     const double *f, const nn_opts *o, double *c, uint8_t *active, nn_stats *st)
 {
     const int64_t n = A->n;
     nn_stats S;
@@ -525,8 +525,10 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
     LmState &H = *(LmState *)L.h_state;
     const Part P = make_part(n);
     const double nd = (double)n, nnz = (double)A->nnz;
-    const double b_grad = 4.0 * (nd + 1) + 12.0 * nnz + 32.0 * nd;
-    const double b_trial = 4.0 * (nd + 1) + 12.0 * nnz + 40.0 * nd;
+    const double *vp64 = A->d16p ? vals64p : nullptr;
+    const double eb = entry_bytes(A, 8.0, vp64, vp64);   // bytes per nonzero
+    const double b_grad = 4.0 * (nd + 1) + eb * nnz + 32.0 * nd;
+    const double b_trial = 4.0 * (nd + 1) + eb * nnz + 40.0 * nd;
     static const int kInitOps[4] = {OP_SUM, OP_MAX, OP_SUM, OP_SUM};
     static const int kGradOps[5] = {OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM};
     static const int kTrialOps[3] = {OP_SUM, OP_SUM, OP_SUM};
@@ -551,7 +553,7 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
     // gradient pass with the KKT report; true when the point is converged
     auto refresh = [&](bool &conv) -> nn_status {
         prof_begin(ctx, KC_GRAD, b_grad);
-        launch_grad(ctx, A, vals, nullptr, c, f, W.g, box);
+        launch_grad(ctx, A, vals, vp64, c, f, W.g, box);
         prof_end(ctx);
         S.spmvs++;
         S.bytes_moved += b_grad;
@@ -576,8 +578,15 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
     // partials (g.s, s.(gn - g), s.s) stay in the host slot.
     auto launch_trial_t = [&](double t) {
         prof_begin(ctx, KC_TRIAL, b_trial);
-        NN_DISPATCH_W(A->wmax, (kl_trial<WM, ColsI32>), P.nb, P, A->sl_off, ColsI32{A->sl_col},
-                      vals, c, L.d, t, f, W.g, L.gn, box, ctx->partials);
+        if (vp64 && A->diag_plan)
+            NN_DISPATCH_W(A->wmax, (kl_trial<WM, ColsDiag>), P.nb, P, A->sl_off,
+                          diag_cols(A, A->d16p), vp64, c, L.d, t, f, W.g, L.gn, box, ctx->partials);
+        else if (vp64)
+            NN_DISPATCH_W(A->wmax, (kl_trial<WM, ColsD16P>), P.nb, P, A->sl_off, ColsD16P{A->d16p},
+                          vp64, c, L.d, t, f, W.g, L.gn, box, ctx->partials);
+        else
+            NN_DISPATCH_W(A->wmax, (kl_trial<WM, ColsI32>), P.nb, P, A->sl_off, ColsI32{A->sl_col},
+                          vals, c, L.d, t, f, W.g, L.gn, box, ctx->partials);
         prof_end(ctx);
         S.spmvs++;
         S.search_trials++;

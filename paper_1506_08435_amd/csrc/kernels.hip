@@ -18,7 +18,7 @@
 #include <cmath>
 
 #include "nnqp_internal.hpp"
-#include "rows.hpp"
+#include "diag.hpp"
 
 namespace nnqp {
 
@@ -36,24 +36,24 @@ Part make_part(int64_t n, int max_blocks)
 
 // ---------------------------------------------------------------- kernels
 template <int WMAX, class Cols>
-__global__ __launch_bounds__(kBlock) void k_matvec(Part P, const int *__restrict__ so, Cols sc,
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_matvec(Part P, const int *__restrict__ so, Cols sc,
                                                    const double *__restrict__ v,
                                                    const double *__restrict__ x, double *__restrict__ y)
 {
-    sell_rows<WMAX>(P, so, sc, v, AllRows(), NoPre(), [&](int j) { return x[j]; },
+    walk_rows<WMAX>(P, so, sc, v, AllRows(), NoPre(), [&](int ub, int l) { return (x + ub)[l]; },
                     [&](int i, double s, int) { y[i] = s; });
 }
 
 // ft = f + (M c) / dt
 template <int WMAX, class Cols>
-__global__ __launch_bounds__(kBlock) void k_transient_rhs(Part P, const int *__restrict__ so, Cols sc,
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_transient_rhs(Part P, const int *__restrict__ so, Cols sc,
                                                           const double *__restrict__ m,
                                                           const double *__restrict__ c,
                                                           const double *__restrict__ f, double dt,
                                                           double *__restrict__ ft)
 {
-    sell_rows<WMAX>(P, so, sc, m, AllRows(), [&](int i) { return f[i]; },
-                    [&](int j) { return c[j]; },
+    walk_rows<WMAX>(P, so, sc, m, AllRows(), [&](int i) { return f[i]; },
+                    [&](int ub, int l) { return (c + ub)[l]; },
                     [&](int i, double s, double fi) { ft[i] = fi + s / dt; });
 }
 
@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kBlock) void k_transient_rhs(Part P, const int *__r
 constexpr uint32_t kOpsGrad = OPS5(OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM);
 
 template <int WMAX, class Cols>
-__global__ __launch_bounds__(kBlock) void k_grad(Part P, const int *__restrict__ so, Cols sc,
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_grad(Part P, const int *__restrict__ so, Cols sc,
                                                  const double *__restrict__ v,
                                                  const double *__restrict__ c,
                                                  const double *__restrict__ f,
@@ -73,8 +73,8 @@ __global__ __launch_bounds__(kBlock) void k_grad(Part P, const int *__restrict__
 {
     double a[5];
     red_init<kOpsGrad, 5>(a);
-    sell_rows<WMAX>(P, so, sc, v, AllRows(), [&](int i) { return Two{c[i], f[i]}; },
-                    [&](int j) { return c[j]; }, [&](int i, double s, Two cf) {
+    walk_rows<WMAX>(P, so, sc, v, AllRows(), [&](int i) { return Two{c[i], f[i]}; },
+                    [&](int ub, int l) { return (c + ub)[l]; }, [&](int i, double s, Two cf) {
         const double gi = s - cf.b;
         const double cv = cf.a;
         g[i] = gi;
@@ -93,15 +93,15 @@ __global__ __launch_bounds__(kBlock) void k_grad(Part P, const int *__restrict__
 constexpr uint32_t kOpsResid = OPS5(OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM);
 
 template <int WMAX, class Cols>
-__global__ __launch_bounds__(kBlock) void k_resid(Part P, const int *__restrict__ so, Cols sc,
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_resid(Part P, const int *__restrict__ so, Cols sc,
                                                   const double *__restrict__ v,
                                                   const double *__restrict__ c,
                                                   const double *__restrict__ f, double *partials)
 {
     double a[5];
     red_init<kOpsResid, 5>(a);
-    sell_rows<WMAX>(P, so, sc, v, AllRows(), [&](int i) { return Two{c[i], f[i]}; },
-                    [&](int j) { return c[j]; }, [&](int, double s, Two cf) {
+    walk_rows<WMAX>(P, so, sc, v, AllRows(), [&](int i) { return Two{c[i], f[i]}; },
+                    [&](int ub, int l) { return (c + ub)[l]; }, [&](int, double s, Two cf) {
                         const double ri = s - cf.b;
                         a[0] += ri * ri;
                         a[1] += (isfinite(ri) && isfinite(cf.a)) ? 0.0 : 1.0;
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kBlock) void k_add(Part P, double *__restrict__ c,
 constexpr uint32_t kOpsTrial = OPS3(OP_SUM, OP_SUM, OP_SUM);
 
 template <int WMAX, class VT, class VD, class Cols>
-__global__ __launch_bounds__(kBlock) void k_trial(Part P, const int *__restrict__ so, Cols sc,
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_trial(Part P, const int *__restrict__ so, Cols sc,
                                                   const VT *__restrict__ v,
                                                   const double *__restrict__ c,
                                                   const VD *__restrict__ d, double t,
@@ -136,14 +136,14 @@ __global__ __launch_bounds__(kBlock) void k_trial(Part P, const int *__restrict_
                                                   const uint8_t *__restrict__ mask,
                                                   double *__restrict__ ks, double *partials, Box B)
 {
-    auto sv = [&](int j) {
-        const double cj = c[j];
-        return proj_box(cj + t * (double)d[j], B) - cj;
+    auto sv = [&](int ub, int l) {
+        const double cj = (c + ub)[l];
+        return proj_box(cj + t * (double)(d + ub)[l], B) - cj;
     };
     double a[3];
     red_init<kOpsTrial, 3>(a);
-    sell_rows<WMAX>(P, so, sc, v, [&](int i) { return mask == nullptr || mask[i] != 0; },
-                    [&](int i) { return Two{sv(i), g[i]}; }, sv, [&](int i, double s, Two sg) {
+    walk_rows<WMAX, 5>(P, so, sc, v, [&](int i) { return mask == nullptr || mask[i] != 0; },
+                    [&](int i) { return Two{sv(0, i), g[i]}; }, sv, [&](int i, double s, Two sg) {
                         if (ks) ks[i] = s;
                         const double si = sg.a;
                         a[0] += sg.b * si;
@@ -177,15 +177,15 @@ __global__ __launch_bounds__(kBlock) void k_ladder(Part P, const int *__restrict
     double a[3 * kLadder];
 #pragma unroll
     for (int k = 0; k < 3 * kLadder; k++) a[k] = 0.0;
-    auto trials = [&](int j, double (&out)[kLadder]) {
-        const double cj = c[j], gj = g[j];
+    auto trials = [&](int ub, int l, double (&out)[kLadder]) {
+        const double cj = (c + ub)[l], gj = (g + ub)[l];
 #pragma unroll
         for (int k = 0; k < kLadder; k++) out[k] = proj_box(cj - L.t[k] * gj, B) - cj;
     };
     auto pre = [&](int i) { return Two{c[i], g[i]}; };
     auto epi = [&](int i, double (&kv)[kLadder], Two cg) {
         double si[kLadder];
-        trials(i, si);
+        trials(0, i, si);
 #pragma unroll
         for (int k = 0; k < kLadder; k++) {
             L.ks[k][i] = kv[k];
@@ -196,8 +196,7 @@ __global__ __launch_bounds__(kBlock) void k_ladder(Part P, const int *__restrict
     };
     // the nine running sums stay in registers for the whole pass, so the
     // entries load NNQP_LADDER_PHASE at a time
-    sell_rows_n<WMAX, kLadder, VT, Cols, decltype(pre), decltype(trials), decltype(epi),
-                NNQP_LADDER_PHASE>(P, so, sc, v, pre, trials, epi);
+    walk_rows_n<WMAX, kLadder, NNQP_LADDER_PHASE>(P, so, sc, v, pre, trials, epi);
     block_partial<0u, 3 * kLadder>(a, slot_ptr(partials, SLOT_U0));
 }
 
@@ -303,32 +302,39 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(
 // p, q are updated in place on the free rows; partials of p.q into SLOT_Q
 // (with TR, also p.p and w.p, which the update needs for |w + alpha p|).
 // Columns outside the free set contribute 0 because z vanishes there.
-template <int WMAX, class VT, class VV, class Cols, bool TR>
-__global__ __launch_bounds__(kBlock) void k_cg_spmv(Part P, const int *__restrict__ so, Cols sc,
-                                                    const VT *__restrict__ v,
-                                                    const uint8_t *__restrict__ mask,
-                                                    const VV *__restrict__ z,
-                                                    VV *__restrict__ p, VV *__restrict__ q,
-                                                    const VV *__restrict__ w,
-                                                    double *partials, DevScalars *S, int j,
-                                                    int max_it, double rtol2)
+// The prologue's scalars, read before anything else of the pass.
+struct CgIn {
+    double rr_stop, rz_old;
+    int tr_hit;
+};
+__device__ __forceinline__ CgIn cg_in(const DevScalars *S, int j)
 {
-    if (S->done) return;
-    // r.z and r.r; the set-up's face counts only before the first iteration
-    // (four values at once hold 66 VGPRs, seven waves per SIMD)
-    const double *slot = slot_ptr(partials, (j & 1) ? SLOT_U1 : SLOT_U0);
-    double u[2], cnt[2] = {0.0, 0.0};
-    combine_partials<0u, 2>(slot, P.nb, u);
-    if (j == 0) combine_partials<0u, 2>(slot + 2 * kMaxBlocks, P.nb, cnt);
+    return CgIn{S->rr_stop, S->rzh[(j - 1) & 1], S->tr_hit};
+}
+
+// u: this thread's partials of r.z and r.r.  Returns the iteration's beta and
+// whether the CG ends here.
+template <bool TR>
+__device__ __forceinline__ bool cg_begin(const CgIn &in, const double *slot, int nb, double (&u)[2],
+                                         DevScalars *S, int j, int max_it, double rtol2,
+                                         double &beta)
+{
+    combine_loaded<0u, 2>(u);
+    double cnt[2] = {0.0, 0.0};   // #free rows and their nonzeros, from the set-up
+    if (j == 0) {
+        load_partials<0u, 2>(slot + 2 * kMaxBlocks, nb, cnt);
+        __syncthreads();
+        combine_loaded<0u, 2>(cnt);
+    }
     const double rz = u[0], rr2 = u[1];
-    const double rr_stop = j == 0 ? rtol2 * rr2 : S->rr_stop;
+    const double rr_stop = j == 0 ? rtol2 * rr2 : in.rr_stop;
     int done = 0;
-    if (TR && j > 0 && S->tr_hit) done = 2;
+    if (TR && j > 0 && in.tr_hit) done = 2;
     else if (!isfinite(rz) || !isfinite(rr2)) done = 4;
     else if ((j == 0 && (rr2 == 0.0 || cnt[0] == 0.0)) || (j > 0 && rr2 <= rr_stop) ||
              j >= max_it || !(rz > 0.0))
         done = 1;
-    const double beta = j == 0 ? 0.0 : rz / S->rzh[(j - 1) & 1];
+    beta = j == 0 ? 0.0 : rz / in.rz_old;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (j == 0) {
             S->rr_stop = rr_stop;
@@ -341,14 +347,33 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(Part P, const int *__restric
             S->it = j;
         }
     }
-    if (done) return;
+    return done != 0;
+}
+
+template <int WMAX, class VT, class VV, class Cols, bool TR>
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cg_spmv(Part P, const int *__restrict__ so, Cols sc,
+                                                    const VT *__restrict__ v,
+                                                    const uint8_t *__restrict__ mask,
+                                                    const VV *__restrict__ z,
+                                                    VV *__restrict__ p, VV *__restrict__ q,
+                                                    const VV *__restrict__ w,
+                                                    double *partials, DevScalars *S, int j,
+                                                    int max_it, double rtol2)
+{
+    if (S->done) return;
+    const CgIn in = cg_in(S, j);
+    const double *slot = slot_ptr(partials, (j & 1) ? SLOT_U1 : SLOT_U0);
+    double u[2], beta;
+    load_partials<0u, 2>(slot, P.nb, u);
+    if (cg_begin<TR>(in, slot, P.nb, u, S, j, max_it, rtol2, beta)) return;
     constexpr int NQ = TR ? 3 : 1;
     double a[NQ];
 #pragma unroll
     for (int k = 0; k < NQ; k++) a[k] = 0.0;
-    sell_rows<WMAX>(P, so, sc, v, [&](int i) { return mask[i] != 0; },
+    walk_rows<WMAX>(P, so, sc, v, [&](int i) { return mask[i] != 0; },
                     [&](int i) { return Three{(double)p[i], (double)q[i], (double)z[i]}; },
-                    [&](int jj) { return (double)z[jj]; }, [&](int i, double kz, Three pqz) {
+                    [&](int ub, int l) { return (z + ub)[l]; },
+                    [&](int i, double kz, Three pqz) {
                         const VV pi = (VV)fma(beta, pqz.a, pqz.c);
                         const VV qi = (VV)fma(beta, pqz.b, kz);
                         p[i] = pi;
@@ -359,6 +384,89 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(Part P, const int *__restric
                             a[2] += (double)w[i] * (double)pi;
                         }
                     });
+    block_partial<0u, NQ>(a, slot_ptr(partials, SLOT_Q));
+}
+
+// The same pass on the diagonal layout when a wavefront has one slice at most
+// (up to kMaxBlocks x kWaves slices, 524,288 rows).  Such a pass is bound by
+// its chain of round trips, not by bytes: the partials, then every load of
+// the slice are issued first (the layout's addresses depend on no index), and
+// the combination of the partials runs while they are in flight.  A slice
+// without free rows is loaded all the same.
+// Two blocks share a CU above kMaxBlocks / 2 blocks, so PH, the entries loaded
+// before the combination, is the whole row below that and eight above it
+// (64 VGPRs).
+template <int WMAX, class VT, class VV, bool TR, int PH>
+__global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
+                                                        const VT *__restrict__ v,
+                                                        const uint8_t *__restrict__ mask,
+                                                        const VV *__restrict__ z,
+                                                        VV *__restrict__ p, VV *__restrict__ q,
+                                                        const VV *__restrict__ w, double *partials,
+                                                        DevScalars *S, int j, int max_it,
+                                                        double rtol2)
+{
+    constexpr int W = diag_width<WMAX>();
+    const int stop = S->done;
+    const CgIn in = cg_in(S, j);
+    const double *slot = slot_ptr(partials, (j & 1) ? SLOT_U1 : SLOT_U0);
+    double u[2], beta;
+    load_partials<0u, 2>(slot, P.nb, u);
+    const int lane = threadIdx.x & 63;
+    const int s0 = blockIdx.x * kWaves + wave_id();
+    const int s = min(s0, P.nslices - 1);   // a wavefront past the last slice loads it and drops it
+    const int row0 = s * kSlice, row = row0 + lane;
+    const bool in_n = row < P.n;
+    const int r = in_n ? row : P.n - 1;
+    const DiagTab<W> t = diag_tab<W>(sc, s);
+    const uint8_t m = mask[r];
+    const VV po = p[r], qo = q[r], zo = z[r];
+    const bool edge = t.kind == DR_EDGE;
+    VT vv[PH];
+    VV xv[PH];
+    auto load = [&](int h) {
+#pragma unroll
+        for (int k = 0; k < PH; k++) {
+            if (h + k >= W) continue;
+            int d, b;
+            diag_entry<W>(t, h + k, d, b);
+            vv[k] = (v + (ptrdiff_t)(b + row0))[lane];
+            if (edge) xv[k] = z[min(max(row + d, 0), P.n - 1)];
+            else xv[k] = (z + (row0 + d))[lane];
+        }
+    };
+    if (t.kind != DR_GENERAL) load(0);
+    if (stop) return;
+    if (cg_begin<TR>(in, slot, P.nb, u, S, j, max_it, rtol2, beta)) return;
+    const bool act = in_n && m != 0 && s0 < P.nslices;
+    double acc[1] = {0.0};
+    if (t.kind != DR_GENERAL) {
+#pragma unroll
+        for (int h = 0; h < W; h += PH) {
+            if (h > 0) load(h);
+#pragma unroll
+            for (int k = 0; k < PH; k++)
+                if (h + k < W) acc[0] = __builtin_fma((double)vv[k], (double)xv[k], acc[0]);
+        }
+    } else {
+        diag_row_gen<1, VV>(sc, v, P.n, s,
+                            [&](int ub, int l, VV (&out)[1]) { out[0] = (z + ub)[l]; }, acc);
+    }
+    constexpr int NQ = TR ? 3 : 1;
+    double a[NQ];
+#pragma unroll
+    for (int k = 0; k < NQ; k++) a[k] = 0.0;
+    if (act) {
+        const VV pi = (VV)fma(beta, (double)po, (double)zo);
+        const VV qi = (VV)fma(beta, (double)qo, acc[0]);
+        p[row] = pi;
+        q[row] = qi;
+        a[0] += (double)pi * (double)qi;
+        if constexpr (TR) {
+            a[1] += (double)pi * (double)pi;
+            a[2] += (double)w[row] * (double)pi;
+        }
+    }
     block_partial<0u, NQ>(a, slot_ptr(partials, SLOT_Q));
 }
 
@@ -374,7 +482,9 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv(Part P, const int *__restric
 // using |w|^2 kept on the device by the recurrence
 // |w + t p|^2 = |w|^2 + 2 t w.p + t^2 p.p; the next matrix pass then ends
 // the CG (done = 2).
-template <class VV, bool TR>
+// ONE: a wavefront has one slice at most, and issues its loads before the
+// partials' combination (as k_cg_spmv_one).
+template <class VV, bool TR, bool ONE>
 __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__restrict__ mask,
                                                       const VV *__restrict__ p,
                                                       const VV *__restrict__ q,
@@ -385,10 +495,25 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
                                                       VV *__restrict__ cdz0, double inv_theta,
                                                       double delta2)
 {
-    if (S->done) return;
+    const int stop = S->done;
+    if constexpr (!ONE)
+        if (stop) return;
+    const double rz = S->rzh[j & 1];
     constexpr int NQ = TR ? 3 : 1;
     double pqa[NQ];
-    combine_partials<0u, NQ>(slot_ptr(partials, SLOT_Q), P.nb, pqa);
+    load_partials<0u, NQ>(slot_ptr(partials, SLOT_Q), P.nb, pqa);
+    struct Own {
+        VV r, q, dm, w, p;
+        uint8_t m;
+    };
+    auto own = [&](int i) { return Own{r[i], q[i], dm[i], w[i], p[i], mask[i]}; };
+    Own o1{};
+    const int i1 = (blockIdx.x * kWaves + wave_id()) * kSlice + (threadIdx.x & 63);
+    if constexpr (ONE) {
+        o1 = own(min(i1, P.n - 1));
+        if (stop) return;
+    }
+    combine_loaded<0u, NQ>(pqa);
     const double pq = pqa[0];
     if (!(pq > 0.0 && isfinite(pq))) {
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -397,7 +522,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
         }
         return;
     }
-    double alpha = S->rzh[j & 1] / pq;
+    double alpha = rz / pq;
     if constexpr (TR) {
         const double pp = pqa[1], wp = pqa[2], ww = S->ww[j & 1];
         double wn = ww + alpha * (2.0 * wp + alpha * pp);
@@ -416,12 +541,11 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
             S->tr_hit = hit;
         }
     }
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for_rows(P, [&](int i, bool act) {
-        if (!act || !mask[i]) return;
-        const VV ri = (VV)((double)r[i] - alpha * (double)q[i]);
-        const VV zi = cres ? (VV)((double)dm[i] * (double)ri * inv_theta) : dm[i] * ri;
-        w[i] = (VV)((double)w[i] + alpha * (double)p[i]);
+    double a[2] = {0.0, 0.0};
+    auto step = [&](int i, const Own &o) {
+        const VV ri = (VV)((double)o.r - alpha * (double)o.q);
+        const VV zi = cres ? (VV)((double)o.dm * (double)ri * inv_theta) : o.dm * ri;
+        w[i] = (VV)((double)o.w + alpha * (double)o.p);
         r[i] = ri;
         z[i] = zi;
         if (cres) {
@@ -430,8 +554,15 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
         }
         a[0] += (double)ri * (double)zi;
         a[1] += (double)ri * (double)ri;
-    });
-    block_partial<kOpsU, 4>(a, slot_ptr(partials, ((j + 1) & 1) ? SLOT_U1 : SLOT_U0));
+    };
+    if constexpr (ONE) {
+        if (i1 < P.n && o1.m) step(i1, o1);
+    } else {
+        for_rows(P, [&](int i, bool act) {
+            if (act && mask[i]) step(i, own(i));
+        });
+    }
+    block_partial<0u, 2>(a, slot_ptr(partials, ((j + 1) & 1) ? SLOT_U1 : SLOT_U0));
     if (blockIdx.x == 0 && threadIdx.x == 0) S->it = j + 1;
 }
 
@@ -441,7 +572,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
 // cb dm res, z += dzn.  The last step leaves r.z in value 0 of `slot` (the
 // slot whose r.r the update or set-up kernel wrote).
 template <int WMAX, class VT, class VV, class Cols>
-__global__ __launch_bounds__(kBlock) void k_cheb(Part P, const int *__restrict__ so, Cols sc,
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cheb(Part P, const int *__restrict__ so, Cols sc,
                                                  const VT *__restrict__ v,
                                                  const uint8_t *__restrict__ mask,
                                                  const VV *__restrict__ dm,
@@ -453,9 +584,9 @@ __global__ __launch_bounds__(kBlock) void k_cheb(Part P, const int *__restrict__
 {
     if (S->done) return;
     double a[1] = {0.0};
-    sell_rows<WMAX>(P, so, sc, v, [&](int i) { return mask[i] != 0; },
+    walk_rows<WMAX>(P, so, sc, v, [&](int i) { return mask[i] != 0; },
                     [&](int i) { return Three{(double)res[i], (double)dzp[i], (double)z[i]}; },
-                    [&](int jj) { return (double)dzp[jj]; }, [&](int i, double kd, Three x) {
+                    [&](int ub, int l) { return (dzp + ub)[l]; }, [&](int i, double kd, Three x) {
                         const double rn = x.a - kd;
                         const double dn = ca * x.b + cb * (double)dm[i] * rn;
                         const VV zn = (VV)(x.c + dn);
@@ -693,7 +824,10 @@ void launch_grad(nn_ctx *ctx, const nn_matrix *A, const double *vals, const doub
                  const double *c, const double *f, double *g, Box B)
 {
     Part P = make_part(A->n);
-    if (vals_p && A->d16p)
+    if (vals_p && A->diag_plan)
+        NN_DISPATCH_W(A->wmax, (k_grad<WM, ColsDiag>), P.nb, P, A->sl_off, diag_cols(A, A->d16p),
+                      vals_p, c, f, g, ctx->partials, B);
+    else if (vals_p && A->d16p)
         NN_DISPATCH_W(A->wmax, (k_grad<WM, ColsD16P>), P.nb, P, A->sl_off, ColsD16P{A->d16p}, vals_p,
                       c, f, g, ctx->partials, B);
     else
@@ -705,7 +839,18 @@ void launch_trial(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double *
                   double t, const double *g, const uint8_t *mask, double *ks, Box B)
 {
     Part P = make_part(A->n);
-    if (V.v32q && A->d16q) {
+    if (A->diag_plan && (V.v32q || V.v64p)) {
+        const ColsDiag cols = diag_cols(A, V.v32q ? A->d16q : A->d16p);
+        if (V.v32q && d.f32)
+            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, float, ColsDiag>), P.nb, P, A->sl_off, cols,
+                          V.v32q, c, d.f32, t, g, mask, ks, ctx->partials, B);
+        else if (V.v32q)
+            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, double, ColsDiag>), P.nb, P, A->sl_off, cols,
+                          V.v32q, c, d.f64, t, g, mask, ks, ctx->partials, B);
+        else
+            NN_DISPATCH_W(A->wmax, (k_trial<WM, double, double, ColsDiag>), P.nb, P, A->sl_off,
+                          cols, V.v64p, c, d.f64, t, g, mask, ks, ctx->partials, B);
+    } else if (V.v32q && A->d16q) {
         const ColsD16Q cols{A->d16q};
         if (d.f32)
             NN_DISPATCH_W(A->wmax, (k_trial<WM, float, float, ColsD16Q>), P.nb, P, A->sl_off, cols,
@@ -758,7 +903,13 @@ void launch_ladder(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double 
         L.t[k] = t[k];
         L.ks[k] = ks[k];
     }
-    if (V.v32q && A->d16q)
+    if (A->diag_plan && V.v32q)
+        NN_DISPATCH_W(A->wmax, (k_ladder<WM, float, ColsDiag>), P.nb, P, A->sl_off,
+                      diag_cols(A, A->d16q), V.v32q, c, g, L, B, ctx->partials);
+    else if (A->diag_plan && V.v64p)
+        NN_DISPATCH_W(A->wmax, (k_ladder<WM, double, ColsDiag>), P.nb, P, A->sl_off,
+                      diag_cols(A, A->d16p), V.v64p, c, g, L, B, ctx->partials);
+    else if (V.v32q && A->d16q)
         NN_DISPATCH_W(A->wmax, (k_ladder<WM, float, ColsD16Q>), P.nb, P, A->sl_off,
                       ColsD16Q{A->d16q}, V.v32q, c, g, L, B, ctx->partials);
     else if (V.v32 && A->sl_d16)
@@ -823,7 +974,15 @@ void launch_cheb(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const Cheb &ch,
     const double ca = ch.ca[step], cb = ch.cb[step];
     const int last = step == ch.degree - 1 ? 1 : 0;
     const int ip = (step - 1) & 1, in = step & 1;
-    if (V.v32 && A->sl_d16) {
+    if (A->diag_plan && V.v32q) {
+        NN_DISPATCH_W(A->wmax, (k_cheb<WM, float, float, ColsDiag>), P.nb, P, A->sl_off,
+                      diag_cols(A, A->d16q), V.v32q, W.mask, W.dm32, W.r32, W.cres32, W.cdz32[ip],
+                      W.cdz32[in], W.z32, ca, cb, last, slot, ctx->partials, ctx->scal);
+    } else if (A->diag_plan && V.v64p) {
+        NN_DISPATCH_W(A->wmax, (k_cheb<WM, double, double, ColsDiag>), P.nb, P, A->sl_off,
+                      diag_cols(A, A->d16p), V.v64p, W.mask, W.dm, W.r, W.cres, W.cdz[ip],
+                      W.cdz[in], W.z, ca, cb, last, slot, ctx->partials, ctx->scal);
+    } else if (V.v32 && A->sl_d16) {
         NN_DISPATCH_W(A->wmax, (k_cheb<WM, float, float, ColsD16>), P.nb, P, A->sl_off,
                       ColsD16{A->sl_d16}, V.v32, W.mask, W.dm32, W.r32, W.cres32, W.cdz32[ip],
                       W.cdz32[in], W.z32, ca, cb, last, slot, ctx->partials, ctx->scal);
@@ -850,7 +1009,31 @@ static void cg_spmv_tr(nn_ctx *ctx, const nn_matrix *A, const Vals &V, int j, in
 {
     Part P = make_part(A->n);
     Workspace &W = ctx->ws;
-    if (V.v32q && A->d16q) {
+    if (A->diag_plan && (V.v32q || V.v64p)) {
+        // one slice per wavefront at most: every load before the prologue
+        const bool one = P.nslices <= P.nb * kWaves, lone = P.nb <= kMaxBlocks / 2;
+        const ColsDiag cols = diag_cols(A, V.v32q ? A->d16q : A->d16p);
+        if (V.v32q && one)
+            NN_DISPATCH_W(A->wmax, (k_cg_spmv_one<WM, float, float, TR, diag_width<WM>()>), P.nb, P,
+                          cols, V.v32q, W.mask, W.z32, W.p32, W.q32, W.w32, ctx->partials, ctx->scal,
+                          j, max_it, rtol * rtol);
+        else if (V.v32q)
+            NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, float, float, ColsDiag, TR>), P.nb, P, A->sl_off,
+                          cols, V.v32q, W.mask, W.z32, W.p32, W.q32, W.w32, ctx->partials,
+                          ctx->scal, j, max_it, rtol * rtol);
+        else if (one && lone)
+            NN_DISPATCH_W(A->wmax, (k_cg_spmv_one<WM, double, double, TR, diag_width<WM>()>), P.nb, P,
+                          cols, V.v64p, W.mask, W.z, W.p0, W.q, W.w, ctx->partials, ctx->scal, j,
+                          max_it, rtol * rtol);
+        else if (one)
+            NN_DISPATCH_W(A->wmax, (k_cg_spmv_one<WM, double, double, TR, 8>), P.nb, P, cols, V.v64p,
+                          W.mask, W.z, W.p0, W.q, W.w, ctx->partials, ctx->scal, j, max_it,
+                          rtol * rtol);
+        else
+            NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, double, double, ColsDiag, TR>), P.nb, P,
+                          A->sl_off, cols, V.v64p, W.mask, W.z, W.p0, W.q, W.w, ctx->partials,
+                          ctx->scal, j, max_it, rtol * rtol);
+    } else if (V.v32q && A->d16q) {
         NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, float, float, ColsD16Q, TR>), P.nb, P, A->sl_off,
                       ColsD16Q{A->d16q}, V.v32q, W.mask, W.z32, W.p32, W.q32, W.w32,
                       ctx->partials, ctx->scal, j, max_it, rtol * rtol);
@@ -886,14 +1069,16 @@ static void cg_update_tr(nn_ctx *ctx, int64_t n, int j, bool f32, const Cheb *ch
     Part P = make_part(n);
     Workspace &W = ctx->ws;
     const double it = ch ? 1.0 / ch->theta : 0.0;
-    if (f32)
-        k_cg_update<float, TR><<<P.nb, kBlock, 0, ctx->stream>>>(
-            P, W.mask, W.p32, W.q32, W.dm32, W.w32, W.r32, W.z32, ctx->partials, ctx->scal, j,
-            ch ? W.cres32 : nullptr, ch ? W.cdz32[0] : nullptr, it, delta2);
-    else
-        k_cg_update<double, TR><<<P.nb, kBlock, 0, ctx->stream>>>(
-            P, W.mask, W.p0, W.q, W.dm, W.w, W.r, W.z, ctx->partials, ctx->scal, j,
-            ch ? W.cres : nullptr, ch ? W.cdz[0] : nullptr, it, delta2);
+    const bool one = P.nslices <= P.nb * kWaves;
+#define NN_UPD(VV, ONE, p_, q_, dm_, w_, r_, z_, cres_, cdz_)                                    \
+    NN_LAUNCH_ROWS((k_cg_update<VV, TR, ONE>), P.nb, P, W.mask, p_, q_, dm_, w_, r_, z_,         \
+                   ctx->partials, ctx->scal, j, ch ? cres_ : nullptr, ch ? cdz_[0] : nullptr, it, \
+                   delta2)
+    if (f32 && one) NN_UPD(float, true, W.p32, W.q32, W.dm32, W.w32, W.r32, W.z32, W.cres32, W.cdz32);
+    else if (f32) NN_UPD(float, false, W.p32, W.q32, W.dm32, W.w32, W.r32, W.z32, W.cres32, W.cdz32);
+    else if (one) NN_UPD(double, true, W.p0, W.q, W.dm, W.w, W.r, W.z, W.cres, W.cdz);
+    else NN_UPD(double, false, W.p0, W.q, W.dm, W.w, W.r, W.z, W.cres, W.cdz);
+#undef NN_UPD
 }
 
 void launch_cg_update(nn_ctx *ctx, int64_t n, int j, bool f32, const Cheb *ch, double delta2)

@@ -151,6 +151,25 @@ inline hipError_t dev_malloc(const DevAlloc &a, T **p, size_t bytes)
     return e;
 }
 
+// Diagonal layout (diag.hpp): the offsets and value bases of a run of slices.
+constexpr int kDiagMax = 32;    // offsets of a run
+constexpr int kDiagHalf = 7;    // offsets > 0 of a regular run (3D P1)
+enum { DR_REGULAR = 0, DR_EDGE = 1, DR_GENERAL = 2 };
+// Regular runs: offsets 0, +-h[0], ..., ascending h; the array of offset h[u]
+// starts at b0 + (u + 1) stride (that of offset 0 at b0), counted from row 0.
+struct DiagReg {
+    int b0, stride;
+    int h[kDiagHalf];
+};
+struct DiagRun {
+    int w;      // offsets, ascending; slots past w repeat offset 0
+    int kind;   // regular, regular with columns that would leave [0, n), general
+    DiagReg reg;
+    int d[kDiagMax];
+    int b[kDiagMax];
+};
+struct DiagPlan;   // host side of the layout (diag.hip)
+
 }  // namespace nnqp
 
 struct nn_matrix {
@@ -176,6 +195,12 @@ struct nn_matrix {
     short *d16q = nullptr;
     float *val32q = nullptr;
     float *kt32q = nullptr;
+    // Diagonal layout, when the pattern has it (diag.hip): then the value
+    // copies above (val64p, kt64p, val32q, kt32q) hold the diagonal arrays and
+    // the index copies (d16p, d16q) the run of each slice and the runs' tables.
+    nnqp::DiagPlan *diag_plan = nullptr;   // null: not looked for yet, or not there
+    bool diag_tried = false;
+    bool d16p_ready = false, d16q_ready = false;   // index copies filled
     double *val = nullptr;     // K values, sliced-ELL order [nsell]
     double *mval = nullptr;    // M values, sliced-ELL order (or null)
     double *diag = nullptr;    // diag(K)
@@ -344,6 +369,26 @@ void launch_pair_f64(nn_ctx *ctx, const nn_matrix *A, const double *src, double 
 // quad copies (layout of nn_matrix::d16q)
 void launch_quad_f32(nn_ctx *ctx, const nn_matrix *A, const float *src, float *dst);
 void launch_quad_d16(nn_ctx *ctx, const nn_matrix *A, const short *src, short *dst);
+// Diagonal layout (diag.hip).  diag_find looks the pattern over once (scratch
+// holds at least 136 bytes per slice); diag_upload writes the tables into an
+// index copy, diag_fill a value array's diagonals; diag_symmetric tells
+// whether every entry read through the opposite triangle has its bits there.
+nn_status diag_find(nn_ctx *ctx, nn_matrix *A, void *scratch);
+nn_status diag_upload(nn_ctx *ctx, const nn_matrix *A, void *index);
+nn_status diag_fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const double *src,
+                    double *dst);
+nn_status diag_fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const float *src,
+                    float *dst);
+void diag_free(nn_matrix *A);
+double diag_entries(const nn_matrix *A);   // stored entries (0: no diagonal layout)
+// bytes per nonzero a pass reads from the copy for values of vb bytes: the
+// diagonal arrays (no index), or values and int16 or int32 indices
+inline double entry_bytes(const nn_matrix *A, double vb, bool copy, bool d16)
+{
+    if (copy && A->diag_plan) return vb * diag_entries(A) / (double)(A->nnz > 0 ? A->nnz : 1);
+    return vb + (d16 ? 2.0 : 4.0);
+}
+nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64);
 // active = 1 where c == lo, 2 where c == hi, else 0
 void launch_active(nn_ctx *ctx, int64_t n, const double *c, uint8_t *active, Box B);
 // out = m/dt + k
@@ -374,8 +419,10 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
 
 nn_status finish_matrix(nn_ctx *ctx, nn_matrix *A);
 
-// The same problem by BLMVM (blmvm.hip); vals are float64 values of A.
-nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const double *f,
+// The same problem by BLMVM (blmvm.hip); vals are float64 values of A, vals64p
+// the same in the layout the passes read, or null.
+nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const double *vals64p,
+                     const double *f,
                      const nn_opts *o, double *c, uint8_t *active, nn_stats *st);
 void lm_release(nn_ctx *ctx);
 

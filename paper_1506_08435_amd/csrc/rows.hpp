@@ -165,18 +165,29 @@ __device__ __forceinline__ void block_partial(double (&a)[NV], double *slot)
 constexpr int kPartWaves = kMaxBlocks / 64;
 static_assert(kMaxBlocks % 64 == 0 && kPartWaves <= kWaves, "one partial per thread");
 
+// The calling thread's partial (issued early, so that other loads follow it)
+// and the combination of the loaded values.
 template <uint32_t OPS, int NV>
-__device__ __forceinline__ void combine_partials(const double *slot, int nb, double (&a)[NV])
+__device__ __forceinline__ void load_partials(const double *slot, int nb, double (&a)[NV])
 {
-    __shared__ double sh[NV][kPartWaves];
-    __syncthreads();   // a second combination reuses sh
     red_init<OPS, NV>(a);
     const int b = threadIdx.x;
     if (b < nb)
 #pragma unroll
-        for (int k = 0; k < NV; k++) a[k] = red_comb(op_of<OPS>(k), a[k], slot[k * kMaxBlocks + b]);
+        for (int k = 0; k < NV; k++) a[k] = slot[k * kMaxBlocks + b];
+}
+
+// (a kernel that combines twice separates the two with a barrier: sh is the
+// same)
+template <uint32_t OPS, int NV>
+__device__ __forceinline__ void combine_loaded(double (&a)[NV])
+{
+    __shared__ double sh[NV][kPartWaves];
     const int lane = threadIdx.x & 63, wid = wave_id();
     if (wid < kPartWaves) {
+#pragma unroll
+        for (int k = 0; k < NV; k++)   // (a sum starts from +0.0)
+            if (op_of<OPS>(k) == OP_SUM) a[k] = 0.0 + a[k];
         wave_red<OPS, NV>(a);
         if (lane == 0)
 #pragma unroll
@@ -186,6 +197,13 @@ __device__ __forceinline__ void combine_partials(const double *slot, int nb, dou
 #pragma unroll
     for (int k = 0; k < NV; k++)
         a[k] = lanes_in_order<kPartWaves>(op_of<OPS>(k), sh[k][lane & (kPartWaves - 1)]);
+}
+
+template <uint32_t OPS, int NV>
+__device__ __forceinline__ void combine_partials(const double *slot, int nb, double (&a)[NV])
+{
+    load_partials<OPS, NV>(slot, nb, a);
+    combine_loaded<OPS, NV>(a);
 }
 
 // ---------------------------------------------------------------- slice walkers

@@ -188,11 +188,12 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         VS.v64p = (vals64p && A->d16p) ? vals64p : nullptr;
     }
     const double vb = mixed ? 4.0 : 8.0;                  // bytes per vector entry in CG
-    // index bytes of the search and CG passes: int16 column offsets when the
-    // pass reads them (float32 values, or the paired float64 layout)
-    const double ib = ((mixed && A->sl_d16) || VS.v64p) ? 2.0 : 4.0;
-    const double spmv_s = 4.0 * (n + 1) + (ib + vb) * A->nnz + 16.0 * n;
-    const double spmv_csr = spmv_s + (4.0 - ib) * A->nnz;   // 4-byte column indices
+    // bytes per nonzero of the search and CG passes: the diagonal arrays, else
+    // the values with int16 column offsets when the pass reads them (float32
+    // values, or the paired float64 layout)
+    const double eb = entry_bytes(A, vb, VS.v32q || VS.v64p, (mixed && A->sl_d16) || VS.v64p);
+    const double spmv_s = 4.0 * (n + 1) + eb * A->nnz + 16.0 * n;
+    const double spmv_csr = 4.0 * (n + 1) + (4.0 + vb) * A->nnz + 16.0 * n;   // 4-byte columns
     Dir dir_g, dir_w;
     dir_g.f64 = W.g;
     if (mixed) dir_w.f32 = W.w32;
@@ -257,7 +258,7 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         // the previous step length issued behind it (one synchronisation for
         // both; the ladder is unused on the last iteration and skipped on a
         // subspace step)
-        // the float64 gradient reads the paired copy when the solve has one
+        // the float64 gradient reads the float64 copy when the solve has one
         const double grad_b = (VS.v64p ? spmv_s : B.spmv()) + 16.0 * n;
         prof_begin(ctx, KC_GRAD, grad_b, B.spmv() + 16.0 * n);
         launch_grad(ctx, A, vals, VS.v64p, c, f, W.g, box);
@@ -449,11 +450,11 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
             // matrix pass on the free rows (indices 4 or 2 B, values 8 or 4 B), z gathered,
             // p and q read and written (and w read in a trust-region solve); update:
             // p, q, dm, w, r read, w, r, z written
-            const double b_spmv = n + 4.0 * nf + (ib + vb) * nzf + (tr ? 6.0 : 5.0) * vb * nf;
+            const double b_spmv = n + 4.0 * nf + eb * nzf + (tr ? 6.0 : 5.0) * vb * nf;
             const double b_upd = n + 8.0 * vb * nf + (chp ? 2.0 * vb * nf : 0.0);
             // Chebyshev pass: matrix on the free rows, dz gathered, res and z
             // read and written, dzp, dm, r read, dzn written
-            const double b_cheb = n + 4.0 * nf + (ib + vb) * nzf + 8.0 * vb * nf;
+            const double b_cheb = n + 4.0 * nf + eb * nzf + 8.0 * vb * nf;
             // the paper's CSR model of the same work: a masked SpMV (4-byte
             // columns, rowptr, gathered and written vector) plus the direction
             // update p = z + beta p as its own pass (read r, dinv, p; write p),
@@ -598,18 +599,20 @@ nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const 
     constexpr int kMaxRestarts = 8;
     Vals VS;
     VS.v64 = A->val;
+    VS.v64p = A->d16p ? A->val64p : nullptr;
+    const double eb = entry_bytes(A, 8.0, VS.v64p, VS.v64p);   // bytes per nonzero
     Cheb cheb;
     if ((rc = cheb_prepare(ctx, A, A->val, A->diag, o->precond_degree, &cheb)) != NN_OK)
         return finish(rc);
     const Cheb *chp = cheb.degree > 1 ? &cheb : nullptr;
     const int csteps = cheb.degree - 1;
     const int chunk = o->cg_chunk > 0 ? o->cg_chunk : 16;
-    const double b_spmv = n + 4.0 * n + 12.0 * A->nnz + 40.0 * n;
+    const double b_spmv = n + 4.0 * n + eb * A->nnz + 40.0 * n;
     const double b_upd = n + 64.0 * n;
     double rel = 1.0;   // ||f - K c|| / ||f|| at c = 0
     for (int restart = 0;; restart++) {
         prof_begin(ctx, KC_GRAD, B.spmv() + 16.0 * n);
-        launch_grad(ctx, A, A->val, A->val64p, c, f, W.g, unbounded);   // g = K c - f
+        launch_grad(ctx, A, A->val, VS.v64p, c, f, W.g, unbounded);   // g = K c - f
         prof_end(ctx);
         S.spmvs++;
         S.bytes_moved += B.spmv() + 16.0 * n;
@@ -641,7 +644,7 @@ nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const 
             ctx->prof_seq = -1;
             if ((rc = read_scalars(ctx)) != NN_OK) return rc;
             const int ran = H.it - it_seen;
-            const double b_cheb = n + 4.0 * n + 12.0 * A->nnz + 64.0 * n;
+            const double b_cheb = n + 4.0 * n + eb * A->nnz + 64.0 * n;
             const double c_spmv = 12.0 * A->nnz + 52.0 * n, c_upd = 56.0 * n;   // CSR model
             for (size_t e = mark; e < ctx->prof_live.size(); e++) {
                 ProfEntry &P = ctx->prof_live[e];

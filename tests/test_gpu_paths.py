@@ -53,3 +53,102 @@ def test_reductions_of_a_diagonal_problem(ctx, n, path):
     assert np.all(c[f <= 0.0] == 0.0)
     assert st["min_c"] == c.min()
     K.free()
+
+
+def _with_zeros(rowptr, col, vals, seed, extra=2):
+    """The same matrix with `extra` explicit zero entries per row at random
+    columns (and their transposes): every 64-row slice then has more distinct
+    column offsets than the diagonal layout takes, and a sum in column order
+    keeps its bits (0 * x adds nothing to a finite sum)."""
+    n = rowptr.size - 1
+    rng = np.random.default_rng(seed)
+    rows = np.repeat(np.arange(n), np.diff(rowptr))
+    r, c = np.repeat(np.arange(n), extra), rng.integers(0, n, extra * n)
+    key = np.concatenate([rows * n + col, r * n + c, c * n + r])
+    data = [np.concatenate([v, np.zeros(2 * extra * n)]) for v in vals]
+    # the first of equal keys is the real entry
+    uniq, first = np.unique(key, return_index=True)
+    rp = np.concatenate([[0], np.cumsum(np.bincount(uniq // n, minlength=n))])
+    return rp, (uniq % n).astype(np.int32), [d[first] for d in data]
+
+
+_DIAG = {
+    # one slice and a bit; slices that span grid lines; slices inside a line;
+    # a line longer than two slices; 3D with fewer and more rows than an
+    # offset reaches; a numbering that shifts (runs); offsets past int16
+    "square_9": lambda: W.square2d(9), "square_33": lambda: W.square2d(33),
+    "square_65": lambda: W.square2d(65), "square_201": lambda: W.square2d(201),
+    "cube_5": lambda: W.cube3d(5), "cube_12": lambda: W.cube3d(12), "cube_21": lambda: W.cube3d(21),
+    "cube_66": lambda: W.cube3d(66), "hole_3": lambda: W.cube_hole(3),
+    "slab": lambda: W.config_transient3d(20, 18, 9, ell=3.0),
+    "wide": lambda: W.box_problem("wide", (200, 170, 3), 1 / 200, W.aniso3d_tensor()),
+}
+
+
+@pytest.mark.parametrize("name", sorted(_DIAG))
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_diagonal_layout_keeps_the_bits(ctx, name, precision):
+    """Solves that read the diagonal layout and solves of the same matrix in a
+    pattern without one (explicit zeros) give the same bits: TRON, with a
+    Chebyshev preconditioner, with a trust radius, BLMVM, Galerkin, a
+    backward-Euler step and products."""
+    import torch
+    from paper_1506_08435_amd import nnqp
+    p = _DIAG[name]()
+    K, F, _ = ctx.assemble(p, with_mass=True)
+    rp, col, val, mval = ctx.matrix_export(K)
+    rpz, colz, (valz, mvalz) = _with_zeros(rp, col, [val, mval], 5)
+    Z = ctx.matrix_from_csr(rpz, colz, valz, mvalz)
+    assert Z.n == K.n and Z.nnz > K.nnz
+    prec = nnqp.NN_MIXED if precision == "mixed" else nnqp.NN_FP64
+    kw = dict(tol=1e-8, inner_rtol=0.3, precision=prec, engine=1, lower=0.0)
+    calls = [lambda A: ctx.solve_nonneg(A, F, **kw)[:2],
+             lambda A: ctx.solve_nonneg(A, F, **kw, precond_degree=3)[:2],
+             lambda A: ctx.solve_nonneg(A, F, **kw, delta0=1e-3 * (K.n ** 0.5))[:2],
+             lambda A: ctx.step_transient(A, 1e-3, F, torch.zeros(K.n, dtype=torch.float64, device=ctx.device),
+                                          **kw)[:2]]
+    if precision == "fp64":
+        x = torch.from_numpy(np.random.default_rng(3).standard_normal(K.n)).to(ctx.device)
+        calls += [lambda A: ctx.solve_nonneg(A, F, tol=1e-6, method=nnqp.NN_BLMVM)[:2],
+                  lambda A: ctx.solve_galerkin(A, F, tol=1e-8, max_cg=20000)[:1],
+                  lambda A: (ctx.matvec(A, x), ctx.matvec(A, x, which=1))]
+    for k, call in enumerate(calls):
+        a, b = call(K), call(Z)
+        torch.cuda.synchronize()
+        for u, w in zip(a, b):
+            assert torch.equal(u, w), (name, precision, k, (u != w).sum().item())
+    K.free()
+    Z.free()
+
+
+def test_matrix_with_one_unequal_pair_matches_oracle(ctx):
+    """K[i, j] and K[j, i] one ulp apart: the entries cannot be shared across
+    the diagonal, every stored value counts.  Products are exact to rounding
+    against numpy in long double, and the solve matches the oracle."""
+    import torch
+    p = W.cube3d(12)
+    S = oracle.assemble(p)
+    val = S.K.copy()
+    rows = np.repeat(np.arange(S.n), np.diff(S.rowptr))
+    off = np.flatnonzero(rows == S.col + 1)[500]
+    val[off] *= 1.0 + 1e-3            # one side only: a visible difference in the product
+    K = ctx.matrix_from_csr(S.rowptr, S.col, val)
+    x = np.random.default_rng(1).standard_normal(S.n)
+    y = ctx.matvec(K, torch.from_numpy(x).to(ctx.device)).cpu().numpy()
+    ref = np.zeros(S.n, dtype=np.longdouble)
+    np.add.at(ref, rows, val.astype(np.longdouble) * x[S.col])
+    mag = np.zeros(S.n)
+    np.add.at(mag, rows, np.abs(val * x[S.col]))
+    assert np.all(np.abs(y - ref) <= 16 * np.finfo(float).eps * mag)
+    # the solver's gradient reads every stored value: the residual of a
+    # one-iteration solve reports |pg| of K c0 - f with K as given
+    F = torch.from_numpy(S.F).to(ctx.device)
+    c0 = torch.from_numpy(np.abs(x)).to(ctx.device)
+    _, _, st = ctx.solve_nonneg(K, F, c=c0.clone(), c0_mode=1, max_outer=0, tol=1e-12, engine=1,
+                                allow_maxit=True)
+    g = np.zeros(S.n, dtype=np.longdouble)
+    np.add.at(g, rows, val.astype(np.longdouble) * np.abs(x)[S.col])
+    g = (g - S.F).astype(float)
+    want = np.sqrt(np.sum(g * g)) / np.sqrt(np.sum(S.F ** 2))
+    assert abs(st["kkt_rel"] - want) <= 1e-12 * want
+    K.free()
