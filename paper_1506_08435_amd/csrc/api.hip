@@ -682,8 +682,12 @@ nn_status nn_solve_nonneg(nn_ctx *ctx, nn_matrix *K, const double *f_dev,
         if ((st = ensure_paired(ctx, K, true)) != NN_OK) return st;
         return blmvm_impl(ctx, K, K->val, K->val64p, f_dev, opts, c_dev, active_dev, stats);
     }
-    if ((st = choose_solo(ctx, K, opts)) == NN_OK)
-        return solo_solve_impl(ctx, K, K->val, K->diag, f_dev, opts, c_dev, active_dev, stats);
+    if ((st = choose_solo(ctx, K, opts)) == NN_OK) {
+        // (the copy is read up to kSoloMaxRows rows)
+        if (K->n <= kSoloMaxRows && (st = ensure_paired(ctx, K, true)) != NN_OK) return st;
+        return solo_solve_impl(ctx, K, K->val, K->val64p, K->diag, f_dev, opts, c_dev, active_dev,
+                               stats);
+    }
     if (st != NN_EMAXIT) return st;   // (NN_EMAXIT: the multi-block passes)
     const float *v32 = nullptr;
     if (opts->precision == NN_MIXED && K->n > 0) {
@@ -736,7 +740,8 @@ nn_status nn_step_transient(nn_ctx *ctx, nn_matrix *K, double dt, const double *
     o.c0_mode = 1;   // warm start from c^(n)
     if (o.method == NN_BLMVM) return blmvm_impl(ctx, K, K->kt, K->kt64p, ctx->ws.ft, &o, c_dev, active_dev, stats);
     if ((st = choose_solo(ctx, K, &o)) == NN_OK)
-        return solo_solve_impl(ctx, K, K->kt, K->kt_diag, ctx->ws.ft, &o, c_dev, active_dev, stats);
+        return solo_solve_impl(ctx, K, K->kt, K->kt64p, K->kt_diag, ctx->ws.ft, &o, c_dev,
+                               active_dev, stats);
     if (st != NN_EMAXIT) return st;
     return solve_impl(ctx, K, K->kt, mixed ? K->kt32 : nullptr, mixed ? K->kt32q : nullptr,
                       mixed ? nullptr : K->kt64p, K->kt_diag, ctx->ws.ft, &o, c_dev, active_dev,

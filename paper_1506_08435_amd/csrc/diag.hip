@@ -327,6 +327,13 @@ nn_status diag_upload(nn_ctx *ctx, const nn_matrix *A, void *index)
     return upload(ctx, *A->diag_plan, index);
 }
 
+bool diag_one_run(const nn_matrix *A, DiagReg *reg)
+{
+    if (!A->diag_plan || A->diag_plan->elo != 0 || A->diag_plan->ehi != (int)A->nslices) return false;
+    *reg = A->diag_plan->main;
+    return true;
+}
+
 double diag_entries(const nn_matrix *A) { return A->diag_plan ? (double)A->diag_plan->entries : 0.0; }
 
 nn_status diag_fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const double *src,

@@ -263,9 +263,10 @@ nn_status check_opts(nn_ctx *ctx, const nn_opts *o);
 constexpr int64_t kSoloMaxRows = 4096;
 // whether the solve of A with options o can run in one workgroup
 bool solo_eligible(const nn_matrix *A, const nn_opts *o);
-// the TRON solve of solver.hip in one workgroup (float64 values `vals`)
-nn_status solo_solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const double *diag,
-                          const double *f, const nn_opts *o, double *c, uint8_t *active,
+// the TRON solve of solver.hip in one workgroup (float64 values `vals`, and
+// their copy vals64p or null)
+nn_status solo_solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals,
+                          const double *vals64p, const double *diag, const double *f, const nn_opts *o, double *c, uint8_t *active,
                           nn_stats *st);
 
 // Rows the fixed work array of nn_solve_nonneg_noalloc holds (noalloc.hip).
@@ -380,6 +381,7 @@ nn_status diag_fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const do
 nn_status diag_fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const float *src,
                     float *dst);
 void diag_free(nn_matrix *A);
+bool diag_one_run(const nn_matrix *A, DiagReg *reg);   // one regular run over all slices
 double diag_entries(const nn_matrix *A);   // stored entries (0: no diagonal layout)
 // bytes per nonzero a pass reads from the copy for values of vb bytes: the
 // diagonal arrays (no index), or values and int16 or int32 indices

@@ -21,7 +21,7 @@
 #include <cstring>
 
 #include "nnqp_internal.hpp"
-#include "rows.hpp"
+#include "diag.hpp"
 
 namespace nnqp {
 
@@ -75,58 +75,37 @@ __host__ __device__ constexpr int solo_lds_rows(int nv) { return nv == 5 ? kSolo
 // Reduced values of a pass, the same in every thread: wavefront shuffles,
 // then the wavefronts' totals combined in wavefront order (a fixed order, so
 // the result is reproducible).
-#ifndef NNQP_SOLO_ONE_BARRIER
-#define NNQP_SOLO_ONE_BARRIER 1
-#endif
-#if NNQP_SOLO_ONE_BARRIER
 // One barrier per reduction: the totals go to one of two halves of sh,
 // alternating between calls (parity, the same in every thread since every
-// thread makes the same calls), and every thread combines them itself, so a
+// thread makes the same calls), and every wavefront combines them itself, so a
 // half is written again only two reductions later, after the next barrier.
+// One or two sums read the totals as broadcast vector loads; more would hold
+// 16 registers each, so they go lane by lane through scalar registers.
 template <uint32_t OPS, int NV>
 __device__ __forceinline__ void wg_reduce(double (&a)[NV], double *sh, int &parity)
 {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wid = wave_id();
     wave_red<OPS, NV>(a);
     double *buf = sh + parity * (kSoloWaves * (kMaxRed + 1));
     parity ^= 1;
     if (lane == 0)
 #pragma unroll
-        for (int k = 0; k < NV; k++) buf[wid * (NV + 1) + k] = a[k];
+        for (int k = 0; k < NV; k++) buf[k * kSoloWaves + wid] = a[k];
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < NV; k++) {
-        const int op = (int)((OPS >> (2 * k)) & 3u);
-        double v = buf[k];
+        if constexpr (NV <= 2) {
+            double v = buf[k * kSoloWaves];
 #pragma unroll
-        for (int w = 1; w < kSoloWaves; w++) v = red_comb(op, v, buf[w * (NV + 1) + k]);
-        a[k] = v;
+            for (int w = 1; w < kSoloWaves; w++)
+                v = red_comb(op_of<OPS>(k), v, buf[k * kSoloWaves + w]);
+            a[k] = v;
+        } else {
+            a[k] = lanes_in_order<kSoloWaves>(op_of<OPS>(k),
+                                              buf[k * kSoloWaves + (lane & (kSoloWaves - 1))]);
+        }
     }
 }
-#else
-template <uint32_t OPS, int NV>
-__device__ __forceinline__ void wg_reduce(double (&a)[NV], double *sh, int &)
-{
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    wave_red<OPS, NV>(a);
-    __syncthreads();
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < NV; k++) sh[wid * (NV + 1) + k] = a[k];
-    __syncthreads();
-    if (threadIdx.x < NV) {
-        const int k = threadIdx.x;
-        const int op = (int)((OPS >> (2 * k)) & 3u);
-        double v = sh[k];
-#pragma nounroll
-        for (int w = 1; w < kSoloWaves; w++) v = red_comb(op, v, sh[w * (NV + 1) + k]);
-        sh[kSoloWaves * (NV + 1) + k] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NV; k++) a[k] = sh[kSoloWaves * (NV + 1) + k];
-}
-#endif
 
 // Rows of the problem, slice by slice over the workgroup's wavefronts:
 // body(i, act) for row i = 64 s + lane of every slice s of this wavefront.
@@ -585,10 +564,486 @@ finish:
     }
 }
 
+// ---------------------------------------------------------------- diagonal layout
+// The same solve where the matrix has the diagonal layout in one regular run:
+// the workgroup holds the matrix in registers.  Thread (wavefront w, lane l)
+// owns the rows of lane l of the slices w, w + 8, ..., NS of them at most (the
+// rows, and so every reduction's order, of the kernel above), with their
+// entries (7 or 15; during a CG the last RK of them in registers, the others
+// read from the caches each pass), p, q, r and w.  Only what
+// neighbours gather lives in LDS, c and one vector y (z of the CG, or the
+// trial step s, formed once per row instead of once per gather), with kSoloPad
+// zeros on both sides so that no gather tests its index, next to g and
+// 1 / diag, which have no room left in registers.  A CG iteration then reads
+// 7 or 15 doubles of LDS per row and no memory.
+//
+// What bounds it: instruction issue of one CU (a 64^2 CG iteration is about 600
+// instructions per wavefront, two wavefronts per SIMD) and its LDS reads (63
+// slices x 7 x 512 B at 128 B per cycle, 1,770 cycles); passes outside the CG
+// also fetch their entries (224 KB).  Measured: 2.45 us per CG iteration and
+// 7 us per other pass on the 64^2 square, the solve 5.5-6.1 -> 1.9-2.0 ms
+// against the kernel above; 13^3 rows 1.48 -> 0.81 ms.  The entries are loaded
+// again at each CG: kept in registers for the whole solve they were spilled
+// inside the CG loop (7.8 us per iteration).
+constexpr int kSoloPad = 512;                               // offsets reach at most this far
+constexpr int kSoloSpan = kSoloLdsRows + 2 * kSoloPad;      // a gathered vector in LDS
+
+struct SoloDiag {
+    int n, nsl;
+    DiagReg reg;
+    const double *val;   // diagonal arrays
+    const double *diag, *f;
+    const int *rp;
+    double *c;
+    uint8_t *active;
+    SoloOut *out;
+    int64_t nnz;
+};
+
+// Global pointers that pass through an empty asm statement (which keeps loads
+// from them out of loop-invariant code) keep their address space.
+typedef const double __attribute__((address_space(1))) *GlobalD;
+typedef const int __attribute__((address_space(1))) *GlobalI;
+
+// Nothing below branches on a row's own state (present, free): a thread
+// without a row holds zero entries, and sums take a zero by a select, so the
+// register arrays see no divergent control flow.
+template <int W, int NS, int RK>
+__device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpts &O, Box B,
+                                                double *shbuf, double *lds)
+{
+    constexpr int H = W / 2, LK = W - RK;   // entries 0 .. LK - 1 are read from memory
+    static_assert(LK <= H, "the diagonal entry and those after it stay in registers");
+    constexpr int T = kSoloBlock;           // row stride between a thread's slices
+    int par = 0;
+    const int n = P.n;
+    const double dn = n;
+    int status = NN_EMAXIT, n_active = 0, outer = 0, cg_its = 0, spmvs = 0, ctr = 0, strl = 0;
+    double bytes = 0.0, normf, kkt_rel = 0.0, kkt_nat = 0.0, min_c = 0.0;
+    const double spmv_b = 4.0 * (dn + 1) + 12.0 * (double)P.nnz + 16.0 * dn;
+    const int lane = threadIdx.x & 63, wid = wave_id();
+    const int i0 = wid * kSlice + lane;     // row of slice t: i0 + 512 t
+    double *const C = lds + kSoloPad + i0;  // C[512 t]: own row
+    double *const Y = lds + kSoloSpan + kSoloPad + i0;
+    double *const G = lds + 2 * kSoloSpan + i0;
+    double *const I = lds + 2 * kSoloSpan + kSoloLdsRows + i0;
+    DiagTab<W> tab;
+    tab.b0 = P.reg.b0;
+    tab.stride = P.reg.stride;
+#pragma unroll
+    for (int u = 0; u < H; u++) tab.h[u] = P.reg.h[u];
+
+    for (int k = threadIdx.x; k < 2 * kSoloSpan; k += T) lds[k] = 0.0;
+    auto mine = [&](int t) { return i0 + t * T < n; };
+#pragma unroll
+    for (int t = 0; t < NS; t++) {
+        const double dg = P.diag[mine(t) ? i0 + t * T : 0];
+        I[t * T] = mine(t) ? 1.0 / dg : 0.0;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+
+    // The entries of slice t from entry k0 on (a slice past the last one reads
+    // slice 0, a valid address).
+    auto load = [&](GlobalD val, int t, int k0, auto &e) {
+        const int s = wid + t * kSoloWaves;
+        const int row0 = s < P.nsl ? s * kSlice : 0;
+#pragma unroll
+        for (int k = 0; k < (int)(sizeof(e) / sizeof(double)); k++) {
+            int d, b;
+            diag_entry<W>(tab, k0 + k, d, b);
+            e[k] = (val + (ptrdiff_t)(b + row0))[lane];
+        }
+    };
+    // Row sum of slice t with the gathered vector X (own-row pointer into
+    // LDS): the first entries in a, the others in e; own: X of the row.
+    auto row_sum = [&](const double *X, int t, const auto &a, const auto &e, double &own) {
+        constexpr int NA = (int)(sizeof(a) / sizeof(double));
+        double xv[W], acc = 0.0;
+#pragma unroll
+        for (int k = 0; k < W; k++) {
+            int d, b;
+            diag_entry<W>(tab, k, d, b);
+            xv[k] = X[t * T + d];
+        }
+        own = xv[H];
+#pragma unroll
+        for (int k = 0; k < W; k++) acc = __builtin_fma(k < NA ? a[k < NA ? k : 0] : e[k < NA ? 0 : k - NA], xv[k], acc);
+        return acc;
+    };
+    // A pass outside the CG, entries from the caches: epi(t, sum, own x) for
+    // every slice t (a slice past the last one has x = 0).  No branch: the
+    // loads of a slice summed under one would sink into it and wait there.
+    auto product = [&](const double *X, auto epi) {
+        GlobalD val = (GlobalD)P.val;
+        asm volatile("" : "+s"(val));   // (loads of this pass, not loop-invariant ones)
+        // the entries of DEP slices in flight (the CG's vectors are not live
+        // here, so there is room for all of a 7-point thread's)
+        constexpr int DEP = W == 7 ? NS : (NS < 5 ? NS : 5);
+        double e[DEP][W];
+#pragma unroll
+        for (int t = 0; t < DEP; t++) load(val, t, 0, e[t]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < NS; t++) {
+            double own;
+            const double acc = row_sum(X, t, e[t % DEP], e[t % DEP], own);
+            if (t + DEP < NS) load(val, t + DEP, 0, e[t % DEP]);
+            epi(t, acc, own);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // ---- start point and load statistics
+    {
+        double a[4];
+        red_init<OPS4(OP_SUM, OP_MAX, OP_SUM, OP_SUM), 4>(a);
+#pragma unroll
+        for (int t = 0; t < NS; t++) {
+            const bool m = mine(t);
+            const int i = m ? i0 + t * T : 0;
+            const double fi = P.f[i];
+            a[0] = m ? a[0] + fi * fi : a[0];
+            a[1] = m ? fmax(a[1], fi) : a[1];
+            a[2] += m && !isfinite(fi) ? 1.0 : 0.0;
+            double cv = O.c0v;
+            if (O.c0_mode != 0) {
+                cv = P.c[i];
+                a[3] += m && !isfinite(cv) ? 1.0 : 0.0;
+                cv = proj_box(cv, B);
+            }
+            C[t * T] = m ? cv : 0.0;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wg_reduce<OPS4(OP_SUM, OP_MAX, OP_SUM, OP_SUM), 4>(a, shbuf, par);
+        bytes += 16.0 * dn;
+        normf = sqrt(a[0]);
+        if (a[2] != 0.0 || a[3] != 0.0) {
+            status = NN_ENONFINITE;
+            goto finish;
+        }
+        if (B.lo == 0.0 && !(a[1] > 0.0)) {
+            // f <= 0 with lower bound 0: c = 0 is the minimiser
+#pragma unroll
+            for (int t = 0; t < NS; t++) C[t * T] = 0.0;
+            n_active = n;
+            status = NN_OK;
+            goto finish;
+        }
+    }
+    {
+        double t_cauchy = 1.0;
+#pragma nounroll
+        for (int it_out = 0;; it_out++) {
+            // what an iteration reads again (loads, row lengths) is kept out
+            // of registers between iterations: the compiler may not take it
+            // for loop-invariant
+            GlobalD f_in = (GlobalD)P.f;
+            GlobalI rp_in = (GlobalI)P.rp;
+            int again = 0;
+            asm volatile("" : "+s"(f_in), "+s"(rp_in), "+s"(again));
+            // ---- 1. gradient g = K c - f and the KKT report
+            double a5[5];
+            red_init<OPS5(OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM), 5>(a5);
+            {
+                double fo[NS];
+#pragma unroll
+                for (int t = 0; t < NS; t++) fo[t] = f_in[mine(t) ? i0 + t * T : 0];
+                product(C, [&](int t, double s, double cv) {
+                    const bool m = mine(t);
+                    const double gi = s - fo[t];
+                    G[t * T] = m ? gi : 0.0;
+                    double pg = cv > B.lo ? (cv < B.hi ? gi : fmax(gi, 0.0)) : fmin(gi, 0.0);
+                    pg = m ? pg : 0.0;
+                    a5[0] += pg * pg;
+                    a5[1] += m && !(isfinite(gi) && isfinite(cv)) ? 1.0 : 0.0;
+                    const double nat = fabs(fmax(cv - B.hi, fmin(gi, cv - B.lo)));
+                    a5[2] = m ? fmax(a5[2], nat) : a5[2];
+                    a5[3] = m ? fmin(a5[3], cv) : a5[3];
+                    a5[4] += m && (cv == B.lo || cv == B.hi) ? 1.0 : 0.0;
+                });
+            }
+            wg_reduce<OPS5(OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM), 5>(a5, shbuf, par);
+            spmvs++;
+            bytes += spmv_b + 16.0 * dn;
+            if (a5[1] != 0.0) {
+                status = NN_ENONFINITE;
+                break;
+            }
+            kkt_rel = sqrt(a5[0]) / normf;
+            kkt_nat = a5[2];
+            min_c = a5[3];
+            n_active = (int)a5[4];
+            outer = it_out;
+            if (kkt_rel <= O.tol) {
+                status = NN_OK;
+                break;
+            }
+            if (it_out >= O.max_outer) break;   // NN_EMAXIT
+
+            // ---- 2. Cauchy point: trials s = P(c - t g) - c (s in Y), K s kept
+            double ksb[NS], ksn[NS];
+            auto trial = [&](double t_, double (&ks)[NS], double &gs, double &sks) {
+#pragma unroll
+                for (int t = 0; t < NS; t++) {
+                    const double ci = C[t * T];
+                    const double si = proj_box(ci - t_ * G[t * T], B) - ci;
+                    Y[t * T] = mine(t) ? si : 0.0;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __syncthreads();
+                double a3[2] = {0.0, 0.0};
+                product(Y, [&](int t, double s, double si) {
+                    ks[t] = s;
+                    a3[0] += G[t * T] * si;
+                    a3[1] += si * s;
+                });
+                wg_reduce<OPS2(OP_SUM, OP_SUM), 2>(a3, shbuf, par);
+                gs = a3[0];
+                sks = a3[1];
+                spmvs++;
+                ctr++;
+                bytes += spmv_b + 16.0 * dn;
+            };
+            double t = t_cauchy, gs, sks;
+#pragma unroll
+            for (int q = 0; q < NS; q++) ksb[q] = ksn[q] = 0.0;
+            trial(t, ksb, gs, sks);
+            if (ok_decrease(gs, sks)) {
+#pragma nounroll
+                for (int k = 0; k < 20; k++) {
+                    double gs2, sks2;
+                    trial(t * kExtrap, ksn, gs2, sks2);
+                    if (!ok_decrease(gs2, sks2)) break;
+                    const bool same = gs2 == gs && sks2 == sks;
+                    t *= kExtrap;
+#pragma unroll
+                    for (int q = 0; q < NS; q++) ksb[q] = ksn[q];
+                    gs = gs2;
+                    sks = sks2;
+                    if (same) break;   // every moving variable has reached its bound
+                }
+            } else {
+                int k = 0;
+#pragma nounroll
+                for (;;) {
+                    t *= kInterp;
+                    trial(t, ksb, gs, sks);
+                    if (ok_decrease(gs, sks) || !(++k < kMaxTrials && gs < 0.0)) break;
+                }
+                if (!ok_decrease(gs, sks)) break;   // rounding floor: NN_EMAXIT
+            }
+            t_cauchy = t;
+            bytes += 24.0 * dn;
+
+            // ---- 3. c = P(c - t g), and Jacobi-PCG on the free face there
+            double p[NS], q[NS], r[NS], w[NS];
+            uint32_t fre = 0;     // free rows of this thread
+            uint32_t live = 0;    // slices with a free row (uniform)
+            double u[4] = {0.0, 0.0, 0.0, 0.0};
+            int len[NS];
+#pragma unroll
+            for (int t2 = 0; t2 < NS; t2++) {
+                const int i = mine(t2) ? i0 + t2 * T : 0;
+                len[t2] = rp_in[i + 1] - rp_in[i];
+            }
+#pragma unroll
+            for (int t2 = 0; t2 < NS; t2++) {
+                const bool m = mine(t2);
+                const double g0 = G[t2 * T];
+                const double cv = proj_box(C[t2 * T] - t * g0, B);
+                C[t2 * T] = m ? cv : 0.0;
+                const double gi = g0 + ksb[t2];
+                G[t2 * T] = m ? gi : 0.0;
+                const bool fr = m && !((cv == B.lo && gi >= 0.0) || (cv == B.hi && gi <= 0.0));
+                const double dmi = fr ? I[t2 * T] : 0.0;
+                const double ri = fr ? -gi : 0.0;
+                const double zi = dmi * ri;
+                p[t2] = q[t2] = w[t2] = 0.0;
+                r[t2] = ri;
+                Y[t2 * T] = zi;
+                u[0] += ri * zi;
+                u[1] += ri * ri;
+                u[2] += fr ? 1.0 : 0.0;
+                u[3] += fr ? (double)len[t2] : 0.0;
+                fre |= fr ? 1u << t2 : 0u;
+                if (__ballot(fr) != 0) live |= 1u << t2;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            wg_reduce<0u, 4>(u, shbuf, par);
+            bytes += 88.0 * dn;
+            // the CG's entries in registers
+            double v[NS][RK];
+            GlobalD val = (GlobalD)P.val;
+            asm volatile("" : "+s"(val));
+#pragma unroll
+            for (int t2 = 0; t2 < NS; t2++) load(val, t2, LK, v[t2]);
+            double rz = u[0], rr = u[1], rz_prev = 0.0;
+            const double nf = u[2], nzf = u[3], rr_stop = O.rtol2 * u[1];
+            int it = 0;
+            bool cg_fail = false;
+#pragma nounroll
+            for (int j = 0;; j++) {
+                if (!isfinite(rz) || !isfinite(rr)) {
+                    status = NN_ENONFINITE;
+                    cg_fail = true;
+                    break;
+                }
+                if ((j == 0 && (rr == 0.0 || nf == 0.0)) || (j > 0 && rr <= rr_stop) ||
+                    j >= O.max_cg || !(rz > 0.0))
+                    break;
+                const double beta = j == 0 ? 0.0 : rz / rz_prev;
+                // p <- z + beta p, q <- K z + beta q on the free rows (K p by
+                // linearity); the others keep p = q = 0 (z = 0 there)
+                double pq[1] = {0.0};
+                if constexpr (LK > 0) asm volatile("" : "+s"(val));
+#pragma unroll
+                for (int t2 = 0; t2 < NS; t2++) {
+                    if (!((live >> t2) & 1)) continue;
+                    double lv[LK > 0 ? LK : 1], zi, kz;
+                    if constexpr (LK > 0) {
+                        load(val, t2, 0, lv);
+                        kz = row_sum(Y, t2, lv, v[t2], zi);
+                    } else {
+                        kz = row_sum(Y, t2, v[t2], v[t2], zi);
+                    }
+                    const double kf = (fre >> t2) & 1 ? kz : 0.0;
+                    const double pi = fma(beta, p[t2], zi);
+                    const double qi = fma(beta, q[t2], kf);
+                    p[t2] = pi;
+                    q[t2] = qi;
+                    pq[0] += pi * qi;
+                    __builtin_amdgcn_sched_barrier(0);   // one slice's gathers in registers at a time
+                }
+                wg_reduce<0u, 1>(pq, shbuf, par);
+                if (!(pq[0] > 0.0 && isfinite(pq[0]))) {
+                    status = isfinite(pq[0]) ? NN_ENOTSPD : NN_ENONFINITE;
+                    cg_fail = true;
+                    break;
+                }
+                const double alpha = rz / pq[0];
+                asm volatile("" : "+s"(again));   // (nor 1 / diag here)
+                double a2[2] = {0.0, 0.0};
+#pragma unroll
+                for (int t2 = 0; t2 < NS; t2++) {
+                    const double ri = r[t2] - alpha * q[t2];
+                    const double zi = I[again + t2 * T] * ri;   // (r = 0 off the free rows)
+                    w[t2] += alpha * p[t2];
+                    r[t2] = ri;
+                    Y[t2 * T] = zi;
+                    a2[0] += ri * zi;
+                    a2[1] += ri * ri;
+                }
+                wg_reduce<0u, 2>(a2, shbuf, par);
+                rz_prev = rz;
+                rz = a2[0];
+                rr = a2[1];
+                it++;
+                spmvs++;
+                bytes += (dn + 4.0 * nf + 12.0 * nzf + 40.0 * nf) + (dn + 64.0 * nf);
+            }
+            cg_its += it;
+            if (cg_fail) break;
+
+            // ---- 4. projected search along w
+            double b3[3];
+            red_init<OPS3(OP_MIN, OP_SUM, OP_SUM), 3>(b3);
+#pragma unroll
+            for (int t2 = 0; t2 < NS; t2++) {
+                // (w = 0 off the free rows: no crossing, nothing added)
+                const double wi = w[t2], ci = C[t2 * T];
+                const double room = wi < 0.0 ? ci - B.lo : B.hi - ci;
+                const double brk = room / fabs(wi);
+                b3[0] = wi != 0.0 ? fmin(b3[0], brk) : b3[0];
+                b3[1] += G[t2 * T] * wi;
+                b3[2] += wi * wi;
+            }
+            wg_reduce<OPS3(OP_MIN, OP_SUM, OP_SUM), 3>(b3, shbuf, par);
+            bytes += 24.0 * dn;
+            const double bmin = b3[0], gw = b3[1], wn = sqrt(b3[2]);
+            if (it > 0 && gw < 0.0 && wn > 0.0) {
+                double ts = 1.0;
+                if (bmin < 1.0) {
+#pragma nounroll
+                    for (int k = 0; k < kMaxTrials; k++) {
+#pragma unroll
+                        for (int t2 = 0; t2 < NS; t2++) {
+                            const double ci = C[t2 * T];
+                            const double si = proj_box(ci + ts * w[t2], B) - ci;
+                            Y[t2 * T] = mine(t2) ? si : 0.0;
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        __syncthreads();
+                        double a3[2] = {0.0, 0.0};
+                        product(Y, [&](int t2, double s, double si) {
+                            const double sf = (fre >> t2) & 1 ? si : 0.0;
+                            a3[0] += G[t2 * T] * sf;
+                            a3[1] += sf * s;
+                        });
+                        wg_reduce<OPS2(OP_SUM, OP_SUM), 2>(a3, shbuf, par);
+                        spmvs++;
+                        strl++;
+                        bytes += spmv_b + 16.0 * dn;
+                        if (ok_decrease(a3[0], a3[1])) break;
+                        ts *= kBack;
+                        if (ts <= bmin) {
+                            ts = bmin;   // no bound is crossed: decrease is guaranteed
+                            break;
+                        }
+                    }
+                }
+                if (ts > 0.0) {
+#pragma unroll
+                    for (int t2 = 0; t2 < NS; t2++) {
+                        const double cn = proj_box(C[t2 * T] + ts * w[t2], B);
+                        C[t2 * T] = mine(t2) ? cn : 0.0;
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    bytes += 24.0 * dn;
+                    __syncthreads();
+                }
+            }
+        }
+    }
+finish:
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < NS; t++) {
+        if (!mine(t)) continue;
+        const int i = i0 + t * T;
+        const double ci = C[t * T];
+        P.c[i] = ci;
+        if (P.active) P.active[i] = ci == B.lo ? 1 : (ci == B.hi ? 2 : 0);
+    }
+    if (threadIdx.x == 0) {
+        SoloOut S = {};
+        S.kkt_rel = kkt_rel;
+        S.kkt_nat_inf = kkt_nat;
+        S.min_c = min_c;
+        S.norm_f = normf;
+        S.bytes = bytes;
+        S.outer_its = outer;
+        S.cg_its = cg_its;
+        S.spmvs = spmvs;
+        S.n_active = n_active;
+        S.cauchy_trials = ctr;
+        S.search_trials = strl;
+        S.status = status;
+        *P.out = S;
+    }
+}
+
+template <int W, int NS, int RK>
+__global__ __launch_bounds__(kSoloBlock, 2) void k_solo_diag(SoloDiag P, SoloOpts O, Box B)
+{
+    __shared__ __align__(16) double shbuf[2 * kSoloWaves * (kMaxRed + 1)];
+    __shared__ double lds[2 * kSoloSpan + 2 * kSoloLdsRows];
+    solo_solve_diag<W, NS, RK>(P, O, B, shbuf, lds);
+}
+
 template <int WMAX, int LDSV>
 __global__ __launch_bounds__(kSoloBlock) void k_solo(SoloProb P, SoloOpts O, Box B)
 {
-    __shared__ double shbuf[2 * kSoloWaves * (kMaxRed + 1)];
+    __shared__ __align__(16) double shbuf[2 * kSoloWaves * (kMaxRed + 1)];
     if constexpr (LDSV > 0) {
         __shared__ double lv[LDSV * solo_lds_rows(LDSV)];
         solo_solve<WMAX, LDSV>(P, O, B, shbuf, lv);
@@ -606,8 +1061,8 @@ bool solo_eligible(const nn_matrix *A, const nn_opts *o)
            o->subspace == 0 && o->verbose == 0;
 }
 
-nn_status solo_solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const double *diag,
-                          const double *f, const nn_opts *o, double *c, uint8_t *active,
+nn_status solo_solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals,
+                          const double *vals64p, const double *diag, const double *f, const nn_opts *o, double *c, uint8_t *active,
                           nn_stats *st)
 {
     const int64_t n = A->n;
@@ -661,9 +1116,29 @@ nn_status solo_solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, c
             hipLaunchKernelGGL((k_solo<WM, 0>), dim3(1), dim3(kSoloBlock), 0, ctx->stream, P,    \
                                O, box);                                                          \
     } while (0)
-    if (A->wmax <= 8) NN_SOLO_LAUNCH(8);
+    // The matrix in registers: one regular run over all slices, offsets inside
+    // the LDS padding, at most eight slices per wavefront.  Above five slices
+    // a thread's 15-point rows leave no room for their first seven entries.
+    DiagReg reg{};
+    const bool one_run = vals64p && n <= kSoloLdsRows && diag_one_run(A, &reg) &&
+                         reg.h[A->wmax <= 8 ? 2 : 6] <= kSoloPad;
+    const int ns = (P.nsl + kSoloWaves - 1) / kSoloWaves;
+    const SoloDiag D{P.n, P.nsl, reg, vals64p, diag, f, A->rowptr, c, active, P.out, A->nnz};
+#define NN_SOLO_DIAG(W, NS, RK)                                                                  \
+    hipLaunchKernelGGL((k_solo_diag<W, NS, RK>), dim3(1), dim3(kSoloBlock), 0, ctx->stream, D, O, \
+                       box)
+    if (one_run && A->wmax <= 8) {
+        if (ns <= 2) NN_SOLO_DIAG(7, 2, 7);
+        else if (ns <= 4) NN_SOLO_DIAG(7, 4, 7);
+        else NN_SOLO_DIAG(7, 8, 7);
+    } else if (one_run) {
+        if (ns <= 2) NN_SOLO_DIAG(15, 2, 15);
+        else if (ns <= 5) NN_SOLO_DIAG(15, 5, 15);
+        else NN_SOLO_DIAG(15, 8, 8);
+    } else if (A->wmax <= 8) NN_SOLO_LAUNCH(8);
     else if (A->wmax <= 16) NN_SOLO_LAUNCH(16);
     else NN_SOLO_LAUNCH(32);
+#undef NN_SOLO_DIAG
 #undef NN_SOLO_LAUNCH
     NN_HIP_TRY(ctx, hipGetLastError());
     SoloOut R;

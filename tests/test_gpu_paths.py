@@ -152,3 +152,46 @@ def test_matrix_with_one_unequal_pair_matches_oracle(ctx):
     want = np.sqrt(np.sum(g * g)) / np.sqrt(np.sum(S.F ** 2))
     assert abs(st["kkt_rel"] - want) <= 1e-12 * want
     K.free()
+
+
+_SOLO = {f"square_{n}": (lambda n=n: W.square2d(n)) for n in (3, 9, 17, 23, 33, 46, 47, 64, 65)}
+_SOLO.update({f"cube_{n}": (lambda n=n: W.cube3d(n)) for n in (4, 9, 11, 12, 14, 15, 17)})
+# offsets that reach further than the padding of the vectors in LDS
+_SOLO["thin"] = lambda: W.box_problem("thin", (700, 4), 1 / 700, W.aniso2d_tensor())
+
+
+@pytest.mark.parametrize("name", sorted(_SOLO))
+def test_one_workgroup_engine_with_the_matrix_in_registers(ctx, name):
+    """One to eight slices per wavefront, 7- and 15-point rows, rows past the
+    last one: the same bits and counts as the engine that reads the matrix from
+    memory (the same matrix with explicit zeros), for the non-negative problem,
+    bounds that exclude zero, bounds on both sides, a warm start and a
+    backward-Euler step."""
+    import torch
+    p = _SOLO[name]()
+    K, F, _ = ctx.assemble(p, with_mass=True)
+    rp, col, val, mval = ctx.matrix_export(K)
+    rpz, colz, (valz, mvalz) = _with_zeros(rp, col, [val, mval], 7, extra=3)
+    Z = ctx.matrix_from_csr(rpz, colz, valz, mvalz)
+    # (3 x 3 cells hold no source: a load on every row)
+    F = F + torch.from_numpy(np.random.default_rng(4).uniform(-0.2, 1.0, K.n) / K.n).to(ctx.device)
+    top = float(ctx.solve_nonneg(K, F, tol=1e-8, engine=1)[0].max())
+    warm = torch.from_numpy(np.random.default_rng(2).uniform(0, top, K.n)).to(ctx.device)
+    for k, kw in enumerate([dict(tol=1e-9, inner_rtol=0.5), dict(tol=1e-9, lower=0.1 * top),
+                            dict(tol=1e-9, lower=-0.2 * top, upper=0.5 * top),
+                            dict(tol=1e-9, c0_mode=1)]):
+        out = []
+        for A in (K, Z):
+            out.append(ctx.solve_nonneg(A, F, engine=2, c=warm.clone(), allow_maxit=True, **kw))
+        (c, a, s), (cz, az, sz) = out
+        assert torch.equal(c, cz) and torch.equal(a, az), (name, k)
+        for key in ("kkt_rel", "kkt_nat_inf", "min_c", "norm_f", "outer_its", "cg_its", "spmvs",
+                    "n_active", "cauchy_trials", "search_trials", "status"):
+            assert s[key] == sz[key], (name, k, key)
+    c, cz = warm.clone(), warm.clone()
+    for _ in range(2):
+        ctx.step_transient(K, 1e-3, F, c, tol=1e-9, engine=2)
+        ctx.step_transient(Z, 1e-3, F, cz, tol=1e-9, engine=2)
+    assert torch.equal(c, cz)
+    K.free()
+    Z.free()
