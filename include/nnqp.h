@@ -378,8 +378,7 @@ nn_status nn_step_transient(nn_ctx *ctx, nn_matrix *K, double dt, const double *
  * members, each member keeps its own step lengths, trust radius, CG scalars
  * and stopping test).  A member's result depends only on its own K, f and
  * start value: it is bitwise the same in any batch, alone or mixed, and for
- * any launch shape.  The CG iterations run as a captured hipGraph; launch
- * shapes are tuned per size class on first use (one short timing pass).
+ * any launch shape.  The steps run as captured hipGraphs.
  *
  *   K, f, c  host arrays of nprob entries (K: matrices of this context's
  *            device; f, c: device [K[p]->n] float64, c in/out as in
@@ -399,7 +398,8 @@ nn_status nn_step_transient(nn_ctx *ctx, nn_matrix *K, double dt, const double *
  * float64, 77 in mixed precision, plus per stored matrix entry (sliced-ELL,
  * rows padded to the longest row of their slice) 14 bytes in float64, 18 in
  * mixed precision (a concatenated copy of every member's matrix; 2 bytes
- * less when a member's columns do not fit int16 offsets from the row).
+ * less when a member's columns do not fit int16 offsets from the row, 6 less
+ * when every member has the diagonal layout).
  */
 nn_status nn_solve_batch(nn_ctx *ctx, int32_t nprob, nn_matrix *const *K,
                          const double *const *f_dev, const nn_opts *opts, double *const *c_dev,

@@ -6,19 +6,23 @@
 // projected search, trust-region update), but the members do not move in
 // lockstep: every member carries its own phase in a device-resident state
 // machine, and one global step advances every member by one step of its own
-// phase.  A global step is four launches over all members:
+// phase.  A global step is two launches over all members, each block working
+// on some slices of one member:
 //
 //   row pass     per slice, by the member's phase: gradient g = K c - f,
 //                Cauchy trial along -g, CG matrix pass, or projected-search
-//                trial along the CG step (one sliced-ELL pass each);
-//   transition   one block per member: combine its slice partials, take the
-//                decision the host takes in the single-problem solver
-//                (convergence, trial accepted, CG step length) and choose
-//                the member's vector operation;
-//   vector pass  per slice, by that operation: Cauchy step with CG set-up,
-//                CG vector update, breakpoint search, or step along w;
-//   transition   combine the vector-pass partials (CG scalars, breakpoint),
-//                choose the member's next phase.
+//                trial along the CG step (one matrix pass each);
+//   vector pass  per slice, by the operation chosen: Cauchy step with CG
+//                set-up, CG vector update, breakpoint search, or step along w.
+//
+// Each pass begins with the member's transition: every block of the member
+// combines the slice partials the pass before left (the same fixed order, the
+// same bits) and takes the decision the host takes in the single-problem
+// solver (convergence, trial accepted, CG step length, next phase).  The
+// member's first block writes the new state to the other of two state arrays,
+// which the next pass reads.  (As launches of their own, one block per member,
+// the two transitions took 4.2 us each and two launch gaps of 2.4 us, of the
+// 32.6 us of a step of 64 members.)
 //
 // A member that needs many iterations therefore does not hold the others
 // back: while it is in a long CG, the others run their own Cauchy searches,
@@ -39,12 +43,9 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
-#include <mutex>
-#include <tuple>
 #include <vector>
 
-#include "nnqp_internal.hpp"
-#include "rows.hpp"
+#include "diag.hpp"
 
 // 1: chunks of global steps replayed as captured graphs; 0: launched one by one
 #ifndef NNQP_BATCH_GRAPH
@@ -56,7 +57,13 @@ namespace nnqp {
 namespace {
 
 constexpr int kBNV = 5;          // values per slice partial
-constexpr int kFinBlock = 256;   // threads of a transition block (one block per member)
+constexpr int kFinBlock = 256;   // threads of a block
+constexpr int kBWaves = kFinBlock / 64;
+// Blocks the running slices are spread over, eight per CU of 256 CUs (64
+// members: 188 ms a solve, 195 with half as many, 205-219 with two to four
+// times as many), and a block's slices at most above that.
+constexpr int kBGrid = 2048;
+constexpr int kBMost = 32;
 constexpr double kMu0 = 0.01;    // sufficient-decrease constant
 constexpr double kExtrap = 10.0; // Cauchy extrapolation factor
 constexpr double kInterp = 0.1;  // Cauchy interpolation factor
@@ -90,26 +97,33 @@ struct BState {
     double delta, normf, tol, rtol2;
     double rz, rr_stop, alpha, beta, n_free, nnz_free;   // CG
     double bmin, wn, ts, stepn;      // projected search along w, step length of the iteration
-    double n, nnz, ib, vb;           // rows, nonzeros, index and value bytes (byte model)
+    double n, nnz, eb, eg, vb;       // rows, nonzeros, bytes per nonzero of the search and CG
+                                     // passes and of the gradient, bytes per vector entry
     // report
     double kkt_rel, kkt_nat, min_c, bytes;
     int n_active, cg_its, spmvs, cauchy_trials, search_trials, refinements, mixed, pad1;
 };
 
-// One entry of the current slice list with everything a pass needs before
-// the member's phase: slice, member, first entry, and width << 7 | rows of the
-// slice that exist.  Rebuilt on the device whenever the list changes, so a
-// wavefront fetches its next slice with one load and no dependent lookups.
-struct SRec {
-    int s, p, off, wv;
+// One block's work: slices [s, s + n) of member p (global numbers); first:
+// the member's first block, which writes its state.
+struct BBlk {
+    int p, s, n, first;
+};
+
+// A member's place in the concatenated vectors and, with the diagonal layout,
+// its offsets: the array of offset h[u] starts at b0 + (u + 1) stride counted
+// from global row 0 (W = 0: another layout).
+struct BTab {
+    int s0, nsl, nrow, W;
+    DiagReg reg;
 };
 
 struct BDev {
     int P, nslices;
-    const int *cnt;                 // [2] slices and members in the current lists
+    const int *cnt;                 // [2] blocks and members in the current lists
     const int *plist;               // members taking part in the current launches
-    const int *slist;               // their slices, member by member
-    SRec *srec;                     // [cnt[0]] records of slist
+    const BBlk *blk;                // their blocks, member by member
+    const BTab *tab;                // per member
     const int *sprob;               // [nslices] member of each slice
     const int *s0, *nrow;           // per member: first slice, rows
     const int *const *so;           // per member sliced-ELL offsets
@@ -124,8 +138,8 @@ struct BDev {
     const double *const *f0;        // per member loads (transient step: f of f + M c/dt)
     const double *const *mv;        // per member capacity values (transient step)
     uint8_t *const *act_out;        // per member active-set outputs (entries may be null)
-    BState *st;
-    double *part;                   // [nslices][kBNV]
+    BState *st, *st2;               // states before the row pass, before the vector pass
+    double *part, *part2;           // [kBNV][nslices]: of the row pass, of the vector pass
     double *pres;                   // [P][kBNV] (start-up reductions)
     // the batch as one block-diagonal sliced-ELL matrix and concatenated
     // vectors (global rows s*64 + lane), copied in at the start of a call
@@ -171,41 +185,39 @@ __device__ __forceinline__ double projb(const BDev &B, double x)
     return y < B.hi ? y : B.hi;
 }
 
-// Walk the slices of the current list grid-stride, one wavefront per slice.
-// For a slice of a member with take(p): body(p, s, global row, local row, row
-// exists, a); every listed slice then stores its wave-combined partials
-// (identities when the member did not take part).
+// The calling block's slices, one wavefront each in turn.  For a slice of a
+// member with take(p): body(p, s, global row, local row, row exists, a); every
+// slice then stores its wave-combined partials (identities when the member did
+// not take part).
 template <int NV, class Take, class Body>
 __device__ __forceinline__ void for_bslices(const BDev &B, const int (&ops)[NV], Take take,
                                             Body body)
 {
+    if ((int)blockIdx.x >= B.cnt[0]) return;
+    const BBlk K = B.blk[blockIdx.x];
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wpb = blockDim.x >> 6;
-    const int nw = gridDim.x * wpb;
-    const int nlist = B.cnt[0];
-    for (int t = blockIdx.x * wpb + wid; t < nlist; t += nw) {
-        const int s = B.slist[t];
+    for (int s = K.s + wid; s < K.s + K.n; s += kBWaves) {
         double a[NV];
 #pragma unroll
         for (int k = 0; k < NV; k++) a[k] = bident(ops[k]);
-        const int p = B.sprob[s];
-        if (take(p)) {
-            const int il = (s - B.s0[p]) * kSlice + lane;
-            body(p, s, s * kSlice + lane, il, il < B.nrow[p], a);
+        if (take(K.p)) {
+            const int il = (s - B.s0[K.p]) * kSlice + lane;
+            body(K.p, s, s * kSlice + lane, il, il < B.nrow[K.p], a);
         }
 #pragma unroll
         for (int k = 0; k < NV; k++) a[k] = bwave(ops[k], a[k]);
         if (lane == 0)
 #pragma unroll
-            for (int k = 0; k < NV; k++) B.part[(size_t)s * kBNV + k] = a[k];
+            for (int k = 0; k < NV; k++) B.part[(size_t)k * B.nslices + s] = a[k];
     }
 }
 
-// Column modes of the batched matrix passes (as in the single-problem
-// kernels): int32 columns, or int16 offsets from the row (float32 values,
-// when every member has them).  Float64 values load with the non-temporal
+// Layouts of the concatenated matrix (as in the single-problem kernels):
+// diagonal arrays where every member has them in one regular run; else, when
+// every member's offsets fit int16, quads of float32 values or pairs of
+// float64 values; else int32 columns.  Float64 values load with the non-temporal
 // hint, float32 values normally (as in the single-problem kernels).
-enum { CM_I32 = 0, CM_D16 = 2, CM_Q4 = 3, CM_P2 = 4 };
+enum { CM_I32 = 0, CM_D16 = 2, CM_Q4 = 3, CM_P2 = 4, CM_DIAG = 5 };
 
 // Position of entry k of lane l in a slice of width w of the quad layout
 // (CM_Q4), relative to the slice's first entry: entries 4j .. 4j+3 of a row
@@ -590,38 +602,98 @@ __device__ __forceinline__ double gsell_row_at(const BDev &B, const VT *__restri
     return acc;
 }
 
-// The same for slice s, reading its first entry and width.
-template <int WMAX, int CM, class VT, class X>
-__device__ __forceinline__ double gsell_row(const BDev &B, const VT *__restrict__ sv, int s, int i,
-                                            X x)
+// Row sum of a diagonal-layout member (see diag.hpp): PH entries per load
+// phase; rows whose columns would leave the member's are held inside it.
+template <int W, int PH, class VT, class X>
+__device__ __forceinline__ double bdiag_row(const BTab &T, const VT *__restrict__ sv, int s, X x)
 {
-    const int off = B.gso[s];
-    return gsell_row_at<WMAX, CM>(B, sv, i, off, (B.gso[s + 1] - off) >> 6, x);
+    using XT = decltype(x(0, 0));
+    DiagTab<W> t;
+    t.b0 = T.reg.b0;
+    t.stride = T.reg.stride;
+#pragma unroll
+    for (int u = 0; u < W / 2; u++) t.h[u] = T.reg.h[u];
+    const int ls = s - T.s0, far = t.h[W / 2 - 1];
+    auto x1 = [&](int ub, int l, XT (&out)[1]) { out[0] = x(ub, l); };
+    double acc[1] = {0.0};
+    if (ls * kSlice >= far && ls * kSlice + kSlice - 1 + far < T.nrow) {
+        diag_row_reg<W, 1, PH, false, XT>(t, sv, 0, s * kSlice, x1, acc);
+    } else {
+        // columns counted from the member's first row, held inside its rows
+        const int r0 = T.s0 * kSlice;
+        auto xl = [&](int, int l, XT (&out)[1]) { out[0] = x(r0, l); };
+        diag_row_reg<W, 1, 4, true, XT>(t, sv + r0, T.nrow, ls * kSlice, xl, acc);
+    }
+    return acc[0];
+}
+
+// The same for slice s of a member in the batch's layout; x(ub, l) is the
+// gathered value of global row ub + l.
+template <int WMAX, int CM, int PH, class VT, class X>
+__device__ __forceinline__ double gsell_row(const BDev &B, const BTab &T, const VT *__restrict__ sv,
+                                            int s, int i, X x)
+{
+    if constexpr (CM == CM_DIAG) {
+        if constexpr (WMAX > 8)
+            if (T.W == 15) return bdiag_row<15, PH>(T, sv, s, x);
+        return bdiag_row<7, PH>(T, sv, s, x);
+    } else {
+        const int off = B.gso[s];
+        return gsell_row_at<WMAX, CM>(B, sv, i, off, (B.gso[s + 1] - off) >> 6,
+                                      [&](int j) { return x(0, j); });
+    }
 }
 
 __device__ __forceinline__ bool running(const BDev &B, int p) { return B.st[p].phase != PH_DONE; }
 
-// Records of the current slice list (see SRec), one thread per entry.
-__global__ void kb_recs(BDev B)
+// Slice s of member p into the diagonal arrays: entry k of a row at b_k + row
+// for the offsets >= 0 (the others are read through the opposite triangle),
+// zero where the row has none, and the zeros in front of the arrays.
+__device__ __forceinline__ void gather_diag(const BDev &B, int p, int s, int src,
+                                            double *__restrict__ gv64, float *__restrict__ gv32)
 {
-    const int nlist = B.cnt[0];
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nlist; t += gridDim.x * blockDim.x) {
-        const int s = B.slist[t];
-        const int p = B.sprob[s];
-        const int off = B.gso[s];
-        const int w = (B.gso[s + 1] - off) >> 6;
-        const int left = B.nrow[p] - (s - B.s0[p]) * kSlice;
-        const int nv = left < 0 ? 0 : (left > kSlice ? kSlice : left);
-        B.srec[t] = SRec{s, p, off, (w << 7) | nv};
+    const int lane = threadIdx.x & 63;
+    const BTab &T = B.tab[p];
+    const int ls = s - T.s0, row = ls * kSlice + lane, i = s * kSlice + lane;
+    const int H = T.W / 2;
+    const int len = row < T.nrow ? B.rowptr[p][row + 1] - B.rowptr[p][row] : 0;
+    const int *sc = B.sc[p];
+    const double *v64 = B.v64[p];
+    const float *v32 = B.v32[p];
+    int cur = 0;
+    auto offset = [&]() { return cur < len ? sc[src + cur * kSlice + lane] - row : 0x7fffffff; };
+    int d = offset();
+    while (d < 0) {   // (entries below the diagonal)
+        cur++;
+        d = offset();
+    }
+    for (int u = 0; u <= H; u++) {
+        const int du = u == 0 ? 0 : T.reg.h[u - 1];
+        const ptrdiff_t b = (ptrdiff_t)T.reg.b0 + (ptrdiff_t)u * T.reg.stride;
+        const bool has = d == du;
+        const int e = src + cur * kSlice + lane;
+        gv64[b + i] = has ? v64[e] : 0.0;
+        if (gv32) gv32[b + i] = has ? v32[e] : 0.f;
+        if (has) {
+            cur++;
+            d = offset();
+        }
+        // rows before the member's first one
+        const int reach = (T.reg.h[H - 1] + kSlice - 1) / kSlice;
+        for (int q = ls; q < reach; q += T.nsl) {
+            const ptrdiff_t at = b + (ptrdiff_t)(T.s0 + q - reach) * kSlice + lane;
+            gv64[at] = 0.0;
+            if (gv32) gv32[at] = 0.f;
+        }
     }
 }
 
 // Copy the members into the concatenated layout (every slice of the batch):
 // c, f, diagonal and row lengths into the global vectors; slice offsets
 // (ebase[p] + the member's own offset), global columns, int16 offsets and
-// values into the global matrix arrays, in the quad layout when int16
-// offsets are made (every member has them), else column-major.  Rows past a member's end get c = 0,
-// f = 0, diagonal 1, length 0; their entries keep their valid columns.
+// values into the global matrix arrays in the batch's layout.  Rows past a
+// member's end get c = 0, f = 0, diagonal 1, length 0; their entries keep their
+// valid columns (zeros in the diagonal layout).
 __global__ void kb_gather(BDev B, const int64_t *__restrict__ ebase, int *__restrict__ gso,
                           int *__restrict__ gcol, short *__restrict__ gd16,
                           double *__restrict__ gv64, float *__restrict__ gv32,
@@ -642,6 +714,10 @@ __global__ void kb_gather(BDev B, const int64_t *__restrict__ ebase, int *__rest
         rlen[i] = row ? B.rowptr[p][il + 1] - B.rowptr[p][il] : 0;
         const int *so = B.so[p];
         const int src = so[ls], w = (so[ls + 1] - src) >> 6;
+        if (layout == CM_DIAG) {
+            gather_diag(B, p, s, src, gv64, gv32);
+            continue;
+        }
         const int dst = (int)(ebase[p] + src);
         if (lane == 0) gso[s] = dst;
         const int *sc = B.sc[p];
@@ -717,52 +793,45 @@ __global__ void kb_transient_rhs(BDev B, double dt, double *__restrict__ ft)
                    });
 }
 
-// g = K c - f over the listed slices (the launch-shape tuner times this pass)
-template <int WMAX, int CM>
-__global__ void kb_grad(BDev B, double *__restrict__ g)
-{
-    const int ops[1] = {OP_SUM};
-    for_bslices<1>(B, ops, [&](int p) { return running(B, p); },
-                   [&](int, int s, int i, int, bool row, double (&a)[1]) {
-                       const double *c = B.cg;
-                       const double kc =
-                           gsell_row<WMAX, CM>(B, B.gv64, s, i, [&](int j) { return c[j]; });
-                       if (!row) return;
-                       g[i] = kc - B.fg[i];
-                       a[0] += g[i];
-                   });
-}
-
-// Combine NV slice partials of member p in a fixed order (thread t takes
-// slices t, t + 256, ...; then a wave butterfly; then the four waves in
-// order).  Every thread of the block calls it; thread 0 gets true and the
-// result, the others false.
+// The calling thread's share of the first NV values of a member's slice
+// partials: slices t, t + 256, ... of the member in order.
 template <int NV>
-__device__ __forceinline__ bool member_reduce(const BDev &B, int p, const int (&ops)[NV],
-                                              double (&a)[NV])
+__device__ __forceinline__ void member_load(const BDev &B, const BTab &T,
+                                            const double *__restrict__ part, const int (&ops)[NV],
+                                            double (&a)[NV])
 {
-    __shared__ double sh[kFinBlock / 64][kBNV];
 #pragma unroll
     for (int k = 0; k < NV; k++) a[k] = bident(ops[k]);
-    const int s1 = B.s0[p] + (B.nrow[p] + kSlice - 1) / kSlice;
-    for (int s = B.s0[p] + threadIdx.x; s < s1; s += kFinBlock)
+    for (int s = T.s0 + threadIdx.x; s < T.s0 + T.nsl; s += kFinBlock)
 #pragma unroll
-        for (int k = 0; k < NV; k++) a[k] = bcomb(ops[k], a[k], B.part[(size_t)s * kBNV + k]);
+        for (int k = 0; k < NV; k++)
+            a[k] = bcomb(ops[k], a[k], part[(size_t)k * B.nslices + s]);
+}
+
+// Combine the threads' shares in a fixed order (a wave butterfly, then the
+// four waves in order) into out (LDS); the caller separates it from the reads
+// with a barrier, and two calls from each other.
+template <int NV>
+__device__ __forceinline__ void member_combine(const int (&ops)[NV], double (&a)[NV], double *out)
+{
+    __shared__ double sh[NV][kBWaves];
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
     for (int k = 0; k < NV; k++) a[k] = bwave(ops[k], a[k]);
-    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (lane == 0)
 #pragma unroll
-        for (int k = 0; k < NV; k++) sh[wid][k] = a[k];
+        for (int k = 0; k < NV; k++) sh[k][wid] = a[k];
     __syncthreads();
-    if (threadIdx.x != 0) return false;
+    if (threadIdx.x < NV) {
+        const int k = threadIdx.x;
+        double v = sh[k][0];
+        // (ops is the same constant in every thread; k is not)
+        int op = ops[0];
 #pragma unroll
-    for (int k = 0; k < NV; k++) {
-        double v = sh[0][k];
-        for (int w = 1; w < kFinBlock / 64; w++) v = bcomb(ops[k], v, sh[w][k]);
-        a[k] = v;
+        for (int q = 1; q < NV; q++) op = k == q ? ops[q] : op;
+        for (int w = 1; w < kBWaves; w++) v = bcomb(op, v, sh[k][w]);
+        out[k] = v;
     }
-    return true;
 }
 
 // start-up reduction: |f|^2, max f, #non-finite f, #non-finite c into pres
@@ -771,195 +840,32 @@ __global__ __launch_bounds__(kFinBlock) void kb_reduce_init(BDev B)
     if ((int)blockIdx.x >= B.cnt[1]) return;
     const int p = B.plist[blockIdx.x];
     const int ops[4] = {OP_SUM, OP_MAX, OP_SUM, OP_SUM};
+    __shared__ double r[4];
     double a[4];
-    if (!member_reduce<4>(B, p, ops, a)) return;
-    for (int k = 0; k < 4; k++) B.pres[(size_t)p * kBNV + k] = a[k];
+    member_load<4>(B, B.tab[p], B.part, ops, a);
+    member_combine<4>(ops, a, r);
+    __syncthreads();
+    if (threadIdx.x < 4) B.pres[(size_t)p * kBNV + threadIdx.x] = r[threadIdx.x];
 }
 
 // ---------------------------------------------------------------- global step
-// Row pass: per listed slice, the matrix pass of the member's phase.
-// (Compiled for eight waves per SIMD, i.e. at most 64 VGPRs, the 512-member
-// batch's pass took 81 instead of 74 us in float64 and 70 instead of 55 us in
-// mixed precision: the compiler then waits for loads earlier.)
-//   GRAD    g = K c - f (float64 values); |pg|^2, #non-finite, ||min(c,g)||_inf,
-//           min c, #(c == 0)
-//   CAUCHY  s = P(c + ttrial g) - c gathered, ks = K s into buffer ksbuf;
-//           g.s, s.Ks, s.s
-//   CG      p <- z + beta p, q <- K z + beta q on the free rows; p.q
-//   SEARCH  s = P(c + ts w) - c on the free rows, K s; g.s, s.Ks, s.s
-template <int WMAX, int CM, class VT, class VV>
-__global__ void kb_rows(BDev B, const VT *__restrict__ gvals, BVec<VV> V)
-{
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wpb = blockDim.x >> 6;
-    const int nw = gridDim.x * wpb;
-    const int nlist = B.cnt[0];
-    const double *__restrict__ c = B.cg;
-    int k = blockIdx.x * wpb + wid;
-    // Software pipeline over the wavefront's slices: the record of the slice
-    // after next, and the phase, CG state and free-row mask of the next one,
-    // are fetched while this slice works, so a slice starts with its matrix
-    // loads.  (No pass of this kernel writes them.)
-    SRec r1 = k < nlist ? B.srec[k] : SRec{0, 0, 0, 0};
-    SRec r2 = k + nw < nlist ? B.srec[k + nw] : SRec{0, 0, 0, 0};
-    int ph1 = k < nlist ? B.st[r1.p].phase : PH_DONE;
-    int cd1 = k < nlist ? B.st[r1.p].cgdone : 1;
-    uint8_t m1 = k < nlist ? V.mask[r1.s * kSlice + lane] : 0;
-    for (; k < nlist; k += nw) {
-        const SRec R = r1;
-        const int ph = ph1;
-        const int cgdone = cd1;
-        const bool free_row = m1 != 0;
-        if (k + nw < nlist) {
-            r1 = r2;
-            ph1 = B.st[r1.p].phase;
-            cd1 = B.st[r1.p].cgdone;
-            m1 = V.mask[r1.s * kSlice + lane];
-            if (k + 2 * nw < nlist) r2 = B.srec[k + 2 * nw];
-        }
-        const int s = R.s;
-        const int p = R.p;
-        const int off = R.off, wsl = R.wv >> 7;   // first entry and width of the slice
-        const BState &S = B.st[p];
-        const int i = s * kSlice + lane;
-        const bool row = lane < (R.wv & 127);
-        double a[kBNV] = {0.0, 0.0, 0.0, 0.0, 0.0};
-        if (ph == PH_GRAD) {
-            a[2] = -INFINITY;
-            a[3] = INFINITY;
-            const double kc = gsell_row_at<WMAX, CM>(B, B.gv64, i, off, wsl, [&](int j) { return c[j]; });
-            if (row) {
-                const double gi = kc - B.fg[i];
-                const double cv = c[i];
-                V.g[i] = gi;
-                const double pg = cv > B.lo ? (cv < B.hi ? gi : fmax(gi, 0.0)) : fmin(gi, 0.0);
-                a[0] = pg * pg;
-                a[1] = (isfinite(gi) && isfinite(cv)) ? 0.0 : 1.0;
-                a[2] = fabs(fmax(cv - B.hi, fmin(gi, cv - B.lo)));
-                a[3] = cv;
-                a[4] = (cv == B.lo || cv == B.hi) ? 1.0 : 0.0;
-            }
-        } else if (ph == PH_CAUCHY) {
-            const double t = S.ttrial;
-            const double *__restrict__ g = V.g;
-            auto sv = [&](int j) {
-                const double cj = c[j];
-                return projb(B, cj + t * g[j]) - cj;
-            };
-            const double ksv = gsell_row_at<WMAX, CM>(B, gvals, i, off, wsl, sv);
-            if (row) {
-                (S.ksbuf ? V.ks1 : V.ks0)[i] = ksv;
-                const double si = sv(i);
-                a[0] = g[i] * si;
-                a[1] = si * ksv;
-                a[2] = si * si;
-            }
-        } else if (ph == PH_CG) {
-            const bool live = cgdone == 0 && row && free_row;
-            if (__ballot(live) != 0) {
-                const VV *__restrict__ z = V.z;
-                // float64 vectors: the own-row values load before the gathers
-                // (2 % faster on the 512-member batch; 5 % slower with
-                // float32 vectors, which load them after)
-                VV pold = VV(0), qold = VV(0), zi = VV(0);
-                if constexpr (sizeof(VV) == 8) {
-                    if (live) {
-                        pold = V.p[i];
-                        qold = V.q[i];
-                        zi = z[i];
-                    }
-                }
-                const double kz =
-                    gsell_row_at<WMAX, CM>(B, gvals, i, off, wsl, [&](int j) { return (double)z[j]; });
-                if (live) {
-                    if constexpr (sizeof(VV) != 8) {
-                        pold = V.p[i];
-                        qold = V.q[i];
-                        zi = z[i];
-                    }
-                    const double beta = S.beta;
-                    const VV pi = (VV)fma(beta, (double)pold, (double)zi);
-                    const VV qi = (VV)fma(beta, (double)qold, kz);
-                    V.p[i] = pi;
-                    V.q[i] = qi;
-                    a[0] = (double)pi * (double)qi;
-                }
-            }
-        } else if (ph == PH_SEARCH) {
-            const bool live = row && free_row;
-            if (__ballot(live) != 0) {
-                const double t = S.ts;
-                const VV *__restrict__ w = V.w;
-                auto sv = [&](int j) {
-                    const double cj = c[j];
-                    return projb(B, cj + t * (double)w[j]) - cj;
-                };
-                const double ksv = gsell_row_at<WMAX, CM>(B, gvals, i, off, wsl, sv);
-                if (live) {
-                    const double si = sv(i);
-                    a[0] = V.g[i] * si;
-                    a[1] = si * ksv;
-                    a[2] = si * si;
-                }
-            }
-        } else {
-            continue;   // no row work: the transition does not read these partials
-        }
-        // wave combination (the phase is uniform in the wave): only the
-        // values the phase reports
-        const int nv = ph == PH_GRAD ? 5 : (ph == PH_CG ? 1 : 3);
-        a[0] = wave_sum(a[0]);
-        if (nv >= 3) {
-            a[1] = wave_sum(a[1]);
-            if (nv == 3) {
-                a[2] = wave_sum(a[2]);
-            } else {
-                a[2] = wave_max(a[2]);
-                a[3] = wave_min(a[3]);
-                a[4] = wave_sum(a[4]);
-            }
-        }
-        if (lane == 0)
-            for (int v = 0; v < nv; v++) B.part[(size_t)s * kBNV + v] = a[v];
-    }
-}
-
 __device__ __forceinline__ void radius_update(BState &S)
 {
     if (isfinite(S.delta) && S.stepn >= 0.99 * S.delta) S.delta *= 4.0;
 }
 
-// First transition: combine the row-pass partials of the member and decide.
-__global__ __launch_bounds__(kFinBlock) void kb_step1(BDev B)
+// First transition: the decision on the row pass's sums a (none when the
+// phase had no row work).
+__device__ __forceinline__ void transition1(BState &S, const double *a)
 {
-    if ((int)blockIdx.x >= B.cnt[1]) return;
-    const int p = B.plist[blockIdx.x];
-    BState &S = B.st[p];
     const int ph = S.phase;
-    double a[kBNV] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    if (ph == PH_GRAD) {
-        const int ops[5] = {OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM};
-        if (!member_reduce<5>(B, p, ops, a)) return;
-    } else if (ph == PH_CAUCHY || ph == PH_SEARCH) {
-        const int ops[3] = {OP_SUM, OP_SUM, OP_SUM};
-        double b[3];
-        if (!member_reduce<3>(B, p, ops, b)) return;
-        a[0] = b[0], a[1] = b[1], a[2] = b[2];
-    } else if (ph == PH_CG) {
-        const int ops[1] = {OP_SUM};
-        double b[1];
-        if (!member_reduce<1>(B, p, ops, b)) return;
-        a[0] = b[0];
-    } else if (threadIdx.x != 0) {
-        return;
-    }
     const double n = S.n, nnz = S.nnz;
-    const double trial_bytes = 4.0 * (n + 1) + (S.ib + S.vb) * nnz + 32.0 * n;
+    const double trial_bytes = 4.0 * (n + 1) + S.eb * nnz + 32.0 * n;
     S.vop = VO_NONE;
     if (ph == PH_GRAD) {
         // gradient, KKT report, convergence test
         S.spmvs++;
-        S.bytes += 4.0 * (n + 1) + (S.ib + 8.0) * nnz + 32.0 * n;
+        S.bytes += 4.0 * (n + 1) + S.eg * nnz + 32.0 * n;
         if (a[1] != 0.0) {
             S.status = NN_ENONFINITE;
             S.phase = PH_DONE;
@@ -1078,133 +984,11 @@ __global__ __launch_bounds__(kFinBlock) void kb_step1(BDev B)
     }
 }
 
-// Vector pass: per listed slice, the operation the first transition chose.
-//   SETUP   c = P(c - t g), g += K s (accepted Cauchy trial); free = not
-//           (c == 0 and g >= 0); dm = 1/diag, r = -g on free rows; z = dm r;
-//           p = q = w = 0; r.z, r.r, #free, nnz of the free rows
-//   UPDATE  w += alpha p, r -= alpha q, z = dm r on free rows; r.z, r.r
-//   BREAK   min over w < 0 of c/(-w), g.w, w.w
-//   APPLYW  c = P(c + ts w)
-template <class VV>
-__global__ void kb_vec(BDev B, BVec<VV> V)
+// Second transition: the decision on the vector pass's sums a, and the phase of
+// the member's next global step.
+__device__ __forceinline__ void transition2(BState &S, const double *a)
 {
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wpb = blockDim.x >> 6;
-    const int nw = gridDim.x * wpb;
-    const int nlist = B.cnt[0];
-    int k = blockIdx.x * wpb + wid;
-    // the same pipeline over the slice records as the row pass; the mask of
-    // the next slice is read ahead too (only a set-up writes a mask, and only
-    // its own slice's, which it does not read)
-    SRec r1 = k < nlist ? B.srec[k] : SRec{0, 0, 0, 0};
-    SRec r2 = k + nw < nlist ? B.srec[k + nw] : SRec{0, 0, 0, 0};
-    int op1 = k < nlist ? B.st[r1.p].vop : VO_NONE;
-    uint8_t m1 = k < nlist ? V.mask[r1.s * kSlice + lane] : 0;
-    for (; k < nlist; k += nw) {
-        const SRec R = r1;
-        const int vop = op1;
-        const bool free_row = m1 != 0;
-        if (k + nw < nlist) {
-            r1 = r2;
-            op1 = B.st[r1.p].vop;
-            m1 = V.mask[r1.s * kSlice + lane];
-            if (k + 2 * nw < nlist) r2 = B.srec[k + 2 * nw];
-        }
-        if (vop == VO_NONE) continue;
-        const int s = R.s;
-        const BState &S = B.st[R.p];
-        const int i = s * kSlice + lane;
-        const bool row = lane < (R.wv & 127);
-        double *__restrict__ c = B.cg;
-        double a[4] = {0.0, 0.0, 0.0, 0.0};
-        if (vop == VO_SETUP) {
-            if (!row) {
-                V.mask[i] = 0;
-                V.dm[i] = V.r[i] = V.z[i] = V.p[i] = V.q[i] = V.w[i] = VV(0);
-            } else {
-                const double gi0 = V.g[i];
-                const double cv = projb(B, c[i] - S.t * gi0);
-                const double gi = gi0 + (S.cur ? V.ks1 : V.ks0)[i];
-                c[i] = cv;
-                V.g[i] = gi;
-                const bool fr = !((cv == B.lo && gi >= 0.0) || (cv == B.hi && gi <= 0.0));
-                const VV dmi = fr ? (VV)(1.0 / B.dg[i]) : VV(0);
-                const VV ri = fr ? (VV)(-gi) : VV(0);
-                const VV zi = dmi * ri;
-                V.mask[i] = fr ? 1 : 0;
-                V.dm[i] = dmi;
-                V.r[i] = ri;
-                V.z[i] = zi;
-                V.p[i] = VV(0);
-                V.q[i] = VV(0);
-                V.w[i] = VV(0);
-                a[0] = (double)ri * (double)zi;
-                a[1] = (double)ri * (double)ri;
-                a[2] = fr ? 1.0 : 0.0;
-                a[3] = fr ? (double)B.rlen[i] : 0.0;
-            }
-        } else if (vop == VO_UPDATE) {
-            if (row && free_row) {
-                const double alpha = S.alpha;
-                const VV ri = (VV)((double)V.r[i] - alpha * (double)V.q[i]);
-                const VV zi = V.dm[i] * ri;
-                V.w[i] = (VV)((double)V.w[i] + alpha * (double)V.p[i]);
-                V.r[i] = ri;
-                V.z[i] = zi;
-                a[0] = (double)ri * (double)zi;
-                a[1] = (double)ri * (double)ri;
-            }
-        } else if (vop == VO_BREAK) {
-            a[0] = INFINITY;
-            if (row) {
-                const double wi = (double)V.w[i];
-                if (wi < 0.0) a[0] = (c[i] - B.lo) / (-wi);
-                else if (wi > 0.0) a[0] = (B.hi - c[i]) / wi;
-                a[1] = V.g[i] * wi;
-                a[2] = wi * wi;
-            }
-        } else {   // VO_APPLYW
-            if (row) c[i] = projb(B, c[i] + S.ts * (double)V.w[i]);
-            continue;
-        }
-        // (an update reports two values, a breakpoint three)
-        a[0] = vop == VO_BREAK ? wave_min(a[0]) : wave_sum(a[0]);
-        a[1] = wave_sum(a[1]);
-        if (vop != VO_UPDATE) {
-            a[2] = wave_sum(a[2]);
-            a[3] = wave_sum(a[3]);
-        }
-        if (lane == 0)
-#pragma unroll
-            for (int v = 0; v < 4; v++) B.part[(size_t)s * kBNV + v] = a[v];
-    }
-}
-
-// Second transition: combine the vector-pass partials and choose the phase
-// of the member's next global step.
-__global__ __launch_bounds__(kFinBlock) void kb_step2(BDev B)
-{
-    if ((int)blockIdx.x >= B.cnt[1]) return;
-    const int p = B.plist[blockIdx.x];
-    BState &S = B.st[p];
     const int vop = S.vop;
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-    if (vop == VO_SETUP) {
-        const int ops[4] = {OP_SUM, OP_SUM, OP_SUM, OP_SUM};
-        if (!member_reduce<4>(B, p, ops, a)) return;
-    } else if (vop == VO_UPDATE) {
-        const int ops[2] = {OP_SUM, OP_SUM};
-        double b[2];
-        if (!member_reduce<2>(B, p, ops, b)) return;
-        a[0] = b[0], a[1] = b[1];
-    } else if (vop == VO_BREAK) {
-        const int ops[3] = {OP_MIN, OP_SUM, OP_SUM};
-        double b[3];
-        if (!member_reduce<3>(B, p, ops, b)) return;
-        a[0] = b[0], a[1] = b[1], a[2] = b[2];
-    } else if (threadIdx.x != 0) {
-        return;
-    }
     const double n = S.n;
     if (vop == VO_SETUP) {
         // CG start on the free face: stop before the first iteration when the
@@ -1231,7 +1015,7 @@ __global__ __launch_bounds__(kFinBlock) void kb_step2(BDev B)
         // iteration done: beta for the next one, stopping test on r.r
         const double rz = a[0], rr = a[1];
         const double nf = S.n_free, nzf = S.nnz_free;
-        S.bytes += n + 4.0 * nf + (S.ib + S.vb) * nzf + 5.0 * S.vb * nf + n + 8.0 * S.vb * nf;
+        S.bytes += n + 4.0 * nf + S.eb * nzf + 5.0 * S.vb * nf + n + 8.0 * S.vb * nf;
         S.it += 1;
         S.cg_its++;
         S.spmvs++;
@@ -1268,29 +1052,363 @@ __global__ __launch_bounds__(kFinBlock) void kb_step2(BDev B)
     S.vop = VO_NONE;
 }
 
-// ---------------------------------------------------------------- host side
-struct Shape {
-    int block = 256;   // threads per block
-    int per_cu = 8;    // blocks per CU (the grid is capped by the slice count)
+// What a pass needs of the member's new state.
+struct BAct {
+    int what;       // row pass: phase (PH_DONE: nothing to do); vector pass: operation
+    int buf;        // row pass: buffer of K s; vector pass: accepted buffer
+    double a, b;    // trial step or beta; alpha, Cauchy step or step along w
 };
 
-// size class -> tuned shape (per process; the class is (log2 rows, widest
-// slice class, precision)).  Contexts on different threads share it, so every
-// access holds shape_mutex(); the launch shape changes no arithmetic.
-std::map<std::tuple<int, int, int>, Shape> &shape_cache()
+// The sums of a pass, first NV values of the member's slice partials, into
+// sums (LDS), every thread of the block; the caller adds a barrier.
+template <int NV>
+__device__ __forceinline__ void member_sums(const BDev &B, const BTab &T, const double *part,
+                                            const int (&ops)[NV], double *sums)
 {
-    static std::map<std::tuple<int, int, int>, Shape> m;
-    return m;
+    double a[NV];
+    member_load<NV>(B, T, part, ops, a);
+    member_combine<NV>(ops, a, sums);
 }
 
-std::mutex &shape_mutex()
+// The member's transition on the partials of the pass before (the first one in
+// a vector pass, the second in a row pass).  Every block of the member comes to
+// the same result; the first one writes the new state to `out`.  The state and
+// the partials of a CG iteration (one value, or two) are loaded together, and
+// a member that stays in its CG needs no more than them: one barrier, after
+// which every thread has the decision.  Anything else goes through the
+// transition itself, on the state in LDS.  ahead() runs once those loads are
+// issued and issues others.  (Reading the block's first slices there, entries
+// and gathers or the update's vectors, measured 1-3 % slower on 64 members:
+// the registers cost more waves than the round trip hidden.)
+template <bool SECOND, class Ahead>
+__device__ __forceinline__ BAct block_transition(const BDev &B, const BBlk &K, const BTab &T,
+                                                 const BState *in, BState *out, BState &S,
+                                                 double *sums, Ahead ahead)
 {
-    static std::mutex mu;
-    return mu;
+    static_assert(sizeof(BState) % sizeof(int) == 0 && sizeof(BState) / sizeof(int) <= kFinBlock,
+                  "one word per thread");
+    constexpr int kWords = sizeof(BState) / sizeof(int);
+    constexpr int NF = SECOND ? 2 : 1;
+    __shared__ double sh[NF][kBWaves];
+    const double *part = SECOND ? B.part2 : B.part;
+    const int word = threadIdx.x < kWords ? reinterpret_cast<const int *>(in + K.p)[threadIdx.x] : 0;
+    double f[NF], f1[NF];
+    const int t1 = T.s0 + threadIdx.x, te = T.s0 + T.nsl;
+#pragma unroll
+    for (int k = 0; k < NF; k++) f1[k] = t1 < te ? part[(size_t)k * B.nslices + t1] : 0.0;
+    ahead();
+#pragma unroll
+    for (int k = 0; k < NF; k++) f[k] = 0.0 + f1[k];
+    for (int s = t1 + kFinBlock; s < te; s += kFinBlock)
+#pragma unroll
+        for (int k = 0; k < NF; k++) f[k] += part[(size_t)k * B.nslices + s];
+    if (threadIdx.x < kWords) reinterpret_cast<int *>(&S)[threadIdx.x] = word;
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int k = 0; k < NF; k++) {
+        f[k] = wave_sum(f[k]);
+        if (lane == 0) sh[k][wid] = f[k];
+    }
+    __syncthreads();
+    auto total = [&](int k) { return ((sh[k][0] + sh[k][1]) + sh[k][2]) + sh[k][3]; };
+    static_assert(kBWaves == 4, "four waves' sums in order");
+    BAct r{SECOND ? (int)PH_DONE : (int)VO_NONE, 0, 0.0, 0.0};
+    bool fast;
+    if constexpr (SECOND) {
+        const double rz = total(0), rr = total(1);
+        fast = S.vop == VO_UPDATE && isfinite(rz) && isfinite(rr) && rr > S.rr_stop &&
+               S.it + 1 < S.max_cg && rz > 0.0;
+        r.what = PH_CG;
+        r.a = rz / S.rz;   // beta
+        if (threadIdx.x == 0) {
+            sums[0] = rz;
+            sums[1] = rr;
+        }
+    } else {
+        const double pq = total(0);
+        fast = S.phase == PH_CG && S.cgdone == 0 && isfinite(pq) && pq > 0.0;
+        r.what = VO_UPDATE;
+        r.b = S.rz / pq;   // alpha
+        if (threadIdx.x == 0) sums[0] = pq;
+    }
+    if (fast && !K.first) return r;
+    __syncthreads();
+    if (!fast) {
+        if constexpr (SECOND) {
+            const int vop = S.vop;
+            if (vop == VO_SETUP) {
+                const int ops[4] = {OP_SUM, OP_SUM, OP_SUM, OP_SUM};
+                member_sums<4>(B, T, part, ops, sums);
+            } else if (vop == VO_BREAK) {
+                const int ops[3] = {OP_MIN, OP_SUM, OP_SUM};
+                member_sums<3>(B, T, part, ops, sums);
+            }
+        } else {
+            const int ph = S.phase;
+            if (ph == PH_GRAD) {
+                const int ops[5] = {OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM};
+                member_sums<5>(B, T, part, ops, sums);
+            } else if (ph == PH_CAUCHY || ph == PH_SEARCH) {
+                const int ops[3] = {OP_SUM, OP_SUM, OP_SUM};
+                member_sums<3>(B, T, part, ops, sums);
+            }
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        if constexpr (SECOND) transition2(S, sums);
+        else transition1(S, sums);
+    }
+    __syncthreads();
+    if (K.first && threadIdx.x < kWords)
+        reinterpret_cast<int *>(out + K.p)[threadIdx.x] = reinterpret_cast<const int *>(&S)[threadIdx.x];
+    if (fast) return r;
+    if constexpr (SECOND) {
+        r.what = S.phase == PH_CG && S.cgdone != 0 ? (int)PH_DONE : S.phase;
+        r.buf = S.ksbuf;
+        r.a = S.phase == PH_CAUCHY ? S.ttrial : (S.phase == PH_SEARCH ? S.ts : S.beta);
+    } else {
+        r.what = S.vop;
+        r.buf = S.cur;
+        r.b = S.vop == VO_SETUP ? S.t : (S.vop == VO_APPLYW ? S.ts : S.alpha);
+    }
+    return r;
 }
 
-int width_class(int wmax) { return wmax <= 8 ? 8 : (wmax <= 16 ? 16 : 32); }
+// Row pass: the second transition of the step before, then per slice the
+// matrix pass of the member's phase.
+//   GRAD    g = K c - f (float64 values); |pg|^2, #non-finite, ||min(c,g)||_inf,
+//           min c, #(c == 0)
+//   CAUCHY  s = P(c + ttrial g) - c gathered, ks = K s into buffer ksbuf;
+//           g.s, s.Ks, s.s
+//   CG      p <- z + beta p, q <- K z + beta q on the free rows; p.q
+//   SEARCH  s = P(c + ts w) - c on the free rows, K s; g.s, s.Ks, s.s
+template <int WMAX, int CM, class VT, class VV>
+__global__ __launch_bounds__(kFinBlock) void kb_rows(BDev B, const VT *__restrict__ gvals,
+                                                     BVec<VV> V)
+{
+    if ((int)blockIdx.x >= B.cnt[0]) return;
+    const BBlk K = B.blk[blockIdx.x];
+    const BTab &T = B.tab[K.p];
+    __shared__ BState S;
+    __shared__ double sums[kBNV];
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int nw = kBWaves;
+    int s = K.s + wid;
+    uint8_t m1 = 0;   // the next slice's flags, read ahead
+    auto ahead = [&] {
+        if (s < K.s + K.n) m1 = V.mask[s * kSlice + lane];
+    };
+    const BAct A = block_transition<true>(B, K, T, B.st, B.st2, S, sums, ahead);
+    const int ph = __builtin_amdgcn_readfirstlane(A.what);
+    // (no row work: the transition does not read these partials)
+    if (ph != PH_GRAD && ph != PH_CAUCHY && ph != PH_CG && ph != PH_SEARCH) return;
+    const double *__restrict__ c = B.cg;
+    for (; s < K.s + K.n; s += nw) {
+        const bool free_row = m1 != 0;
+        if (s + nw < K.s + K.n) m1 = V.mask[(s + nw) * kSlice + lane];
+        const int i = s * kSlice + lane;
+        const bool row = (s - T.s0) * kSlice + lane < T.nrow;
+        double a[kBNV] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        if (ph == PH_GRAD) {
+            a[2] = -INFINITY;
+            a[3] = INFINITY;
+            const double kc = gsell_row<WMAX, CM, 4>(B, T, B.gv64, s, i,
+                                                  [&](int ub, int l) { return (c + ub)[l]; });
+            if (row) {
+                const double gi = kc - B.fg[i];
+                const double cv = c[i];
+                V.g[i] = gi;
+                const double pg = cv > B.lo ? (cv < B.hi ? gi : fmax(gi, 0.0)) : fmin(gi, 0.0);
+                a[0] = pg * pg;
+                a[1] = (isfinite(gi) && isfinite(cv)) ? 0.0 : 1.0;
+                a[2] = fabs(fmax(cv - B.hi, fmin(gi, cv - B.lo)));
+                a[3] = cv;
+                a[4] = (cv == B.lo || cv == B.hi) ? 1.0 : 0.0;
+            }
+        } else if (ph == PH_CAUCHY) {
+            const double t = A.a;
+            const double *__restrict__ g = V.g;
+            auto sv = [&](int ub, int l) {
+                const double cj = (c + ub)[l];
+                return projb(B, cj + t * (g + ub)[l]) - cj;
+            };
+            const double ksv = gsell_row<WMAX, CM, 4>(B, T, gvals, s, i, sv);
+            if (row) {
+                (A.buf ? V.ks1 : V.ks0)[i] = ksv;
+                const double si = sv(0, i);
+                a[0] = g[i] * si;
+                a[1] = si * ksv;
+                a[2] = si * si;
+            }
+        } else if (ph == PH_CG) {
+            const bool live = row && free_row;
+            if (__ballot(live) != 0) {
+                const VV *__restrict__ z = V.z;
+                // the own-row values load before the gathers
+                VV pold = VV(0), qold = VV(0), zi = VV(0);
+                if (live) {
+                    pold = V.p[i];
+                    qold = V.q[i];
+                    zi = z[i];
+                }
+                const double kz = gsell_row<WMAX, CM, 8>(B, T, gvals, s, i,
+                                                         [&](int ub, int l) { return (z + ub)[l]; });
+                if (live) {
+                    const double beta = A.a;
+                    const VV pi = (VV)fma(beta, (double)pold, (double)zi);
+                    const VV qi = (VV)fma(beta, (double)qold, kz);
+                    V.p[i] = pi;
+                    V.q[i] = qi;
+                    a[0] = (double)pi * (double)qi;
+                }
+            }
+        } else {   // PH_SEARCH
+            const bool live = row && free_row;
+            if (__ballot(live) != 0) {
+                const double t = A.a;
+                const VV *__restrict__ w = V.w;
+                auto sv = [&](int ub, int l) {
+                    const double cj = (c + ub)[l];
+                    return projb(B, cj + t * (double)(w + ub)[l]) - cj;
+                };
+                const double ksv = gsell_row<WMAX, CM, 4>(B, T, gvals, s, i, sv);
+                if (live) {
+                    const double si = sv(0, i);
+                    a[0] = V.g[i] * si;
+                    a[1] = si * ksv;
+                    a[2] = si * si;
+                }
+            }
+        }
+        // wave combination (the phase is uniform in the wave): only the
+        // values the phase reports
+        const int nv = ph == PH_GRAD ? 5 : (ph == PH_CG ? 1 : 3);
+        a[0] = wave_sum(a[0]);
+        if (nv >= 3) {
+            a[1] = wave_sum(a[1]);
+            if (nv == 3) {
+                a[2] = wave_sum(a[2]);
+            } else {
+                a[2] = wave_max(a[2]);
+                a[3] = wave_min(a[3]);
+                a[4] = wave_sum(a[4]);
+            }
+        }
+        if (lane == 0)
+            for (int v = 0; v < nv; v++) B.part[(size_t)v * B.nslices + s] = a[v];
+    }
+}
 
+// Vector pass: the first transition, then per slice the operation it chose.
+//   SETUP   c = P(c - t g), g += K s (accepted Cauchy trial); free = not
+//           (c == 0 and g >= 0); dm = 1/diag, r = -g on free rows; z = dm r;
+//           p = q = w = 0; r.z, r.r, #free, nnz of the free rows
+//   UPDATE  w += alpha p, r -= alpha q, z = dm r on free rows; r.z, r.r
+//   BREAK   min over w < 0 of c/(-w), g.w, w.w
+//   APPLYW  c = P(c + ts w)
+template <class VV>
+__global__ __launch_bounds__(kFinBlock) void kb_vec(BDev B, BVec<VV> V)
+{
+    if ((int)blockIdx.x >= B.cnt[0]) return;
+    const BBlk K = B.blk[blockIdx.x];
+    const BTab &T = B.tab[K.p];
+    __shared__ BState S;
+    __shared__ double sums[kBNV];
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    int s = K.s + wid;
+    // the mask of the next slice is read ahead (only a set-up writes a mask,
+    // and only its own slice's, which it does not read)
+    uint8_t m1 = 0;
+    auto ahead = [&] {
+        if (s < K.s + K.n) m1 = V.mask[s * kSlice + lane];
+    };
+    const BAct A = block_transition<false>(B, K, T, B.st2, B.st, S, sums, ahead);
+    const int vop = __builtin_amdgcn_readfirstlane(A.what);
+    if (vop == VO_NONE) return;
+    for (; s < K.s + K.n; s += kBWaves) {
+        const bool free_row = m1 != 0;
+        if (s + kBWaves < K.s + K.n) m1 = V.mask[(s + kBWaves) * kSlice + lane];
+        const int i = s * kSlice + lane;
+        const bool row = (s - T.s0) * kSlice + lane < T.nrow;
+        double *__restrict__ c = B.cg;
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+        if (vop == VO_SETUP) {
+            if (!row) {
+                V.mask[i] = 0;
+                V.dm[i] = V.r[i] = V.z[i] = V.p[i] = V.q[i] = V.w[i] = VV(0);
+            } else {
+                const double gi0 = V.g[i];
+                const double cv = projb(B, c[i] - A.b * gi0);
+                const double gi = gi0 + (A.buf ? V.ks1 : V.ks0)[i];
+                c[i] = cv;
+                V.g[i] = gi;
+                const bool fr = !((cv == B.lo && gi >= 0.0) || (cv == B.hi && gi <= 0.0));
+                const VV dmi = fr ? (VV)(1.0 / B.dg[i]) : VV(0);
+                const VV ri = fr ? (VV)(-gi) : VV(0);
+                const VV zi = dmi * ri;
+                V.mask[i] = fr ? 1 : 0;
+                V.dm[i] = dmi;
+                V.r[i] = ri;
+                V.z[i] = zi;
+                V.p[i] = VV(0);
+                V.q[i] = VV(0);
+                V.w[i] = VV(0);
+                a[0] = (double)ri * (double)zi;
+                a[1] = (double)ri * (double)ri;
+                a[2] = fr ? 1.0 : 0.0;
+                a[3] = fr ? (double)B.rlen[i] : 0.0;
+            }
+        } else if (vop == VO_UPDATE) {
+            if (row && free_row) {
+                const double alpha = A.b;
+                const VV ri = (VV)((double)V.r[i] - alpha * (double)V.q[i]);
+                const VV zi = V.dm[i] * ri;
+                V.w[i] = (VV)((double)V.w[i] + alpha * (double)V.p[i]);
+                V.r[i] = ri;
+                V.z[i] = zi;
+                a[0] = (double)ri * (double)zi;
+                a[1] = (double)ri * (double)ri;
+            }
+        } else if (vop == VO_BREAK) {
+            a[0] = INFINITY;
+            if (row) {
+                const double wi = (double)V.w[i];
+                if (wi < 0.0) a[0] = (c[i] - B.lo) / (-wi);
+                else if (wi > 0.0) a[0] = (B.hi - c[i]) / wi;
+                a[1] = V.g[i] * wi;
+                a[2] = wi * wi;
+            }
+        } else {   // VO_APPLYW
+            if (row) c[i] = projb(B, c[i] + A.b * (double)V.w[i]);
+            continue;
+        }
+        // (an update reports two values, a breakpoint three)
+        a[0] = vop == VO_BREAK ? wave_min(a[0]) : wave_sum(a[0]);
+        a[1] = wave_sum(a[1]);
+        if (vop != VO_UPDATE) {
+            a[2] = wave_sum(a[2]);
+            a[3] = wave_sum(a[3]);
+        }
+        if (lane == 0) {
+            const int nv = vop == VO_UPDATE ? 2 : (vop == VO_BREAK ? 3 : 4);
+            for (int v = 0; v < nv; v++) B.part2[(size_t)v * B.nslices + s] = a[v];
+        }
+    }
+}
+
+// Second transition on its own, in place: the states the host reads (and the
+// next chunk's first row pass, which finds no vector operation to decide on).
+__global__ __launch_bounds__(kFinBlock) void kb_step2(BDev B)
+{
+    if ((int)blockIdx.x >= B.cnt[1]) return;
+    const int p = B.plist[blockIdx.x];
+    __shared__ BState S;
+    __shared__ double sums[kBNV];
+    block_transition<true>(B, BBlk{p, 0, 0, 1}, B.tab[p], B.st, B.st, S, sums, [] {});
+}
+
+// ---------------------------------------------------------------- host side
 // The same with the kernel's own begin and end recorded into e0, e1 when
 // they are not null (hipExtLaunchKernelGGL).
 #ifndef NNQP_BATCH_PAIRS
@@ -1409,13 +1527,13 @@ double row_bytes(const BState &S)
     const double n = S.n, nnz = S.nnz;
     switch (S.phase) {
     case PH_GRAD:
-        return 4.0 * (n + 1) + (S.ib + 8.0) * nnz + 32.0 * n;
+        return 4.0 * (n + 1) + S.eg * nnz + 32.0 * n;
     case PH_CAUCHY:
     case PH_SEARCH:
-        return 4.0 * (n + 1) + (S.ib + S.vb) * nnz + 32.0 * n;
+        return 4.0 * (n + 1) + S.eb * nnz + 32.0 * n;
     case PH_CG:
         return S.cgdone ? 0.0
-                        : n + 4.0 * S.n_free + (S.ib + S.vb) * S.nnz_free + 5.0 * S.vb * S.n_free;
+                        : n + 4.0 * S.n_free + S.eb * S.nnz_free + 5.0 * S.vb * S.n_free;
     default:
         return 0.0;
     }
@@ -1490,16 +1608,36 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     // offset pairs, one 16-byte load per value pair): 95-97 instead of
     // 90-106 us (its quad layout was no faster, column-major int16 offsets
     // slower).
-    const bool quad = mixed && all_d16;
-    const bool pair = !mixed && all_d16 && NNQP_BATCH_PAIRS;
-    const int layout = quad ? CM_Q4 : (pair ? CM_P2 : CM_I32);
-    const double ib = quad || pair ? 2.0 : 4.0;   // bytes per column index
+    // diagonal arrays when every member has them in one regular run
+    bool all_diag = true;
+    std::vector<DiagReg> dreg(P);
+    {
+        size_t scratch = 0;
+        for (int p = 0; p < P; p++)
+            if (K[p]->n > 0 && !K[p]->diag_tried)
+                scratch = std::max(scratch, sizeof(short) * (size_t)std::max<int64_t>(K[p]->nsell, 1));
+        void *tmp = nullptr;
+        if (scratch > 0 && dev_malloc(ctx->al, &tmp, scratch) != hipSuccess)
+            return fail(ctx, NN_EOOM, "batch workspace allocation failed");
+        nn_status rc = NN_OK;
+        for (int p = 0; p < P && rc == NN_OK && all_diag; p++) {
+            if (K[p]->n == 0) continue;
+            rc = diag_find(ctx, K[p], tmp);
+            all_diag = rc == NN_OK && diag_one_run(K[p], &dreg[p]);
+        }
+        dev_free(ctx->al, tmp);
+        if (rc != NN_OK) return rc;
+    }
+    const bool quad = !all_diag && mixed && all_d16;
+    const bool pair = !all_diag && !mixed && all_d16 && NNQP_BATCH_PAIRS;
+    const int layout = all_diag ? CM_DIAG : quad ? CM_Q4 : (pair ? CM_P2 : CM_I32);
 
     // ---- tables, work vectors, lists, pinned state mirrors
     Arena A(ctx->al);
     int *d_sprob = A.d<int>(S), *d_s0 = A.d<int>(P), *d_nrow = A.d<int>(P);
-    int *d_list = A.d<int>((size_t)2 + P + S);
-    SRec *d_srec = A.d<SRec>(S);
+    int *d_list = A.d<int>((size_t)2 + P);
+    BBlk *d_blk = A.d<BBlk>(S);
+    BTab *d_tab = A.d<BTab>(P);
     const int **d_so = A.d<const int *>(P), **d_sc = A.d<const int *>(P),
               **d_rp = A.d<const int *>(P);
     const short **d_sd = A.d<const short *>(P);
@@ -1509,8 +1647,9 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     const float **d_v32 = A.d<const float *>(P);
     double **d_c = A.d<double *>(P);
     uint8_t **d_act = A.d<uint8_t *>(P);
-    BState *d_st = A.d<BState>(P);
-    double *d_part = A.d<double>((size_t)S * kBNV), *d_pres = A.d<double>((size_t)P * kBNV);
+    BState *d_st = A.d<BState>(P), *d_st2 = A.d<BState>(P);
+    double *d_part = A.d<double>((size_t)S * kBNV), *d_part2 = A.d<double>((size_t)S * kBNV),
+           *d_pres = A.d<double>((size_t)P * kBNV);
     double *g = A.d<double>(R), *ks0 = A.d<double>(R), *ks1 = A.d<double>(R);
     uint8_t *mask = A.d<uint8_t>(R);
     // concatenated layout: vectors and the block-diagonal matrix
@@ -1524,7 +1663,7 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     double *cg = A.d<double>(R), *fg = A.d<double>(R), *dg = A.d<double>(R);
     int *rlen = A.d<int>(R);
     double *ft = fg;   // a transient step's loads f + M c/dt are formed in place
-    int *gso = A.d<int>(S + 1), *gcol = A.d<int>(E);
+    int *gso = A.d<int>(S + 1), *gcol = all_diag ? nullptr : A.d<int>(E);
     int64_t *d_ebase = A.d<int64_t>(P);
     double *gv64 = A.d<double>(E);
     float *gv32 = mixed ? A.d<float>(E) : nullptr;
@@ -1547,10 +1686,13 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     constexpr int kStage = 4;
     BState *st_stage[kStage];
     int *lst_stage[kStage];
+    BBlk *blk_stage[kStage];
     for (int k = 0; k < kStage; k++) {
         st_stage[k] = A.h<BState>(P);
-        lst_stage[k] = A.h<int>((size_t)2 + P + S);
+        lst_stage[k] = A.h<int>((size_t)2 + P);
+        blk_stage[k] = A.h<BBlk>(S);
     }
+    BTab *tabs = A.h<BTab>(P);
     if (!A.ok) return fail(ctx, NN_EOOM, "batch workspace allocation failed");
     Events ev_st, ev_lst, ev_t;
     if (!ev_st.create(kStage, hipEventDisableTiming) ||
@@ -1583,6 +1725,19 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         NN_HIP_TRY(ctx, hipMemcpyAsync(d_s0, s0.data(), sizeof(int) * P, hipMemcpyHostToDevice, st));
         NN_HIP_TRY(ctx,
                    hipMemcpyAsync(d_nrow, nrow.data(), sizeof(int) * P, hipMemcpyHostToDevice, st));
+        for (int p = 0; p < P; p++) {
+            BTab t{};
+            t.s0 = s0[p];
+            t.nsl = nsl[p];
+            t.nrow = nrow[p];
+            if (all_diag && nrow[p] > 0) {
+                t.W = K[p]->wmax <= 8 ? 7 : 15;
+                t.reg = dreg[p];
+                t.reg.b0 = (int)(ebase[p] + dreg[p].b0 - (int64_t)s0[p] * kSlice);
+            }
+            tabs[p] = t;
+        }
+        NN_HIP_TRY(ctx, hipMemcpyAsync(d_tab, tabs, sizeof(BTab) * P, hipMemcpyHostToDevice, st));
         NN_HIP_TRY(ctx, hipMemcpyAsync(d_ebase, ebase.data(), sizeof(int64_t) * P,
                                        hipMemcpyHostToDevice, st));
         const int e_total = (int)E;
@@ -1595,8 +1750,8 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     B.nslices = (int)S;
     B.cnt = d_list;
     B.plist = d_list + 2;
-    B.slist = d_list + 2 + P;
-    B.srec = d_srec;
+    B.blk = d_blk;
+    B.tab = d_tab;
     B.sprob = d_sprob;
     B.s0 = d_s0;
     B.nrow = d_nrow;
@@ -1613,7 +1768,9 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     B.mv = d_mv;
     B.act_out = d_act;
     B.st = d_st;
+    B.st2 = d_st2;
     B.part = d_part;
+    B.part2 = d_part2;
     B.pres = d_pres;
     B.gso = gso;
     B.gcol = gcol;
@@ -1641,7 +1798,8 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         M.rtol2 = o->inner_rtol * o->inner_rtol;
         M.n = (double)nrow[p];
         M.nnz = (double)K[p]->nnz;
-        M.ib = ib;
+        M.eb = entry_bytes(K[p], vb, all_diag, quad || pair);
+        M.eg = entry_bytes(K[p], 8.0, all_diag, quad || pair);
         M.vb = vb;
         M.mixed = mixed ? 1 : 0;
     }
@@ -1660,19 +1818,13 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
                    hipSuccess &&
                hipStreamSynchronize(st) == hipSuccess;
     };
-    // The members still running, and their slices, as device lists: rebuilt
-    // and uploaded only when the set changes.
+    // The members still running and their blocks, as device lists: rebuilt
+    // and uploaded only when the set changes.  A block takes `per` slices of
+    // one member, four at a time (one per wavefront): as many as spread the
+    // running slices over kBGrid blocks, at most kBMost (results do not depend
+    // on it).
     std::vector<char> sel(P, 0), sel_cur(P, 2);
-    int n_sl = 0, n_pr = 0;
-    // The slice records read the concatenated layout's slice offsets (gso),
-    // which kb_gather writes: they are built once it has run, and again
-    // whenever the list changes after that.
-    bool layout_ready = false;
-    auto build_recs = [&]() -> bool {
-        hipLaunchKernelGGL(kb_recs, dim3((unsigned)std::max(1, (n_sl + 255) / 256)), dim3(256), 0, st,
-                           B);
-        return hipGetLastError() == hipSuccess;
-    };
+    int n_bl = 0, n_pr = 0;
     auto select = [&]() -> bool {
         bool same = true;
         for (int p = 0; p < P; p++) {
@@ -1684,22 +1836,29 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         lst_next = (lst_next + 1) % kStage;
         if (hipEventSynchronize(ev_lst.ev[k]) != hipSuccess) return false;
         int *h = lst_stage[k];
-        int np = 0, ns = 0;
+        BBlk *bl = blk_stage[k];
+        int np = 0, nb = 0;
+        int64_t ns = 0;
+        for (int p = 0; p < P; p++)
+            if (sel[p]) ns += nsl[p];
+        const int per = (int)std::min<int64_t>(
+            kBMost, std::max<int64_t>(1, (ns + (int64_t)kBGrid * kBWaves - 1) / ((int64_t)kBGrid * kBWaves)) * kBWaves);
         for (int p = 0; p < P; p++) {
             sel_cur[p] = sel[p];
             if (!sel[p]) continue;
             h[2 + np++] = p;
-            for (int t = 0; t < nsl[p]; t++) h[2 + P + ns++] = s0[p] + t;
+            for (int t = 0; t < nsl[p]; t += per)
+                bl[nb++] = BBlk{p, s0[p] + t, std::min(per, nsl[p] - t), t == 0 ? 1 : 0};
         }
-        h[0] = ns;
+        h[0] = nb;
         h[1] = np;
-        n_sl = ns;
+        n_bl = nb;
         n_pr = np;
-        if (hipMemcpyAsync(d_list, h, sizeof(int) * ((size_t)2 + P + ns), hipMemcpyHostToDevice,
-                           st) != hipSuccess ||
-            hipEventRecord(ev_lst.ev[k], st) != hipSuccess)
-            return false;
-        return !layout_ready || build_recs();
+        return hipMemcpyAsync(d_list, h, sizeof(int) * ((size_t)2 + np), hipMemcpyHostToDevice, st) ==
+                   hipSuccess &&
+               (nb == 0 || hipMemcpyAsync(d_blk, bl, sizeof(BBlk) * nb, hipMemcpyHostToDevice, st) ==
+                               hipSuccess) &&
+               hipEventRecord(ev_lst.ev[k], st) == hipSuccess;
     };
 
     int num_cu = 256;
@@ -1708,11 +1867,7 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         if (hipGetDeviceProperties(&prop, ctx->device) == hipSuccess && prop.multiProcessorCount > 0)
             num_cu = prop.multiProcessorCount;
     }
-    Shape sh;
-    auto grid_for = [&](const Shape &t, int64_t slices) {
-        const int64_t blocks = (slices + t.block / 64 - 1) / (t.block / 64);
-        return (int)std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)num_cu * t.per_cu));
-    };
+    auto grid_for = [&](int blocks) { return (unsigned)std::max(1, blocks); };
 
     NN_HIP_TRY(ctx, push() ? hipSuccess : hipErrorUnknown);
     NN_HIP_TRY(ctx, select() ? hipSuccess : hipErrorUnknown);
@@ -1720,18 +1875,16 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
 
     // ---- transient right-hand sides (from c^n, before the start point is set)
     if (transient)
-        NN_BDISPATCH(wmax, (kb_transient_rhs<WM>), grid_for(sh, n_sl), sh.block, st, B, dt, ft);
+        NN_BDISPATCH(wmax, (kb_transient_rhs<WM>), grid_for(n_bl), kFinBlock, st, B, dt, ft);
     // ---- the members into the concatenated layout
     {
         const int64_t blocks = std::min<int64_t>((S + 3) / 4, (int64_t)num_cu * 8);
         hipLaunchKernelGGL(kb_gather, dim3((int)std::max<int64_t>(blocks, 1)), dim3(256), 0, st, B,
                            (const int64_t *)d_ebase, gso, gcol, gd16, gv64, gv32, dg, rlen,
                            transient ? 0 : 1, layout);
-        layout_ready = true;
-        NN_HIP_TRY(ctx, build_recs() ? hipSuccess : hipErrorUnknown);
     }
     // ---- start point and load statistics
-    hipLaunchKernelGGL(kb_init, dim3(grid_for(sh, n_sl)), dim3(sh.block), 0, st, B,
+    hipLaunchKernelGGL(kb_init, dim3(grid_for(n_bl)), dim3(kFinBlock), 0, st, B,
                        o->c0_mode == 1 ? 1 : 0, std::min(std::max(o->c0_value, o->lower), o->upper));
     hipLaunchKernelGGL(kb_reduce_init, dim3(std::max(n_pr, 1)), dim3(kFinBlock), 0, st, B);
     NN_HIP_TRY(ctx, hipMemcpyAsync(pres, d_pres, sizeof(double) * P * kBNV, hipMemcpyDeviceToHost,
@@ -1757,87 +1910,35 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     NN_HIP_TRY(ctx, push() ? hipSuccess : hipErrorUnknown);
     NN_HIP_TRY(ctx, select() ? hipSuccess : hipErrorUnknown);
 
-    // ---- launch shape for this size class
-    const auto key = std::make_tuple((int)std::log2((double)R), width_class(wmax), (int)mixed);
-    auto &cache = shape_cache();
-    bool cached = false;
-    {
-        std::lock_guard<std::mutex> lk(shape_mutex());
-        auto it = cache.find(key);
-        if (it != cache.end()) {
-            sh = it->second;
-            cached = true;
-        }
-    }
-    if (!cached && n_pr > 0) {
-        // time the gradient pass over all running members for each candidate
-        // shape; it writes only g and the slice partials, which the first
-        // global step overwrites
-        float best = INFINITY;
-        Shape pick = sh;
-        for (int blk : {256, 512, 1024})
-            for (int per_cu : {2, 4, 8}) {
-                if (blk * per_cu > 4096) continue;
-                const Shape cand{blk, per_cu};
-                const int gsz = grid_for(cand, n_sl);
-                if (quad) NN_BDISPATCH(wmax, (kb_grad<WM, CM_Q4>), gsz, blk, st, B, g);   // warm-up
-                else if (pair) NN_BDISPATCH(wmax, (kb_grad<WM, CM_P2>), gsz, blk, st, B, g);
-                else NN_BDISPATCH(wmax, (kb_grad<WM, CM_I32>), gsz, blk, st, B, g);
-                NN_HIP_TRY(ctx, hipEventRecord(t0, st));
-                for (int rep = 0; rep < 3; rep++)
-                    if (quad) NN_BDISPATCH(wmax, (kb_grad<WM, CM_Q4>), gsz, blk, st, B, g);
-                    else if (pair) NN_BDISPATCH(wmax, (kb_grad<WM, CM_P2>), gsz, blk, st, B, g);
-                    else NN_BDISPATCH(wmax, (kb_grad<WM, CM_I32>), gsz, blk, st, B, g);
-                NN_HIP_TRY(ctx, hipEventRecord(t1, st));
-                NN_HIP_TRY(ctx, hipEventSynchronize(t1));
-                float ms = 0.f;
-                NN_HIP_TRY(ctx, hipEventElapsedTime(&ms, t0, t1));
-                if (ms < best) {
-                    best = ms;
-                    pick = cand;
-                }
-            }
-        sh = pick;
-        {
-            std::lock_guard<std::mutex> lk(shape_mutex());
-            cache[key] = sh;
-        }
-        if (o->verbose)
-            std::fprintf(stderr,
-                         "nnqp batch shape: %lld rows, slice width %d -> %d threads, %d blocks/CU\n",
-                         (long long)R, wmax, sh.block, sh.per_cu);
-        NN_HIP_TRY(ctx, hipEventRecord(t0, st));   // the call's clock restarts after tuning
-    }
-    const int blk = sh.block;
-
-    // ---- one global step on stream s with grids gr (slices) and fg (members),
-    // the row and vector passes optionally bracketed by timing events
-    // (with events, the row and vector passes record their own begin and
-    // end into ev[0..1] and ev[2..3])
-    auto step = [&](hipStream_t s, int gr, int fg, hipEvent_t *ev) {
+    // ---- one global step on stream s with gr blocks, the row and vector passes
+    // optionally recording their own begin and end into ev[0..1] and ev[2..3]
+    auto step = [&](hipStream_t s, unsigned gr, hipEvent_t *ev) {
         hipEvent_t e0 = ev ? ev[0] : nullptr, e1 = ev ? ev[1] : nullptr;
-        if (quad)
-            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_Q4, float, float>), gr, blk, s, e0, e1, B,
+        if (all_diag && mixed)
+            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_DIAG, float, float>), gr, kFinBlock, s, e0, e1, B,
+                            (const float *)gv32, V32);
+        else if (all_diag)
+            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_DIAG, double, double>), gr, kFinBlock, s, e0, e1, B,
+                            (const double *)gv64, V64);
+        else if (quad)
+            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_Q4, float, float>), gr, kFinBlock, s, e0, e1, B,
                             (const float *)gv32, V32);
         else if (mixed)
-            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_I32, float, float>), gr, blk, s, e0, e1, B,
+            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_I32, float, float>), gr, kFinBlock, s, e0, e1, B,
                             (const float *)gv32, V32);
         else if (pair)
-            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_P2, double, double>), gr, blk, s, e0, e1, B,
+            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_P2, double, double>), gr, kFinBlock, s, e0, e1, B,
                             (const double *)gv64, V64);
         else
-            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_I32, double, double>), gr, blk, s, e0, e1, B,
+            NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_I32, double, double>), gr, kFinBlock, s, e0, e1, B,
                             (const double *)gv64, V64);
-        hipLaunchKernelGGL(kb_step1, dim3(fg), dim3(kFinBlock), 0, s, B);
-        if (ev && mixed)
-            hipExtLaunchKernelGGL((kb_vec<float>), dim3(gr), dim3(blk), 0, s, ev[2], ev[3], 0, B, V32);
-        else if (ev)
-            hipExtLaunchKernelGGL((kb_vec<double>), dim3(gr), dim3(blk), 0, s, ev[2], ev[3], 0, B, V64);
-        else if (mixed)
-            hipLaunchKernelGGL((kb_vec<float>), dim3(gr), dim3(blk), 0, s, B, V32);
-        else
-            hipLaunchKernelGGL((kb_vec<double>), dim3(gr), dim3(blk), 0, s, B, V64);
-        hipLaunchKernelGGL(kb_step2, dim3(fg), dim3(kFinBlock), 0, s, B);
+        e0 = ev ? ev[2] : nullptr, e1 = ev ? ev[3] : nullptr;
+        if (mixed) NN_BLAUNCH_EV((kb_vec<float>), gr, kFinBlock, s, e0, e1, B, V32);
+        else NN_BLAUNCH_EV((kb_vec<double>), gr, kFinBlock, s, e0, e1, B, V64);
+    };
+    // the last transition of a chunk
+    auto settle = [&](hipStream_t s, int members) {
+        hipLaunchKernelGGL(kb_step2, dim3(std::max(members, 1)), dim3(kFinBlock), 0, s, B);
     };
 
     // ---- chunks of global steps.  Without profiling a chunk is captured
@@ -1855,18 +1956,19 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         ctx->cap_stream = nullptr;
         use_graph = false;
     }
-    auto graph_for = [&](int slices) -> hipGraphExec_t {
+    auto graph_for = [&](int blocks) -> hipGraphExec_t {
         int cls = 0;
-        while ((1 << cls) < slices) cls++;
+        while ((1 << cls) < blocks) cls++;
         auto it = graphs.by_class.find(cls);
         if (it != graphs.by_class.end()) return it->second.exec;
-        const int gr = grid_for(sh, (int64_t)1 << cls);
-        const int fg = std::min(P, 1 << cls);   // a listed member owns at least one slice
+        const unsigned gr = 1u << cls;
+        const int fg = std::min(P, 1 << cls);   // a listed member owns at least one block
         if (hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeRelaxed) != hipSuccess) {
             (void)hipGetLastError();
             return nullptr;
         }
-        for (int k = 0; k < chunk; k++) step(ctx->cap_stream, gr, fg, nullptr);
+        for (int k = 0; k < chunk; k++) step(ctx->cap_stream, gr, nullptr);
+        settle(ctx->cap_stream, fg);
         hipGraph_t gph = nullptr;
         const bool ended = hipStreamEndCapture(ctx->cap_stream, &gph) == hipSuccess && gph;
         (void)hipGetLastError();
@@ -1899,7 +2001,7 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             break;
         }
         if (n_pr == 0) break;
-        const int gr = grid_for(sh, n_sl);
+        const unsigned gr = grid_for(n_bl);
         if (ctx->prof) {
             // one step; algorithmic bytes of the row pass from the states
             double brow = 0.0, brow_csr = 0.0;
@@ -1908,7 +2010,8 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
                     brow += row_bytes(hs[p]);
                     brow_csr += row_bytes_csr(hs[p]);
                 }
-            step(st, gr, std::max(n_pr, 1), ev_step.ev.data());
+            step(st, gr, ev_step.ev.data());
+            settle(st, n_pr);
             steps++;
             if (!pull()) {
                 err = fail(ctx, NN_EHIP, "batch read-back");
@@ -1924,14 +2027,15 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             (void)hipGetLastError();
             continue;
         }
-        hipGraphExec_t ex = use_graph ? graph_for(n_sl) : nullptr;
+        hipGraphExec_t ex = use_graph ? graph_for(n_bl) : nullptr;
         if (ex) {
             if (hipGraphLaunch(ex, st) != hipSuccess) {
                 err = fail(ctx, NN_EHIP, "graph launch");
                 break;
             }
         } else {
-            for (int k = 0; k < chunk; k++) step(st, gr, std::max(n_pr, 1), nullptr);
+            for (int k = 0; k < chunk; k++) step(st, gr, nullptr);
+            settle(st, n_pr);
         }
         steps += chunk;
         if (!pull()) {
