@@ -195,3 +195,103 @@ def test_one_workgroup_engine_with_the_matrix_in_registers(ctx, name):
     assert torch.equal(c, cz)
     K.free()
     Z.free()
+
+
+def _fan(m, every):
+    """A free hub with m ring nodes, every `every`-th of them free, inside a
+    Dirichlet ring: the hub's row has 1 + ceil(m / every) columns of m
+    triangles.  A small square beside it holds ordinary rows."""
+    from paper_1506_08435_amd.workloads import Problem
+    sq = W.square2d(9)
+    a = 2 * np.pi * np.arange(m) / m
+    ring = np.stack([np.cos(a), np.sin(a)], 1)
+    xy = np.concatenate([sq.coords, [[5.0, 5.0]], 5.0 + ring, 5.0 + 2.0 * ring])
+    s = len(sq.coords)
+    hub, r0, q0 = s, s + 1, s + 1 + m
+    i = np.arange(m)
+    j = (i + 1) % m
+    el = np.concatenate([
+        np.stack([r0 + i, r0 + j, hub + 0 * i], 1),
+        np.stack([r0 + i, q0 + i, q0 + j], 1),
+        np.stack([q0 + j, r0 + j, r0 + i], 1),
+        sq.elems])
+    fixed = np.concatenate([sq.dirichlet, [0], (i % every != 0).astype(np.uint8), np.ones(m, np.uint8)])
+    rng = np.random.default_rng(m)
+    D = np.array([[[2.0, 0.3], [0.3, 1.0]]])
+    return Problem(name="fan", dim=2, coords=xy, elems=el.astype(np.int32), D=D,
+                   kscale=np.concatenate([rng.uniform(0.5, 2.0, 3 * m),
+                                          np.random.default_rng(1).uniform(0.5, 2.0, len(sq.elems))]),
+                   f_elem=rng.uniform(-1, 1, len(el)),
+                   dirichlet=fixed.astype(np.uint8), cells=(1, 1), h=1.0,
+                   dirichlet_values=rng.uniform(0, 1, len(xy)))
+
+
+# the longest row and the most elements at a node that the device phase takes,
+# one more of each, and a hub far past both
+@pytest.mark.parametrize("m,every", [(47, 1), (48, 1), (96, 3), (97, 3), (300, 1)])
+@pytest.mark.parametrize("mass", [False, True])
+def test_assembly_with_a_hub(ctx, m, every, mass):
+    """Sums of at most 300 products of float64: within 300 ulp of the largest."""
+    p = _fan(m, every)
+    K, F, dof = ctx.assemble(p, with_mass=mass)
+    S = oracle.assemble(p, with_mass=mass)
+    out = ctx.matrix_export(K)
+    assert np.array_equal(out[0], S.rowptr) and np.array_equal(out[1], S.col)
+    assert np.array_equal(dof, S.dof)
+    tol = 300 * np.finfo(np.float64).eps
+    assert np.abs(out[2] - S.K).max() <= tol * np.abs(S.K).max()
+    if mass:
+        assert np.abs(out[3] - S.M).max() <= tol * np.abs(S.M).max()
+    assert np.abs(F.cpu().numpy() - S.F).max() <= tol * max(np.abs(S.F).max(), np.abs(S.K).max())
+    # rows of the same mesh without the hub: the same bits on either path
+    q = _fan(40, 1)
+    Q, _, _ = ctx.assemble(q, with_mass=mass)
+    qr, qc, qv = ctx.matrix_export(Q)[:3]
+    n = int((W.square2d(9).dirichlet == 0).sum())
+    k = qr[n]
+    assert np.array_equal(out[0][: n + 1], qr[: n + 1]) and np.array_equal(out[1][:k], qc[:k])
+    assert np.array_equal(out[2][:k], qv[:k])
+    Q.free()
+    K.free()
+
+
+@pytest.mark.parametrize("what", ["node", "coord", "D", "f", "ks", "dval", "order", "none"])
+def test_assembly_refusals(ctx, what):
+    """Each kind of bad input is refused with its own status, and the node
+    ids before everything else; the outcome of a mesh without elements or
+    nodes stays what it was."""
+    from paper_1506_08435_amd import nnqp
+    import dataclasses
+    p = W.config_transient3d(5, 4, 3, ell=2.0)
+    p = dataclasses.replace(p, coords=p.coords.copy(), elems=p.elems.copy(), D=p.D.copy(),
+                            f_elem=p.f_elem.copy(), kscale=np.ones(len(p.elems)),
+                            dirichlet=p.dirichlet.copy(), dirichlet_values=np.zeros(len(p.coords)))
+    p.dirichlet[0] = 1
+    status, text = nnqp.NN_ENONFINITE, None
+    if what in ("node", "order"):
+        p.elems[-1, 1] = len(p.coords)
+        status, text = nnqp.NN_EINVAL, "out of range"
+    if what in ("coord", "order"):
+        p.coords[-1, 0] = np.nan
+        text = text or "coordinate"
+    if what == "D":
+        p.D[0, 0, 0] = np.inf
+        text = "diffusivity"
+    if what in ("f", "order"):
+        p.f_elem[3] = np.nan
+        text = text or "source"
+    if what in ("ks", "f"):
+        p.kscale[3] = 0.0          # the same element: its source is looked at first
+        text = text or "kscale"
+    if what == "dval":
+        p.dirichlet_values[0] = -np.inf
+        text = "Dirichlet"
+    if what == "none":
+        q = dataclasses.replace(p, elems=p.elems[:0], f_elem=p.f_elem[:0], kscale=p.kscale[:0])
+        with pytest.raises(nnqp.NnError) as e:
+            ctx.assemble(q)
+        assert e.value.status == nnqp.NN_ENOTSPD and "row 0" in str(e.value)
+        return
+    with pytest.raises(nnqp.NnError) as e:
+        ctx.assemble(p)
+    assert e.value.status == status and text in str(e.value)
