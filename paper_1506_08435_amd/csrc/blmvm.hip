@@ -10,7 +10,7 @@
 //   1. Pair pass (one kernel over the rows): pg at the current point, the new
 //      y = pg - pg_prev when a step was just taken, and every inner product
 //      the compact representation needs (s_j.pg, y_j.pg, s_j.y, y_j.y, s.s).
-//   2. Coefficient kernel (one wavefront): accepts the new pair when
+//   2. Coefficient kernel (one block): accepts the new pair when
 //      s.y > 1e-12 |s| |y| (else drops it; a full memory then loses its
 //      oldest pair), sets gamma = s.y / y.y, and solves the small triangular
 //      systems of the compact form (Byrd, Nocedal & Schnabel 1994)
@@ -26,7 +26,8 @@
 //      d (capped at the first crossing); otherwise projected backtracking
 //      c(t) = P(c + t d), t = 1, 1/2, ..., until the sufficient-decrease test
 //      holds, finishing with the exact step on the segment [0, crossing] if t
-//      reaches it.  Each trial is one matrix pass that gathers P(c + t d) and
+//      reaches it.  Each trial is one matrix pass that gathers P(c + t d), at
+//      t = 1 as the direction pass left it, and
 //      returns the gradient K c(t) - f at the trial point.
 //   5. Step: c <- c(t), s stored in the next pair slot, g updated; done by
 //      the next iteration's pair pass (one pass over the rows fewer), or by a
@@ -66,8 +67,6 @@ struct LmState {
     double yy[kLmMax][kLmMax];   // y_a . y_b by slot
     double sc[kLmMax];           // coefficient of s_slot in H pg
     double yc[kLmMax];           // coefficient of y_slot in H pg
-    double bmin, gd;             // direction: first bound crossing, g.d
-    double gs, sks;              // trial at t = 1: g.s, s.(gn - g)
 };
 
 // slot j is live in the pair pass: a stored pair, or the pair being formed
@@ -77,21 +76,82 @@ __device__ __forceinline__ bool lm_live(int j, int M, int count, int head, int p
     return (pending && j == head) || (age >= 1 && age <= count) || (count == M && j == head);
 }
 
+// The pair pass holds 4M + 3 accumulators per lane (95 VGPRs at M = 5), so
+// one 1024-thread block fits a CU: it runs one block per CU and walks more
+// slices per wavefront instead of queueing a second round of blocks.
+constexpr int kPairBlocks = 256;
+
+// Wavefront totals of NV sums: a[j] of the lanes 16 q .. 16 q + 15 becomes the
+// total of value wave_sums_value<NV>(j, q), the bits wave_sum would give.  The
+// levels 32 and 16 of the butterfly add the same pair in both its lanes, so
+// two values share a register after each: a swap of half the lanes between
+// them and one addition, and the last four levels run on a quarter of the
+// values.  At 23 values a wavefront issues 130 instructions instead of 410; a
+// full CU issues them for four wavefronts on each SIMD (pair pass of 166 k
+// rows, five pairs: 11.4 -> 7.4 us).
+template <int NV>
+__host__ __device__ constexpr int wave_sums_regs() { return (NV + 3) / 4; }
+template <int NV>
+__device__ __forceinline__ int wave_sums_value(int j, int q)
+{
+    constexpr int G = wave_sums_regs<NV>();   // q = 0: j, 1: j + G, 2: j + 2G, 3: j + 3G
+    return j + G * q;
+}
+
+__device__ __forceinline__ void swap32(double &a, double &b)   // a: low halves, b: high halves
+{
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double(h[0], l[0]);
+    b = __hiloint2double(h[1], l[1]);
+}
+__device__ __forceinline__ void swap16(double &a, double &b)   // a: even rows, b: odd rows
+{
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double(h[0], l[0]);
+    b = __hiloint2double(h[1], l[1]);
+}
+
+template <int NV>
+__device__ __forceinline__ void wave_sums(double (&a)[NV])
+{
+    constexpr int G = wave_sums_regs<NV>();
+    const auto add = [](double x, double y) { return x + y; };
+#pragma unroll
+    for (int j = 0; j < G; j++) {
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) v[q] = j + G * q < NV ? a[j + G * q] : 0.0;
+        // lanes 0..31: values 0 and 1, lanes 32..63: values 2 and 3
+        swap32(v[0], v[2]);
+        swap32(v[1], v[3]);
+        double x = v[0] + v[2], y = v[1] + v[3];
+        swap16(x, y);
+        x = x + y;
+        x = wave_level<8>(x, add);
+        x = wave_level<4>(x, add);
+        x = wave_level<2>(x, add);
+        a[j] = wave_level<1>(x, add);
+    }
+}
+
 // Block total of NV sums (fixed order: butterfly within the wavefront, waves
 // in order) stored as this block's partial part[k * kMaxBlocks + block].
 template <int NV>
 __device__ __forceinline__ void block_sums(double (&a)[NV], double *part)
 {
-    __shared__ double sh[kWaves][NV];
+    constexpr int G = wave_sums_regs<NV>();
+    __shared__ double sh[kWaves][4 * G];
     const int lane = threadIdx.x & 63, wid = wave_id();
+    wave_sums<NV>(a);
+    if ((lane & 15) == 0)
 #pragma unroll
-    for (int k = 0; k < NV; k++) a[k] = wave_sum(a[k]);
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < NV; k++) sh[wid][k] = a[k];
+        for (int j = 0; j < G; j++) sh[wid][wave_sums_value<NV>(j, lane >> 4)] = a[j];
     __syncthreads();
     for (int k = threadIdx.x; k < NV; k += kBlock) {
         double v = sh[0][k];
+#pragma unroll
         for (int w = 1; w < kWaves; w++) v += sh[w][k];
         part[k * kMaxBlocks + blockIdx.x] = v;
     }
@@ -124,24 +184,39 @@ __global__ __launch_bounds__(kBlock) void kl_pairs(Part P, double *__restrict__ 
     for (int k = 0; k < NV; k++) a[k] = 0.0;
     for_rows(P, [&](int i, bool act) {
         if (!act) return;
+        // every load of the row is issued here, before the state decides what
+        // is used (slots that hold no pair hold finite numbers)
         double ci = c[i], gi = g[i], sn = 0.0;
+        const double pg0 = pg[i];
+        double di = 0.0, gni = 0.0;
         if (apply) {
-            const double cn = proj_box(ci + t * d[i], B);
+            di = d[i];
+            gni = gn[i];
+        }
+        double sv[M], yv[M];
+#pragma unroll
+        for (int j = 0; j < M; j++) {
+            sv[j] = S[j * ld + i];
+            yv[j] = Y[j * ld + i];
+        }
+        if (apply) {
+            const double cn = proj_box(ci + t * di, B);
             sn = cn - ci;
             ci = cn;
-            gi = gscale == 1.0 ? gn[i] : gi + gscale * (gn[i] - gi);
+            gi = gscale == 1.0 ? gni : gi + gscale * (gni - gi);
             c[i] = ci;
             g[i] = gi;
             S[head * ld + i] = sn;
         } else if (pending) {
-            sn = S[head * ld + i];
+#pragma unroll
+            for (int j = 0; j < M; j++) sn = j == head ? sv[j] : sn;
         }
         const double pgi = ci > B.lo ? (ci < B.hi ? gi : fmax(gi, 0.0)) : fmin(gi, 0.0);
         a[0] += pgi * pgi;
         a[1] += (isfinite(ci) && isfinite(gi)) ? 0.0 : 1.0;
         double yn = 0.0;
         if (pending) {
-            yn = pgi - pg[i];
+            yn = pgi - pg0;
             Y[head * ld + i] = yn;
             a[2 + 4 * M] += sn * sn;
         }
@@ -150,8 +225,8 @@ __global__ __launch_bounds__(kBlock) void kl_pairs(Part P, double *__restrict__ 
         for (int j = 0; j < M; j++) {
             if (!live[j]) continue;
             const bool fresh = pending && j == head;
-            const double sj = fresh ? sn : S[j * ld + i];
-            const double yj = fresh ? yn : Y[j * ld + i];
+            const double sj = fresh ? sn : sv[j];
+            const double yj = fresh ? yn : yv[j];
             a[2 + j] += sj * pgi;
             a[2 + M + j] += yj * pgi;
             if (pending) {
@@ -163,144 +238,185 @@ __global__ __launch_bounds__(kBlock) void kl_pairs(Part P, double *__restrict__ 
     block_sums<NV>(a, part);
 }
 
-// 2. coefficient kernel: one wavefront.  The lanes combine the block
-// partials (lane-strided sums, then a butterfly: fixed order) and stage the
-// S'Y and Y'Y tables in LDS; lane 0 does the small algebra.
+// 2. coefficient kernel: one block.  Each wavefront combines the block
+// partials of a few of the pair pass's values (lane-strided sums, then a
+// butterfly: fixed order) and the first one does the small algebra, every
+// lane the same, in registers: the tables are read from LDS by age (oldest
+// first) in one go, and loops over the pairs are unrolled with the bounds as
+// conditions.  As one wavefront whose lane 0 indexed private arrays by age it
+// spent 14.7 us on chains of scratch and LDS accesses (five pairs), now 4.2.
+constexpr int kCoefWaves = 8;
+
 template <int M>
-__global__ __launch_bounds__(64) void kl_coef(int nb, LmState *st, const double *part, int applied)
+__global__ __launch_bounds__(64 * kCoefWaves) void kl_coef(int nb, LmState *st, const double *part,
+                                                           int applied)
 {
     constexpr int NV = 4 * M + 3;
     __shared__ double t[NV];
     __shared__ double sy[M][M], yy[M][M];
-    const int lane = threadIdx.x;
-    // every load is issued before the first use (the state scalars, the
-    // tables and the partials), so their latencies overlap
+    const int lane = threadIdx.x & 63, wid = wave_id();
     const int count0 = st->count, head0 = st->head, pend0 = st->pending;
+    const int acc0 = st->accepted, rej0 = st->rejected;
     const double gam0 = st->gamma;
-    double tsy = 0.0, tyy = 0.0;
-    if (lane < M * M) {
-        tsy = st->sy[lane / M][lane % M];
-        tyy = st->yy[lane / M][lane % M];
+    if (threadIdx.x < M * M) {
+        sy[threadIdx.x / M][threadIdx.x % M] = st->sy[threadIdx.x / M][threadIdx.x % M];
+        yy[threadIdx.x / M][threadIdx.x % M] = st->yy[threadIdx.x / M][threadIdx.x % M];
     }
     {
-        double acc[NV];
+        constexpr int KW = (NV + kCoefWaves - 1) / kCoefWaves, R = kPairBlocks / 64;
+        double x[KW][R];
 #pragma unroll
-        for (int k = 0; k < NV; k++) acc[k] = 0.0;
-        // nb <= kMaxBlocks = 512: at most eight blocks per lane
+        for (int q = 0; q < KW; q++)
 #pragma unroll
-        for (int r = 0; r < kMaxBlocks / 64; r++) {
-            const int b = lane + 64 * r;
-            if (b < nb)
+            for (int r = 0; r < R; r++) {
+                const int k = min(wid + q * kCoefWaves, NV - 1);
+                x[q][r] = part[k * kMaxBlocks + lane + 64 * r];   // inside the array for every lane
+            }
 #pragma unroll
-                for (int k = 0; k < NV; k++) acc[k] += part[k * kMaxBlocks + b];
+        for (int q = 0; q < KW; q++) {
+            double v = 0.0;   // (an absent block adds +0.0, which changes no sum from +0.0)
+#pragma unroll
+            for (int r = 0; r < R; r++) v += lane + 64 * r < nb ? x[q][r] : 0.0;
+            v = wave_sum(v);
+            if (lane == 0 && wid + q * kCoefWaves < NV) t[wid + q * kCoefWaves] = v;
         }
-#pragma unroll
-        for (int k = 0; k < NV; k++) {
-            const double v = wave_sum(acc[k]);
-            if (lane == 0) t[k] = v;
-        }
-    }
-    if (lane < M * M) {
-        sy[lane / M][lane % M] = tsy;
-        yy[lane / M][lane % M] = tyy;
     }
     __syncthreads();
+    if (wid != 0) return;
+    int count = count0, head = head0;
+    double gam = gam0;
+    const bool pending = pend0 || applied;
+    bool ok = false;
+    if (pending) {
+        const double sny = t[2 + 2 * M + head], yny = t[2 + 3 * M + head], ss = t[2 + 4 * M];
+        ok = isfinite(sny) && isfinite(yny) && yny > 0.0 && sny > kLmCurv * sqrt(ss) * sqrt(yny);
+        if (ok) {
+            // column `head` of S'Y and Y'Y against every pair that stays
+            if (lane < M && lm_live(lane, M, count, head, 1)) {
+                const double syv = t[2 + 2 * M + lane], yyv = t[2 + 3 * M + lane];
+                sy[lane][head] = st->sy[lane][head] = syv;
+                yy[lane][head] = st->yy[lane][head] = yyv;
+                yy[head][lane] = st->yy[head][lane] = yyv;
+            }
+            count = count < M ? count + 1 : M;
+            head = (head + 1) % M;
+            gam = sny / yny;
+        } else if (count == M) {
+            count = M - 1;   // its oldest pair was overwritten
+        }
+    }
+    // (one wavefront: its LDS writes precede its reads)
+    __builtin_amdgcn_wave_barrier();
+    // compact-form coefficients over the pairs, oldest first
+    double R[M][M], Q[M][M], u[M], w[M], p[M], z[M], tp[M];
+    int sl[M];
+#pragma unroll
+    for (int k = 0; k < M; k++) {
+        sl[k] = (head - count + k + 2 * M) % M;
+        u[k] = t[2 + sl[k]];
+        w[k] = t[2 + M + sl[k]];
+        p[k] = z[k] = tp[k] = 0.0;
+    }
+#pragma unroll
+    for (int a = 0; a < M; a++)
+#pragma unroll
+        for (int b = 0; b < M; b++) {
+            if (b >= a) R[a][b] = sy[sl[a]][sl[b]];
+            Q[a][b] = yy[sl[a]][sl[b]];
+        }
+#pragma unroll
+    for (int a = M - 1; a >= 0; a--)
+        if (a < count) {
+            double v = u[a];
+#pragma unroll
+            for (int b = a + 1; b < M; b++)
+                if (b < count) v -= R[a][b] * p[b];
+            p[a] = v / R[a][a];
+        }
+#pragma unroll
+    for (int a = 0; a < M; a++)
+        if (a < count) {
+            double v = R[a][a] * p[a] - gam * w[a];
+#pragma unroll
+            for (int b = 0; b < M; b++)
+                if (b < count) v += gam * Q[a][b] * p[b];
+            z[a] = v;
+        }
+#pragma unroll
+    for (int a = 0; a < M; a++)
+        if (a < count) {
+            double v = z[a];
+#pragma unroll
+            for (int b = 0; b < a; b++) v -= R[b][a] * tp[b];
+            tp[a] = v / R[a][a];
+        }
+    if (lane < M) {
+        // the lane's slot: its age, or none
+        double scv = 0.0, ycv = 0.0;
+#pragma unroll
+        for (int a = 0; a < M; a++)
+            if (a < count && sl[a] == lane) {
+                scv = tp[a];
+                ycv = -gam * p[a];
+            }
+        st->sc[lane] = scv;
+        st->yc[lane] = ycv;
+    }
     if (lane == 0) {
-        int count = count0, head = head0;
-        double gam = gam0;
         st->pg2 = t[0];
         st->nonfinite = t[1];
-        if (pend0 || applied) {
-            const double sny = t[2 + 2 * M + head], yny = t[2 + 3 * M + head], ss = t[2 + 4 * M];
-            const bool ok = isfinite(sny) && isfinite(yny) && yny > 0.0 &&
-                            sny > kLmCurv * sqrt(ss) * sqrt(yny);
-            if (ok) {
-                // column `head` of S'Y and Y'Y against every pair that stays
-                for (int j = 0; j < M; j++) {
-                    if (!lm_live(j, M, count, head, 1)) continue;
-                    sy[j][head] = t[2 + 2 * M + j];
-                    yy[j][head] = t[2 + 3 * M + j];
-                    yy[head][j] = t[2 + 3 * M + j];
-                }
-                count = count < M ? count + 1 : M;
-                head = (head + 1) % M;
-                gam = sny / yny;
-                st->accepted++;
-            } else {
-                if (count == M) count = M - 1;   // its oldest pair was overwritten
-                st->rejected++;
-            }
+        if (pending) {
+            if (ok) st->accepted = acc0 + 1;
+            else st->rejected = rej0 + 1;
             st->pending = 0;
         }
         st->count = count;
         st->head = head;
         st->gamma = gam;
-        // compact-form coefficients over the pairs, oldest first
-        int sl[M];
-        double u[M], w[M], p[M], z[M], tp[M];
-        for (int k = 0; k < count; k++) {
-            sl[k] = (head - count + k + 2 * M) % M;
-            u[k] = t[2 + sl[k]];
-            w[k] = t[2 + M + sl[k]];
-        }
-        for (int a = count - 1; a >= 0; a--) {
-            double v = u[a];
-            for (int b = a + 1; b < count; b++) v -= sy[sl[a]][sl[b]] * p[b];
-            p[a] = v / sy[sl[a]][sl[a]];
-        }
-        for (int a = 0; a < count; a++) {
-            double v = sy[sl[a]][sl[a]] * p[a] - gam * w[a];
-            for (int b = 0; b < count; b++) v += gam * yy[sl[a]][sl[b]] * p[b];
-            z[a] = v;
-        }
-        for (int a = 0; a < count; a++) {
-            double v = z[a];
-            for (int b = 0; b < a; b++) v -= sy[sl[b]][sl[a]] * tp[b];
-            tp[a] = v / sy[sl[a]][sl[a]];
-        }
-        double sc[M], yc[M];
-        for (int j = 0; j < M; j++) {
-            sc[j] = 0.0;
-            yc[j] = 0.0;
-        }
-        for (int a = 0; a < count; a++) {
-            sc[sl[a]] = tp[a];
-            yc[sl[a]] = -gam * p[a];
-        }
-        for (int j = 0; j < M; j++) {
-            st->sc[j] = sc[j];
-            st->yc[j] = yc[j];
-        }
-    }
-    __syncthreads();
-    if (lane < M * M) {
-        st->sy[lane / M][lane % M] = sy[lane / M][lane % M];
-        st->yy[lane / M][lane % M] = yy[lane / M][lane % M];
     }
 }
 
-// Line-search summary for the host: combines the direction pass partials
-// (SLOT_Q: first crossing, g.d) and the trial's (host slot: g.s, s.(gn - g))
-// into the state, so one small copy returns everything.
-__global__ __launch_bounds__(64) void kl_summary(int nb, LmState *st, double *partials)
+// What the host reads after a direction and its first trial, written straight
+// into its pinned memory (a copy behind the kernel is one more launch in the chain).
+struct LmHost {
+    int count;
+    double gamma, pg2, nonfinite;
+    double bmin, gd;             // direction: first bound crossing, g.d
+    double gs, sks;              // trial at t = 1: g.s, s.(gn - g)
+};
+
+// Combines the direction pass partials (SLOT_Q: first crossing, g.d) and the
+// trial's (host slot: g.s, s.(gn - g)), one wavefront each (lane-strided, then
+// a butterfly: fixed order).
+__global__ __launch_bounds__(256) void kl_summary(int nb, const LmState *st, const double *partials,
+                                                  LmHost *out)
 {
-    const double *q = slot_ptr(partials, SLOT_Q), *h = slot_ptr(partials, SLOT_HOST);
-    double bm = INFINITY, gd = 0.0, gs = 0.0, sks = 0.0;
-    for (int b = threadIdx.x; b < nb; b += 64) {
-        bm = fmin(bm, q[b]);
-        gd += q[kMaxBlocks + b];
-        gs += h[b];
-        sks += h[kMaxBlocks + b];
-    }
-    bm = wave_min(bm);
-    gd = wave_sum(gd);
-    gs = wave_sum(gs);
-    sks = wave_sum(sks);
+    const int lane = threadIdx.x & 63, wid = wave_id();
+    const double *q = partials + (size_t)(wid < 2 ? SLOT_Q : SLOT_HOST) * kMaxRed * kMaxBlocks +
+                      (wid & 1) * kMaxBlocks;
+    constexpr int R = kMaxBlocks / 64;
+    double x[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) x[r] = q[lane + 64 * r];   // inside the slot for every lane
     if (threadIdx.x == 0) {
-        st->bmin = bm;
-        st->gd = gd;
-        st->gs = gs;
-        st->sks = sks;
+        out->count = st->count;
+        out->gamma = st->gamma;
+        out->pg2 = st->pg2;
+        out->nonfinite = st->nonfinite;
+    }
+    if (wid == 0) {
+        double v = INFINITY;
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            if (lane + 64 * r < nb) v = fmin(v, x[r]);
+        v = wave_min(v);
+        if (lane == 0) out->bmin = v;
+    } else {
+        double v = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; r++) v += lane + 64 * r < nb ? x[r] : 0.0;
+        v = wave_sum(v);
+        if (lane == 0) (wid == 1 ? out->gd : wid == 2 ? out->gs : out->sks) = v;
     }
 }
 
@@ -318,7 +434,7 @@ __global__ void kl_state_init(LmState *st, double gamma)
 }
 
 // 3. direction pass: d = -H pg, outward components at a bound zeroed;
-// first crossing (min), g.d, d.d
+// first crossing (min), g.d, d.d; ct: the point P(c + d) of the first trial
 template <int M>
 __global__ __launch_bounds__(kBlock) void kl_dir(Part P, const double *__restrict__ c,
                                                  const double *__restrict__ g,
@@ -326,7 +442,8 @@ __global__ __launch_bounds__(kBlock) void kl_dir(Part P, const double *__restric
                                                  const double *__restrict__ S,
                                                  const double *__restrict__ Y, int64_t ld,
                                                  const LmState *__restrict__ st, Box B,
-                                                 double *__restrict__ d, double *partials)
+                                                 double *__restrict__ d, double *__restrict__ ct,
+                                                 double *partials)
 {
     const int count = st->count, head = st->head;
     const double gam = st->gamma;
@@ -343,34 +460,48 @@ __global__ __launch_bounds__(kBlock) void kl_dir(Part P, const double *__restric
     red_init<kOps, 3>(a);
     for_rows(P, [&](int i, bool act) {
         if (!act) return;
-        double di = -gam * pg[i];
+        // (all loads first, as in the pair pass)
+        const double pgi = pg[i], ci = c[i], gi = g[i];
+        double sv[M], yv[M];
+#pragma unroll
+        for (int j = 0; j < M; j++) {
+            sv[j] = S[j * ld + i];
+            yv[j] = Y[j * ld + i];
+        }
+        double di = -gam * pgi;
 #pragma unroll
         for (int j = 0; j < M; j++)
-            if (live[j]) di -= sc[j] * S[j * ld + i] + yc[j] * Y[j * ld + i];
-        const double ci = c[i];
+            if (live[j]) di -= sc[j] * sv[j] + yc[j] * yv[j];
         if ((ci <= B.lo && di < 0.0) || (ci >= B.hi && di > 0.0)) di = 0.0;
         d[i] = di;
+        ct[i] = proj_box(ci + di, B);
         if (di < 0.0) a[0] = fmin(a[0], (ci - B.lo) / (-di));
         else if (di > 0.0) a[0] = fmin(a[0], (B.hi - ci) / di);
-        a[1] += g[i] * di;
+        a[1] += gi * di;
         a[2] += di * di;
     });
     block_partial<kOps, 3>(a, slot_ptr(partials, SLOT_Q));
 }
 
 // 4. trial: gathers c(t) = P(c + t d), writes gn = K c(t) - f; g.s, s.(gn - g), s.s
-// with s = c(t) - c
-template <int WMAX, class Cols>
+// with s = c(t) - c.  FIRST (t = 1, every iteration): the direction pass has
+// written c(1), so one vector is gathered instead of two and no projection
+// runs per entry (166 k rows: 10.0 -> 7.7 us); a backtracking step forms c(t)
+// as it gathers.
+template <int WMAX, class Cols, bool FIRST>
 __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void kl_trial(Part P, const int *__restrict__ so, Cols cols,
                                                    const double *__restrict__ v,
                                                    const double *__restrict__ c,
-                                                   const double *__restrict__ d, double t,
+                                                   const double *__restrict__ d,
+                                                   const double *__restrict__ c1, double t,
                                                    const double *__restrict__ f,
                                                    const double *__restrict__ g,
                                                    double *__restrict__ gn, Box B,
                                                    double *partials)
 {
-    auto ct = [&](int ub, int l) { return proj_box((c + ub)[l] + t * (d + ub)[l], B); };
+    auto ct = [&](int ub, int l) {
+        return FIRST ? (c1 + ub)[l] : proj_box((c + ub)[l] + t * (d + ub)[l], B);
+    };
     constexpr uint32_t kOps = OPS3(OP_SUM, OP_SUM, OP_SUM);
     double a[3];
     red_init<kOps, 3>(a);
@@ -407,11 +538,6 @@ __global__ __launch_bounds__(kBlock) void kl_step(Part P, double *__restrict__ c
     if (blockIdx.x == 0 && threadIdx.x == 0) st->pending = 1;
 }
 
-// The pair pass holds 4M + 3 accumulators per lane (95 VGPRs at M = 5), so
-// one 1024-thread block fits a CU: it runs one block per CU and walks more
-// slices per wavefront instead of queueing a second round of blocks.
-constexpr int kPairBlocks = 256;
-
 // Pair pass and coefficients; with apply, the pending step (t, gscale) is
 // taken inside the pair pass.
 template <int M>
@@ -423,14 +549,14 @@ void launch_pairs_coef(nn_ctx *ctx, const Part &P, double *c, double *g, Box B, 
     kl_pairs<M><<<P1.nb, kBlock, 0, ctx->stream>>>(P1, c, g, L.pg, L.S, L.Y, L.cap,
                                                    (const LmState *)L.state, B, L.part,
                                                    apply ? 1 : 0, L.d, t, L.gn, gscale);
-    kl_coef<M><<<1, 64, 0, ctx->stream>>>(P1.nb, (LmState *)L.state, L.part, apply ? 1 : 0);
+    kl_coef<M><<<1, 64 * kCoefWaves, 0, ctx->stream>>>(P1.nb, (LmState *)L.state, L.part, apply ? 1 : 0);
 }
 
 template <int M>
 void launch_coef(nn_ctx *ctx, const Part &P)
 {
     const Part P1 = make_part(P.n, kPairBlocks);
-    kl_coef<M><<<1, 64, 0, ctx->stream>>>(P1.nb, (LmState *)ctx->lm.state, ctx->lm.part, 0);
+    kl_coef<M><<<1, 64 * kCoefWaves, 0, ctx->stream>>>(P1.nb, (LmState *)ctx->lm.state, ctx->lm.part, 0);
 }
 
 template <int M>
@@ -438,7 +564,8 @@ void launch_dir(nn_ctx *ctx, const Part &P, const double *c, const double *g, Bo
 {
     LmWork &L = ctx->lm;
     kl_dir<M><<<P.nb, kBlock, 0, ctx->stream>>>(P, c, g, L.pg, L.S, L.Y, L.cap,
-                                                (const LmState *)L.state, B, L.d, ctx->partials);
+                                                (const LmState *)L.state, B, L.d,
+                                                ctx->ws.q, ctx->partials);
 }
 
 #define NN_LM_DISPATCH(m, fn, ...)                  \
@@ -466,7 +593,7 @@ nn_status ensure_lm(nn_ctx *ctx, int64_t n, int m)
     if (e == hipSuccess) e = dev_malloc(ctx->al, &L.gn, sizeof(double) * cap);
     if (e == hipSuccess) e = dev_malloc(ctx->al, &L.part, sizeof(double) * kLmNV * kMaxBlocks);
     if (e == hipSuccess) e = dev_malloc(ctx->al, &L.state, sizeof(LmState));
-    if (e == hipSuccess) e = hipHostMalloc(&L.h_state, sizeof(LmState), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&L.h_state, sizeof(LmHost), hipHostMallocDefault);
     if (e != hipSuccess) {
         lm_release(ctx);
         return fail(ctx, NN_EOOM, std::string("BLMVM workspace: ") + hipGetErrorString(e));
@@ -522,7 +649,7 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
     if ((rc = ensure_lm(ctx, n, M)) != NN_OK) return rc;
     Workspace &W = ctx->ws;
     LmWork &L = ctx->lm;
-    LmState &H = *(LmState *)L.h_state;
+    LmHost &H = *(LmHost *)L.h_state;
     const Part P = make_part(n);
     const double nd = (double)n, nnz = (double)A->nnz;
     const double *vp64 = A->d16p ? vals64p : nullptr;
@@ -571,22 +698,24 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
     if ((rc = refresh(conv)) != NN_OK) return finish(rc);
     if (conv) return finish(NN_OK);
     kl_state_init<<<1, 1, 0, ctx->stream>>>((LmState *)L.state, 1.0);
-    std::memset(L.h_state, 0, sizeof(LmState));
+    std::memset(L.h_state, 0, sizeof(LmHost));
 
     const double vp = 8.0 * n;   // bytes of one vector pass
     // Trial at step t along d: gathers P(c + t d), writes K c(t) - f; the
     // partials (g.s, s.(gn - g), s.s) stay in the host slot.
-    auto launch_trial_t = [&](double t) {
+    auto launch_trial_t = [&](double t, bool after_dir) {
         prof_begin(ctx, KC_TRIAL, b_trial);
-        if (vp64 && A->diag_plan)
-            NN_DISPATCH_W(A->wmax, (kl_trial<WM, ColsDiag>), P.nb, P, A->sl_off,
-                          diag_cols(A, A->d16p), vp64, c, L.d, t, f, W.g, L.gn, box, ctx->partials);
-        else if (vp64)
-            NN_DISPATCH_W(A->wmax, (kl_trial<WM, ColsD16P>), P.nb, P, A->sl_off, ColsD16P{A->d16p},
-                          vp64, c, L.d, t, f, W.g, L.gn, box, ctx->partials);
-        else
-            NN_DISPATCH_W(A->wmax, (kl_trial<WM, ColsI32>), P.nb, P, A->sl_off, ColsI32{A->sl_col},
-                          vals, c, L.d, t, f, W.g, L.gn, box, ctx->partials);
+        auto go = [&](auto first, auto cols, const double *v) {
+            NN_DISPATCH_W(A->wmax, (kl_trial<WM, decltype(cols), decltype(first)::value>), P.nb, P,
+                          A->sl_off, cols, v, c, L.d, W.q, t, f, W.g, L.gn, box, ctx->partials);
+        };
+        auto pick = [&](auto first) {
+            if (vp64 && A->diag_plan) go(first, diag_cols(A, A->d16p), vp64);
+            else if (vp64) go(first, ColsD16P{A->d16p}, vp64);
+            else go(first, ColsI32{A->sl_col}, vals);
+        };
+        if (after_dir) pick(std::true_type());
+        else pick(std::false_type());
         prof_end(ctx);
         S.spmvs++;
         S.search_trials++;
@@ -607,10 +736,9 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         prof_begin(ctx, KC_OTHER, vp * (4.0 + 2.0 * live));
         NN_LM_DISPATCH(M, launch_dir, ctx, P, c, W.g, box);
         prof_end(ctx);
-        launch_trial_t(1.0);
-        kl_summary<<<1, 64, 0, ctx->stream>>>(P.nb, (LmState *)L.state, ctx->partials);
-        NN_HIP_TRY(ctx, hipMemcpyAsync(L.h_state, L.state, sizeof(LmState),
-                                       hipMemcpyDeviceToHost, ctx->stream));
+        launch_trial_t(1.0, true);
+        kl_summary<<<1, 256, 0, ctx->stream>>>(P.nb, (const LmState *)L.state, ctx->partials, &H);
+        NN_HIP_TRY(ctx, hipGetLastError());
         NN_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         bmin = H.bmin;
         gd = H.gd;
@@ -686,7 +814,7 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
                 if (t <= bmin || k + 1 >= kLmMaxTrials) {
                     // exact step on the segment before the first crossing
                     t = bmin;
-                    launch_trial_t(t);
+                    launch_trial_t(t, false);
                     if ((rc = read_trial(gs, sks)) != NN_OK) return finish(rc);
                     if (!(sks > 0.0))
                         return finish(fail(ctx, NN_ENOTSPD, "non-positive curvature along the direction"));
@@ -694,7 +822,7 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
                     t *= gscale;
                     break;
                 }
-                launch_trial_t(t);
+                launch_trial_t(t, false);
                 if ((rc = read_trial(gs, sks)) != NN_OK) return finish(rc);
             }
         }

@@ -295,3 +295,22 @@ def test_assembly_refusals(ctx, what):
     with pytest.raises(nnqp.NnError) as e:
         ctx.assemble(p)
     assert e.value.status == status and text in str(e.value)
+
+
+# every memory size the pair pass, the coefficients and the direction are
+# compiled for, and more rows than the pair pass has lanes (256 x 1024)
+@pytest.mark.parametrize("mesh,m", [("square", m) for m in range(1, 9)] + [("cube", 5)])
+def test_blmvm_memories(ctx, mesh, m):
+    """Both methods end with |pg| <= 1e-11 |f|: the minimisers differ by at
+    most that times the condition number, about n^(2/d) times the anisotropy
+    (1e3): 1e-11 * 4e3 * 1e3 * 0.1 (pg is far from the worst direction)."""
+    from paper_1506_08435_amd import nnqp
+    p = W.square2d(33) if mesh == "square" else W.cube3d(66)
+    K, F, _ = ctx.assemble(p)
+    ref = ctx.solve_nonneg(K, F, tol=1e-11)[0].cpu().numpy().copy()
+    tol = 1e-11 if mesh == "square" else 1e-8
+    c, _, st = ctx.solve_nonneg(K, F, tol=tol, method=nnqp.NN_BLMVM, lmm_vectors=m)
+    c = c.cpu().numpy()
+    assert st["kkt_rel"] <= tol and c.min() >= 0.0
+    assert np.abs(c - ref).max() <= (4e-6 if mesh == "square" else 4e-3) * np.abs(ref).max()
+    K.free()
