@@ -5,6 +5,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <thread>
 
 #include "nnqp_internal.hpp"
 
@@ -66,30 +67,69 @@ nn_status ensure_workspace(nn_ctx *ctx, int64_t n)
     return NN_OK;
 }
 
-nn_status host_reduce(nn_ctx *ctx, int64_t n, int nv, const int *ops, double *out)
+// One block copies the partials into the host's memory and announces them.
+// 512 threads: one per block of a slot.
+__global__ __launch_bounds__(kMaxBlocks) void k_publish(Publish A, Publish B, HostFlow *F,
+                                                        unsigned long long seq)
 {
-    const Part P = make_part(n);
-    // partials are laid out [value][block]: copy the first nv rows
-    const size_t count = (size_t)(nv - 1) * kMaxBlocks + P.nb;
-    NN_HIP_TRY(ctx, hipMemcpyAsync(ctx->h_part, ctx->partials, sizeof(double) * count,
-                                   hipMemcpyDeviceToHost, ctx->stream));
-    NN_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    for (int k = 0; k < nv; k++) {
-        double a = ops[k] == OP_SUM ? 0.0 : (ops[k] == OP_MIN ? INFINITY : -INFINITY);
-        for (int b = 0; b < P.nb; b++) {
-            const double v = ctx->h_part[(size_t)k * kMaxBlocks + b];
-            a = ops[k] == OP_SUM ? a + v : (ops[k] == OP_MIN ? std::fmin(a, v) : std::fmax(a, v));
+    const int b = threadIdx.x;
+    if (b < A.nb)
+        for (int k = 0; k < A.nv; k++) F->part[k * kMaxBlocks + b] = A.src[k * kMaxBlocks + b];
+    if (b < B.nb)
+        for (int k = 0; k < B.nv; k++)
+            F->part[(A.nv + k) * kMaxBlocks + b] = B.src[k * kMaxBlocks + b];
+    __threadfence_system();
+    __syncthreads();
+    if (b == 0)
+        __hip_atomic_store(&F->pub, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+nn_status flow_wait(nn_ctx *ctx, const std::function<bool()> &ready)
+{
+    // The stream is asked only after a while (asking costs microseconds); if
+    // it holds no work any more, the words are final.
+    for (int64_t spin = 1; !ready(); spin++) {
+        if (spin % 8192 != 0) {
+            __builtin_ia32_pause();
+            continue;
         }
-        out[k] = a;
+        const hipError_t e = hipStreamQuery(ctx->stream);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            std::this_thread::yield();
+            continue;
+        }
+        if (e == hipSuccess && ready()) break;
+        return fail(ctx, NN_EHIP, std::string("waiting for the device: ") +
+                                      (e == hipSuccess ? "no answer" : hipGetErrorString(e)));
     }
     return NN_OK;
 }
 
-nn_status read_scalars(nn_ctx *ctx)
+nn_status publish(nn_ctx *ctx, const Publish &a, const Publish &b)
 {
-    NN_HIP_TRY(ctx, hipMemcpyAsync(ctx->h_scal, ctx->scal, sizeof(DevScalars), hipMemcpyDeviceToHost,
-                                   ctx->stream));
-    NN_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    const unsigned long long seq = ++ctx->flow_pub;
+    k_publish<<<1, kMaxBlocks, 0, ctx->stream>>>(a, b, ctx->flow, seq);
+    NN_HIP_TRY(ctx, hipGetLastError());
+    const unsigned long long *w = &ctx->flow->pub;
+    return flow_wait(ctx, [w, seq] { return __atomic_load_n(w, __ATOMIC_ACQUIRE) >= seq; });
+}
+
+double published(const nn_ctx *ctx, int at, int k, int nb, int op)
+{
+    const double *h = ctx->flow->part + (size_t)(at + k) * kMaxBlocks;
+    double a = op == OP_SUM ? 0.0 : (op == OP_MIN ? INFINITY : -INFINITY);
+    for (int b = 0; b < nb; b++)
+        a = op == OP_SUM ? a + h[b] : (op == OP_MIN ? std::fmin(a, h[b]) : std::fmax(a, h[b]));
+    return a;
+}
+
+nn_status host_reduce(nn_ctx *ctx, int64_t n, int nv, const int *ops, double *out)
+{
+    const Part P = make_part(n);
+    const nn_status rc = publish(ctx, Publish{ctx->partials, nv, P.nb});
+    if (rc != NN_OK) return rc;
+    for (int k = 0; k < nv; k++) out[k] = published(ctx, 0, k, P.nb, ops[k]);
     return NN_OK;
 }
 
@@ -335,13 +375,10 @@ static nn_status create_impl(nn_ctx **out, int device, void *hip_stream, const D
     ctx->stream = (hipStream_t)hip_stream;
     const size_t part_bytes = sizeof(double) * kSlots * kMaxBlocks * kMaxRed;
     bool ok = dev_malloc(ctx->al, &ctx->partials, part_bytes) == hipSuccess &&
-              hipHostMalloc(&ctx->h_part, sizeof(double) * kMaxBlocks * kMaxRed,
-                            hipHostMallocDefault) == hipSuccess &&
-              hipHostMalloc(&ctx->h_multi, sizeof(double) * kMaxBlocks * (5 + 3 * kLadder),
-                            hipHostMallocDefault) == hipSuccess &&
               dev_malloc(ctx->al, &ctx->scal, sizeof(DevScalars)) == hipSuccess &&
-              hipHostMalloc(&ctx->h_scal, sizeof(DevScalars), hipHostMallocDefault) == hipSuccess &&
+              hipHostMalloc(&ctx->flow, sizeof(HostFlow), hipHostMallocCoherent) == hipSuccess &&
               hipEventCreate(&ctx->ev0) == hipSuccess && hipEventCreate(&ctx->ev1) == hipSuccess;
+    if (ok) std::memset((void *)ctx->flow, 0, sizeof(HostFlow));
     if (ok) {
         ok = hipMemsetAsync(ctx->partials, 0, part_bytes, ctx->stream) == hipSuccess &&
              hipMemsetAsync(ctx->scal, 0, sizeof(DevScalars), ctx->stream) == hipSuccess &&
@@ -426,10 +463,8 @@ void nn_destroy(nn_ctx *ctx)
         dev_free(ctx->al, v);
     lm_release(ctx);
     dev_free(ctx->al, ctx->partials);
-    if (ctx->h_part) (void)hipHostFree(ctx->h_part);
-    if (ctx->h_multi) (void)hipHostFree(ctx->h_multi);
     dev_free(ctx->al, ctx->scal);
-    if (ctx->h_scal) (void)hipHostFree(ctx->h_scal);
+    if (ctx->flow) (void)hipHostFree(ctx->flow);
     if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
     if (ctx->ev0) (void)hipEventDestroy(ctx->ev0);
     if (ctx->ev1) (void)hipEventDestroy(ctx->ev1);

@@ -1678,6 +1678,7 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         V64.p = A.d<double>(R), V64.q = A.d<double>(R), V64.dm = A.d<double>(R);
     }
     BState *hs = A.h<BState>(P);
+    BState *land[2] = {A.h<BState>(P), A.h<BState>(P)};
     double *pres = A.h<double>((size_t)P * kBNV);
     const void **tab = (const void **)A.h<void *>((size_t)P * 12);
     // Uploads from pinned memory read their source when they execute, so
@@ -1694,8 +1695,9 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     }
     BTab *tabs = A.h<BTab>(P);
     if (!A.ok) return fail(ctx, NN_EOOM, "batch workspace allocation failed");
-    Events ev_st, ev_lst, ev_t;
+    Events ev_st, ev_lst, ev_land, ev_t;
     if (!ev_st.create(kStage, hipEventDisableTiming) ||
+        !ev_land.create(2, hipEventDisableTiming) ||
         !ev_lst.create(kStage, hipEventDisableTiming) || !ev_t.create(2, hipEventDefault))
         return fail(ctx, NN_EHIP, "event creation");
     hipEvent_t t0 = ev_t.ev[0], t1 = ev_t.ev[1];
@@ -1813,10 +1815,17 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
                    hipSuccess &&
                hipEventRecord(ev_st.ev[k], st) == hipSuccess;
     };
-    auto pull = [&]() {
-        return hipMemcpyAsync(hs, d_st, sizeof(BState) * P, hipMemcpyDeviceToHost, st) ==
+    // The states as the chunk enqueued last leaves them: pull(k) into landing
+    // buffer k; look(k) waits for it and makes them the states in hs.
+    auto pull = [&](int k) {
+        return hipMemcpyAsync(land[k], d_st, sizeof(BState) * P, hipMemcpyDeviceToHost, st) ==
                    hipSuccess &&
-               hipStreamSynchronize(st) == hipSuccess;
+               hipEventRecord(ev_land.ev[k], st) == hipSuccess;
+    };
+    auto look = [&](int k) {
+        if (hipEventSynchronize(ev_land.ev[k]) != hipSuccess) return false;
+        std::memcpy(hs, land[k], sizeof(BState) * P);
+        return true;
     };
     // The members still running and their blocks, as device lists: rebuilt
     // and uploaded only when the set changes.  A block takes `per` slices of
@@ -1994,7 +2003,7 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     const int64_t max_steps =
         (int64_t)(o->max_outer + 1) * (4 + 2 * kMaxTrials + 21 + o->max_cg) + 16;
     nn_status err = NN_OK;
-    int64_t steps = 0;
+    int64_t steps = 0, chunks = 0;
     while (steps < max_steps) {
         if (!select()) {
             err = fail(ctx, NN_EHIP, "batch list upload");
@@ -2013,7 +2022,7 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             step(st, gr, ev_step.ev.data());
             settle(st, n_pr);
             steps++;
-            if (!pull()) {
+            if (!pull(0) || !look(0)) {
                 err = fail(ctx, NN_EHIP, "batch read-back");
                 break;
             }
@@ -2038,7 +2047,13 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             settle(st, n_pr);
         }
         steps += chunk;
-        if (!pull()) {
+        // One chunk stays enqueued behind the one whose states are looked at,
+        // so the device does not wait for the read-back, the list and the
+        // launch (85 us a chunk, where its 16 steps take 360 on 64 members of
+        // 32^2 to 256^2 cells).  The lists lag by a chunk: a member that has
+        // finished returns from its launches at once.
+        const int k = chunks++ & 1;
+        if (!pull(k) || (chunks > 1 && !look(k ^ 1))) {
             err = fail(ctx, NN_EHIP, "batch read-back");
             break;
         }
@@ -2054,6 +2069,9 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
                          (long long)steps, nr, P, ncg, hs[0].outer, hs[0].kkt_rel);
         }
     }
+    // (after the last look every member had finished, or the guard has hit)
+    if (err == NN_OK && chunks > 0 && !look((int)((chunks - 1) & 1)))
+        err = fail(ctx, NN_EHIP, "batch read-back");
     if (err == NN_OK && steps >= max_steps) {
         for (int p = 0; p < P; p++)
             if (hs[p].phase != PH_DONE) {

@@ -379,17 +379,18 @@ __global__ __launch_bounds__(64 * kCoefWaves) void kl_coef(int nb, LmState *st, 
 // What the host reads after a direction and its first trial, written straight
 // into its pinned memory (a copy behind the kernel is one more launch in the chain).
 struct LmHost {
-    int count;
+    unsigned long long seq;      // number of the summary, stored last
     double gamma, pg2, nonfinite;
     double bmin, gd;             // direction: first bound crossing, g.d
     double gs, sks;              // trial at t = 1: g.s, s.(gn - g)
+    int count;
 };
 
 // Combines the direction pass partials (SLOT_Q: first crossing, g.d) and the
 // trial's (host slot: g.s, s.(gn - g)), one wavefront each (lane-strided, then
 // a butterfly: fixed order).
 __global__ __launch_bounds__(256) void kl_summary(int nb, const LmState *st, const double *partials,
-                                                  LmHost *out)
+                                                  LmHost *out, unsigned long long seq)
 {
     const int lane = threadIdx.x & 63, wid = wave_id();
     const double *q = partials + (size_t)(wid < 2 ? SLOT_Q : SLOT_HOST) * kMaxRed * kMaxBlocks +
@@ -418,6 +419,10 @@ __global__ __launch_bounds__(256) void kl_summary(int nb, const LmState *st, con
         v = wave_sum(v);
         if (lane == 0) (wid == 1 ? out->gd : wid == 2 ? out->gs : out->sks) = v;
     }
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&out->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // drop every stored pair (before the coefficients are formed again)
@@ -593,7 +598,7 @@ nn_status ensure_lm(nn_ctx *ctx, int64_t n, int m)
     if (e == hipSuccess) e = dev_malloc(ctx->al, &L.gn, sizeof(double) * cap);
     if (e == hipSuccess) e = dev_malloc(ctx->al, &L.part, sizeof(double) * kLmNV * kMaxBlocks);
     if (e == hipSuccess) e = dev_malloc(ctx->al, &L.state, sizeof(LmState));
-    if (e == hipSuccess) e = hipHostMalloc(&L.h_state, sizeof(LmHost), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&L.h_state, sizeof(LmHost), hipHostMallocCoherent);
     if (e != hipSuccess) {
         lm_release(ctx);
         return fail(ctx, NN_EOOM, std::string("BLMVM workspace: ") + hipGetErrorString(e));
@@ -731,15 +736,18 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
     // first trial t = 1 (both line searches start there); one synchronisation
     // returns the state, the direction summary and the trial.
     double bmin = INFINITY, gd = 0.0, gs1 = 0.0, sks1 = 0.0;
+    unsigned long long n_summary = 0;
     auto direction_and_first_trial = [&]() -> nn_status {
         const double live = std::min(H.count + 1, M);
         prof_begin(ctx, KC_OTHER, vp * (4.0 + 2.0 * live));
         NN_LM_DISPATCH(M, launch_dir, ctx, P, c, W.g, box);
         prof_end(ctx);
         launch_trial_t(1.0, true);
-        kl_summary<<<1, 256, 0, ctx->stream>>>(P.nb, (const LmState *)L.state, ctx->partials, &H);
+        kl_summary<<<1, 256, 0, ctx->stream>>>(P.nb, (const LmState *)L.state, ctx->partials, &H, ++n_summary);
         NN_HIP_TRY(ctx, hipGetLastError());
-        NN_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        const nn_status r2 = flow_wait(
+            ctx, [&] { return __atomic_load_n(&H.seq, __ATOMIC_ACQUIRE) == n_summary; });
+        if (r2 != NN_OK) return r2;
         bmin = H.bmin;
         gd = H.gd;
         gs1 = H.gs;

@@ -302,6 +302,15 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(
 // p, q are updated in place on the free rows; partials of p.q into SLOT_Q
 // (with TR, also p.p and w.p, which the update needs for |w + alpha p|).
 // Columns outside the free set contribute 0 because z vanishes there.
+// The CG solve has ended: its scalars to the host (one thread, behind its own
+// stores to them).
+__device__ inline void flow_end(const CgLink &L)
+{
+    L.F->scal = *L.S;
+    __hip_atomic_store(&L.F->end, (unsigned long long)L.epoch, __ATOMIC_RELEASE,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The prologue's scalars, read before anything else of the pass.
 struct CgIn {
     double rr_stop, rz_old;
@@ -316,9 +325,10 @@ __device__ __forceinline__ CgIn cg_in(const DevScalars *S, int j)
 // whether the CG ends here.
 template <bool TR>
 __device__ __forceinline__ bool cg_begin(const CgIn &in, const double *slot, int nb, double (&u)[2],
-                                         DevScalars *S, int j, int max_it, double rtol2,
+                                         const CgLink &L, int j, int max_it, double rtol2,
                                          double &beta)
 {
+    DevScalars *const S = L.S;
     combine_loaded<0u, 2>(u);
     double cnt[2] = {0.0, 0.0};   // #free rows and their nonzeros, from the set-up
     if (j == 0) {
@@ -345,6 +355,10 @@ __device__ __forceinline__ bool cg_begin(const CgIn &in, const double *slot, int
         if (done) {
             S->done = done;
             S->it = j;
+            flow_end(L);
+        } else {
+            __hip_atomic_store(&L.F->cg, ((unsigned long long)L.epoch << 32) | (unsigned)(j + 1),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
     return done != 0;
@@ -357,15 +371,16 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cg_spmv(Part P, 
                                                     const VV *__restrict__ z,
                                                     VV *__restrict__ p, VV *__restrict__ q,
                                                     const VV *__restrict__ w,
-                                                    double *partials, DevScalars *S, int j,
+                                                    double *partials, CgLink L, int j,
                                                     int max_it, double rtol2)
 {
+    const DevScalars *const S = L.S;
     if (S->done) return;
     const CgIn in = cg_in(S, j);
     const double *slot = slot_ptr(partials, (j & 1) ? SLOT_U1 : SLOT_U0);
     double u[2], beta;
     load_partials<0u, 2>(slot, P.nb, u);
-    if (cg_begin<TR>(in, slot, P.nb, u, S, j, max_it, rtol2, beta)) return;
+    if (cg_begin<TR>(in, slot, P.nb, u, L, j, max_it, rtol2, beta)) return;
     constexpr int NQ = TR ? 3 : 1;
     double a[NQ];
 #pragma unroll
@@ -403,10 +418,11 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
                                                         const VV *__restrict__ z,
                                                         VV *__restrict__ p, VV *__restrict__ q,
                                                         const VV *__restrict__ w, double *partials,
-                                                        DevScalars *S, int j, int max_it,
+                                                        CgLink L, int j, int max_it,
                                                         double rtol2)
 {
     constexpr int W = diag_width<WMAX>();
+    const DevScalars *const S = L.S;
     const int stop = S->done;
     const CgIn in = cg_in(S, j);
     const double *slot = slot_ptr(partials, (j & 1) ? SLOT_U1 : SLOT_U0);
@@ -437,7 +453,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
     };
     if (t.kind != DR_GENERAL) load(0);
     if (stop) return;
-    if (cg_begin<TR>(in, slot, P.nb, u, S, j, max_it, rtol2, beta)) return;
+    if (cg_begin<TR>(in, slot, P.nb, u, L, j, max_it, rtol2, beta)) return;
     const bool act = in_n && m != 0 && s0 < P.nslices;
     double acc[1] = {0.0};
     if (t.kind != DR_GENERAL) {
@@ -491,10 +507,11 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
                                                       const VV *__restrict__ dm,
                                                       VV *__restrict__ w, VV *__restrict__ r,
                                                       VV *__restrict__ z, double *partials,
-                                                      DevScalars *S, int j, VV *__restrict__ cres,
+                                                      CgLink L, int j, VV *__restrict__ cres,
                                                       VV *__restrict__ cdz0, double inv_theta,
                                                       double delta2)
 {
+    DevScalars *const S = L.S;
     const int stop = S->done;
     if constexpr (!ONE)
         if (stop) return;
@@ -519,6 +536,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             S->done = isfinite(pq) ? 3 : 4;
             S->it = j;
+            flow_end(L);
         }
         return;
     }
@@ -618,7 +636,8 @@ __global__ __launch_bounds__(kBlock) void k_gersh(Part P, const int *__restrict_
 
 // Largest step along w before a free variable reaches a bound:
 // min over w_i < 0 of (c_i - lo) / (-w_i) and over w_i > 0 of (hi - c_i) / w_i
-// (+inf for hi = +inf), g.w, w.w
+// (+inf for hi = +inf), g.w, w.w; partials into SLOT_Q, so that a trial may
+// follow before they are read
 constexpr uint32_t kOpsBrk = OPS3(OP_MIN, OP_SUM, OP_SUM);
 
 template <class VV>
@@ -637,7 +656,7 @@ __global__ __launch_bounds__(kBlock) void k_breakpoint(Part P, const double *__r
         a[1] += g[i] * wi;
         a[2] += wi * wi;
     });
-    block_partial<kOpsBrk, 3>(a, slot_ptr(partials, SLOT_HOST));
+    block_partial<kOpsBrk, 3>(a, slot_ptr(partials, SLOT_Q));
 }
 
 __global__ __launch_bounds__(kBlock) void k_active(Part P, const double *__restrict__ c,
@@ -1009,50 +1028,51 @@ static void cg_spmv_tr(nn_ctx *ctx, const nn_matrix *A, const Vals &V, int j, in
 {
     Part P = make_part(A->n);
     Workspace &W = ctx->ws;
+    const CgLink L{ctx->scal, ctx->flow, ctx->flow_cg};
     if (A->diag_plan && (V.v32q || V.v64p)) {
         // one slice per wavefront at most: every load before the prologue
         const bool one = P.nslices <= P.nb * kWaves, lone = P.nb <= kMaxBlocks / 2;
         const ColsDiag cols = diag_cols(A, V.v32q ? A->d16q : A->d16p);
         if (V.v32q && one)
             NN_DISPATCH_W(A->wmax, (k_cg_spmv_one<WM, float, float, TR, diag_width<WM>()>), P.nb, P,
-                          cols, V.v32q, W.mask, W.z32, W.p32, W.q32, W.w32, ctx->partials, ctx->scal,
+                          cols, V.v32q, W.mask, W.z32, W.p32, W.q32, W.w32, ctx->partials, L,
                           j, max_it, rtol * rtol);
         else if (V.v32q)
             NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, float, float, ColsDiag, TR>), P.nb, P, A->sl_off,
                           cols, V.v32q, W.mask, W.z32, W.p32, W.q32, W.w32, ctx->partials,
-                          ctx->scal, j, max_it, rtol * rtol);
+                          L, j, max_it, rtol * rtol);
         else if (one && lone)
             NN_DISPATCH_W(A->wmax, (k_cg_spmv_one<WM, double, double, TR, diag_width<WM>()>), P.nb, P,
-                          cols, V.v64p, W.mask, W.z, W.p0, W.q, W.w, ctx->partials, ctx->scal, j,
+                          cols, V.v64p, W.mask, W.z, W.p0, W.q, W.w, ctx->partials, L, j,
                           max_it, rtol * rtol);
         else if (one)
             NN_DISPATCH_W(A->wmax, (k_cg_spmv_one<WM, double, double, TR, 8>), P.nb, P, cols, V.v64p,
-                          W.mask, W.z, W.p0, W.q, W.w, ctx->partials, ctx->scal, j, max_it,
+                          W.mask, W.z, W.p0, W.q, W.w, ctx->partials, L, j, max_it,
                           rtol * rtol);
         else
             NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, double, double, ColsDiag, TR>), P.nb, P,
                           A->sl_off, cols, V.v64p, W.mask, W.z, W.p0, W.q, W.w, ctx->partials,
-                          ctx->scal, j, max_it, rtol * rtol);
+                          L, j, max_it, rtol * rtol);
     } else if (V.v32q && A->d16q) {
         NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, float, float, ColsD16Q, TR>), P.nb, P, A->sl_off,
                       ColsD16Q{A->d16q}, V.v32q, W.mask, W.z32, W.p32, W.q32, W.w32,
-                      ctx->partials, ctx->scal, j, max_it, rtol * rtol);
+                      ctx->partials, L, j, max_it, rtol * rtol);
     } else if (V.v32 && A->sl_d16) {
         NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, float, float, ColsD16, TR>), P.nb, P, A->sl_off,
                       ColsD16{A->sl_d16}, V.v32, W.mask, W.z32, W.p32, W.q32, W.w32,
-                      ctx->partials, ctx->scal, j, max_it, rtol * rtol);
+                      ctx->partials, L, j, max_it, rtol * rtol);
     } else if (V.v32) {
         NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, float, float, ColsI32, TR>), P.nb, P, A->sl_off,
                       ColsI32{A->sl_col}, V.v32, W.mask, W.z32, W.p32, W.q32, W.w32,
-                      ctx->partials, ctx->scal, j, max_it, rtol * rtol);
+                      ctx->partials, L, j, max_it, rtol * rtol);
     } else if (V.v64p && A->d16p) {
         NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, double, double, ColsD16P, TR>), P.nb, P, A->sl_off,
                       ColsD16P{A->d16p}, V.v64p, W.mask, W.z, W.p0, W.q, W.w, ctx->partials,
-                      ctx->scal, j, max_it, rtol * rtol);
+                      L, j, max_it, rtol * rtol);
     } else {
         NN_DISPATCH_W(A->wmax, (k_cg_spmv<WM, double, double, ColsI32, TR>), P.nb, P, A->sl_off,
                       ColsI32{A->sl_col}, V.v64, W.mask, W.z, W.p0, W.q, W.w, ctx->partials,
-                      ctx->scal, j, max_it, rtol * rtol);
+                      L, j, max_it, rtol * rtol);
     }
 }
 
@@ -1068,11 +1088,12 @@ static void cg_update_tr(nn_ctx *ctx, int64_t n, int j, bool f32, const Cheb *ch
 {
     Part P = make_part(n);
     Workspace &W = ctx->ws;
+    const CgLink L{ctx->scal, ctx->flow, ctx->flow_cg};
     const double it = ch ? 1.0 / ch->theta : 0.0;
     const bool one = P.nslices <= P.nb * kWaves;
 #define NN_UPD(VV, ONE, p_, q_, dm_, w_, r_, z_, cres_, cdz_)                                    \
     NN_LAUNCH_ROWS((k_cg_update<VV, TR, ONE>), P.nb, P, W.mask, p_, q_, dm_, w_, r_, z_,         \
-                   ctx->partials, ctx->scal, j, ch ? cres_ : nullptr, ch ? cdz_[0] : nullptr, it, \
+                   ctx->partials, L, j, ch ? cres_ : nullptr, ch ? cdz_[0] : nullptr, it,        \
                    delta2)
     if (f32 && one) NN_UPD(float, true, W.p32, W.q32, W.dm32, W.w32, W.r32, W.z32, W.cres32, W.cdz32);
     else if (f32) NN_UPD(float, false, W.p32, W.q32, W.dm32, W.w32, W.r32, W.z32, W.cres32, W.cdz32);

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -59,6 +60,25 @@ struct DevScalars {
                            // 3 breakdown, 4 non-finite
     int it;                // CG iterations done
     int tr_hit;            // the last update stopped w on the trust-region boundary
+};
+
+// Pinned host memory that kernels write while the host polls it, so that the
+// host follows a solve without a copy and a stream synchronisation at each
+// decision (16 to 23 us each, of which the device idles most).  A word only
+// grows; the data it announces is stored before it (release, system scope).
+struct HostFlow {
+    alignas(64) unsigned long long pub;   // number of the last published reduction
+    alignas(64) unsigned long long cg;    // CG solve's number << 32 | iterations begun
+    alignas(64) unsigned long long end;   // number of the last CG solve that ended
+    alignas(64) DevScalars scal;          // its scalars
+    alignas(64) double part[kMaxBlocks * (5 + 3 * kLadder)];   // published partials
+};
+
+// What the CG kernels of one solve share.
+struct CgLink {
+    DevScalars *S;
+    HostFlow *F;
+    unsigned epoch;   // the CG solve's number
 };
 
 // ---------------------------------------------------------------- objects
@@ -220,10 +240,10 @@ struct nn_ctx {
     hipStream_t cap_stream = nullptr;  // private stream for graph capture (batched CG)
     std::string err;
     double *partials = nullptr;      // [kSlots][kMaxBlocks][kMaxRed]
-    double *h_part = nullptr;        // pinned host copy of one slot
-    double *h_multi = nullptr;       // pinned host copy of the gradient + Cauchy ladder partials
     nnqp::DevScalars *scal = nullptr;
-    nnqp::DevScalars *h_scal = nullptr;  // pinned mirror
+    nnqp::HostFlow *flow = nullptr;  // pinned; see HostFlow
+    unsigned long long flow_pub = 0; // reductions published so far
+    unsigned flow_cg = 0;            // CG solves begun so far
     nnqp::Workspace ws;
     nnqp::LmWork lm;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -280,7 +300,20 @@ void sell_offsets(const int64_t *rowptr, int64_t n, std::vector<int64_t> &off, i
 // Device CSR values (ordered by rowptr) -> sliced-ELL arrays of A (col, vals, diag).
 nn_status sell_build(nn_ctx *ctx, nn_matrix *A, const int64_t *rowptr_host, const double *csr_val,
                      const double *csr_mval);
-nn_status read_scalars(nn_ctx *ctx);
+// Waits until the words of ctx->flow (or another pinned word that the stream's
+// kernels write) satisfy ready(); an error, or a stream that has run dry
+// without it, ends the wait.
+nn_status flow_wait(nn_ctx *ctx, const std::function<bool()> &ready);
+// Partials [value][block] of up to two slots to ctx->flow->part, one after the
+// other, and the wait for them.
+struct Publish {
+    const double *src;
+    int nv, nb;
+};
+nn_status publish(nn_ctx *ctx, const Publish &a, const Publish &b = Publish{nullptr, 0, 0});
+// The combination, in block order, of value k of published partials that start
+// at `at` (in values).
+double published(const nn_ctx *ctx, int at, int k, int nb, int op);
 // Combine the host-slot partials of the last reduction kernel over n rows;
 // ops[k] is OP_SUM / OP_MIN / OP_MAX for value k.
 nn_status host_reduce(nn_ctx *ctx, int64_t n, int nv, const int *ops, double *out);

@@ -111,36 +111,53 @@ nn_status cheb_prepare(nn_ctx *ctx, const nn_matrix *A, const double *vals, cons
     return NN_OK;
 }
 
-// One synchronisation for the gradient report (5 values, host slot) and the
-// Cauchy ladder (3 kLadder values from SLOT_U0 on); both combined in block order.
+// One wait for the gradient report (5 values, host slot) and the Cauchy ladder
+// (3 kLadder values from SLOT_U0 on); both combined in block order.
 static nn_status read_grad_and_ladder(nn_ctx *ctx, int64_t n, double *grad, double *ladder)
 {
     const Part P = make_part(n), PL = make_part(n, kLadderBlocks);
-    double *h = ctx->h_multi;
-    const size_t ng = (size_t)4 * kMaxBlocks + P.nb;
-    const size_t nl = (size_t)(3 * kLadder - 1) * kMaxBlocks + PL.nb;
-    NN_HIP_TRY(ctx, hipMemcpyAsync(h, ctx->partials, sizeof(double) * ng, hipMemcpyDeviceToHost,
-                                   ctx->stream));
-    const double *lsrc = ctx->partials + (size_t)SLOT_U0 * kMaxRed * kMaxBlocks;
-    NN_HIP_TRY(ctx, hipMemcpyAsync(h + (size_t)5 * kMaxBlocks, lsrc, sizeof(double) * nl,
-                                   hipMemcpyDeviceToHost, ctx->stream));
-    NN_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    const nn_status rc =
+        publish(ctx, Publish{ctx->partials, 5, P.nb},
+                Publish{ctx->partials + (size_t)SLOT_U0 * kMaxRed * kMaxBlocks, 3 * kLadder, PL.nb});
+    if (rc != NN_OK) return rc;
     static const int kGradOps[5] = {OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM};
-    for (int k = 0; k < 5; k++) {
-        const int op = kGradOps[k];
-        double a = op == OP_SUM ? 0.0 : (op == OP_MIN ? INFINITY : -INFINITY);
-        for (int b = 0; b < P.nb; b++) {
-            const double v = h[(size_t)k * kMaxBlocks + b];
-            a = op == OP_SUM ? a + v : (op == OP_MIN ? std::fmin(a, v) : std::fmax(a, v));
-        }
-        grad[k] = a;
-    }
-    for (int k = 0; k < 3 * kLadder; k++) {
-        double a = 0.0;
-        for (int b = 0; b < PL.nb; b++) a += h[(size_t)(5 + k) * kMaxBlocks + b];
-        ladder[k] = a;
-    }
+    for (int k = 0; k < 5; k++) grad[k] = published(ctx, 0, k, P.nb, kGradOps[k]);
+    for (int k = 0; k < 3 * kLadder; k++) ladder[k] = published(ctx, 5, k, PL.nb, OP_SUM);
     return NN_OK;
+}
+
+// Runs one CG solve behind its set-up: enqueue(j) launches iteration j.  The
+// device reports each iteration that begins, and the end; the host keeps
+// `ahead` iterations enqueued beyond the last one begun.  A launch after the
+// end returns at once, but costs 2 us, so it is two: the iteration that covers
+// the host's way to a launch and one behind it (262 k rows float64: 2, 3, 4, 6
+// ahead 12.1, 12.4, 12.7, 13.1 ms; 90 k rows with float32 values, whose
+// iterations take 8 us, 26.7 +- 0.3 ms at any of them).  With a synchronisation
+// each 16 iterations instead the two took 18.6 and 38.5 ms.
+constexpr int kAhead = 2;
+
+template <class Enqueue>
+static nn_status run_cg(nn_ctx *ctx, const nn_opts *o, Enqueue enqueue)
+{
+    const int ahead = o->cg_chunk > 0 ? std::min(o->cg_chunk, kAhead) : kAhead;
+    const unsigned long long epoch = ctx->flow_cg;
+    const HostFlow *F = ctx->flow;
+    for (int j = 0;;) {
+        unsigned long long begun = 0;
+        bool ended = false;
+        const nn_status rc = flow_wait(ctx, [&] {
+            ended = __atomic_load_n(&F->end, __ATOMIC_ACQUIRE) == epoch;
+            const unsigned long long w = __atomic_load_n(&F->cg, __ATOMIC_RELAXED);
+            begun = (w >> 32) == epoch ? (w & 0xffffffffull) : 0;
+            return ended || (unsigned long long)j < begun + ahead;
+        });
+        if (rc != NN_OK) return rc;
+        if (ended) return NN_OK;
+        ctx->prof_seq = j;
+        enqueue(j++);
+        ctx->prof_seq = -1;
+        NN_HIP_TRY(ctx, hipGetLastError());
+    }
 }
 
 nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const float *vals32,
@@ -171,7 +188,7 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
     nn_status rc = ensure_workspace(ctx, n);
     if (rc != NN_OK) return rc;
     Workspace &W = ctx->ws;
-    DevScalars &H = *ctx->h_scal;
+    DevScalars &H = ctx->flow->scal;
     const Bytes B{(double)n, (double)A->nnz};
     const double tol = o->tol;
     // Mixed precision: the searches and the inner CG use float32 values (and
@@ -233,12 +250,7 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
     double t_cauchy = 1.0;
     double delta = o->delta0 > 0.0 ? o->delta0 : INFINITY;
     const bool tr = std::isfinite(delta);   // CG truncated at the trust-region boundary
-    // CG iterations enqueued between convergence reads: a fixed chunk, or
-    // (cg_chunk 0) a first chunk of at most 16 sized from the previous inner
-    // solve's count, so a short inner solve enqueues fewer launches that find
-    // it finished (each returns at once, but still costs a few microseconds)
-    const int chunk = o->cg_chunk > 0 ? o->cg_chunk : 16;
-    int cg_guess = chunk;   // iterations of the previous inner solve
+    bool crossed = true;      // the last projected search needed a trial
     nn_status result = NN_EMAXIT;
     bool subspace = false;    // this iteration continues the subspace loop (no Cauchy step)
     int sub_run = 0;          // subspace steps taken in the current outer iteration
@@ -415,36 +427,32 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         const double delta_rem = delta - step_outer;
         const double delta2 = tr ? std::max(delta_rem, 0.0) * std::max(delta_rem, 0.0) : INFINITY;
         prof_begin(ctx, KC_OTHER, 40.0 * n);
+        ctx->flow_cg++;
         launch_cg_setup(ctx, A, diag, c, W.g, cg_ks, mixed, box,
                         subspace ? FACE_INTERIOR : FACE_BINDING, chp);
         prof_end(ctx);
         S.bytes_moved += 88.0 * n;
         for (int st = 1; st <= csteps; st++) launch_cheb(ctx, A, VS, cheb, st, SLOT_U0);
-        int it_seen = 0, j_next = 0;
+        int it_seen = 0;
         H.done = tr && !(delta_rem > 0.0) ? 2 : 0;   // no room left: no CG step
-        for (int round = 0; !H.done; round++) {
+        if (!H.done) {
             const size_t mark = ctx->prof_live.size();
-            const int this_chunk = o->cg_chunk > 0 || round > 0
-                                       ? chunk
-                                       : std::max(2, std::min(chunk, cg_guess + 2));
-            for (int k = 0; k < this_chunk; k++, j_next++) {
-                ctx->prof_seq = k;
+            rc = run_cg(ctx, o, [&](int j) {
                 prof_begin(ctx, KC_CG_SPMV, -1.0);
-                launch_cg_spmv(ctx, A, VS, j_next, o->max_cg, o->inner_rtol, tr);
+                launch_cg_spmv(ctx, A, VS, j, o->max_cg, o->inner_rtol, tr);
                 prof_end(ctx);
                 prof_begin(ctx, KC_CG_UPDATE, -1.0);
-                launch_cg_update(ctx, n, j_next, mixed, chp, delta2);
+                launch_cg_update(ctx, n, j, mixed, chp, delta2);
                 prof_end(ctx);
-                const int slot = ((j_next + 1) & 1) ? SLOT_U1 : SLOT_U0;
+                const int slot = ((j + 1) & 1) ? SLOT_U1 : SLOT_U0;
                 for (int st = 1; st <= csteps; st++) {
                     prof_begin(ctx, KC_OTHER, -1.0);
                     launch_cheb(ctx, A, VS, cheb, st, slot);
                     prof_end(ctx);
                 }
-            }
-            ctx->prof_seq = -1;
-            if ((rc = read_scalars(ctx)) != NN_OK) return rc;
-            const int ran = H.it - it_seen;
+            });
+            if (rc != NN_OK) return rc;
+            const int ran = H.it;
             // byte model of the launches that did work; the rest exited at once
             const double nf = H.n_free, nzf = H.nnz_free;
             // matrix pass on the free rows (indices 4 or 2 B, values 8 or 4 B), z gathered,
@@ -464,16 +472,15 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
             const double c_upd = 7.0 * vb * nf;
             for (size_t e = mark; e < ctx->prof_live.size(); e++) {
                 ProfEntry &P = ctx->prof_live[e];
-                P.valid = P.seq >= 0 && P.seq < ran;   // the chunk's launches that did work
+                P.valid = P.seq >= 0 && P.seq < ran;   // the launches that did work
                 P.bytes = P.cls == KC_CG_SPMV ? b_spmv : (P.cls == KC_OTHER ? b_cheb : b_upd);
                 P.bytes_csr = P.cls == KC_CG_SPMV ? c_spmv : (P.cls == KC_OTHER ? b_cheb : c_upd);
             }
             S.bytes_moved += ran * (b_spmv + b_upd + csteps * b_cheb);
             S.spmvs += ran * (1 + csteps);
-            it_seen = H.it;
+            it_seen = ran;
         }
         S.cg_its += it_seen;
-        if (H.done != 2 || it_seen > 0) cg_guess = it_seen;
         // |pg| on the CG face at the Cauchy point: r.r at the CG set-up, kept
         // on the device as rtol^2 r.r in the stop threshold
         if (!subspace && H.done != 2) pg_cauchy = std::sqrt(H.rr_stop) / o->inner_rtol;
@@ -481,28 +488,50 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         if (H.done == 3) return finish(fail(ctx, NN_ENOTSPD, "non-positive curvature in CG"));
         const bool on_boundary = H.done == 2;   // the CG step stopped on the trust region
 
-        // ---- 4. projected search along w
+        // ---- 4. projected search along w: first crossing, g.w, w.w, and,
+        // where the last search needed one, the first trial (t = 1) behind it,
+        // so that one wait covers both (a trial that turns out not to be
+        // needed costs one matrix pass and is not counted)
         prof_begin(ctx, KC_OTHER, 24.0 * n);
         launch_breakpoint(ctx, n, c, dir_w, W.g, box);
         prof_end(ctx);
         S.bytes_moved += 24.0 * n;
-        if ((rc = host_reduce(ctx, n, 3, kBrkOps, red)) != NN_OK) return rc;
+        auto trial_w = [&](double t) {
+            prof_begin(ctx, KC_TRIAL, spmv_s + 16.0 * n, spmv_csr + 16.0 * n);
+            launch_trial(ctx, A, VS, c, dir_w, t, W.g, W.mask, nullptr, box);
+            prof_end(ctx);
+        };
+        const Part Pn = make_part(n);
+        const Publish p_brk{ctx->partials + (size_t)SLOT_Q * kMaxRed * kMaxBlocks, 3, Pn.nb};
+        const bool early = crossed && !tr && it_seen > 0;
+        double tred[3] = {0.0, 0.0, 0.0};
+        if (early) {
+            trial_w(1.0);
+            rc = publish(ctx, p_brk, Publish{ctx->partials, 3, Pn.nb});
+            for (int k = 0; k < 3; k++) tred[k] = published(ctx, 3, k, Pn.nb, kTrialOps[k]);
+        } else {
+            rc = publish(ctx, p_brk);
+        }
+        if (rc != NN_OK) return rc;
+        for (int k = 0; k < 3; k++) red[k] = published(ctx, 0, k, Pn.nb, kBrkOps[k]);
         const double bmin = red[0], gw = red[1], wn = std::sqrt(red[2]);
         bool new_face = false;   // the step reached a bound the CG face did not hold
         if (it_seen > 0 && gw < 0.0 && wn > 0.0) {
             // |w| <= delta_rem up to rounding: the CG kept it in the ball
             double tmax = std::min(1.0, delta_rem / wn);
             double ts = tmax;
-            if (bmin < tmax) {
+            crossed = bmin < tmax;
+            if (crossed) {
                 for (int k = 0; k < kMaxTrials; k++) {
-                    prof_begin(ctx, KC_TRIAL, spmv_s + 16.0 * n, spmv_csr + 16.0 * n);
-                    launch_trial(ctx, A, VS, c, dir_w, ts, W.g, W.mask, nullptr, box);
-                    prof_end(ctx);
                     S.spmvs++;
                     S.search_trials++;
                     S.bytes_moved += spmv_s + 16.0 * n;
-                    if ((rc = host_reduce(ctx, n, 3, kTrialOps, red)) != NN_OK) return rc;
-                    const double g2 = red[0], s2 = red[1];
+                    // (without a trust region tmax = 1, the trial made above)
+                    if (k > 0 || !early) {
+                        trial_w(ts);
+                        if ((rc = host_reduce(ctx, n, 3, kTrialOps, tred)) != NN_OK) return rc;
+                    }
+                    const double g2 = tred[0], s2 = tred[1];
                     if (g2 < 0.0 && g2 + 0.5 * s2 <= kMu0 * g2) break;
                     ts *= kBack;
                     if (ts <= bmin) {
@@ -574,7 +603,7 @@ nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const 
     nn_status rc = ensure_workspace(ctx, n);
     if (rc != NN_OK) return rc;
     Workspace &W = ctx->ws;
-    DevScalars &H = *ctx->h_scal;
+    DevScalars &H = ctx->flow->scal;
     const Bytes B{(double)n, (double)A->nnz};
     static const int kInitOps[4] = {OP_SUM, OP_MAX, OP_SUM, OP_SUM};
     static const int kResidOps[5] = {OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM};
@@ -606,7 +635,6 @@ nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const 
         return finish(rc);
     const Cheb *chp = cheb.degree > 1 ? &cheb : nullptr;
     const int csteps = cheb.degree - 1;
-    const int chunk = o->cg_chunk > 0 ? o->cg_chunk : 16;
     const double b_spmv = n + 4.0 * n + eb * A->nnz + 40.0 * n;
     const double b_upd = n + 64.0 * n;
     double rel = 1.0;   // ||f - K c|| / ||f|| at c = 0
@@ -617,46 +645,40 @@ nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const 
         S.spmvs++;
         S.bytes_moved += B.spmv() + 16.0 * n;
         prof_begin(ctx, KC_OTHER, 40.0 * n);
+        ctx->flow_cg++;
         launch_cg_setup(ctx, A, A->diag, c, W.g, nullptr, false, unbounded, FACE_ALL, chp);
         prof_end(ctx);
         S.bytes_moved += 88.0 * n;
         for (int st = 1; st <= csteps; st++) launch_cheb(ctx, A, VS, cheb, st, SLOT_U0);
         const double rtol = std::min(0.5, o->tol / rel);
         const int budget = o->max_cg - S.cg_its;
-        int it_seen = 0, j_next = 0;
-        for (;;) {
-            const size_t mark = ctx->prof_live.size();
-            for (int k = 0; k < chunk; k++, j_next++) {
-                ctx->prof_seq = k;
-                prof_begin(ctx, KC_CG_SPMV, -1.0);
-                launch_cg_spmv(ctx, A, VS, j_next, budget, rtol);
+        const size_t mark = ctx->prof_live.size();
+        rc = run_cg(ctx, o, [&](int j) {
+            prof_begin(ctx, KC_CG_SPMV, -1.0);
+            launch_cg_spmv(ctx, A, VS, j, budget, rtol);
+            prof_end(ctx);
+            prof_begin(ctx, KC_CG_UPDATE, -1.0);
+            launch_cg_update(ctx, n, j, false, chp);
+            prof_end(ctx);
+            const int slot = ((j + 1) & 1) ? SLOT_U1 : SLOT_U0;
+            for (int st = 1; st <= csteps; st++) {
+                prof_begin(ctx, KC_OTHER, -1.0);
+                launch_cheb(ctx, A, VS, cheb, st, slot);
                 prof_end(ctx);
-                prof_begin(ctx, KC_CG_UPDATE, -1.0);
-                launch_cg_update(ctx, n, j_next, false, chp);
-                prof_end(ctx);
-                const int slot = ((j_next + 1) & 1) ? SLOT_U1 : SLOT_U0;
-                for (int st = 1; st <= csteps; st++) {
-                    prof_begin(ctx, KC_OTHER, -1.0);
-                    launch_cheb(ctx, A, VS, cheb, st, slot);
-                    prof_end(ctx);
-                }
             }
-            ctx->prof_seq = -1;
-            if ((rc = read_scalars(ctx)) != NN_OK) return rc;
-            const int ran = H.it - it_seen;
-            const double b_cheb = n + 4.0 * n + eb * A->nnz + 64.0 * n;
-            const double c_spmv = 12.0 * A->nnz + 52.0 * n, c_upd = 56.0 * n;   // CSR model
-            for (size_t e = mark; e < ctx->prof_live.size(); e++) {
-                ProfEntry &P = ctx->prof_live[e];
-                P.valid = P.seq >= 0 && P.seq < ran;   // the chunk's launches that did work
-                P.bytes = P.cls == KC_CG_SPMV ? b_spmv : (P.cls == KC_OTHER ? b_cheb : b_upd);
-                P.bytes_csr = P.cls == KC_CG_SPMV ? c_spmv : (P.cls == KC_OTHER ? b_cheb : c_upd);
-            }
-            S.bytes_moved += ran * (b_spmv + b_upd + csteps * b_cheb);
-            S.spmvs += ran * (1 + csteps);
-            it_seen = H.it;
-            if (H.done) break;
+        });
+        if (rc != NN_OK) return rc;
+        const int ran = H.it, it_seen = ran;
+        const double b_cheb = n + 4.0 * n + eb * A->nnz + 64.0 * n;
+        const double c_spmv = 12.0 * A->nnz + 52.0 * n, c_upd = 56.0 * n;   // CSR model
+        for (size_t e = mark; e < ctx->prof_live.size(); e++) {
+            ProfEntry &P = ctx->prof_live[e];
+            P.valid = P.seq >= 0 && P.seq < ran;   // the launches that did work
+            P.bytes = P.cls == KC_CG_SPMV ? b_spmv : (P.cls == KC_OTHER ? b_cheb : b_upd);
+            P.bytes_csr = P.cls == KC_CG_SPMV ? c_spmv : (P.cls == KC_OTHER ? b_cheb : c_upd);
         }
+        S.bytes_moved += ran * (b_spmv + b_upd + csteps * b_cheb);
+        S.spmvs += ran * (1 + csteps);
         S.cg_its += it_seen;
         if (H.done == 4) return finish(fail(ctx, NN_ENONFINITE, "non-finite value in CG"));
         if (H.done == 3) return finish(fail(ctx, NN_ENOTSPD, "non-positive curvature in CG"));

@@ -314,3 +314,64 @@ def test_blmvm_memories(ctx, mesh, m):
     assert st["kkt_rel"] <= tol and c.min() >= 0.0
     assert np.abs(c - ref).max() <= (4e-6 if mesh == "square" else 4e-3) * np.abs(ref).max()
     K.free()
+
+
+# iterations enqueued ahead of the device (solves), steps of a chunk (batch):
+# the same bits for any number, with a trust region (early ends) and without
+@pytest.mark.parametrize("what", ["tron", "radius", "mixed", "cheb", "galerkin", "batch"])
+def test_work_enqueued_ahead_does_not_matter(ctx, what):
+    from paper_1506_08435_amd import nnqp
+    kw = {"radius": {"delta0": 1e-3}, "mixed": {"precision": nnqp.NN_MIXED},
+          "cheb": {"precond_degree": 3}}.get(what, {})
+    if what == "batch":
+        members = [ctx.assemble(W.batch_problem(i, n_range=(8, 40)))[:2] for i in range(5)]
+    else:
+        K, F, _ = ctx.assemble(W.cube3d(19))
+    got = []
+    for chunk in (1, 2, 16, 0):
+        if what == "batch":
+            c = ctx.solve_batch([m[0] for m in members], [m[1] for m in members], tol=1e-10,
+                                cg_chunk=chunk)[0]
+            got.append((b"".join(x.cpu().numpy().tobytes() for x in c),))
+        elif what == "galerkin":
+            c, st = ctx.solve_galerkin(K, F, tol=1e-10, cg_chunk=chunk)[:2]
+            got.append((c.cpu().numpy().tobytes(), st["cg_its"], st["spmvs"], st["bytes_moved"]))
+        else:
+            c, _, st = ctx.solve_nonneg(K, F, tol=1e-10, cg_chunk=chunk, **kw)
+            got.append((c.cpu().numpy().tobytes(), st["cg_its"], st["spmvs"], st["search_trials"],
+                        st["bytes_moved"], st["n_active"]))
+    assert all(g == got[0] for g in got), [g[1:] for g in got]
+
+
+def test_solves_on_several_threads(ctx):
+    """One context, stream and matrix per thread, several solves each at the
+    same time: the bits of a solve alone."""
+    import threading
+    import torch
+    from paper_1506_08435_amd import nnqp
+    sizes = [21, 24, 27]
+    alone = []
+    for n in sizes:
+        K, F, _ = ctx.assemble(W.cube3d(n))
+        alone.append(ctx.solve_nonneg(K, F, tol=1e-10)[0].cpu().numpy().copy())
+        K.free()
+    got, errors = {}, []
+
+    def work(i):
+        try:
+            c = nnqp.Context(0, stream=torch.cuda.Stream(0))
+            K, F, _ = c.assemble(W.cube3d(sizes[i]))
+            got[i] = [c.solve_nonneg(K, F, tol=1e-10)[0].cpu().numpy().copy() for _ in range(4)]
+            K.free()
+            c.close()
+        except Exception as e:   # noqa: BLE001 (reported by the main thread)
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for i in range(3):
+        assert all(np.array_equal(x, alone[i]) for x in got[i]), i
