@@ -125,10 +125,26 @@ __global__ __launch_bounds__(kBlock) void k_add(Part P, double *__restrict__ c,
 // Trial point of a projected search: s = P(c + t d) - c, formed for every
 // gathered column; ks = K s; report g.s, s.Ks, s.s.  Rows with mask == 0 are
 // skipped when a mask is given (there d = 0, so s = 0 and they add nothing).
+// BRK: the breakpoint pass (k_breakpoint) of the same direction in the same
+// launch, its values into SLOT_Q; it reads nothing that the trial's rows have
+// not loaded, so a launch of its own (3.8 us on 262 k rows, 18 us on 2 M)
+// goes.
 constexpr uint32_t kOpsTrial = OPS3(OP_SUM, OP_SUM, OP_SUM);
+constexpr uint32_t kOpsBrk = OPS3(OP_MIN, OP_SUM, OP_SUM);
 
-template <int WMAX, class VT, class VD, class Cols>
-__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_trial(Part P, const int *__restrict__ so, Cols sc,
+// Largest step along w before a free variable reaches a bound:
+// min over w_i < 0 of (c_i - lo) / (-w_i) and over w_i > 0 of (hi - c_i) / w_i
+// (+inf for hi = +inf), g.w, w.w
+__device__ __forceinline__ void breakpoint(double ci, double wi, double gi, const Box &B, double (&a)[3])
+{
+    if (wi < 0.0) a[0] = fmin(a[0], (ci - B.lo) / (-wi));
+    else if (wi > 0.0) a[0] = fmin(a[0], (B.hi - ci) / wi);
+    a[1] += gi * wi;
+    a[2] += wi * wi;
+}
+
+template <int WMAX, class VT, class VD, class Cols, bool BRK>
+__global__ __launch_bounds__(kBlock, BRK ? 8 : walk_waves<Cols>()) void k_trial(Part P, const int *__restrict__ so, Cols sc,
                                                   const VT *__restrict__ v,
                                                   const double *__restrict__ c,
                                                   const VD *__restrict__ d, double t,
@@ -140,8 +156,9 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_trial(Part P, co
         const double cj = (c + ub)[l];
         return proj_box(cj + t * (double)(d + ub)[l], B) - cj;
     };
-    double a[3];
+    double a[3], brk[3];
     red_init<kOpsTrial, 3>(a);
+    red_init<kOpsBrk, 3>(brk);
     walk_rows<WMAX, 5>(P, so, sc, v, [&](int i) { return mask == nullptr || mask[i] != 0; },
                     [&](int i) { return Two{sv(0, i), g[i]}; }, sv, [&](int i, double s, Two sg) {
                         if (ks) ks[i] = s;
@@ -149,8 +166,10 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_trial(Part P, co
                         a[0] += sg.b * si;
                         a[1] += si * s;
                         a[2] += si * si;
+                        if constexpr (BRK) breakpoint(c[i], (double)d[i], sg.b, B, brk);
                     });
     block_partial<kOpsTrial, 3>(a, slot_ptr(partials, SLOT_HOST));
+    if constexpr (BRK) block_partial<kOpsBrk, 3>(brk, slot_ptr(partials, SLOT_Q));
 }
 
 // Cauchy ladder: the projected steepest-descent trial s_k = P(c - t_k g) - c
@@ -237,7 +256,9 @@ __global__ __launch_bounds__(kBlock) void k_init(Part P, double *__restrict__ c,
     block_partial<kOpsInit, 4>(a, slot_ptr(partials, SLOT_HOST));
 }
 
-// Set-up of the inner CG on the face of (c, g + ks):
+// Set-up of the inner CG on the face of (c, g + ks), behind the Cauchy step
+// c <- P(c + t g) of length t (t != 0; a launch of its own before: 3.3 us on
+// 262 k rows, and c and g twice):
 //   g <- g + ks (gradient at the Cauchy point), free = not (c == 0 and g >= 0),
 //   dm = 1/diag on free rows and 0 elsewhere (the mask folded into the
 //   Jacobi preconditioner), r = -g on free rows, z = dm r, p = q = w = 0.
@@ -247,7 +268,7 @@ constexpr uint32_t kOpsU = OPS4(OP_SUM, OP_SUM, OP_SUM, OP_SUM);
 template <class VV>
 __global__ __launch_bounds__(kBlock) void k_cg_setup(
     Part P, const int *__restrict__ rp, const double *__restrict__ diag,
-    const double *__restrict__ c, double *__restrict__ g, const double *__restrict__ ks,
+    double *__restrict__ c, double *__restrict__ g, const double *__restrict__ ks, double t,
     uint8_t *__restrict__ mask, VV *__restrict__ dm, VV *__restrict__ r, VV *__restrict__ z,
     VV *__restrict__ p, VV *__restrict__ q, VV *__restrict__ w, double *partials, DevScalars *S,
     Box B, int face, VV *__restrict__ cres, VV *__restrict__ cdz0, VV *__restrict__ cdz1,
@@ -256,9 +277,15 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(
     double a[4] = {0.0, 0.0, 0.0, 0.0};
     for_rows(P, [&](int i, bool act) {
         if (!act) return;
-        const double gi = ks ? g[i] + ks[i] : g[i];
-        if (ks) g[i] = gi;
-        const double cv = c[i];
+        double cv = c[i], gi = g[i];
+        if (t != 0.0) {
+            cv = proj_box(cv + t * gi, B);
+            c[i] = cv;
+        }
+        if (ks) {
+            gi = gi + ks[i];
+            g[i] = gi;
+        }
         const bool fr = face == FACE_ALL ? true
                       : face == FACE_INTERIOR ? (cv != B.lo && cv != B.hi)
                       : !((cv == B.lo && gi >= 0.0) || (cv == B.hi && gi <= 0.0));
@@ -634,12 +661,7 @@ __global__ __launch_bounds__(kBlock) void k_gersh(Part P, const int *__restrict_
     block_partial<OP_MAX, 1>(a, slot_ptr(partials, SLOT_HOST));
 }
 
-// Largest step along w before a free variable reaches a bound:
-// min over w_i < 0 of (c_i - lo) / (-w_i) and over w_i > 0 of (hi - c_i) / w_i
-// (+inf for hi = +inf), g.w, w.w; partials into SLOT_Q, so that a trial may
-// follow before they are read
-constexpr uint32_t kOpsBrk = OPS3(OP_MIN, OP_SUM, OP_SUM);
-
+// The breakpoint pass on its own (no trial beside it); partials into SLOT_Q.
 template <class VV>
 __global__ __launch_bounds__(kBlock) void k_breakpoint(Part P, const double *__restrict__ c,
                                                        const VV *__restrict__ w,
@@ -650,11 +672,7 @@ __global__ __launch_bounds__(kBlock) void k_breakpoint(Part P, const double *__r
     red_init<kOpsBrk, 3>(a);
     for_rows(P, [&](int i, bool act) {
         if (!act) return;
-        const double wi = (double)w[i];
-        if (wi < 0.0) a[0] = fmin(a[0], (c[i] - B.lo) / (-wi));
-        else if (wi > 0.0) a[0] = fmin(a[0], (B.hi - c[i]) / wi);
-        a[1] += g[i] * wi;
-        a[2] += wi * wi;
+        breakpoint(c[i], (double)w[i], g[i], B, a);
     });
     block_partial<kOpsBrk, 3>(a, slot_ptr(partials, SLOT_Q));
 }
@@ -855,61 +873,35 @@ void launch_grad(nn_ctx *ctx, const nn_matrix *A, const double *vals, const doub
 }
 
 void launch_trial(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double *c, Dir d,
-                  double t, const double *g, const uint8_t *mask, double *ks, Box B)
+                  double t, const double *g, const uint8_t *mask, double *ks, Box B, bool brk)
 {
     Part P = make_part(A->n);
-    if (A->diag_plan && (V.v32q || V.v64p)) {
-        const ColsDiag cols = diag_cols(A, V.v32q ? A->d16q : A->d16p);
-        if (V.v32q && d.f32)
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, float, ColsDiag>), P.nb, P, A->sl_off, cols,
-                          V.v32q, c, d.f32, t, g, mask, ks, ctx->partials, B);
-        else if (V.v32q)
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, double, ColsDiag>), P.nb, P, A->sl_off, cols,
-                          V.v32q, c, d.f64, t, g, mask, ks, ctx->partials, B);
-        else
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, double, double, ColsDiag>), P.nb, P, A->sl_off,
-                          cols, V.v64p, c, d.f64, t, g, mask, ks, ctx->partials, B);
-    } else if (V.v32q && A->d16q) {
-        const ColsD16Q cols{A->d16q};
-        if (d.f32)
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, float, ColsD16Q>), P.nb, P, A->sl_off, cols,
-                          V.v32q, c, d.f32, t, g, mask, ks, ctx->partials, B);
-        else
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, double, ColsD16Q>), P.nb, P, A->sl_off, cols,
-                          V.v32q, c, d.f64, t, g, mask, ks, ctx->partials, B);
-    } else if (V.v32 && A->sl_d16) {
-        const ColsD16 cols{A->sl_d16};
-        if (d.f32)
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, float, ColsD16>), P.nb, P, A->sl_off, cols,
-                          V.v32, c, d.f32, t, g, mask, ks, ctx->partials, B);
-        else
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, double, ColsD16>), P.nb, P, A->sl_off, cols,
-                          V.v32, c, d.f64, t, g, mask, ks, ctx->partials, B);
-    } else if (V.v32) {
-        const ColsI32 cols{A->sl_col};
-        if (d.f32)
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, float, ColsI32>), P.nb, P, A->sl_off, cols,
-                          V.v32, c, d.f32, t, g, mask, ks, ctx->partials, B);
-        else
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, float, double, ColsI32>), P.nb, P, A->sl_off, cols,
-                          V.v32, c, d.f64, t, g, mask, ks, ctx->partials, B);
-    } else if (V.v64p && A->d16p) {
-        const ColsD16P cols{A->d16p};
-        if (d.f32)
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, double, float, ColsD16P>), P.nb, P, A->sl_off, cols,
-                          V.v64p, c, d.f32, t, g, mask, ks, ctx->partials, B);
-        else
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, double, double, ColsD16P>), P.nb, P, A->sl_off, cols,
-                          V.v64p, c, d.f64, t, g, mask, ks, ctx->partials, B);
-    } else {
-        const ColsI32 cols{A->sl_col};
-        if (d.f32)
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, double, float, ColsI32>), P.nb, P, A->sl_off, cols,
-                          V.v64, c, d.f32, t, g, mask, ks, ctx->partials, B);
-        else
-            NN_DISPATCH_W(A->wmax, (k_trial<WM, double, double, ColsI32>), P.nb, P, A->sl_off, cols,
-                          V.v64, c, d.f64, t, g, mask, ks, ctx->partials, B);
-    }
+    auto go = [&](auto cols, const auto *v, const auto *dv) {
+        using Cols = decltype(cols);
+        using VT = std::remove_cv_t<std::remove_pointer_t<decltype(v)>>;
+        using VD = std::remove_cv_t<std::remove_pointer_t<decltype(dv)>>;
+        if constexpr (std::is_same_v<VT, VD>) {   // the CG step's type
+            if (brk) {
+                NN_DISPATCH_W(A->wmax, (k_trial<WM, VT, VD, Cols, true>), P.nb, P, A->sl_off, cols,
+                              v, c, dv, t, g, mask, ks, ctx->partials, B);
+                return;
+            }
+        }
+        NN_DISPATCH_W(A->wmax, (k_trial<WM, VT, VD, Cols, false>), P.nb, P, A->sl_off, cols, v, c,
+                      dv, t, g, mask, ks, ctx->partials, B);
+    };
+    // float32 values: the Cauchy direction is float64, the CG step float32
+    auto go32 = [&](auto cols, const float *v) {
+        if (d.f32) go(cols, v, d.f32);
+        else go(cols, v, d.f64);
+    };
+    if (A->diag_plan && V.v32q) go32(diag_cols(A, A->d16q), V.v32q);
+    else if (A->diag_plan && V.v64p) go(diag_cols(A, A->d16p), V.v64p, d.f64);
+    else if (V.v32q && A->d16q) go32(ColsD16Q{A->d16q}, V.v32q);
+    else if (V.v32 && A->sl_d16) go32(ColsD16{A->sl_d16}, V.v32);
+    else if (V.v32) go32(ColsI32{A->sl_col}, V.v32);
+    else if (V.v64p && A->d16p) go(ColsD16P{A->d16p}, V.v64p, d.f64);
+    else go(ColsI32{A->sl_col}, V.v64, d.f64);
 }
 
 void launch_ladder(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double *c,
@@ -966,21 +958,20 @@ void launch_add(nn_ctx *ctx, int64_t n, double *c, const double *w)
     k_add<double><<<P.nb, kBlock, 0, ctx->stream>>>(P, c, w);
 }
 
-void launch_cg_setup(nn_ctx *ctx, const nn_matrix *A, const double *diag, const double *c,
-                     double *g, const double *ks, bool f32, Box B, int face,
-                     const Cheb *ch)
+void launch_cg_setup(nn_ctx *ctx, const nn_matrix *A, const double *diag, double *c, double *g,
+                     const double *ks, double t, bool f32, Box B, int face, const Cheb *ch)
 {
     Part P = make_part(A->n);
     Workspace &W = ctx->ws;
     const double it = ch ? 1.0 / ch->theta : 0.0;
     if (f32)
         k_cg_setup<float><<<P.nb, kBlock, 0, ctx->stream>>>(
-            P, A->rowptr, diag, c, g, ks, W.mask, W.dm32, W.r32, W.z32, W.p32, W.q32, W.w32,
+            P, A->rowptr, diag, c, g, ks, t, W.mask, W.dm32, W.r32, W.z32, W.p32, W.q32, W.w32,
             ctx->partials, ctx->scal, B, face, ch ? W.cres32 : nullptr,
             ch ? W.cdz32[0] : nullptr, ch ? W.cdz32[1] : nullptr, it);
     else
         k_cg_setup<double><<<P.nb, kBlock, 0, ctx->stream>>>(
-            P, A->rowptr, diag, c, g, ks, W.mask, W.dm, W.r, W.z, W.p0, W.q, W.w, ctx->partials,
+            P, A->rowptr, diag, c, g, ks, t, W.mask, W.dm, W.r, W.z, W.p0, W.q, W.w, ctx->partials,
             ctx->scal, B, face, ch ? W.cres : nullptr, ch ? W.cdz[0] : nullptr,
             ch ? W.cdz[1] : nullptr, it);
 }

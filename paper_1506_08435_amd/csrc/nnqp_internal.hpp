@@ -351,22 +351,23 @@ void launch_init(nn_ctx *ctx, int64_t n, double *c, const double *f, int mode, d
 // #(c at a bound) sum
 void launch_grad(nn_ctx *ctx, const nn_matrix *A, const double *vals, const double *vals_p,
                  const double *c, const double *f, double *g, Box B);
-// [host] s = P(c + t d) - c gathered, ks = A s; g.s, s.As, s.s (sums); rows with mask == 0 skipped
+// [host] s = P(c + t d) - c gathered, ks = A s; g.s, s.As, s.s (sums); rows with mask == 0 skipped;
+// brk: with the values of launch_breakpoint for the direction d
 void launch_trial(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double *c, Dir d,
-                  double t, const double *g, const uint8_t *mask, double *ks, Box B);
+                  double t, const double *g, const uint8_t *mask, double *ks, Box B,
+                  bool brk = false);
 // [SLOT_U0..U1, 15 values] Cauchy ladder: for k < kLadder, s_k = P(c - t[k] g) - c,
 // ks[k] = A s_k; g.s_k, s_k.A s_k, s_k.s_k as values 3k..3k+2
 void launch_ladder(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double *c,
                    const double *g, const double *t, double *const *ks, Box B);
 // c = P(c + t d)
 void launch_apply(nn_ctx *ctx, int64_t n, double *c, Dir d, double t, Box B);
-// CG set-up on the face of (c, g + ks) (every row not binding: not at lo with
+// CG set-up, behind the step c = P(c + t g) when t != 0, on the face of (c, g + ks) (every row not binding: not at lo with
 // g >= 0, not at hi with g <= 0: FACE_BINDING; every row: FACE_ALL; every row
 // strictly inside the bounds: FACE_INTERIOR); partials of r.z,
 // r.r, #free, nnz(free) in SLOT_U0; f32 selects the float32 CG vectors
-void launch_cg_setup(nn_ctx *ctx, const nn_matrix *A, const double *diag, const double *c,
-                     double *g, const double *ks, bool f32, Box B, int face,
-                     const Cheb *ch = nullptr);
+void launch_cg_setup(nn_ctx *ctx, const nn_matrix *A, const double *diag, double *c, double *g,
+                     const double *ks, double t, bool f32, Box B, int face, const Cheb *ch);
 // Chebyshev step `step` (1..degree-1) on the free rows; the last one writes
 // r.z into value 0 of partial slot `slot`
 void launch_cheb(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const Cheb &ch, int step,

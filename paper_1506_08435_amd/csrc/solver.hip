@@ -323,6 +323,7 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
             break;
         }
         const double *cg_ks = nullptr;   // Cauchy-step product added to g at the CG set-up
+        double cauchy_step = 0.0;
         if (subspace) {
             S.subspace_its++;
         } else {
@@ -414,10 +415,7 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
                 }
             }
             t_cauchy = t;
-            prof_begin(ctx, KC_OTHER, 24.0 * n);
-            launch_apply(ctx, n, c, dir_g, -t, box);
-            prof_end(ctx);
-            S.bytes_moved += 24.0 * n;
+            cauchy_step = -t;   // taken by the CG set-up
             step_outer = std::sqrt(ss);
             cg_ks = best_ks;
         }
@@ -426,12 +424,13 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         // of the current point on a subspace step), inside the radius left
         const double delta_rem = delta - step_outer;
         const double delta2 = tr ? std::max(delta_rem, 0.0) * std::max(delta_rem, 0.0) : INFINITY;
-        prof_begin(ctx, KC_OTHER, 40.0 * n);
+        const double b_step = cauchy_step != 0.0 ? 8.0 * n : 0.0;   // c written
+        prof_begin(ctx, KC_OTHER, 40.0 * n + b_step);
         ctx->flow_cg++;
-        launch_cg_setup(ctx, A, diag, c, W.g, cg_ks, mixed, box,
+        launch_cg_setup(ctx, A, diag, c, W.g, cg_ks, cauchy_step, mixed, box,
                         subspace ? FACE_INTERIOR : FACE_BINDING, chp);
         prof_end(ctx);
-        S.bytes_moved += 88.0 * n;
+        S.bytes_moved += 88.0 * n + b_step;
         for (int st = 1; st <= csteps; st++) launch_cheb(ctx, A, VS, cheb, st, SLOT_U0);
         int it_seen = 0;
         H.done = tr && !(delta_rem > 0.0) ? 2 : 0;   // no room left: no CG step
@@ -489,16 +488,12 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         const bool on_boundary = H.done == 2;   // the CG step stopped on the trust region
 
         // ---- 4. projected search along w: first crossing, g.w, w.w, and,
-        // where the last search needed one, the first trial (t = 1) behind it,
-        // so that one wait covers both (a trial that turns out not to be
-        // needed costs one matrix pass and is not counted)
-        prof_begin(ctx, KC_OTHER, 24.0 * n);
-        launch_breakpoint(ctx, n, c, dir_w, W.g, box);
-        prof_end(ctx);
-        S.bytes_moved += 24.0 * n;
-        auto trial_w = [&](double t) {
+        // where the last search needed one, the first trial (t = 1) in the
+        // same launch, so that one wait covers both (a trial that turns out
+        // not to be needed costs one matrix pass and is not counted)
+        auto trial_w = [&](double t, bool brk) {
             prof_begin(ctx, KC_TRIAL, spmv_s + 16.0 * n, spmv_csr + 16.0 * n);
-            launch_trial(ctx, A, VS, c, dir_w, t, W.g, W.mask, nullptr, box);
+            launch_trial(ctx, A, VS, c, dir_w, t, W.g, W.mask, nullptr, box, brk);
             prof_end(ctx);
         };
         const Part Pn = make_part(n);
@@ -506,10 +501,14 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         const bool early = crossed && !tr && it_seen > 0;
         double tred[3] = {0.0, 0.0, 0.0};
         if (early) {
-            trial_w(1.0);
+            trial_w(1.0, true);
             rc = publish(ctx, p_brk, Publish{ctx->partials, 3, Pn.nb});
             for (int k = 0; k < 3; k++) tred[k] = published(ctx, 3, k, Pn.nb, kTrialOps[k]);
         } else {
+            prof_begin(ctx, KC_OTHER, 24.0 * n);
+            launch_breakpoint(ctx, n, c, dir_w, W.g, box);
+            prof_end(ctx);
+            S.bytes_moved += 24.0 * n;
             rc = publish(ctx, p_brk);
         }
         if (rc != NN_OK) return rc;
@@ -528,7 +527,7 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
                     S.bytes_moved += spmv_s + 16.0 * n;
                     // (without a trust region tmax = 1, the trial made above)
                     if (k > 0 || !early) {
-                        trial_w(ts);
+                        trial_w(ts, false);
                         if ((rc = host_reduce(ctx, n, 3, kTrialOps, tred)) != NN_OK) return rc;
                     }
                     const double g2 = tred[0], s2 = tred[1];
@@ -646,7 +645,7 @@ nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const 
         S.bytes_moved += B.spmv() + 16.0 * n;
         prof_begin(ctx, KC_OTHER, 40.0 * n);
         ctx->flow_cg++;
-        launch_cg_setup(ctx, A, A->diag, c, W.g, nullptr, false, unbounded, FACE_ALL, chp);
+        launch_cg_setup(ctx, A, A->diag, c, W.g, nullptr, 0.0, false, unbounded, FACE_ALL, chp);
         prof_end(ctx);
         S.bytes_moved += 88.0 * n;
         for (int st = 1; st <= csteps; st++) launch_cheb(ctx, A, VS, cheb, st, SLOT_U0);
