@@ -1,7 +1,7 @@
 // P1 assembly of the stiffness matrix K, capacity matrix M and load F.
 //
 // The mesh is uploaded once and everything after the size checks runs on the
-// device (a 96 x 96 x 24 slab with K and M, 208 k rows: 4.2 ms, 1.4 of them in
+// device (a 96 x 96 x 24 slab with K and M, 208 k rows: 4.1 ms, 1.1 of them in
 // kernels and most of the rest in the transfer of 48 MB; 38 ms with a symbolic
 // phase on the host's threads): validation, free-DOF numbering (scan),
 // node-to-element incidence (count, scan, fill, sort each node's few elements),
@@ -350,43 +350,63 @@ void scan(hipStream_t st, int64_t n, Get get, Put put, int64_t *sums, int64_t *t
     ka_scan_put<<<nb, 256, 0, st>>>(n, get, put, sums);
 }
 
-// elements at each node (cnt zero on entry)
+// elements at each node (cnt zero on entry), and the place of each in its
+// node's list (in any order): 149 us for 5.3 M, the rate of the atomics, which
+// the fill behind it then does without (218 -> 20 us)
 __global__ __launch_bounds__(256) void ka_count(int64_t m, const int *__restrict__ elems,
-                                                int *__restrict__ cnt)
+                                                int *__restrict__ cnt, int *__restrict__ place)
 {
     for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < m; t += (int64_t)gridDim.x * 256)
-        atomicAdd(&cnt[elems[t]], 1);
+        place[t] = atomicAdd(&cnt[elems[t]], 1);
 }
 
-// every element into its nodes' lists (in any order; left counts down to zero)
-__global__ __launch_bounds__(256) void ka_fill(int64_t ne, int nv, const int *__restrict__ elems,
-                                               const int64_t *__restrict__ ptr, int *__restrict__ left,
-                                               int *__restrict__ list)
+// every element into its nodes' lists
+template <int NV>
+__global__ __launch_bounds__(256) void ka_fill(int64_t m, const int *__restrict__ elems,
+                                               const int64_t *__restrict__ ptr,
+                                               const int *__restrict__ place, int *__restrict__ list)
 {
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < ne; e += (int64_t)gridDim.x * 256)
-        for (int a = 0; a < nv; a++) {
-            const int v = elems[e * nv + a];
-            list[ptr[v] + atomicSub(&left[v], 1) - 1] = (int)e;
-        }
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < m; t += (int64_t)gridDim.x * 256)
+        list[ptr[elems[t]] + place[t]] = (int)(t / NV);
 }
 
-// Each node's elements in increasing order (insertion: the lists are short;
-// a longer one has no row here, or sends the mesh to the host).
+__device__ __forceinline__ void insertion_sort(int *x, int n)
+{
+    for (int i = 1; i < n; i++) {
+        const int e = x[i];
+        int k = i;
+        while (k > 0 && x[k - 1] > e) {
+            x[k] = x[k - 1];
+            k--;
+        }
+        x[k] = e;
+    }
+}
+
+// Each node's elements in increasing order (insertion: the lists are short and
+// nearly sorted; a longer one has no row here, or sends the mesh to the host).
+// The lists of a block's 256 nodes are one range: it goes through LDS when it
+// fits (32 elements a node), where the sort's dependent accesses are cheap
+// (228 k nodes of 24 elements: 167 -> 50 us).
+constexpr int kSortLds = 256 * 32;
+
 __global__ __launch_bounds__(256) void ka_sort(int64_t nn, const int64_t *__restrict__ ptr,
                                                int *__restrict__ list)
 {
-    const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (v >= nn) return;
-    const int64_t a = ptr[v], b = ptr[v + 1];
-    if (b - a > kIncMax) return;
-    for (int64_t i = a + 1; i < b; i++) {
-        const int e = list[i];
-        int64_t k = i;
-        while (k > a && list[k - 1] > e) {
-            list[k] = list[k - 1];
-            k--;
-        }
-        list[k] = e;
+    __shared__ int s[kSortLds];
+    const int64_t v0 = (int64_t)blockIdx.x * 256, v = v0 + threadIdx.x;
+    const int64_t r0 = ptr[v0], r1 = ptr[min(v0 + 256, nn)];
+    const int64_t a = v < nn ? ptr[v] : r1, b = v < nn ? ptr[v + 1] : r1;
+    const int len = b - a > kIncMax ? 0 : (int)(b - a);
+    if (r1 - r0 <= kSortLds) {
+        const int m = (int)(r1 - r0);
+        for (int i = threadIdx.x; i < m; i += 256) s[i] = list[r0 + i];
+        __syncthreads();
+        insertion_sort(s + (a - r0), len);
+        __syncthreads();
+        for (int i = threadIdx.x; i < m; i += 256) list[r0 + i] = s[i];
+    } else {
+        insertion_sort(list + a, len);
     }
 }
 
@@ -798,8 +818,8 @@ nn_status assemble_impl(nn_ctx *ctx, const nn_mesh *mesh, const double *D, int64
     const Part pe = part(4 * ue * nv), pc = part(8 * un * dim), pD = part(8 * (size_t)nD * dim * dim),
                pk = part(kscale ? 8 * ue : 0), pf = part(8 * ue), pv = part(dvals ? 8 * un : 0),
                pm = part(un), pdof = part(4 * un), pfree = part(4 * un), pcnt = part(4 * un),
-               pptr = part(8 * (un + 1)), pinc = part(4 * ue * nv), plen = part(4 * un),
-               pwid = part(4 * (un / kSlice + 2)), psum = part(8 * (un / kScan + 2)),
+               pptr = part(8 * (un + 1)), pinc = part(4 * ue * nv), pplace = part(4 * ue * nv),
+               plen = part(4 * un), pwid = part(4 * (un / kSlice + 2)), psum = part(8 * (un / kScan + 2)),
                pfl = part(sizeof(AsmFlags)), pF = part(F_dev ? 0 : 8 * un);
     DevBuf buf(ctx->al);
     if (dev_malloc(ctx->al, &buf.p, total) != hipSuccess) return fail(ctx, NN_EOOM, "assembly scratch");
@@ -831,7 +851,7 @@ nn_status assemble_impl(nn_ctx *ctx, const nn_mesh *mesh, const double *D, int64
     if (dvals) NN_HIP_TRY(ctx, up(pv, dvals));
     const uint8_t *mask = (const uint8_t *)at(pm);
     int *dof = (int *)at(pdof), *free_node = (int *)at(pfree), *cnt = (int *)at(pcnt);
-    int *list = (int *)at(pinc), *rowlen = (int *)at(plen), *width = (int *)at(pwid);
+    int *list = (int *)at(pinc), *place = (int *)at(pplace), *rowlen = (int *)at(plen), *width = (int *)at(pwid);
     int64_t *ptr = (int64_t *)at(pptr), *sums = (int64_t *)at(psum);
     const int *elems = (const int *)at(pe);
     AsmArgs args;
@@ -892,7 +912,7 @@ nn_status assemble_impl(nn_ctx *ctx, const nn_mesh *mesh, const double *D, int64
     if ((rc = hip(e, "matrix allocation")) != NN_OK) return cleanup(rc);
     int *rowptr = M->rowptr, *so = M->sl_off;
     e = hipMemsetAsync(cnt, 0, sizeof(int) * un, st);
-    if (e == hipSuccess && ne > 0) ka_count<<<grid(ne * nv), 256, 0, st>>>(ne * nv, elems, cnt);
+    if (e == hipSuccess && ne > 0) ka_count<<<grid(ne * nv), 256, 0, st>>>(ne * nv, elems, cnt, place);
     scan(st, nn, [cnt] __device__(int64_t v) { return cnt[v]; },
          [cnt, ptr, nn] __device__(int64_t v, int64_t k) {
              ptr[v] = k;
@@ -900,7 +920,8 @@ nn_status assemble_impl(nn_ctx *ctx, const nn_mesh *mesh, const double *D, int64
          },
          sums, &flags->inc);
     if (ne > 0) {
-        ka_fill<<<grid(ne), 256, 0, st>>>(ne, nv, elems, ptr, cnt, list);
+        if (dim == 2) ka_fill<3><<<grid(ne * nv), 256, 0, st>>>(ne * nv, elems, ptr, place, list);
+        else ka_fill<4><<<grid(ne * nv), 256, 0, st>>>(ne * nv, elems, ptr, place, list);
         ka_sort<<<(unsigned)((nn + 255) / 256), 256, 0, st>>>(nn, ptr, list);
     }
     if (n > 0) {
