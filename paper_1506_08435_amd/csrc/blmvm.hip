@@ -139,7 +139,7 @@ __device__ __forceinline__ void wave_sums(double (&a)[NV])
 // Block total of NV sums (fixed order: butterfly within the wavefront, waves
 // in order) stored as this block's partial part[k * kMaxBlocks + block].
 template <int NV>
-__device__ __forceinline__ void block_sums(double (&a)[NV], double *part)
+__device__ __forceinline__ void block_sums(double (&a)[NV], double *part, const Part &P)
 {
     constexpr int G = wave_sums_regs<NV>();
     __shared__ double sh[kWaves][4 * G];
@@ -153,7 +153,7 @@ __device__ __forceinline__ void block_sums(double (&a)[NV], double *part)
         double v = sh[0][k];
 #pragma unroll
         for (int w = 1; w < kWaves; w++) v += sh[w][k];
-        part[k * kMaxBlocks + blockIdx.x] = v;
+        part[k * kMaxBlocks + block_id(P)] = v;
     }
 }
 
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(kBlock) void kl_pairs(Part P, double *__restrict__ 
             }
         }
     });
-    block_sums<NV>(a, part);
+    block_sums<NV>(a, part, P);
 }
 
 // 2. coefficient kernel: one block.  Each wavefront combines the block
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kBlock) void kl_dir(Part P, const double *__restric
         a[1] += gi * di;
         a[2] += di * di;
     });
-    block_partial<kOps, 3>(a, slot_ptr(partials, SLOT_Q));
+    block_partial<kOps, 3>(a, slot_ptr(partials, SLOT_Q), block_id(P));
 }
 
 // 4. trial: gathers c(t) = P(c + t d), writes gn = K c(t) - f; g.s, s.(gn - g), s.s
@@ -519,7 +519,7 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void kl_trial(Part P, c
                         a[1] += x.a * (gni - x.c);
                         a[2] += x.a * x.a;
                     });
-    block_partial<kOps, 3>(a, slot_ptr(partials, SLOT_HOST));
+    block_partial<kOps, 3>(a, slot_ptr(partials, SLOT_HOST), block_id(P));
 }
 
 // 5. step: c <- P(c + t d), s -> slot head, g <- g + gscale (gn - g)

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void kd_offsets(Part P, const int *__restrict_
 {
     const int lane = threadIdx.x & 63;
     const int s = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-    if (s >= P.nslices) return;
+    if (s >= P.nslices()) return;
     const int row = s * kSlice + lane, off = so[s];
     const int len = row < P.n ? rp[row + 1] - rp[row] : 0;
     constexpr int kNone = 0x7fffffff;
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void kd_fill(Part P, const int *__restrict__ s
 {
     const int lane = threadIdx.x & 63;
     const int nw = gridDim.x * 4;
-    for (int s = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)); s < P.nslices;
+    for (int s = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)); s < P.nslices();
          s += nw) {
         const int row = s * kSlice + lane, off = so[s];
         const int len = row < P.n ? rp[row + 1] - rp[row] : 0;
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void kd_symmetric(Part P, const int *__restric
     const int nw = gridDim.x * 4;
     auto bits = [](double x) { return __double_as_longlong(x); };
     int bad = 0;
-    for (int s = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)); s < P.nslices;
+    for (int s = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)); s < P.nslices();
          s += nw) {
         if (mirrored[srun[s]] == 0) continue;
         const DiagRun &r = runs[srun[s]];
@@ -181,7 +181,7 @@ nn_status fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const T *src,
     const int *srun = (const int *)index;
     const DiagRun *runs = (const DiagRun *)(srun + D.srun.size());
     const int *mir = (const int *)(runs + D.runs.size());
-    const int nb = std::max(1, std::min((P.nslices + 3) / 4, 4096));
+    const int nb = std::max(1, std::min((P.nslices() + 3) / 4, 4096));
     // zeros: the rows before a run from row 0 on (the kernel writes the rest)
     if (D.runs[D.srun[0]].kind != DR_GENERAL || D.mirrored[D.srun[0]])
         NN_HIP_TRY(ctx, hipMemsetAsync(dst, 0, sizeof(T) * (size_t)D.entries, ctx->stream));
@@ -438,7 +438,7 @@ nn_status diag_find(nn_ctx *ctx, nn_matrix *A, void *scratch)
             const int *srun = (const int *)scratch;
             const DiagRun *runs = (const DiagRun *)(srun + D->srun.size());
             NN_HIP_TRY(ctx, hipMemsetAsync(flag, 0, sizeof(int), ctx->stream));
-            kd_symmetric<<<std::max(1, std::min((P.nslices + 3) / 4, 4096)), 256, 0, ctx->stream>>>(
+            kd_symmetric<<<std::max(1, std::min((P.nslices() + 3) / 4, 4096)), 256, 0, ctx->stream>>>(
                 P, A->sl_off, A->sl_col, A->rowptr, srun, runs, (const int *)(runs + D->runs.size()),
                 A->val, A->mval, flag);
             NN_HIP_TRY(ctx, hipGetLastError());

@@ -158,7 +158,7 @@ __device__ __forceinline__ void diag_rows(const Part &P, const ColsDiag &D,
     const int nw = P.nb * kWaves;
     using XT = decltype(x(0, 0));
     auto x1 = [&](int ub, int l, XT (&out)[1]) { out[0] = x(ub, l); };
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += nw) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += nw) {
         const int row = s * kSlice + lane;
         const bool act = row < P.n && active(row);
         const PV pv = act ? pre(row) : PV();
@@ -177,7 +177,7 @@ __device__ __forceinline__ void diag_rows_n(const Part &P, const ColsDiag &D,
     constexpr int W = diag_width<WMAX>();
     const int lane = threadIdx.x & 63, wid = wave_id();
     const int nw = P.nb * kWaves;
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += nw) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += nw) {
         const int row = s * kSlice + lane;
         const bool act = row < P.n;
         const PV pv = act ? pre(row) : PV();

@@ -22,15 +22,25 @@
 
 namespace nnqp {
 
-Part make_part(int64_t n, int max_blocks)
+// Neighbouring blocks share an XCD where that was measured faster: passes with
+// one slice per wavefront at most (up to 524,288 rows: solves of 62^3, 71^3 and
+// the 9^3-celled hole 12.0 -> 11.5, 21.4 -> 19.9, 26.1 -> 24.5 ms, 79^3 Galerkin
+// 12.2 -> 10.7), and float32 passes of any size (100^3, 127^3: 26.4 -> 23.9,
+// 79.8 -> 78.7 ms).  Larger float64 passes stream from HBM, and it costs them
+// more than the reuse gives (81^3, 89^3, 99^3, 127^3 rows: 32.7 -> 31.4,
+// 31.5 -> 32.7, 40.0 -> 38.9, 130.6 -> 138.9 ms).
+Part make_part(int64_t n, int max_blocks, bool f32)
 {
     Part p;
     p.n = (int)n;
-    p.nslices = (int)((n + kSlice - 1) / kSlice);
-    int64_t nb = (p.nslices + kWaves - 1) / kWaves;
+    int64_t nb = (p.nslices() + kWaves - 1) / kWaves;
     if (nb < 1) nb = 1;
     if (nb > max_blocks) nb = max_blocks;
     p.nb = (int)nb;
+    if (f32 || p.nslices() <= nb * kWaves) {
+        const int64_t last = (p.nslices() % (nb * kWaves) + kWaves - 1) / kWaves;
+        p.heavy = (int)(last < nb ? last : 0);
+    }
     return p;
 }
 
@@ -85,7 +95,7 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_grad(Part P, con
         a[3] = fmin(a[3], cv);
         a[4] += (cv == B.lo || cv == B.hi) ? 1.0 : 0.0;
     });
-    block_partial<kOpsGrad, 5>(a, slot_ptr(partials, SLOT_HOST));
+    block_partial<kOpsGrad, 5>(a, slot_ptr(partials, SLOT_HOST), block_id(P));
 }
 
 // Residual report of an unconstrained solve: r = K c - f (not stored);
@@ -109,7 +119,7 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_resid(Part P, co
                         a[3] = fmin(a[3], cf.a);
                         a[4] += cf.a < 0.0 ? 1.0 : 0.0;
                     });
-    block_partial<kOpsResid, 5>(a, slot_ptr(partials, SLOT_HOST));
+    block_partial<kOpsResid, 5>(a, slot_ptr(partials, SLOT_HOST), block_id(P));
 }
 
 // c += w (no projection: the unconstrained solve)
@@ -168,8 +178,8 @@ __global__ __launch_bounds__(kBlock, BRK ? 8 : walk_waves<Cols>()) void k_trial(
                         a[2] += si * si;
                         if constexpr (BRK) breakpoint(c[i], (double)d[i], sg.b, B, brk);
                     });
-    block_partial<kOpsTrial, 3>(a, slot_ptr(partials, SLOT_HOST));
-    if constexpr (BRK) block_partial<kOpsBrk, 3>(brk, slot_ptr(partials, SLOT_Q));
+    block_partial<kOpsTrial, 3>(a, slot_ptr(partials, SLOT_HOST), block_id(P));
+    if constexpr (BRK) block_partial<kOpsBrk, 3>(brk, slot_ptr(partials, SLOT_Q), block_id(P));
 }
 
 // Cauchy ladder: the projected steepest-descent trial s_k = P(c - t_k g) - c
@@ -216,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void k_ladder(Part P, const int *__restrict
     // the nine running sums stay in registers for the whole pass, so the
     // entries load NNQP_LADDER_PHASE at a time
     walk_rows_n<WMAX, kLadder, NNQP_LADDER_PHASE>(P, so, sc, v, pre, trials, epi);
-    block_partial<0u, 3 * kLadder>(a, slot_ptr(partials, SLOT_U0));
+    block_partial<0u, 3 * kLadder>(a, slot_ptr(partials, SLOT_U0), block_id(P));
 }
 
 // c = P(c + t d)
@@ -253,7 +263,7 @@ __global__ __launch_bounds__(kBlock) void k_init(Part P, double *__restrict__ c,
             c[i] = proj_box(cv, B);
         }
     });
-    block_partial<kOpsInit, 4>(a, slot_ptr(partials, SLOT_HOST));
+    block_partial<kOpsInit, 4>(a, slot_ptr(partials, SLOT_HOST), block_id(P));
 }
 
 // Set-up of the inner CG on the face of (c, g + ks), behind the Cauchy step
@@ -310,7 +320,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_setup(
         a[2] += fr ? 1.0 : 0.0;
         a[3] += fr ? (double)(rp[i + 1] - rp[i]) : 0.0;
     });
-    block_partial<kOpsU, 4>(a, slot_ptr(partials, SLOT_U0));
+    block_partial<kOpsU, 4>(a, slot_ptr(partials, SLOT_U0), block_id(P));
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         S->done = 0;
         S->it = 0;
@@ -392,7 +402,7 @@ __device__ __forceinline__ bool cg_begin(const CgIn &in, const double *slot, int
 }
 
 template <int WMAX, class VT, class VV, class Cols, bool TR>
-__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cg_spmv(Part P, const int *__restrict__ so, Cols sc,
+__global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cg_spmv(Part P0, const int *__restrict__ so, Cols sc,
                                                     const VT *__restrict__ v,
                                                     const uint8_t *__restrict__ mask,
                                                     const VV *__restrict__ z,
@@ -401,6 +411,9 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cg_spmv(Part P, 
                                                     double *partials, CgLink L, int j,
                                                     int max_it, double rtol2)
 {
+    // (what the launcher's choice of the kernel says about make_part's)
+    Part P = P0;
+    if constexpr (std::is_same_v<Cols, ColsDiag> && std::is_same_v<VV, double>) P.heavy = -1;
     const DevScalars *const S = L.S;
     if (S->done) return;
     const CgIn in = cg_in(S, j);
@@ -426,7 +439,7 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cg_spmv(Part P, 
                             a[2] += (double)w[i] * (double)pi;
                         }
                     });
-    block_partial<0u, NQ>(a, slot_ptr(partials, SLOT_Q));
+    block_partial<0u, NQ>(a, slot_ptr(partials, SLOT_Q), block_id(P));
 }
 
 // The same pass on the diagonal layout when a wavefront has one slice at most
@@ -439,7 +452,7 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cg_spmv(Part P, 
 // before the combination, is the whole row below that and eight above it
 // (64 VGPRs).
 template <int WMAX, class VT, class VV, bool TR, int PH>
-__global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
+__global__ __launch_bounds__(kBlock, PH < diag_width<WMAX>() ? 8 : 1) void k_cg_spmv_one(Part P0, ColsDiag sc,
                                                         const VT *__restrict__ v,
                                                         const uint8_t *__restrict__ mask,
                                                         const VV *__restrict__ z,
@@ -448,6 +461,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
                                                         CgLink L, int j, int max_it,
                                                         double rtol2)
 {
+    Part P = P0;
+    P.heavy = 0;   // make_part's choice for a pass of one slice per wavefront
     constexpr int W = diag_width<WMAX>();
     const DevScalars *const S = L.S;
     const int stop = S->done;
@@ -456,8 +471,9 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
     double u[2], beta;
     load_partials<0u, 2>(slot, P.nb, u);
     const int lane = threadIdx.x & 63;
-    const int s0 = blockIdx.x * kWaves + wave_id();
-    const int s = min(s0, P.nslices - 1);   // a wavefront past the last slice loads it and drops it
+    const int blk = block_id(P);
+    const int s0 = blk * kWaves + wave_id();
+    const int s = min(s0, P.nslices() - 1);   // a wavefront past the last slice loads it and drops it
     const int row0 = s * kSlice, row = row0 + lane;
     const bool in_n = row < P.n;
     const int r = in_n ? row : P.n - 1;
@@ -481,7 +497,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
     if (t.kind != DR_GENERAL) load(0);
     if (stop) return;
     if (cg_begin<TR>(in, slot, P.nb, u, L, j, max_it, rtol2, beta)) return;
-    const bool act = in_n && m != 0 && s0 < P.nslices;
+    const bool act = in_n && m != 0 && s0 < P.nslices();
     double acc[1] = {0.0};
     if (t.kind != DR_GENERAL) {
 #pragma unroll
@@ -510,7 +526,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
             a[2] += (double)w[row] * (double)pi;
         }
     }
-    block_partial<0u, NQ>(a, slot_ptr(partials, SLOT_Q));
+    block_partial<0u, NQ>(a, slot_ptr(partials, SLOT_Q), blk);
 }
 
 // CG iteration j, vector update on free rows.
@@ -528,7 +544,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_spmv_one(Part P, ColsDiag sc,
 // ONE: a wavefront has one slice at most, and issues its loads before the
 // partials' combination (as k_cg_spmv_one).
 template <class VV, bool TR, bool ONE>
-__global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__restrict__ mask,
+__global__ __launch_bounds__(kBlock) void k_cg_update(Part P0, const uint8_t *__restrict__ mask,
                                                       const VV *__restrict__ p,
                                                       const VV *__restrict__ q,
                                                       const VV *__restrict__ dm,
@@ -538,6 +554,9 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
                                                       VV *__restrict__ cdz0, double inv_theta,
                                                       double delta2)
 {
+    Part P = P0;
+    if constexpr (ONE) P.heavy = 0;
+    else if constexpr (std::is_same_v<VV, double>) P.heavy = -1;
     DevScalars *const S = L.S;
     const int stop = S->done;
     if constexpr (!ONE)
@@ -552,7 +571,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
     };
     auto own = [&](int i) { return Own{r[i], q[i], dm[i], w[i], p[i], mask[i]}; };
     Own o1{};
-    const int i1 = (blockIdx.x * kWaves + wave_id()) * kSlice + (threadIdx.x & 63);
+    const int blk = block_id(P);
+    const int i1 = (blk * kWaves + wave_id()) * kSlice + (threadIdx.x & 63);
     if constexpr (ONE) {
         o1 = own(min(i1, P.n - 1));
         if (stop) return;
@@ -607,7 +627,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_update(Part P, const uint8_t *__r
             if (act && mask[i]) step(i, own(i));
         });
     }
-    block_partial<0u, 2>(a, slot_ptr(partials, ((j + 1) & 1) ? SLOT_U1 : SLOT_U0));
+    block_partial<0u, 2>(a, slot_ptr(partials, ((j + 1) & 1) ? SLOT_U1 : SLOT_U0), blk);
     if (blockIdx.x == 0 && threadIdx.x == 0) S->it = j + 1;
 }
 
@@ -640,7 +660,7 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cheb(Part P, con
                         z[i] = zn;
                         a[0] += (double)r[i] * (double)zn;
                     });
-    if (last) block_partial<OP_SUM, 1>(a, slot_ptr(partials, slot));
+    if (last) block_partial<OP_SUM, 1>(a, slot_ptr(partials, slot), block_id(P));
 }
 
 // Gershgorin bound of the spectrum of D^-1 A: max over rows of sum_j |a_ij| / a_ii
@@ -658,7 +678,7 @@ __global__ __launch_bounds__(kBlock) void k_gersh(Part P, const int *__restrict_
         for (int k = 0; k < w; k++) sum += fabs(v[off + k * kSlice + lane]);
         a[0] = fmax(a[0], sum / diag[i]);
     });
-    block_partial<OP_MAX, 1>(a, slot_ptr(partials, SLOT_HOST));
+    block_partial<OP_MAX, 1>(a, slot_ptr(partials, SLOT_HOST), block_id(P));
 }
 
 // The breakpoint pass on its own (no trial beside it); partials into SLOT_Q.
@@ -674,7 +694,7 @@ __global__ __launch_bounds__(kBlock) void k_breakpoint(Part P, const double *__r
         if (!act) return;
         breakpoint(c[i], (double)w[i], g[i], B, a);
     });
-    block_partial<kOpsBrk, 3>(a, slot_ptr(partials, SLOT_Q));
+    block_partial<kOpsBrk, 3>(a, slot_ptr(partials, SLOT_Q), block_id(P));
 }
 
 __global__ __launch_bounds__(kBlock) void k_active(Part P, const double *__restrict__ c,
@@ -702,7 +722,7 @@ __global__ __launch_bounds__(kBlock) void k_pair(Part P, const int *__restrict__
                                                  const T *__restrict__ src, T *__restrict__ dst)
 {
     const int lane = threadIdx.x & 63, wid = wave_id();
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += P.nb * kWaves) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += P.nb * kWaves) {
         const int off = so[s], w = (so[s + 1] - off) / kSlice, wp = 2 * (w / 2);
         for (int k = 0; k < w; k++) {
             const int from = off + k * kSlice + lane;
@@ -721,7 +741,7 @@ __global__ __launch_bounds__(kBlock) void k_quad(Part P, const int *__restrict__
                                                  const T *__restrict__ src, T *__restrict__ dst)
 {
     const int lane = threadIdx.x & 63, wid = wave_id();
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += P.nb * kWaves) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += P.nb * kWaves) {
         const int off = so[s], w = (so[s + 1] - off) / kSlice;
         const int nq = w / 4, np = (w - 4 * nq) / 2;
         for (int k = 0; k < w; k++) {
@@ -828,7 +848,7 @@ __global__ __launch_bounds__(kBlock) void k_sell_d16(Part P, const int *__restri
             sd[e] = (short)max(-32768, min(32767, d));
         }
     });
-    block_partial<OP_MAX, 1>(a, slot_ptr(partials, SLOT_HOST));
+    block_partial<OP_MAX, 1>(a, slot_ptr(partials, SLOT_HOST), block_id(P));
 }
 
 // ---------------------------------------------------------------- launchers
@@ -875,7 +895,7 @@ void launch_grad(nn_ctx *ctx, const nn_matrix *A, const double *vals, const doub
 void launch_trial(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double *c, Dir d,
                   double t, const double *g, const uint8_t *mask, double *ks, Box B, bool brk)
 {
-    Part P = make_part(A->n);
+    Part P = make_part(A->n, kMaxBlocks, V.v32 || V.v32q);
     auto go = [&](auto cols, const auto *v, const auto *dv) {
         using Cols = decltype(cols);
         using VT = std::remove_cv_t<std::remove_pointer_t<decltype(v)>>;
@@ -908,7 +928,7 @@ void launch_ladder(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double 
                    const double *g, const double *t, double *const *ks, Box B)
 {
     // 3 kLadder accumulators per lane: one 1024-thread block per CU
-    Part P = make_part(A->n, kLadderBlocks);
+    Part P = make_part(A->n, kLadderBlocks, V.v32 || V.v32q);
     Ladder L;
     for (int k = 0; k < kLadder; k++) {
         L.t[k] = t[k];
@@ -939,7 +959,7 @@ void launch_ladder(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const double 
 
 void launch_apply(nn_ctx *ctx, int64_t n, double *c, Dir d, double t, Box B)
 {
-    Part P = make_part(n);
+    Part P = make_part(n, kMaxBlocks, d.f32);
     if (d.f32) k_apply<float><<<P.nb, kBlock, 0, ctx->stream>>>(P, c, d.f32, t, B);
     else k_apply<double><<<P.nb, kBlock, 0, ctx->stream>>>(P, c, d.f64, t, B);
 }
@@ -961,7 +981,7 @@ void launch_add(nn_ctx *ctx, int64_t n, double *c, const double *w)
 void launch_cg_setup(nn_ctx *ctx, const nn_matrix *A, const double *diag, double *c, double *g,
                      const double *ks, double t, bool f32, Box B, int face, const Cheb *ch)
 {
-    Part P = make_part(A->n);
+    Part P = make_part(A->n, kMaxBlocks, f32);
     Workspace &W = ctx->ws;
     const double it = ch ? 1.0 / ch->theta : 0.0;
     if (f32)
@@ -979,7 +999,7 @@ void launch_cg_setup(nn_ctx *ctx, const nn_matrix *A, const double *diag, double
 void launch_cheb(nn_ctx *ctx, const nn_matrix *A, const Vals &V, const Cheb &ch, int step,
                  int slot)
 {
-    Part P = make_part(A->n);
+    Part P = make_part(A->n, kMaxBlocks, V.v32 || V.v32q);
     Workspace &W = ctx->ws;
     const double ca = ch.ca[step], cb = ch.cb[step];
     const int last = step == ch.degree - 1 ? 1 : 0;
@@ -1017,12 +1037,12 @@ template <bool TR>
 static void cg_spmv_tr(nn_ctx *ctx, const nn_matrix *A, const Vals &V, int j, int max_it,
                        double rtol)
 {
-    Part P = make_part(A->n);
+    Part P = make_part(A->n, kMaxBlocks, V.v32 || V.v32q);
     Workspace &W = ctx->ws;
     const CgLink L{ctx->scal, ctx->flow, ctx->flow_cg};
     if (A->diag_plan && (V.v32q || V.v64p)) {
         // one slice per wavefront at most: every load before the prologue
-        const bool one = P.nslices <= P.nb * kWaves, lone = P.nb <= kMaxBlocks / 2;
+        const bool one = P.nslices() <= P.nb * kWaves, lone = P.nb <= kMaxBlocks / 2;
         const ColsDiag cols = diag_cols(A, V.v32q ? A->d16q : A->d16p);
         if (V.v32q && one)
             NN_DISPATCH_W(A->wmax, (k_cg_spmv_one<WM, float, float, TR, diag_width<WM>()>), P.nb, P,
@@ -1077,11 +1097,11 @@ void launch_cg_spmv(nn_ctx *ctx, const nn_matrix *A, const Vals &V, int j, int m
 template <bool TR>
 static void cg_update_tr(nn_ctx *ctx, int64_t n, int j, bool f32, const Cheb *ch, double delta2)
 {
-    Part P = make_part(n);
+    Part P = make_part(n, kMaxBlocks, f32);
     Workspace &W = ctx->ws;
     const CgLink L{ctx->scal, ctx->flow, ctx->flow_cg};
     const double it = ch ? 1.0 / ch->theta : 0.0;
-    const bool one = P.nslices <= P.nb * kWaves;
+    const bool one = P.nslices() <= P.nb * kWaves;
 #define NN_UPD(VV, ONE, p_, q_, dm_, w_, r_, z_, cres_, cdz_)                                    \
     NN_LAUNCH_ROWS((k_cg_update<VV, TR, ONE>), P.nb, P, W.mask, p_, q_, dm_, w_, r_, z_,         \
                    ctx->partials, L, j, ch ? cres_ : nullptr, ch ? cdz_[0] : nullptr, it,        \
@@ -1101,7 +1121,7 @@ void launch_cg_update(nn_ctx *ctx, int64_t n, int j, bool f32, const Cheb *ch, d
 
 void launch_breakpoint(nn_ctx *ctx, int64_t n, const double *c, Dir w, const double *g, Box B)
 {
-    Part P = make_part(n);
+    Part P = make_part(n, kMaxBlocks, w.f32);
     if (w.f32)
         k_breakpoint<float><<<P.nb, kBlock, 0, ctx->stream>>>(P, c, w.f32, g, ctx->partials, B);
     else
@@ -1172,7 +1192,7 @@ void launch_csr_to_sell(nn_ctx *ctx, nn_matrix *A, const double *csr_val, const 
     Part P = make_part(A->n);
     k_csr_to_sell<<<P.nb, kBlock, 0, ctx->stream>>>(P, A->rowptr, A->col, csr_val, csr_mval,
                                                     A->sl_off, A->sl_col, A->val, A->mval);
-    k_sell_tail<<<1, kBlock, 0, ctx->stream>>>((int)A->n, P.nslices, A->sl_off, A->sl_col, A->val,
+    k_sell_tail<<<1, kBlock, 0, ctx->stream>>>((int)A->n, P.nslices(), A->sl_off, A->sl_col, A->val,
                                                A->mval);
 }
 

@@ -30,13 +30,18 @@ constexpr int kMaxRed = 8;         // values per reduction
 constexpr int kLadder = 3;         // step lengths of one Cauchy ladder pass (odd)
 constexpr int kLadderBlocks = 256; // blocks of a ladder pass
 
+// (twelve bytes: eight more move the CG passes' arguments into a fourth 64-byte
+// line, which cost solves of 100^3 to 127^3 rows 1 %)
 struct Part {
     int n = 0;        // rows
-    int nslices = 0;  // ceil(n / 64)
     int nb = 0;       // blocks
+    int heavy = -1;   // -1, or neighbouring blocks on one XCD (block_id): the first blocks,
+                      // which walk one slice per wavefront more than the rest
+    __host__ __device__ int nslices() const { return (int)(((unsigned)n + kSlice - 1u) / kSlice); }
 };
 
-Part make_part(int64_t n, int max_blocks = kMaxBlocks);
+// f32: a pass of a mixed-precision solve over float32 values or vectors
+Part make_part(int64_t n, int max_blocks = kMaxBlocks, bool f32 = false);
 
 // ---------------------------------------------------------------- reductions
 // A reduction kernel leaves one partial per block and value in a slot of

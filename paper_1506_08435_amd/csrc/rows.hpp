@@ -18,6 +18,25 @@ namespace nnqp {
 // 43 VGPRs with it).
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
+// The row block a workgroup takes.  Workgroups go round-robin to the eight
+// XCDs, each with an L2 of its own; a matrix row reads vector entries (and, in
+// the diagonal layout, stored values) of rows up to a grid plane away, some 4
+// to 16 blocks.  With P.heavy >= 0 each XCD takes a contiguous eighth of the row
+// blocks, the same in every pass; make_part says when.  The blocks that walk
+// one slice more than the others (the first P.heavy) are dealt out by
+// themselves: left contiguous they load two or three XCDs with all of the
+// second round (89^3 rows: 31.6 -> 38.0 ms instead of 32.7).  Which workgroup
+// computes a block's partials does not change them.
+__device__ __forceinline__ int block_id(const Part &P)
+{
+    if (P.heavy < 0) return blockIdx.x;
+    const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
+    const int h = P.heavy >> 3, hr = P.heavy & 7, t = P.nb >> 3, tr = P.nb & 7;
+    const int h0 = x * h + min(x, hr), t0 = x * t + min(x, tr);   // before this XCD's
+    const int nh = h + (x < hr ? 1 : 0);
+    return i < nh ? h0 + i : P.heavy + (t0 - h0) + (i - nh);
+}
+
 // ---------------------------------------------------------------- reductions
 template <uint32_t OPS>
 __device__ __forceinline__ constexpr int op_of(int k)
@@ -135,11 +154,12 @@ __device__ __forceinline__ double lanes_in_order(int op, double x)
     return v;
 }
 
-// Store this block's total of a[] as its partial: slot[k * kMaxBlocks + block].
+// Store this block's total of a[] as its partial: slot[k * kMaxBlocks + blk],
+// blk = block_id.
 // The wavefronts' totals meet in LDS once (one barrier); the first wavefront
 // reads them one per lane and combines them in wavefront order.
 template <uint32_t OPS, int NV>
-__device__ __forceinline__ void block_partial(double (&a)[NV], double *slot)
+__device__ __forceinline__ void block_partial(double (&a)[NV], double *slot, int blk)
 {
     __shared__ double sh[NV][kWaves];
     const int lane = threadIdx.x & 63, wid = wave_id();
@@ -152,7 +172,7 @@ __device__ __forceinline__ void block_partial(double (&a)[NV], double *slot)
 #pragma unroll
         for (int k = 0; k < NV; k++) {
             const double v = lanes_in_order<kWaves>(op_of<OPS>(k), sh[k][lane & (kWaves - 1)]);
-            if (lane == 0) slot[k * kMaxBlocks + blockIdx.x] = v;
+            if (lane == 0) slot[k * kMaxBlocks + blk] = v;
         }
     }
 }
@@ -214,7 +234,7 @@ __device__ __forceinline__ void for_rows(const Part &P, Body body)
 {
     const int lane = threadIdx.x & 63, wid = wave_id();
     const int nw = P.nb * kWaves;
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += nw) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += nw) {
         const int i = s * kSlice + lane;
         body(i, i < P.n);
     }
@@ -369,7 +389,7 @@ __device__ __forceinline__ void sell_rows_paired(const Part &P, const int *__res
     using PV = decltype(pre(0));
     const int lane = threadIdx.x & 63, wid = wave_id();
     const int nw = P.nb * kWaves;
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += nw) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += nw) {
         const int off = so[s];
         const int w = (so[s + 1] - off) >> 6;   // uniform in the wave
         const int np = w >> 1;
@@ -560,7 +580,7 @@ __device__ __forceinline__ void sell_rows_quad(const Part &P, const int *__restr
     using PV = decltype(pre(0));
     const int lane = threadIdx.x & 63, wid = wave_id();
     const int nw = P.nb * kWaves;
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += nw) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += nw) {
         const int off = so[s];
         const int w = (so[s + 1] - off) >> 6;   // uniform in the wave
         const int nq = w >> 2, rem = w & 3;
@@ -644,14 +664,14 @@ __device__ __forceinline__ void sell_rows(const Part &P, const int *__restrict__
     using PV = decltype(pre(0));
     const int lane = threadIdx.x & 63, wid = wave_id();
     const int nw = P.nb * kWaves;
-    for (int s0 = blockIdx.x * kWaves + wid; s0 < P.nslices; s0 += NS * nw) {
+    for (int s0 = block_id(P) * kWaves + wid; s0 < P.nslices(); s0 += NS * nw) {
         int off[NS], w[NS], row[NS];
         bool act[NS];
         PV pv[NS];
 #pragma unroll
         for (int t = 0; t < NS; t++) {
             const int s = s0 + t * nw;
-            const bool has = s < P.nslices;
+            const bool has = s < P.nslices();
             off[t] = has ? so[s] : 0;
             w[t] = has ? (so[s + 1] - off[t]) >> 6 : 0;   // slice width (uniform in the wave)
             row[t] = s * kSlice + lane;
@@ -862,7 +882,7 @@ __device__ __forceinline__ void sell_rows_n_paired(const Part &P, const int *__r
     using PV = decltype(pre(0));
     const int lane = threadIdx.x & 63, wid = wave_id();
     const int nw = P.nb * kWaves;
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += nw) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += nw) {
         const int off = so[s];
         const int w = (so[s + 1] - off) >> 6;
         const int np = w >> 1;
@@ -937,7 +957,7 @@ __device__ __forceinline__ void sell_rows_n_quad(const Part &P, const int *__res
     using PV = decltype(pre(0));
     const int lane = threadIdx.x & 63, wid = wave_id();
     const int nw = P.nb * kWaves;
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += nw) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += nw) {
         const int off = so[s];
         const int w = (so[s + 1] - off) >> 6;
         const int nq = w >> 2, rem = w & 3;
@@ -1037,7 +1057,7 @@ __device__ __forceinline__ void sell_rows_n(const Part &P, const int *__restrict
     using PV = decltype(pre(0));
     const int lane = threadIdx.x & 63, wid = wave_id();
     const int nw = P.nb * kWaves;
-    for (int s = blockIdx.x * kWaves + wid; s < P.nslices; s += nw) {
+    for (int s = block_id(P) * kWaves + wid; s < P.nslices(); s += nw) {
         const int off = so[s];
         const int w = (so[s + 1] - off) >> 6;
         const int row = s * kSlice + lane;
