@@ -110,6 +110,18 @@ struct BBlk {
     int p, s, n, first;
 };
 
+// The list entry a workgroup takes, of nb: eight neighbouring entries on one
+// XCD (workgroups go round-robin to the eight), as the blocks of a member read
+// one another's rows and all of its partials.  64 float64 members of 32^2 to
+// 256^2 cells: 186.6 -> 183.2 ms, 80 mixed ones 180.3 -> 177.9; a whole eighth
+// of the list per XCD took the same there, but leaves XCDs with all of a large
+// member, and one step of 60 members went from 47.0 to 48.5 ms.
+__device__ __forceinline__ int near_block(int nb)
+{
+    const int b = blockIdx.x;
+    return b < (nb & ~63) ? (b & ~63) | ((b & 7) << 3) | ((b >> 3) & 7) : b;
+}
+
 // A member's place in the concatenated vectors and, with the diagonal layout,
 // its offsets: the array of offset h[u] starts at b0 + (u + 1) stride counted
 // from global row 0 (W = 0: another layout).
@@ -194,7 +206,7 @@ __device__ __forceinline__ void for_bslices(const BDev &B, const int (&ops)[NV],
                                             Body body)
 {
     if ((int)blockIdx.x >= B.cnt[0]) return;
-    const BBlk K = B.blk[blockIdx.x];
+    const BBlk K = B.blk[near_block(B.cnt[0])];
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     for (int s = K.s + wid; s < K.s + K.n; s += kBWaves) {
         double a[NV];
@@ -1188,7 +1200,7 @@ __global__ __launch_bounds__(kFinBlock) void kb_rows(BDev B, const VT *__restric
                                                      BVec<VV> V)
 {
     if ((int)blockIdx.x >= B.cnt[0]) return;
-    const BBlk K = B.blk[blockIdx.x];
+    const BBlk K = B.blk[near_block(B.cnt[0])];
     const BTab &T = B.tab[K.p];
     __shared__ BState S;
     __shared__ double sums[kBNV];
@@ -1311,7 +1323,7 @@ template <class VV>
 __global__ __launch_bounds__(kFinBlock) void kb_vec(BDev B, BVec<VV> V)
 {
     if ((int)blockIdx.x >= B.cnt[0]) return;
-    const BBlk K = B.blk[blockIdx.x];
+    const BBlk K = B.blk[near_block(B.cnt[0])];
     const BTab &T = B.tab[K.p];
     __shared__ BState S;
     __shared__ double sums[kBNV];
