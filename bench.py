@@ -47,8 +47,9 @@ CSRC = os.path.join(ROOT, "paper_1506_08435_amd", "csrc")
 # sources that decide what a kernel reads and writes: its code, the slice
 # walkers, the constants and the host code that chooses layouts and launches
 KERNEL_SOURCES = {
-    "single": ("kernels.hip", "rows.hpp", "nnqp_internal.hpp", "solver.hip", "api.hip"),
-    "batch": ("batch.hip", "rows.hpp", "nnqp_internal.hpp", "api.hip"),
+    "single": ("kernels.hip", "rows.hpp", "diag.hpp", "diag.hip", "nnqp_internal.hpp", "solver.hip",
+               "api.hip"),
+    "batch": ("batch.hip", "rows.hpp", "diag.hpp", "diag.hip", "nnqp_internal.hpp", "api.hip"),
 }
 
 
@@ -533,7 +534,7 @@ def main():
                     help="TRON's subspace loop (1) or a Cauchy step every iteration (0, the "
                          "library default); the minimiser is the same")
     ap.add_argument("--cg-chunk", type=int, default=16,
-                    help="CG iterations between convergence reads (0: adaptive first chunk)")
+                    help="CG iterations enqueued ahead at most; steps of a batched chunk (0: no limit; 16)")
     ap.add_argument("--engine", type=int, choices=[0, 1, 2], default=0,
                     help="single-problem solves: 0 = by size (one workgroup up to 4,096 rows), "
                          "1 = multi-block passes, 2 = one workgroup")
