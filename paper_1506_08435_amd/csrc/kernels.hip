@@ -23,8 +23,8 @@
 namespace nnqp {
 
 // Neighbouring blocks share an XCD where that was measured faster: passes with
-// one slice per wavefront at most (up to 524,288 rows: solves of 62^3, 71^3 and
-// the 9^3-celled hole 12.0 -> 11.5, 21.4 -> 19.9, 26.1 -> 24.5 ms, 79^3 Galerkin
+// one slice per wavefront at most (up to 524,288 rows: solves of 63^3, 71^3 and
+// the holed cube of k = 9 12.0 -> 11.5, 21.4 -> 19.9, 26.1 -> 24.5 ms, 79^3 Galerkin
 // 12.2 -> 10.7), and float32 passes of any size (100^3, 127^3: 26.4 -> 23.9,
 // 79.8 -> 78.7 ms).  Larger float64 passes stream from HBM, and it costs them
 // more than the reuse gives (81^3, 89^3, 99^3, 127^3 rows: 32.7 -> 31.4,
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kBlock) void k_add(Part P, double *__restrict__ c,
 // skipped when a mask is given (there d = 0, so s = 0 and they add nothing).
 // BRK: the breakpoint pass (k_breakpoint) of the same direction in the same
 // launch, its values into SLOT_Q; it reads nothing that the trial's rows have
-// not loaded, so a launch of its own (3.8 us on 262 k rows, 18 us on 2 M)
+// not loaded, so a launch of its own (3.8 us on 250 k rows, 18 us on 2 M)
 // goes.
 constexpr uint32_t kOpsTrial = OPS3(OP_SUM, OP_SUM, OP_SUM);
 constexpr uint32_t kOpsBrk = OPS3(OP_MIN, OP_SUM, OP_SUM);
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kBlock) void k_init(Part P, double *__restrict__ c,
 
 // Set-up of the inner CG on the face of (c, g + ks), behind the Cauchy step
 // c <- P(c + t g) of length t (t != 0; a launch of its own before: 3.3 us on
-// 262 k rows, and c and g twice):
+// 250 k rows, and c and g twice):
 //   g <- g + ks (gradient at the Cauchy point), free = not (c == 0 and g >= 0),
 //   dm = 1/diag on free rows and 0 elsewhere (the mask folded into the
 //   Jacobi preconditioner), r = -g on free rows, z = dm r, p = q = w = 0.
@@ -450,7 +450,8 @@ __global__ __launch_bounds__(kBlock, walk_waves<Cols>()) void k_cg_spmv(Part P0,
 // without free rows is loaded all the same.
 // Two blocks share a CU above kMaxBlocks / 2 blocks, so PH, the entries loaded
 // before the combination, is the whole row below that and eight above it
-// (64 VGPRs).
+// (64 VGPRs; all values of the row but the vector in phases of 8, 5 or 4 took
+// a solve of 493 k rows from 12.2 to 12.6, 12.8 and 12.9 ms).
 template <int WMAX, class VT, class VV, bool TR, int PH>
 __global__ __launch_bounds__(kBlock, PH < diag_width<WMAX>() ? 8 : 1) void k_cg_spmv_one(Part P0, ColsDiag sc,
                                                         const VT *__restrict__ v,

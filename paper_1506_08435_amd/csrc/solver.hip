@@ -130,7 +130,7 @@ static nn_status read_grad_and_ladder(nn_ctx *ctx, int64_t n, double *grad, doub
 // device reports each iteration that begins, and the end; the host keeps
 // `ahead` iterations enqueued beyond the last one begun.  A launch after the
 // end returns at once, but costs 2 us, so it is two: the iteration that covers
-// the host's way to a launch and one behind it (262 k rows float64: 2, 3, 4, 6
+// the host's way to a launch and one behind it (250 k rows float64: 2, 3, 4, 6
 // ahead 12.1, 12.4, 12.7, 13.1 ms; 90 k rows with float32 values, whose
 // iterations take 8 us, 26.7 +- 0.3 ms at any of them).  With a synchronisation
 // each 16 iterations instead the two took 18.6 and 38.5 ms.

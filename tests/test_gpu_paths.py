@@ -375,3 +375,39 @@ def test_solves_on_several_threads(ctx):
     assert not errors, errors
     for i in range(3):
         assert all(np.array_equal(x, alone[i]) for x in got[i]), i
+
+
+@pytest.mark.parametrize("what", ["galerkin", "blmvm", "one"])
+def test_solves_without_the_copies(what):
+    """Solves that read a matrix's copies only for speed: with every further
+    allocation refused a fresh matrix is solved from its sliced-ELL arrays, to
+    the same bits."""
+    import torch
+    from paper_1506_08435_amd import nnqp
+    refuse = [False]
+
+    def alloc(nbytes):
+        if refuse[0]:
+            return None
+        return torch.cuda.caching_allocator_alloc(nbytes, 0, torch.cuda.current_stream(0))
+
+    c = nnqp.Context(0, allocator=(alloc, torch.cuda.caching_allocator_delete))
+    p = W.cube3d(10 if what == "one" else 20)
+
+    def solve(K, F):
+        if what == "galerkin":
+            return c.solve_galerkin(K, F, tol=1e-10)[0].cpu().numpy().copy()
+        kw = {"method": nnqp.NN_BLMVM} if what == "blmvm" else {}
+        return c.solve_nonneg(K, F, tol=1e-10, **kw)[0].cpu().numpy().copy()
+
+    K1, F1, _ = c.assemble(p)
+    K2, F2, _ = c.assemble(p)
+    a = solve(K1, F1)
+    refuse[0] = True
+    b = solve(K2, F2)
+    assert np.array_equal(a, b)
+    refuse[0] = False
+    assert np.array_equal(a, solve(K2, F2))
+    K1.free()
+    K2.free()
+    c.close()
