@@ -67,21 +67,39 @@ nn_status ensure_workspace(nn_ctx *ctx, int64_t n)
     return NN_OK;
 }
 
-// One block copies the partials into the host's memory and announces them.
-// 512 threads: one per block of a slot.
-__global__ __launch_bounds__(kMaxBlocks) void k_publish(Publish A, Publish B, HostFlow *F,
-                                                        unsigned long long seq)
+// One block per value combines its partials, in block order, and stores the
+// result where the host polls for it.  One lane adds them out of LDS, eight
+// reads ahead: 1 us for 245 blocks.  With the partials copied out instead the
+// host read up to 57 KB that had just arrived and added 14 dependent chains
+// (63^3 unknowns 11.5 -> 11.05 ms, 96 x 96 x 24 step 3.44 -> 3.22).
+__global__ __launch_bounds__(256) void k_publish(Publish A, Publish B, HostFlow *F,
+                                                 unsigned long long seq)
 {
-    const int b = threadIdx.x;
-    if (b < A.nb)
-        for (int k = 0; k < A.nv; k++) F->part[k * kMaxBlocks + b] = A.src[k * kMaxBlocks + b];
-    if (b < B.nb)
-        for (int k = 0; k < B.nv; k++)
-            F->part[(A.nv + k) * kMaxBlocks + b] = B.src[k * kMaxBlocks + b];
-    __threadfence_system();
+    __shared__ double sh[kMaxBlocks];
+    const bool second = (int)blockIdx.x >= A.nv;
+    const int k = second ? blockIdx.x - A.nv : blockIdx.x, nb = second ? B.nb : A.nb;
+    const double *src = (second ? B.src : A.src) + (size_t)k * kMaxBlocks;
+    const int op = (int)(((second ? B.ops : A.ops) >> (2 * k)) & 3u);
+    for (int b = threadIdx.x; b < nb; b += 256) sh[b] = src[b];
     __syncthreads();
-    if (b == 0)
-        __hip_atomic_store(&F->pub, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (threadIdx.x != 0) return;
+    auto all = [&](double a, auto comb) {
+        int b = 0;
+        for (; b + 8 <= nb; b += 8) {
+            double v[8];
+#pragma unroll
+            for (int q = 0; q < 8; q++) v[q] = sh[b + q];
+#pragma unroll
+            for (int q = 0; q < 8; q++) a = comb(a, v[q]);
+        }
+        for (; b < nb; b++) a = comb(a, sh[b]);
+        return a;
+    };
+    const double a = op == OP_SUM   ? all(0.0, [](double x, double y) { return x + y; })
+                     : op == OP_MIN ? all(INFINITY, [](double x, double y) { return fmin(x, y); })
+                                    : all(-INFINITY, [](double x, double y) { return fmax(x, y); });
+    F->val[blockIdx.x].v = a;
+    __hip_atomic_store(&F->val[blockIdx.x].pub, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 nn_status flow_wait(nn_ctx *ctx, const std::function<bool()> &ready)
@@ -109,27 +127,22 @@ nn_status flow_wait(nn_ctx *ctx, const std::function<bool()> &ready)
 nn_status publish(nn_ctx *ctx, const Publish &a, const Publish &b)
 {
     const unsigned long long seq = ++ctx->flow_pub;
-    k_publish<<<1, kMaxBlocks, 0, ctx->stream>>>(a, b, ctx->flow, seq);
+    k_publish<<<a.nv + b.nv, 256, 0, ctx->stream>>>(a, b, ctx->flow, seq);
     NN_HIP_TRY(ctx, hipGetLastError());
-    const unsigned long long *w = &ctx->flow->pub;
-    return flow_wait(ctx, [w, seq] { return __atomic_load_n(w, __ATOMIC_ACQUIRE) >= seq; });
-}
-
-double published(const nn_ctx *ctx, int at, int k, int nb, int op)
-{
-    const double *h = ctx->flow->part + (size_t)(at + k) * kMaxBlocks;
-    double a = op == OP_SUM ? 0.0 : (op == OP_MIN ? INFINITY : -INFINITY);
-    for (int b = 0; b < nb; b++)
-        a = op == OP_SUM ? a + h[b] : (op == OP_MIN ? std::fmin(a, h[b]) : std::fmax(a, h[b]));
-    return a;
+    const HostFlow::Value *v = ctx->flow->val;
+    int k = a.nv + b.nv - 1;
+    return flow_wait(ctx, [&] {
+        while (k >= 0 && __atomic_load_n(&v[k].pub, __ATOMIC_ACQUIRE) == seq) k--;
+        return k < 0;
+    });
 }
 
 nn_status host_reduce(nn_ctx *ctx, int64_t n, int nv, const int *ops, double *out)
 {
     const Part P = make_part(n);
-    const nn_status rc = publish(ctx, Publish{ctx->partials, nv, P.nb});
+    const nn_status rc = publish(ctx, Publish(ctx->partials, nv, P.nb, ops));
     if (rc != NN_OK) return rc;
-    for (int k = 0; k < nv; k++) out[k] = published(ctx, 0, k, P.nb, ops[k]);
+    for (int k = 0; k < nv; k++) out[k] = ctx->flow->val[k].v;
     return NN_OK;
 }
 

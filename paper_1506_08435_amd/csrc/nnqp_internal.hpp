@@ -46,7 +46,7 @@ Part make_part(int64_t n, int max_blocks = kMaxBlocks, bool f32 = false);
 // ---------------------------------------------------------------- reductions
 // A reduction kernel leaves one partial per block and value in a slot of
 // ctx->partials ([slot][value][block]); nothing is combined with atomics.
-// Results the host needs are combined on the host in block order; results the
+// Results the host needs are combined by publish() in block order; results the
 // next kernel needs (CG scalars) are combined by every block of that kernel in
 // the same fixed order, so all blocks hold bitwise identical values.
 enum { SLOT_HOST = 0, SLOT_U0 = 1, SLOT_U1 = 2, SLOT_Q = 3, kSlots = 4 };
@@ -72,11 +72,14 @@ struct DevScalars {
 // decision (16 to 23 us each, of which the device idles most).  A word only
 // grows; the data it announces is stored before it (release, system scope).
 struct HostFlow {
-    alignas(64) unsigned long long pub;   // number of the last published reduction
+    struct alignas(16) Value {
+        double v;
+        unsigned long long pub;           // number of the reduction it belongs to
+    };
+    alignas(64) Value val[5 + 3 * kLadder];   // published reductions
     alignas(64) unsigned long long cg;    // CG solve's number << 32 | iterations begun
     alignas(64) unsigned long long end;   // number of the last CG solve that ended
     alignas(64) DevScalars scal;          // its scalars
-    alignas(64) double part[kMaxBlocks * (5 + 3 * kLadder)];   // published partials
 };
 
 // What the CG kernels of one solve share.
@@ -309,16 +312,20 @@ nn_status sell_build(nn_ctx *ctx, nn_matrix *A, const int64_t *rowptr_host, cons
 // kernels write) satisfy ready(); an error, or a stream that has run dry
 // without it, ends the wait.
 nn_status flow_wait(nn_ctx *ctx, const std::function<bool()> &ready);
-// Partials [value][block] of up to two slots to ctx->flow->part, one after the
-// other, and the wait for them.
+// The partials [value][block] of up to two slots, each value combined in block
+// order with its operation (ops[k], OP_SUM / OP_MIN / OP_MAX), into
+// ctx->flow->val, one slot after the other, and the wait for them.
 struct Publish {
-    const double *src;
-    int nv, nb;
+    const double *src = nullptr;
+    int nv = 0, nb = 0;
+    uint32_t ops = 0;   // two bits per value
+    Publish() = default;
+    Publish(const double *src_, int nv_, int nb_, const int *ops_) : src(src_), nv(nv_), nb(nb_)
+    {
+        for (int k = 0; k < nv; k++) ops |= (uint32_t)ops_[k] << (2 * k);
+    }
 };
-nn_status publish(nn_ctx *ctx, const Publish &a, const Publish &b = Publish{nullptr, 0, 0});
-// The combination, in block order, of value k of published partials that start
-// at `at` (in values).
-double published(const nn_ctx *ctx, int at, int k, int nb, int op);
+nn_status publish(nn_ctx *ctx, const Publish &a, const Publish &b = Publish());
 // Combine the host-slot partials of the last reduction kernel over n rows;
 // ops[k] is OP_SUM / OP_MIN / OP_MAX for value k.
 nn_status host_reduce(nn_ctx *ctx, int64_t n, int nv, const int *ops, double *out);

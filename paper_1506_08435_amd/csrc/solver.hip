@@ -116,13 +116,15 @@ nn_status cheb_prepare(nn_ctx *ctx, const nn_matrix *A, const double *vals, cons
 static nn_status read_grad_and_ladder(nn_ctx *ctx, int64_t n, double *grad, double *ladder)
 {
     const Part P = make_part(n), PL = make_part(n, kLadderBlocks);
-    const nn_status rc =
-        publish(ctx, Publish{ctx->partials, 5, P.nb},
-                Publish{ctx->partials + (size_t)SLOT_U0 * kMaxRed * kMaxBlocks, 3 * kLadder, PL.nb});
-    if (rc != NN_OK) return rc;
     static const int kGradOps[5] = {OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM};
-    for (int k = 0; k < 5; k++) grad[k] = published(ctx, 0, k, P.nb, kGradOps[k]);
-    for (int k = 0; k < 3 * kLadder; k++) ladder[k] = published(ctx, 5, k, PL.nb, OP_SUM);
+    static const int kSums[3 * kLadder] = {};   // OP_SUM
+    const nn_status rc =
+        publish(ctx, Publish(ctx->partials, 5, P.nb, kGradOps),
+                Publish(ctx->partials + (size_t)SLOT_U0 * kMaxRed * kMaxBlocks, 3 * kLadder, PL.nb,
+                        kSums));
+    if (rc != NN_OK) return rc;
+    for (int k = 0; k < 5; k++) grad[k] = ctx->flow->val[k].v;
+    for (int k = 0; k < 3 * kLadder; k++) ladder[k] = ctx->flow->val[5 + k].v;
     return NN_OK;
 }
 
@@ -497,13 +499,13 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
             prof_end(ctx);
         };
         const Part Pn = make_part(n);
-        const Publish p_brk{ctx->partials + (size_t)SLOT_Q * kMaxRed * kMaxBlocks, 3, Pn.nb};
+        const Publish p_brk(ctx->partials + (size_t)SLOT_Q * kMaxRed * kMaxBlocks, 3, Pn.nb, kBrkOps);
         const bool early = crossed && !tr && it_seen > 0;
         double tred[3] = {0.0, 0.0, 0.0};
         if (early) {
             trial_w(1.0, true);
-            rc = publish(ctx, p_brk, Publish{ctx->partials, 3, Pn.nb});
-            for (int k = 0; k < 3; k++) tred[k] = published(ctx, 3, k, Pn.nb, kTrialOps[k]);
+            rc = publish(ctx, p_brk, Publish(ctx->partials, 3, Pn.nb, kTrialOps));
+            for (int k = 0; k < 3; k++) tred[k] = ctx->flow->val[3 + k].v;
         } else {
             prof_begin(ctx, KC_OTHER, 24.0 * n);
             launch_breakpoint(ctx, n, c, dir_w, W.g, box);
@@ -512,7 +514,7 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
             rc = publish(ctx, p_brk);
         }
         if (rc != NN_OK) return rc;
-        for (int k = 0; k < 3; k++) red[k] = published(ctx, 0, k, Pn.nb, kBrkOps[k]);
+        for (int k = 0; k < 3; k++) red[k] = ctx->flow->val[k].v;
         const double bmin = red[0], gw = red[1], wn = std::sqrt(red[2]);
         bool new_face = false;   // the step reached a bound the CG face did not hold
         if (it_seen > 0 && gw < 0.0 && wn > 0.0) {
