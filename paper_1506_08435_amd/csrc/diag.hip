@@ -12,7 +12,6 @@
 // quarters of the slices are regular (the unrolled stencil widths), and where
 // K and M have the same bits on both sides of the diagonal; other patterns
 // (unstructured numberings) keep the other layouts.
-#include <algorithm>
 #include <memory>
 #include <new>
 #include <vector>
@@ -21,18 +20,7 @@
 
 namespace nnqp {
 
-struct DiagPlan {
-    std::vector<int> srun;        // run of each slice
-    std::vector<DiagRun> runs;
-    std::vector<int> mirrored;    // run: offsets < 0 read through the opposite triangle
-    int64_t entries = 0;          // length of a value array
-    int lo = 0, hi = 0, elo = 0, ehi = 0;   // slices of the main run (ColsDiag)
-    DiagReg main{};
-};
-
 namespace {
-
-constexpr int kDiagRunsMax = 4096;
 
 // Distinct offsets of each slice, ascending, at most kDiagMax: one wavefront
 // per slice.  Each lane holds a cursor in its row (columns ascend), the next
@@ -191,110 +179,6 @@ nn_status fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const T *src,
     return NN_OK;
 }
 
-struct PatternRun {
-    int s0, s1;
-    std::vector<int> d;
-};
-
-// Bases of the runs' arrays.  False when the arrays or tables do not fit or
-// too few slices are regular.
-bool lay_out(const nn_matrix *A, const std::vector<PatternRun> &pat, DiagPlan *D)
-{
-    const int64_t n = A->n;
-    const int W = A->wmax <= 8 ? 7 : 15;   // diag_width of the kernels' instance
-    D->srun.assign((size_t)A->nslices, 0);
-    int64_t regular = 0;
-    for (const PatternRun &p : pat) {
-        const int w = (int)p.d.size();
-        const int64_t rows = (int64_t)(p.s1 - p.s0) * kSlice;
-        bool sym = true;
-        for (int d : p.d)
-            if (d < 0 && !std::binary_search(p.d.begin(), p.d.end(), -d)) sym = false;
-        const int dmin = p.d.front(), dmax = p.d.back();
-        // slices that store their offsets < 0: all without the opposite
-        // offsets, none in a run from row 0 on, else those whose row i - d may
-        // lie before the run
-        const int64_t reach = (-(int64_t)std::min(dmin, 0) + kSlice - 1) / kSlice;
-        const bool front = sym && p.s0 == 0;
-        const int head = !sym ? p.s1 - p.s0 : (front ? 0 : (int)std::min<int64_t>(p.s1 - p.s0, reach));
-        // arrays of the offsets >= 0: equal lengths (zeros in front when the
-        // run starts at row 0), so that their bases are b0 + u stride
-        const int64_t pad = front ? reach * kSlice : 0;
-        const int64_t stride = rows + pad;
-        const int64_t b0 = D->entries + pad - (int64_t)p.s0 * kSlice;
-        int nup = 0;
-        for (int d : p.d) nup += d >= 0;
-        D->entries += nup * stride;
-        std::vector<int64_t> base(w);
-        for (int k = 0, u = 0; k < w; k++) {
-            if (p.d[k] >= 0) {
-                base[k] = b0 + stride * u++;
-            } else {
-                base[k] = D->entries - (int64_t)p.s0 * kSlice;   // (head slices only)
-                D->entries += (int64_t)head * kSlice;
-            }
-        }
-        if (D->entries > A->nsell) return false;
-        const bool reg = sym && w == W;
-        auto edge = [&](int s) {
-            return (int64_t)s * kSlice + dmin < 0 || (int64_t)s * kSlice + kSlice - 1 + dmax >= n;
-        };
-        auto kind = [&](int s) {
-            if (!reg || s < p.s0 + head) return (int)DR_GENERAL;
-            return edge(s) ? (int)DR_EDGE : (int)DR_REGULAR;
-        };
-        DiagReg g{};
-        g.b0 = (int)b0;
-        g.stride = (int)stride;
-        if (reg)
-            for (int u = 0; u < W / 2; u++) g.h[u] = p.d[W / 2 + 1 + u];
-        // sub-runs: consecutive slices of one kind, stored or mirrored alike
-        int e0 = p.s0 + head, in0 = 0, in1 = 0;
-        for (int s = p.s0; s < p.s1;) {
-            const bool in_head = s < p.s0 + head;
-            int t = s + 1;
-            while (t < p.s1 && (t < p.s0 + head) == in_head && kind(t) == kind(s)) t++;
-            DiagRun r{};
-            r.w = w;
-            r.kind = kind(s);
-            r.reg = g;
-            int64_t zero = b0;
-            for (int k = 0; k < w; k++) {
-                int64_t b = base[k];
-                if (p.d[k] < 0 && !in_head)
-                    b = base[std::lower_bound(p.d.begin(), p.d.end(), -p.d[k]) - p.d.begin()] + p.d[k];
-                r.d[k] = p.d[k];
-                r.b[k] = (int)b;
-                if (p.d[k] == 0) zero = b;
-            }
-            for (int k = w; k < kDiagMax; k++) {
-                r.d[k] = 0;
-                r.b[k] = (int)zero;
-            }
-            if (r.kind != DR_GENERAL) regular += t - s;
-            if (r.kind == DR_REGULAR && t - s > in1 - in0) {
-                in0 = s;
-                in1 = t;
-            }
-            const int id = (int)D->runs.size();
-            if (id >= kDiagRunsMax) return false;
-            D->runs.push_back(r);
-            D->mirrored.push_back(in_head ? 0 : 1);
-            for (int q = s; q < t; q++) D->srun[q] = id;
-            s = t;
-        }
-        if (reg && p.s1 - e0 > D->ehi - D->elo) {   // the main run: the longest regular one
-            D->elo = e0;
-            D->ehi = p.s1;
-            D->lo = in0;
-            D->hi = in1;
-            D->main = g;
-        }
-    }
-    const size_t bytes = sizeof(int) * D->srun.size() + (sizeof(DiagRun) + sizeof(int)) * D->runs.size();
-    return bytes <= sizeof(short) * (size_t)A->nsell && 4 * regular >= 3 * A->nslices;
-}
-
 }  // namespace
 
 ColsDiag diag_cols(const nn_matrix *A, const void *index)
@@ -404,32 +288,8 @@ nn_status diag_find(nn_ctx *ctx, nn_matrix *A, void *scratch)
                                            hipMemcpyDeviceToHost, ctx->stream));
         }
         NN_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-        // runs: a segment joins the run before it when one's offsets contain
-        // the other's (whole slices in the first line of a grid plane lack
-        // the offsets to the line before), up to the regular width: slices
-        // where the numbering shifts hold the offsets of both sides
-        const int W = A->wmax <= 8 ? 7 : 15;
-        std::vector<PatternRun> pat;
-        for (size_t q = 0; q < m; q++) {
-            const int s0 = first[q], s1 = q + 1 < m ? first[q + 1] : (int)ns;
-            const int *l = &lists[(some ? q : (size_t)s0) * kDiagMax], *e = l + h[s0];
-            if (!pat.empty() && (int)pat.back().d.size() <= W &&
-                std::includes(pat.back().d.begin(), pat.back().d.end(), l, e)) {
-                pat.back().s1 = s1;
-            } else if (!pat.empty() && h[s0] <= W &&
-                       std::includes(l, e, pat.back().d.begin(), pat.back().d.end())) {
-                pat.back().s1 = s1;
-                pat.back().d.assign(l, e);
-            } else {
-                PatternRun p;
-                p.s0 = s0;
-                p.s1 = s1;
-                p.d.assign(l, e);
-                pat.push_back(p);
-            }
-        }
         std::unique_ptr<DiagPlan> D(new DiagPlan());
-        bool fits = lay_out(A, pat, D.get());
+        bool fits = diag_plan(A->n, ns, A->nsell, A->wmax, first, h.data(), lists.data(), some, D.get());
         if (fits) {
             // the flag goes through the reduction partials, free between passes
             int *flag = reinterpret_cast<int *>(ctx->partials), differ = 0;

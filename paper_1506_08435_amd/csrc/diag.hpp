@@ -24,9 +24,9 @@
 
 namespace nnqp {
 
-// Unrolled entries of a walk: a 2D P1 stencil has 7 offsets, a 3D one 15.
+// Unrolled entries of a walk: the offsets of a regular row.
 template <int WMAX>
-constexpr int diag_width() { return WMAX <= 8 ? 7 : 15; }
+constexpr int diag_width() { return diag_regular(WMAX); }
 
 // The layout as Cols of walk_rows.  Slices [elo, ehi) are the main run, whose
 // offsets and bases are kernel arguments (no lookup); [lo, hi) are its slices

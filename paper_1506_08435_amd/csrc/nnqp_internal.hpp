@@ -9,6 +9,7 @@
 #include <string>
 #include <vector>
 
+#include "diag_plan.hpp"
 #include "nnqp.h"
 
 namespace nnqp {
@@ -24,7 +25,6 @@ namespace nnqp {
 // the next kernel.  Two 1024-thread blocks per CU fill its 32 wave slots.
 constexpr int kBlock = 1024;
 constexpr int kWaves = kBlock / 64;
-constexpr int kSlice = 64;
 constexpr int kMaxBlocks = 512;    // 2 workgroups per CU on 256 CUs
 constexpr int kMaxRed = 8;         // values per reduction
 constexpr int kLadder = 3;         // step lengths of one Cauchy ladder pass (odd)
@@ -178,25 +178,6 @@ inline hipError_t dev_malloc(const DevAlloc &a, T **p, size_t bytes)
     *p = static_cast<T *>(v);
     return e;
 }
-
-// Diagonal layout (diag.hpp): the offsets and value bases of a run of slices.
-constexpr int kDiagMax = 32;    // offsets of a run
-constexpr int kDiagHalf = 7;    // offsets > 0 of a regular run (3D P1)
-enum { DR_REGULAR = 0, DR_EDGE = 1, DR_GENERAL = 2 };
-// Regular runs: offsets 0, +-h[0], ..., ascending h; the array of offset h[u]
-// starts at b0 + (u + 1) stride (that of offset 0 at b0), counted from row 0.
-struct DiagReg {
-    int b0, stride;
-    int h[kDiagHalf];
-};
-struct DiagRun {
-    int w;      // offsets, ascending; slots past w repeat offset 0
-    int kind;   // regular, regular with columns that would leave [0, n), general
-    DiagReg reg;
-    int d[kDiagMax];
-    int b[kDiagMax];
-};
-struct DiagPlan;   // host side of the layout (diag.hip)
 
 }  // namespace nnqp
 
