@@ -102,27 +102,20 @@ __global__ __launch_bounds__(256) void k_publish(Publish A, Publish B, HostFlow 
     __hip_atomic_store(&F->val[blockIdx.x].pub, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-nn_status flow_wait(nn_ctx *ctx, const std::function<bool()> &ready)
+int flow_look(nn_ctx *ctx)
 {
-    // The stream is asked only after a while (asking costs microseconds); if
-    // it holds no work any more, the words are final.
-    for (int64_t spin = 1; !ready(); spin++) {
-        if (spin % 8192 != 0) {
-            __builtin_ia32_pause();
-            continue;
-        }
-        const hipError_t e = hipStreamQuery(ctx->stream);
-        if (e == hipErrorNotReady) {
-            (void)hipGetLastError();
-            std::this_thread::yield();
-            continue;
-        }
-        if (e == hipSuccess && ready()) break;
-        return fail(ctx, NN_EHIP, std::string("waiting for the device: ") +
-                                      (e == hipSuccess ? "no answer" : hipGetErrorString(e)));
+    const hipError_t e = hipStreamQuery(ctx->stream);
+    if (e == hipSuccess) return FLOW_DRY;
+    if (e == hipErrorNotReady) {
+        (void)hipGetLastError();
+        std::this_thread::yield();
+        return FLOW_RUNNING;
     }
-    return NN_OK;
+    fail(ctx, NN_EHIP, std::string("waiting for the device: ") + hipGetErrorString(e));
+    return FLOW_ERROR;
 }
+
+nn_status flow_lost(nn_ctx *ctx) { return fail(ctx, NN_EHIP, "waiting for the device: no answer"); }
 
 nn_status publish(nn_ctx *ctx, const Publish &a, const Publish &b)
 {

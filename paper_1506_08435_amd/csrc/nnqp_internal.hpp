@@ -5,7 +5,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <functional>
 #include <string>
 #include <vector>
 
@@ -289,10 +288,30 @@ void sell_offsets(const int64_t *rowptr, int64_t n, std::vector<int64_t> &off, i
 // Device CSR values (ordered by rowptr) -> sliced-ELL arrays of A (col, vals, diag).
 nn_status sell_build(nn_ctx *ctx, nn_matrix *A, const int64_t *rowptr_host, const double *csr_val,
                      const double *csr_mval);
+// One look at the stream by a host that polls: running, run dry (the pinned
+// words are final), or an error (reported).
+enum { FLOW_RUNNING = 0, FLOW_DRY = 1, FLOW_ERROR = 2 };
+int flow_look(nn_ctx *ctx);
+nn_status flow_lost(nn_ctx *ctx);   // a stream that ran dry without the awaited word
 // Waits until the words of ctx->flow (or another pinned word that the stream's
 // kernels write) satisfy ready(); an error, or a stream that has run dry
-// without it, ends the wait.
-nn_status flow_wait(nn_ctx *ctx, const std::function<bool()> &ready);
+// without it, ends the wait.  The stream is asked only after a while (asking
+// costs microseconds).
+template <class Ready>
+nn_status flow_wait(nn_ctx *ctx, Ready ready)
+{
+    for (int64_t spin = 1; !ready(); spin++) {
+        if (spin % 8192 != 0) {
+            __builtin_ia32_pause();
+            continue;
+        }
+        const int f = flow_look(ctx);
+        if (f == FLOW_RUNNING) continue;
+        if (f == FLOW_ERROR) return NN_EHIP;
+        return ready() ? NN_OK : flow_lost(ctx);
+    }
+    return NN_OK;
+}
 // The partials [value][block] of up to two slots, each value combined in block
 // order with its operation (ops[k], OP_SUM / OP_MIN / OP_MAX), into
 // ctx->flow->val, one slot after the other, and the wait for them.
