@@ -298,14 +298,8 @@ static nn_status fill_copy(nn_ctx *ctx, nn_matrix *K, const float *src, float *d
     return NN_OK;
 }
 
-// (the copies a solve reads for speed only: Galerkin, BLMVM, one workgroup, and
-// patterns without int16 offsets run from the sliced-ELL arrays when refused)
-static nn_status try_paired(nn_ctx *ctx, nn_matrix *K, bool f64)
-{
-    return without_copy(ctx, ensure_paired(ctx, K, f64));
-}
-
-nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64)
+// (K's lock is held)
+static nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64, bool &formed)
 {
     if (K->n == 0) return NN_OK;
     const size_t m = (size_t)std::max<int64_t>(K->nsell, 1);
@@ -313,32 +307,99 @@ nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64)
     if (K->val32 && !K->val32q) {
         if ((st = ensure_index(ctx, K, true)) != NN_OK) return st;
         if (K->d16q) {
+            formed = true;
             float *v = nullptr;
             if (dev_malloc(K->al, &v, sizeof(float) * m) != hipSuccess)
                 return fail(ctx, NN_EOOM, "float32 copy allocation");
+            if ((st = fill_copy(ctx, K, K->val32, v)) != NN_OK) {
+                dev_free(K->al, v);
+                return st;
+            }
             K->val32q = v;
-            if ((st = fill_copy(ctx, K, K->val32, v)) != NN_OK) return st;
         }
     }
     if (f64 && !K->val64p) {
         if ((st = ensure_index(ctx, K, false)) != NN_OK) return st;
         if (K->d16p) {
+            formed = true;
             double *v = nullptr;
             if (dev_malloc(K->al, &v, sizeof(double) * m) != hipSuccess)
                 return fail(ctx, NN_EOOM, "float64 copy allocation");
+            if ((st = fill_copy(ctx, K, K->val, v)) != NN_OK) {
+                dev_free(K->al, v);
+                return st;
+            }
             K->val64p = v;
-            if ((st = fill_copy(ctx, K, K->val, v)) != NN_OK) return st;
         }
     }
     NN_HIP_TRY(ctx, hipGetLastError());
     return NN_OK;
 }
 
+// The end of a call's work on K's copies (its lock is held): contexts on other
+// streams wait for what it enqueued, and it for what they did.
+static nn_status settle(nn_ctx *ctx, nn_matrix *K, nn_status st, bool formed)
+{
+    hipError_t e = hipSuccess;
+    if (K->pending && K->form_stream != ctx->stream) {
+        e = hipEventQuery(K->form_done);
+        if (e == hipSuccess) K->pending = false;
+        else if (e == hipErrorNotReady) (void)hipGetLastError(), e = hipStreamWaitEvent(ctx->stream, K->form_done, 0);
+    }
+    if (formed && e == hipSuccess) {
+        if (!K->form_done) e = hipEventCreateWithFlags(&K->form_done, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventRecord(K->form_done, ctx->stream);
+        K->form_stream = ctx->stream;
+        K->pending = e == hipSuccess;
+    }
+    if (st == NN_OK && e != hipSuccess) return fail(ctx, NN_EHIP, hipGetErrorString(e));
+    return st;
+}
+
+nn_status present_copies(nn_ctx *ctx, nn_matrix *K, Copies *out)
+{
+    std::lock_guard<std::mutex> lock(K->copies);
+    *out = Copies{K->val32, K->val32q, K->val64p};
+    return settle(ctx, K, NN_OK, false);
+}
+
+nn_status ensure_val32(nn_ctx *ctx, nn_matrix *K, const float **v32)
+{
+    std::lock_guard<std::mutex> lock(K->copies);
+    bool formed = false;
+    nn_status st = NN_OK;
+    if (K->n > 0 && !K->val32) {
+        if (dev_malloc(K->al, &K->val32, sizeof(float) * std::max<int64_t>(K->nsell, 1)) != hipSuccess)
+            return fail(ctx, NN_EOOM, "float32 value allocation");
+        launch_to_f32(ctx, K->nsell, K->val, K->val32);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) st = fail(ctx, NN_EHIP, hipGetErrorString(e));
+        formed = true;
+    }
+    *v32 = K->val32;
+    return settle(ctx, K, st, formed);
+}
+
+// `needed`: a refused allocation fails the call; else (the copies that a solve
+// reads for speed only: Galerkin, BLMVM, one workgroup, and patterns without
+// int16 offsets) the solve runs from the sliced-ELL arrays.
+static nn_status ensure_copies(nn_ctx *ctx, nn_matrix *K, bool f64, bool needed, Copies *out)
+{
+    std::lock_guard<std::mutex> lock(K->copies);
+    bool formed = false;
+    nn_status st = ensure_paired(ctx, K, f64, formed);
+    if (!needed) st = without_copy(ctx, st);
+    st = settle(ctx, K, st, formed);
+    *out = Copies{K->val32, K->val32q, K->val64p};
+    return st;
+}
+
 // M/dt + K values for a backward-Euler step (formed once per dt, kept with K).
 // `paired`: the single-problem solver will read the copy for this precision
 // (the batched solver reads the column-major values only).  Every copy that
 // exists is re-formed when dt changes.
-nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, bool paired)
+static nn_status form_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, bool paired,
+                                bool &formed)
 {
     const int64_t n = K->n;
     if (n == 0) return NN_OK;
@@ -347,6 +408,7 @@ nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, boo
     bool want64p = paired && !mixed && NNQP_PAIR_F64;
     nn_status st = NN_OK;
     if (want32q || want64p) {
+        formed = !(mixed ? K->d16q_ready : K->d16p_ready);
         st = ensure_index(ctx, K, mixed);
         if (!K->sl_d16) st = without_copy(ctx, st);
         if (st != NN_OK) return st;
@@ -356,6 +418,7 @@ nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, boo
     const bool fresh = K->kt && K->kt_dt == dt;
     if (fresh && (!mixed || K->kt32) && (!want32q || K->kt32q) && (!want64p || K->kt64p))
         return NN_OK;
+    formed = true;
     // each buffer is guarded on its own: a call that got one of them and was
     // refused the other leaves the first in place, and a later call takes
     // only the missing one (the values are formed below whenever kt_dt != dt)
@@ -379,6 +442,16 @@ nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, boo
     NN_HIP_TRY(ctx, hipGetLastError());
     K->kt_dt = dt;
     return NN_OK;
+}
+
+nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, bool paired,
+                           Copies *out)
+{
+    std::lock_guard<std::mutex> lock(K->copies);
+    bool formed = false;
+    const nn_status st = settle(ctx, K, form_transient(ctx, K, dt, mixed, paired, formed), formed);
+    *out = Copies{K->kt32, K->kt32q, K->kt64p};
+    return st;
 }
 
 }  // namespace nnqp
@@ -671,6 +744,7 @@ nn_status nn_matrix_export(nn_ctx *ctx, const nn_matrix *A, int64_t *rowptr, int
 nn_status nn_matrix_bytes(const nn_matrix *A, int precision, size_t *bytes)
 {
     if (!A || !bytes) return NN_EINVAL;
+    std::lock_guard<std::mutex> lock(A->copies);
     const double n = (double)A->n, nnz = (double)A->nnz, ns = (double)A->nsell;
     double b = 4.0 * (n + 1) + 4.0 * nnz;                   // CSR pattern
     b += 4.0 * (A->nslices + 1) + 12.0 * ns + 8.0 * n;      // sliced-ELL columns, values, diag
@@ -708,6 +782,7 @@ void nn_matrix_free(nn_ctx *ctx, nn_matrix *A)
     for (float *p : fv)
         dev_free(A->al, p);
     diag_free(A);
+    if (A->form_done) (void)hipEventDestroy(A->form_done);
     delete A;
 }
 
@@ -745,34 +820,26 @@ nn_status nn_solve_nonneg(nn_ctx *ctx, nn_matrix *K, const double *f_dev,
     if (!K || (K->n > 0 && (!f_dev || !c_dev))) return fail(ctx, NN_EINVAL, "null argument");
     nn_status st = check_opts(ctx, opts);
     if (st != NN_OK) return st;
+    Copies C;
     if (opts->method == NN_BLMVM) {
-        if ((st = try_paired(ctx, K, true)) != NN_OK) return st;
-        return blmvm_impl(ctx, K, K->val, K->val64p, f_dev, opts, c_dev, active_dev, stats);
+        if ((st = ensure_copies(ctx, K, true, false, &C)) != NN_OK) return st;
+        return blmvm_impl(ctx, K, K->val, C.v64p, f_dev, opts, c_dev, active_dev, stats);
     }
     if ((st = choose_solo(ctx, K, opts)) == NN_OK) {
         // (the copy is read up to kSoloMaxRows rows)
-        if (K->n <= kSoloMaxRows && (st = try_paired(ctx, K, true)) != NN_OK) return st;
-        return solo_solve_impl(ctx, K, K->val, K->val64p, K->diag, f_dev, opts, c_dev, active_dev,
+        if (K->n <= kSoloMaxRows && (st = ensure_copies(ctx, K, true, false, &C)) != NN_OK) return st;
+        return solo_solve_impl(ctx, K, K->val, C.v64p, K->diag, f_dev, opts, c_dev, active_dev,
                                stats);
     }
     if (st != NN_EMAXIT) return st;   // (NN_EMAXIT: the multi-block passes)
     const float *v32 = nullptr;
-    if (opts->precision == NN_MIXED && K->n > 0) {
-        if (!K->val32) {
-            if (dev_malloc(K->al, &K->val32, sizeof(float) * std::max<int64_t>(K->nsell, 1)) != hipSuccess)
-                return fail(ctx, NN_EOOM, "float32 value allocation");
-            launch_to_f32(ctx, K->nsell, K->val, K->val32);
-            NN_HIP_TRY(ctx, hipGetLastError());
-        }
-        v32 = K->val32;
-    }
+    if (opts->precision == NN_MIXED && K->n > 0 && (st = ensure_val32(ctx, K, &v32)) != NN_OK) return st;
     // the copies the CG and search passes read
     const bool pair64 = NNQP_PAIR_F64 && v32 == nullptr;
-    if ((v32 || pair64) &&
-        (st = K->sl_d16 ? ensure_paired(ctx, K, pair64) : try_paired(ctx, K, pair64)) != NN_OK)
+    if ((v32 || pair64) && (st = ensure_copies(ctx, K, pair64, K->sl_d16 != nullptr, &C)) != NN_OK)
         return st;
-    return solve_impl(ctx, K, K->val, v32, v32 ? K->val32q : nullptr, v32 ? nullptr : K->val64p,
-                      K->diag, f_dev, opts, c_dev, active_dev, stats);
+    return solve_impl(ctx, K, K->val, v32, v32 ? C.v32q : nullptr, v32 ? nullptr : C.v64p, K->diag,
+                      f_dev, opts, c_dev, active_dev, stats);
 }
 
 nn_status nn_solve_galerkin(nn_ctx *ctx, nn_matrix *K, const double *f_dev, const nn_opts *opts,
@@ -784,8 +851,9 @@ nn_status nn_solve_galerkin(nn_ctx *ctx, nn_matrix *K, const double *f_dev, cons
     if (st != NN_OK) return st;
     if (opts->precision != NN_FP64)
         return fail(ctx, NN_EINVAL, "the Galerkin solve runs in float64 only");
-    if ((st = try_paired(ctx, K, true)) != NN_OK) return st;
-    return galerkin_impl(ctx, K, f_dev, opts, c_dev, stats);
+    Copies C;
+    if ((st = ensure_copies(ctx, K, true, false, &C)) != NN_OK) return st;
+    return galerkin_impl(ctx, K, C.v64p, f_dev, opts, c_dev, stats);
 }
 
 nn_status nn_step_transient(nn_ctx *ctx, nn_matrix *K, double dt, const double *f_dev,
@@ -802,19 +870,19 @@ nn_status nn_step_transient(nn_ctx *ctx, nn_matrix *K, double dt, const double *
     const bool mixed = opts->precision == NN_MIXED;
     if (n == 0) return solve_impl(ctx, K, K->val, nullptr, nullptr, nullptr, K->diag, f_dev, opts,
                                     c_dev, active_dev, stats);
-    if ((st = ensure_transient(ctx, K, dt, mixed, true)) != NN_OK) return st;
+    Copies C;
+    if ((st = ensure_transient(ctx, K, dt, mixed, true, &C)) != NN_OK) return st;
     if ((st = ensure_workspace(ctx, n)) != NN_OK) return st;
     launch_transient_rhs(ctx, K, c_dev, f_dev, dt, ctx->ws.ft);
     nn_opts o = *opts;
     o.c0_mode = 1;   // warm start from c^(n)
-    if (o.method == NN_BLMVM) return blmvm_impl(ctx, K, K->kt, K->kt64p, ctx->ws.ft, &o, c_dev, active_dev, stats);
+    if (o.method == NN_BLMVM) return blmvm_impl(ctx, K, K->kt, C.v64p, ctx->ws.ft, &o, c_dev, active_dev, stats);
     if ((st = choose_solo(ctx, K, &o)) == NN_OK)
-        return solo_solve_impl(ctx, K, K->kt, K->kt64p, K->kt_diag, ctx->ws.ft, &o, c_dev,
-                               active_dev, stats);
+        return solo_solve_impl(ctx, K, K->kt, C.v64p, K->kt_diag, ctx->ws.ft, &o, c_dev, active_dev,
+                               stats);
     if (st != NN_EMAXIT) return st;
-    return solve_impl(ctx, K, K->kt, mixed ? K->kt32 : nullptr, mixed ? K->kt32q : nullptr,
-                      mixed ? nullptr : K->kt64p, K->kt_diag, ctx->ws.ft, &o, c_dev, active_dev,
-                      stats);
+    return solve_impl(ctx, K, K->kt, mixed ? C.v32 : nullptr, mixed ? C.v32q : nullptr,
+                      mixed ? nullptr : C.v64p, K->kt_diag, ctx->ws.ft, &o, c_dev, active_dev, stats);
 }
 
 // Shared checks of the batched entry points: arguments, options, and that
@@ -877,8 +945,9 @@ static nn_status step_transient_batch_body(nn_ctx *ctx, int32_t nprob, nn_matrix
     nn_status st = check_batch(ctx, nprob, K, f_dev, opts, c_dev, true);
     if (st != NN_OK) return st;
     const bool mixed = opts->precision == NN_MIXED;
+    Copies C;
     for (int p = 0; p < nprob; p++)
-        if ((st = ensure_transient(ctx, K[p], dt, mixed, false)) != NN_OK) return st;
+        if ((st = ensure_transient(ctx, K[p], dt, mixed, false, &C)) != NN_OK) return st;
     if (nprob == 0) {
         ctx->err.clear();
         return NN_OK;

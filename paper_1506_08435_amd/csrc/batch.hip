@@ -1596,11 +1596,10 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             return fail(ctx, NN_EINVAL, "batch too large: total rows must stay below 2^31");
         for (int t = 0; t < nsl[p]; t++) sprob.push_back(p);
         if (n > 0) wmax = std::max(wmax, K[p]->wmax);
-        if (mixed && n > 0 && !transient && !K[p]->val32) {
-            if (dev_malloc(K[p]->al, &K[p]->val32, sizeof(float) * std::max<int64_t>(K[p]->nsell, 1)) !=
-                hipSuccess)
-                return fail(ctx, NN_EOOM, "float32 value allocation");
-            launch_to_f32(ctx, K[p]->nsell, K[p]->val, K[p]->val32);
+        const float *v32 = nullptr;
+        if (mixed && n > 0 && !transient) {
+            const nn_status rc = ensure_val32(ctx, K[p], &v32);
+            if (rc != NN_OK) return rc;
         }
     }
     if (S == 0) {
@@ -1625,15 +1624,18 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     std::vector<DiagReg> dreg(P);
     {
         size_t scratch = 0;
-        for (int p = 0; p < P; p++)
+        for (int p = 0; p < P; p++) {
+            std::lock_guard<std::mutex> lock(K[p]->copies);
             if (K[p]->n > 0 && !K[p]->diag_tried)
                 scratch = std::max(scratch, sizeof(short) * (size_t)std::max<int64_t>(K[p]->nsell, 1));
+        }
         void *tmp = nullptr;
         if (scratch > 0 && dev_malloc(ctx->al, &tmp, scratch) != hipSuccess)
             return fail(ctx, NN_EOOM, "batch workspace allocation failed");
         nn_status rc = NN_OK;
         for (int p = 0; p < P && rc == NN_OK && all_diag; p++) {
             if (K[p]->n == 0) continue;
+            std::lock_guard<std::mutex> lock(K[p]->copies);
             rc = diag_find(ctx, K[p], tmp);
             all_diag = rc == NN_OK && diag_one_run(K[p], &dreg[p]);
         }

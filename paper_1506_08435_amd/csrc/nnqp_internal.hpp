@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -135,6 +136,12 @@ struct Vals {
     const double *v64p = nullptr;  // v64 in the paired layout (with A->d16p), or null
 };
 
+// The copies of a matrix that a call may read, as they were under its lock.
+struct Copies {
+    const float *v32 = nullptr, *v32q = nullptr;
+    const double *v64p = nullptr;
+};
+
 // Bounds lo <= c <= hi of a constrained solve (hi may be +inf; lo finite).
 // Default: the non-negative QP.  Projection P(x) = min(max(x, lo), hi), with
 // NaN mapped to lo.
@@ -189,6 +196,14 @@ struct nn_matrix {
     int *sl_off = nullptr;     // [nslices+1] first entry of each 64-row slice
     int *sl_col = nullptr;     // [nsell] column of each sliced-ELL entry (padding: own row)
     short *sl_d16 = nullptr;   // [nsell] col - row as int16 when every offset fits, else null
+    // A matrix may be read by several contexts, each on its thread and stream.
+    // What solves add to it below (copies, the diagonal layout, the transient
+    // values) is formed under this lock, and a context on another stream waits
+    // for the event of what was formed last.
+    mutable std::mutex copies;
+    hipEvent_t form_done = nullptr;
+    hipStream_t form_stream = nullptr;
+    bool pending = false;      // form_done has not been seen to have passed
     // Paired copies for the CG and search passes of the single-problem solver
     // (made when sl_d16 exists): within each slice, entries 2k and 2k+1 of a
     // row sit side by side (one 8- or 16-byte value load and one 4-byte offset
@@ -436,7 +451,6 @@ inline double entry_bytes(const nn_matrix *A, double vb, bool copy, bool d16)
     if (copy && A->diag_plan) return vb * diag_entries(A) / (double)(A->nnz > 0 ? A->nnz : 1);
     return vb + (d16 ? 2.0 : 4.0);
 }
-nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64);
 // active = 1 where c == lo, 2 where c == hi, else 0
 void launch_active(nn_ctx *ctx, int64_t n, const double *c, uint8_t *active, Box B);
 // out = m/dt + k
@@ -475,8 +489,9 @@ nn_status blmvm_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
 void lm_release(nn_ctx *ctx);
 
 // Unconstrained Galerkin solve K c = f by Jacobi-PCG from c = 0 (solver.hip).
-nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const nn_opts *o,
-                        double *c, nn_stats *st);
+// vals64p: the values in the layout the passes read, or null.
+nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals64p, const double *f,
+                        const nn_opts *o, double *c, nn_stats *st);
 
 // ---------------------------------------------------------------- batched solver (batch.hip)
 // P problems solved together; arrays are host arrays of P entries (see
@@ -490,6 +505,11 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
 // precision, their float32 copy; with `paired`, also the copy the
 // single-problem solver reads at this precision (paired float64 or quad
 // float32, with their int16 offsets).
-nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, bool paired);
+nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, bool paired,
+                           Copies *out);
+// The copies of K's values that are there (none is formed).
+nn_status present_copies(nn_ctx *ctx, nn_matrix *K, Copies *out);
+// The float32 values of K.
+nn_status ensure_val32(nn_ctx *ctx, nn_matrix *K, const float **v32);
 
 }  // namespace nnqp

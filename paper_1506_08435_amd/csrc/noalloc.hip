@@ -111,7 +111,9 @@ extern "C" nn_status nn_solve_nonneg_noalloc(nn_ctx *ctx, nn_matrix *K, const do
     if (opts->precond_degree > 1)
         return fail(ctx, NN_EINVAL, "nn_solve_nonneg_noalloc uses the Jacobi preconditioner only");
     const bool mixed = opts->precision == NN_MIXED;
-    if (mixed && K->n > 0 && !K->val32)
+    Copies C;
+    if ((st = present_copies(ctx, K, &C)) != NN_OK) return st;
+    if (mixed && K->n > 0 && !C.v32)
         return fail(ctx, NN_EINVAL,
                     "nn_solve_nonneg_noalloc: the matrix has no float32 copy yet (a mixed "
                     "nn_solve_nonneg call forms it)");
@@ -150,8 +152,8 @@ extern "C" nn_status nn_solve_nonneg_noalloc(nn_ctx *ctx, nn_matrix *K, const do
     const bool prof = ctx->prof;
     ctx->prof = false;
     const nn_status rc =
-        solve_impl(ctx, K, K->val, mixed ? K->val32 : nullptr, mixed ? K->val32q : nullptr,
-                   mixed ? nullptr : K->val64p, K->diag, f_dev, opts, c_dev, active_dev, stats);
+        solve_impl(ctx, K, K->val, mixed ? C.v32 : nullptr, mixed ? C.v32q : nullptr,
+                   mixed ? nullptr : C.v64p, K->diag, f_dev, opts, c_dev, active_dev, stats);
     ctx->prof = prof;
     std::swap(ctx->scal, scal);
     std::swap(ctx->partials, partials);

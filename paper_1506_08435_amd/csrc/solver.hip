@@ -581,8 +581,8 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
 // recursive residual, and the report gives the true residual ||K c - f||,
 // min c, max c and the number of negative entries (the DMP statistics of
 // Table Tab:S5_cube_dmp).
-nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const nn_opts *o,
-                        double *c, nn_stats *st)
+nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals64p, const double *f,
+                        const nn_opts *o, double *c, nn_stats *st)
 {
     const int64_t n = A->n;
     nn_stats S;
@@ -629,7 +629,7 @@ nn_status galerkin_impl(nn_ctx *ctx, const nn_matrix *A, const double *f, const 
     constexpr int kMaxRestarts = 8;
     Vals VS;
     VS.v64 = A->val;
-    VS.v64p = A->d16p ? A->val64p : nullptr;
+    VS.v64p = A->d16p ? vals64p : nullptr;
     const double eb = entry_bytes(A, 8.0, VS.v64p, VS.v64p);   // bytes per nonzero
     Cheb cheb;
     if ((rc = cheb_prepare(ctx, A, A->val, A->diag, o->precond_degree, &cheb)) != NN_OK)

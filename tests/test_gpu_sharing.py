@@ -1,0 +1,70 @@
+"""One matrix read by several contexts, each on its thread and stream."""
+import threading
+
+import numpy as np
+import pytest
+
+from paper_1506_08435_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _call(nnqp, what, c, K, F):
+    import torch
+    kw = dict(tol=1e-10)
+    if what == "galerkin":
+        return c.solve_galerkin(K, F, **kw)[0]
+    if what == "step":
+        c0 = torch.zeros(K.n, dtype=torch.float64, device=c.device)
+        torch.cuda.current_stream(0).synchronize()
+        return c.step_transient(K, 1e-3, F, c0, **kw)[0]
+    if what in ("batch", "batch_mixed"):
+        if what == "batch_mixed":
+            kw.update(precision=nnqp.NN_MIXED)
+        return c.solve_batch([K], [F], **kw)[0][0]
+    if what == "blmvm":
+        kw.update(method=nnqp.NN_BLMVM)
+    if what == "mixed":
+        kw.update(precision=nnqp.NN_MIXED)
+    return c.solve_nonneg(K, F, **kw)[0]
+
+
+# what a solve adds to a matrix (copies, layout, transient values) is formed by
+# whichever of the threads comes first and read by all
+@pytest.mark.parametrize("what", ["galerkin", "blmvm", "one", "tron", "mixed", "step", "batch", "batch_mixed"])
+def test_first_solves_of_a_matrix_on_several_threads(what):
+    import torch
+    from paper_1506_08435_amd import nnqp
+    p = W.cube3d(14 if what == "one" else 20)
+    home = nnqp.Context(0)
+    streams = [torch.cuda.Stream(0) for _ in range(3)]
+    ctxs = [nnqp.Context(0, stream=s) for s in streams]
+    K, F, _ = home.assemble(p, with_mass=True)
+    alone = _call(nnqp, what, home, K, F).cpu().numpy().copy()
+    K.free()
+    for _ in range(3):
+        K, F, _ = home.assemble(p, with_mass=True)
+        torch.cuda.synchronize()
+        gate, got, errors = threading.Barrier(3), {}, []
+
+        def work(i):
+            try:
+                with torch.cuda.stream(streams[i]):
+                    gate.wait()
+                    c = _call(nnqp, what, ctxs[i], K, F)
+                    streams[i].synchronize()
+                    got[i] = c.cpu().numpy().copy()
+            except Exception as e:   # noqa: BLE001 (reported by the main thread)
+                errors.append(e)
+
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(3)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not errors, errors
+        assert all(np.array_equal(got[i], alone) for i in range(3))
+        K.free()
+    for c in ctxs:
+        c.close()
+    home.close()
