@@ -259,6 +259,7 @@ class Context:
         F = t.empty(max(n, 1), dtype=t.float64, device=self.device)
         dof = np.empty(coords.shape[0], dtype=np.int64)
         h = ctypes.c_void_p()
+        self._behind_caller()
         st = self.lib.nn_assemble(self.handle, ctypes.byref(mesh), _ptr(D), nD, _ptr(ks), _ptr(f),
                                   _ptr(dmask), _ptr(dv), int(with_mass), ctypes.byref(h), _ptr(F),
                                   _ptr(dof))
@@ -300,10 +301,23 @@ class Context:
         return int(b.value)
 
     # ---------------------------------------------------------------- compute
+    def _behind_caller(self):
+        """The caller's tensors (and those made here) live on torch's current
+        stream: a context on another stream starts behind the work queued there.
+        Returns the current stream when it is another one."""
+        cur = self.torch.cuda.current_stream(self.device)
+        if cur.cuda_stream == self.stream.cuda_stream:
+            return None
+        self.stream.wait_stream(cur)
+        return cur
+
     def matvec(self, A: Matrix, x, which: int = 0, out=None):
         t = self.torch
         y = out if out is not None else t.empty(max(A.n, 1), dtype=t.float64, device=self.device)
+        cur = self._behind_caller()
         self._check(self.lib.nn_matvec(self.handle, A.handle, which, _ptr(x), _ptr(y)), "nn_matvec")
+        if cur is not None:   # (the other calls return when their results are there)
+            cur.wait_stream(self.stream)
         return y[:A.n]
 
     def solve_nonneg(self, A: Matrix, f, opts: Optional[Opts] = None, c=None, active=None,
@@ -317,6 +331,7 @@ class Context:
         if active is None:
             active = t.empty(max(A.n, 1), dtype=t.uint8, device=self.device)
         st_out = Stats()
+        self._behind_caller()
         st = self.lib.nn_solve_nonneg(self.handle, A.handle, _ptr(f), ctypes.byref(o), _ptr(c),
                                       _ptr(active), ctypes.byref(st_out))
         self._check(st, "nn_solve_nonneg", allow=(NN_OK, NN_EMAXIT) if allow_maxit else (NN_OK,))
@@ -332,6 +347,7 @@ class Context:
         with the solution) and active.  Returns (c, active, stats dict)."""
         o = opts if opts is not None else default_opts(**kw)
         st_out = Stats()
+        self._behind_caller()
         st = self.lib.nn_solve_nonneg_noalloc(self.handle, A.handle, _ptr(f), ctypes.byref(o),
                                               _ptr(c), _ptr(active), ctypes.byref(st_out))
         self._check(st, "nn_solve_nonneg_noalloc",
@@ -350,6 +366,7 @@ class Context:
         if c is None:
             c = t.empty(max(A.n, 1), dtype=t.float64, device=self.device)
         st_out = Stats()
+        self._behind_caller()
         st = self.lib.nn_solve_galerkin(self.handle, A.handle, _ptr(f), ctypes.byref(o), _ptr(c),
                                         ctypes.byref(st_out))
         self._check(st, "nn_solve_galerkin", allow=(NN_OK, NN_EMAXIT) if allow_maxit else (NN_OK,))
@@ -364,6 +381,7 @@ class Context:
         if active is None:
             active = t.empty(max(A.n, 1), dtype=t.uint8, device=self.device)
         st_out = Stats()
+        self._behind_caller()
         st = self.lib.nn_step_transient(self.handle, A.handle, float(dt), _ptr(f), ctypes.byref(o),
                                         _ptr(c), _ptr(active), ctypes.byref(st_out))
         self._check(st, "nn_step_transient", allow=(NN_OK, NN_EMAXIT) if allow_maxit else (NN_OK,))
@@ -392,6 +410,7 @@ class Context:
         ca = arr(*[_ptr(c) for c in cs])
         aa = arr(*[_ptr(a) for a in actives])
         st_arr = (Stats * max(P, 1))()
+        self._behind_caller()
         st = self.lib.nn_solve_batch(self.handle, P, Ka, fa, ctypes.byref(o), ca, aa, st_arr)
         if not allow_fail:
             self._check(st, "nn_solve_batch")
@@ -413,6 +432,7 @@ class Context:
             actives = [t.empty(max(A.n, 1), dtype=t.uint8, device=self.device) for A in As]
         arr = ctypes.c_void_p * max(P, 1)
         st_arr = (Stats * max(P, 1))()
+        self._behind_caller()
         st = self.lib.nn_step_transient_batch(
             self.handle, P, arr(*[A.handle for A in As]), float(dt), arr(*[_ptr(f) for f in fs]),
             ctypes.byref(o), arr(*[_ptr(c) for c in cs]), arr(*[_ptr(a) for a in actives]), st_arr)

@@ -68,3 +68,53 @@ def test_first_solves_of_a_matrix_on_several_threads(what):
     for c in ctxs:
         c.close()
     home.close()
+
+
+# a context on a stream of its own, tensors of the current stream with work
+# still queued on them: the call starts behind that work
+@pytest.mark.parametrize("what", ["warm start", "load", "product", "zeros", "assembly", "batch"])
+def test_calls_start_behind_the_callers_stream(what):
+    import torch
+    from paper_1506_08435_amd import nnqp
+    c = nnqp.Context(0, stream=torch.cuda.Stream(0))
+    p = W.cube3d(18)
+    K, F, _ = c.assemble(p)
+    rng = np.random.default_rng(3)
+    host = torch.from_numpy(rng.uniform(0.0, 1e-3, K.n)).pin_memory()
+    late = torch.empty(K.n, dtype=torch.float64, device=c.device)
+    kw = dict(tol=1e-10)
+
+    def call(x, wait):
+        if what == "assembly":
+            # F is made by the call on the block that `x` gives back
+            if wait:
+                torch.cuda.synchronize()
+            del x
+            A, G, _ = c.assemble(p)
+            A.free()
+            return G
+        if wait:
+            torch.cuda.synchronize()
+        if what == "warm start":
+            return c.solve_nonneg(K, F, c=x, c0_mode=1, **kw)[0]
+        if what == "load":
+            return c.solve_nonneg(K, x, **kw)[0]
+        if what == "product":
+            return c.matvec(K, x) * 2.0        # read on the current stream
+        if what == "batch":
+            return c.solve_batch([K], [x], **kw)[0][0]
+        return c.solve_nonneg(K, F, **kw)[0]   # zeros made by the call
+
+    out = []
+    for wait in (True, False):
+        late.fill_(0.5)
+        torch.cuda.synchronize()
+        torch.cuda._sleep(100_000_000)         # some 50 ms at 2 GHz
+        late.copy_(host, non_blocking=True)
+        x = late if what != "assembly" else torch.full((K.n,), 0.25, dtype=torch.float64, device=c.device)
+        y = call(x, wait)
+        out.append(y.cpu().numpy().copy())
+        del x, y
+    assert np.array_equal(*out)
+    K.free()
+    c.close()
