@@ -242,8 +242,7 @@ namespace nnqp {
 #define NNQP_PAIR_F64 1   // float64 solves read the paired layout when it exists
 #endif
 
-// A refused copy that the solve can do without: nothing is left of the refusal.
-static nn_status without_copy(nn_ctx *ctx, nn_status st)
+nn_status without_copy(nn_ctx *ctx, nn_status st)
 {
     if (st != NN_EOOM) return st;
     (void)hipGetLastError();
@@ -264,6 +263,10 @@ static nn_status ensure_index(nn_ctx *ctx, nn_matrix *K, bool f32)
     if (!idx && dev_malloc(K->al, &idx, sizeof(short) * m) != hipSuccess)
         return fail(ctx, NN_EOOM, "index copy allocation");
     nn_status st = diag_find(ctx, K, idx);
+    if (st == NN_EOOM) {   // no host memory to look for it: another layout, for good
+        st = without_copy(ctx, st);
+        K->diag_tried = true;
+    }
     if (st == NN_OK && K->diag_plan) st = diag_upload(ctx, K, idx);
     if (st != NN_OK) {
         dev_free(K->al, idx);

@@ -1629,10 +1629,11 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             if (K[p]->n > 0 && !K[p]->diag_tried)
                 scratch = std::max(scratch, sizeof(short) * (size_t)std::max<int64_t>(K[p]->nsell, 1));
         }
+        // (the layout is read for speed only: without room to look for it the
+        // batch takes another)
         void *tmp = nullptr;
-        if (scratch > 0 && dev_malloc(ctx->al, &tmp, scratch) != hipSuccess)
-            return fail(ctx, NN_EOOM, "batch workspace allocation failed");
         nn_status rc = NN_OK;
+        if (scratch > 0 && dev_malloc(ctx->al, &tmp, scratch) != hipSuccess) rc = NN_EOOM;
         for (int p = 0; p < P && rc == NN_OK && all_diag; p++) {
             if (K[p]->n == 0) continue;
             std::lock_guard<std::mutex> lock(K[p]->copies);
@@ -1640,7 +1641,8 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             all_diag = rc == NN_OK && diag_one_run(K[p], &dreg[p]);
         }
         dev_free(ctx->al, tmp);
-        if (rc != NN_OK) return rc;
+        if (rc != NN_OK) all_diag = false;
+        if ((rc = without_copy(ctx, rc)) != NN_OK) return rc;
     }
     const bool quad = !all_diag && mixed && all_d16;
     const bool pair = !all_diag && !mixed && all_d16 && NNQP_BATCH_PAIRS;

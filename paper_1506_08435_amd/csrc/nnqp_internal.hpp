@@ -507,6 +507,8 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
 // float32, with their int16 offsets).
 nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, bool paired,
                            Copies *out);
+// A refused copy that the call can do without: nothing is left of the refusal.
+nn_status without_copy(nn_ctx *ctx, nn_status st);
 // The copies of K's values that are there (none is formed).
 nn_status present_copies(nn_ctx *ctx, nn_matrix *K, Copies *out);
 // The float32 values of K.
