@@ -64,6 +64,14 @@ constexpr int kBWaves = kFinBlock / 64;
 // times as many), and a block's slices at most above that.
 constexpr int kBGrid = 2048;
 constexpr int kBMost = 32;
+// Slices above which a launch of its own forms the shares of a member's partials
+// (kb_share).  Without it each of the member's blocks (one per kBMost slices)
+// adds up every partial, which grows with the square: one member of 127^3 rows,
+// 31,256 slices, 445 -> 189 ms a solve and 69.3 -> 24.1 a backward-Euler step,
+// 3,907 slices (two of 64^3) 40.2 -> 37.1 and 25.0 -> 20.1.  Below the line the
+// two launches a step cost more than they save: 3,151 slices 227 -> 239 and
+// 33.5 -> 31.3, 1,623 slices 13.2 -> 15.8 and 4.0 -> 4.5.
+constexpr int kBLarge = 3584;
 constexpr double kMu0 = 0.01;    // sufficient-decrease constant
 constexpr double kExtrap = 10.0; // Cauchy extrapolation factor
 constexpr double kInterp = 0.1;  // Cauchy interpolation factor
@@ -127,6 +135,7 @@ __device__ __forceinline__ int near_block(int nb)
 // from global row 0 (W = 0: another layout).
 struct BTab {
     int s0, nsl, nrow, W;
+    int share;      // large members: place in the shares (kb_share), else -1
     DiagReg reg;
 };
 
@@ -152,6 +161,8 @@ struct BDev {
     uint8_t *const *act_out;        // per member active-set outputs (entries may be null)
     BState *st, *st2;               // states before the row pass, before the vector pass
     double *part, *part2;           // [kBNV][nslices]: of the row pass, of the vector pass
+    const int *large;               // the large members
+    double *shares;                 // [large member][kBNV][kFinBlock] (kb_share)
     double *pres;                   // [P][kBNV] (start-up reductions)
     // the batch as one block-diagonal sliced-ELL matrix and concatenated
     // vectors (global rows s*64 + lane), copied in at the start of a call
@@ -805,19 +816,24 @@ __global__ void kb_transient_rhs(BDev B, double dt, double *__restrict__ ft)
                    });
 }
 
-// The calling thread's share of the first NV values of a member's slice
-// partials: slices t, t + 256, ... of the member in order.
+// Partials of a member as its transition reads them: value k of place s at
+// v[k * ld + s], s = s0 .. s0 + n - 1.
+struct BPart {
+    const double *v;
+    size_t ld;
+    int s0, n;
+};
+
+// The calling thread's share of the first NV values of a member's partials:
+// places t, t + 256, ... in order.
 template <int NV>
-__device__ __forceinline__ void member_load(const BDev &B, const BTab &T,
-                                            const double *__restrict__ part, const int (&ops)[NV],
-                                            double (&a)[NV])
+__device__ __forceinline__ void member_load(const BPart &Q, const int (&ops)[NV], double (&a)[NV])
 {
 #pragma unroll
     for (int k = 0; k < NV; k++) a[k] = bident(ops[k]);
-    for (int s = T.s0 + threadIdx.x; s < T.s0 + T.nsl; s += kFinBlock)
+    for (int s = Q.s0 + threadIdx.x; s < Q.s0 + Q.n; s += kFinBlock)
 #pragma unroll
-        for (int k = 0; k < NV; k++)
-            a[k] = bcomb(ops[k], a[k], part[(size_t)k * B.nslices + s]);
+        for (int k = 0; k < NV; k++) a[k] = bcomb(ops[k], a[k], Q.v[(size_t)k * Q.ld + s]);
 }
 
 // Combine the threads' shares in a fixed order (a wave butterfly, then the
@@ -854,7 +870,7 @@ __global__ __launch_bounds__(kFinBlock) void kb_reduce_init(BDev B)
     const int ops[4] = {OP_SUM, OP_MAX, OP_SUM, OP_SUM};
     __shared__ double r[4];
     double a[4];
-    member_load<4>(B, B.tab[p], B.part, ops, a);
+    member_load<4>(BPart{B.part, (size_t)B.nslices, B.tab[p].s0, B.tab[p].nsl}, ops, a);
     member_combine<4>(ops, a, r);
     __syncthreads();
     if (threadIdx.x < 4) B.pres[(size_t)p * kBNV + threadIdx.x] = r[threadIdx.x];
@@ -1074,11 +1090,10 @@ struct BAct {
 // The sums of a pass, first NV values of the member's slice partials, into
 // sums (LDS), every thread of the block; the caller adds a barrier.
 template <int NV>
-__device__ __forceinline__ void member_sums(const BDev &B, const BTab &T, const double *part,
-                                            const int (&ops)[NV], double *sums)
+__device__ __forceinline__ void member_sums(const BPart &Q, const int (&ops)[NV], double *sums)
 {
     double a[NV];
-    member_load<NV>(B, T, part, ops, a);
+    member_load<NV>(Q, ops, a);
     member_combine<NV>(ops, a, sums);
 }
 
@@ -1102,18 +1117,20 @@ __device__ __forceinline__ BAct block_transition(const BDev &B, const BBlk &K, c
     constexpr int kWords = sizeof(BState) / sizeof(int);
     constexpr int NF = SECOND ? 2 : 1;
     __shared__ double sh[NF][kBWaves];
-    const double *part = SECOND ? B.part2 : B.part;
+    const BPart Q = T.share >= 0
+                        ? BPart{B.shares + (size_t)T.share * kBNV * kFinBlock, kFinBlock, 0, kFinBlock}
+                        : BPart{SECOND ? B.part2 : B.part, (size_t)B.nslices, T.s0, T.nsl};
     const int word = threadIdx.x < kWords ? reinterpret_cast<const int *>(in + K.p)[threadIdx.x] : 0;
     double f[NF], f1[NF];
-    const int t1 = T.s0 + threadIdx.x, te = T.s0 + T.nsl;
+    const int t1 = Q.s0 + threadIdx.x, te = Q.s0 + Q.n;
 #pragma unroll
-    for (int k = 0; k < NF; k++) f1[k] = t1 < te ? part[(size_t)k * B.nslices + t1] : 0.0;
+    for (int k = 0; k < NF; k++) f1[k] = t1 < te ? Q.v[(size_t)k * Q.ld + t1] : 0.0;
     ahead();
 #pragma unroll
     for (int k = 0; k < NF; k++) f[k] = 0.0 + f1[k];
     for (int s = t1 + kFinBlock; s < te; s += kFinBlock)
 #pragma unroll
-        for (int k = 0; k < NF; k++) f[k] += part[(size_t)k * B.nslices + s];
+        for (int k = 0; k < NF; k++) f[k] += Q.v[(size_t)k * Q.ld + s];
     if (threadIdx.x < kWords) reinterpret_cast<int *>(&S)[threadIdx.x] = word;
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 #pragma unroll
@@ -1150,19 +1167,19 @@ __device__ __forceinline__ BAct block_transition(const BDev &B, const BBlk &K, c
             const int vop = S.vop;
             if (vop == VO_SETUP) {
                 const int ops[4] = {OP_SUM, OP_SUM, OP_SUM, OP_SUM};
-                member_sums<4>(B, T, part, ops, sums);
+                member_sums<4>(Q, ops, sums);
             } else if (vop == VO_BREAK) {
                 const int ops[3] = {OP_MIN, OP_SUM, OP_SUM};
-                member_sums<3>(B, T, part, ops, sums);
+                member_sums<3>(Q, ops, sums);
             }
         } else {
             const int ph = S.phase;
             if (ph == PH_GRAD) {
                 const int ops[5] = {OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM};
-                member_sums<5>(B, T, part, ops, sums);
+                member_sums<5>(Q, ops, sums);
             } else if (ph == PH_CAUCHY || ph == PH_SEARCH) {
                 const int ops[3] = {OP_SUM, OP_SUM, OP_SUM};
-                member_sums<3>(B, T, part, ops, sums);
+                member_sums<3>(Q, ops, sums);
             }
         }
         __syncthreads();
@@ -1409,6 +1426,45 @@ __global__ __launch_bounds__(kFinBlock) void kb_vec(BDev B, BVec<VV> V)
     }
 }
 
+// The shares of the large members: what thread t of a transition's block would
+// add up of the member's partials, places t, t + 256, ... in order, so that a
+// block of the member reads 256 numbers per value instead of one per slice.
+// Block: one value of one member, 64 of its 256 shares.
+template <bool SECOND>
+__global__ __launch_bounds__(64) void kb_share(BDev B)
+{
+    const int m = blockIdx.x / (kBNV * kBWaves), k = blockIdx.x / kBWaves % kBNV;
+    const int p = B.large[m], t = (blockIdx.x % kBWaves) * 64 + threadIdx.x;
+    const BState &S = (SECOND ? B.st : B.st2)[p];
+    // values and operation of the pass behind it (as the transitions read them)
+    int nv = 0, op = OP_SUM;
+    if constexpr (SECOND) {
+        const int vop = S.vop;
+        nv = vop == VO_SETUP ? 4 : vop == VO_UPDATE ? 2 : vop == VO_BREAK ? 3 : 0;
+        if (vop == VO_BREAK && k == 0) op = OP_MIN;
+    } else {
+        const int ph = S.phase;
+        nv = ph == PH_GRAD ? 5 : ph == PH_CAUCHY || ph == PH_SEARCH ? 3 : ph == PH_CG && S.cgdone == 0 ? 1 : 0;
+        if (ph == PH_GRAD && k == 2) op = OP_MAX;
+        if (ph == PH_GRAD && k == 3) op = OP_MIN;
+    }
+    if (k >= nv) return;
+    const BTab &T = B.tab[p];
+    const double *v = (SECOND ? B.part2 : B.part) + (size_t)k * B.nslices + T.s0;
+    double a = bident(op);
+    constexpr int U = 16;   // loads in flight
+    int s = t;
+    for (; s + (U - 1) * kFinBlock < T.nsl; s += U * kFinBlock) {
+        double x[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) x[u] = v[s + u * kFinBlock];
+#pragma unroll
+        for (int u = 0; u < U; u++) a = bcomb(op, a, x[u]);
+    }
+    for (; s < T.nsl; s += kFinBlock) a = bcomb(op, a, v[s]);
+    B.shares[((size_t)m * kBNV + k) * kFinBlock + t] = a;
+}
+
 // Second transition on its own, in place: the states the host reads (and the
 // next chunk's first row pass, which finds no vector operation to decide on).
 __global__ __launch_bounds__(kFinBlock) void kb_step2(BDev B)
@@ -1609,6 +1665,9 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         return NN_OK;
     }
     const int64_t R = S * kSlice;
+    std::vector<int> large;   // members whose shares are formed by a launch of their own
+    for (int p = 0; p < P; p++)
+        if (nsl[p] > kBLarge) large.push_back(p);
     bool all_d16 = true;
     for (int p = 0; p < P; p++)
         if (K[p]->n > 0 && !K[p]->sl_d16) all_d16 = false;
@@ -1666,6 +1725,8 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     BState *d_st = A.d<BState>(P), *d_st2 = A.d<BState>(P);
     double *d_part = A.d<double>((size_t)S * kBNV), *d_part2 = A.d<double>((size_t)S * kBNV),
            *d_pres = A.d<double>((size_t)P * kBNV);
+    int *d_large = large.empty() ? nullptr : A.d<int>(large.size());
+    double *d_shares = large.empty() ? nullptr : A.d<double>(large.size() * kBNV * kFinBlock);
     double *g = A.d<double>(R), *ks0 = A.d<double>(R), *ks1 = A.d<double>(R);
     uint8_t *mask = A.d<uint8_t>(R);
     // concatenated layout: vectors and the block-diagonal matrix
@@ -1743,8 +1804,9 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         NN_HIP_TRY(ctx, hipMemcpyAsync(d_s0, s0.data(), sizeof(int) * P, hipMemcpyHostToDevice, st));
         NN_HIP_TRY(ctx,
                    hipMemcpyAsync(d_nrow, nrow.data(), sizeof(int) * P, hipMemcpyHostToDevice, st));
-        for (int p = 0; p < P; p++) {
+        for (int p = 0, l = 0; p < P; p++) {
             BTab t{};
+            t.share = nsl[p] > kBLarge ? l++ : -1;
             t.s0 = s0[p];
             t.nsl = nsl[p];
             t.nrow = nrow[p];
@@ -1755,6 +1817,9 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             }
             tabs[p] = t;
         }
+        if (d_large)
+            NN_HIP_TRY(ctx, hipMemcpyAsync(d_large, large.data(), sizeof(int) * large.size(),
+                                           hipMemcpyHostToDevice, st));
         NN_HIP_TRY(ctx, hipMemcpyAsync(d_tab, tabs, sizeof(BTab) * P, hipMemcpyHostToDevice, st));
         NN_HIP_TRY(ctx, hipMemcpyAsync(d_ebase, ebase.data(), sizeof(int64_t) * P,
                                        hipMemcpyHostToDevice, st));
@@ -1790,6 +1855,8 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     B.part = d_part;
     B.part2 = d_part2;
     B.pres = d_pres;
+    B.large = d_large;
+    B.shares = d_shares;
     B.gso = gso;
     B.gcol = gcol;
     B.gd16 = gd16;
@@ -1957,9 +2024,12 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
         else
             NN_BDISPATCH_EV(wmax, (kb_rows<WM, CM_I32, double, double>), gr, kFinBlock, s, e0, e1, B,
                             (const double *)gv64, V64);
+        const unsigned ns = (unsigned)(large.size() * kBNV * kBWaves);
+        if (ns) hipLaunchKernelGGL(kb_share<false>, dim3(ns), dim3(64), 0, s, B);
         e0 = ev ? ev[2] : nullptr, e1 = ev ? ev[3] : nullptr;
         if (mixed) NN_BLAUNCH_EV((kb_vec<float>), gr, kFinBlock, s, e0, e1, B, V32);
         else NN_BLAUNCH_EV((kb_vec<double>), gr, kFinBlock, s, e0, e1, B, V64);
+        if (ns) hipLaunchKernelGGL(kb_share<true>, dim3(ns), dim3(64), 0, s, B);
     };
     // the last transition of a chunk
     auto settle = [&](hipStream_t s, int members) {
