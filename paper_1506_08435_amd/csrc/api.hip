@@ -301,13 +301,13 @@ static nn_status fill_copy(nn_ctx *ctx, nn_matrix *K, const float *src, float *d
     return NN_OK;
 }
 
-// (K's lock is held)
+// The copy of one precision, f64 or else float32 (K's lock is held).
 static nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64, bool &formed)
 {
     if (K->n == 0) return NN_OK;
     const size_t m = (size_t)std::max<int64_t>(K->nsell, 1);
     nn_status st = NN_OK;
-    if (K->val32 && !K->val32q) {
+    if (!f64 && K->val32 && !K->val32q) {
         if ((st = ensure_index(ctx, K, true)) != NN_OK) return st;
         if (K->d16q) {
             formed = true;

@@ -118,3 +118,24 @@ def test_calls_start_behind_the_callers_stream(what):
     assert np.array_equal(*out)
     K.free()
     c.close()
+
+
+def _entries(c, K):
+    """Stored sliced-ELL entries of a matrix: slices of 64 rows as wide as their
+    longest row."""
+    n = np.diff(c.matrix_export(K)[0])
+    return sum(64 * int(n[a:a + 64].max()) for a in range(0, K.n, 64))
+
+
+# a solve in float64 adds the float64 copy (10 bytes an entry) and no other
+@pytest.mark.parametrize("what", ["galerkin", "blmvm", "one", "tron"])
+def test_float64_solves_make_no_float32_copy(what):
+    from paper_1506_08435_amd import nnqp
+    c = nnqp.Context(0)
+    K, F, _ = c.assemble(W.cube3d(14 if what == "one" else 20))
+    c.solve_batch([K], [F], tol=1e-8, precision=nnqp.NN_MIXED)   # float32 values are there
+    before = K.bytes()
+    _call(nnqp, what, c, K, F)
+    assert K.bytes() - before == 10 * _entries(c, K)
+    K.free()
+    c.close()
