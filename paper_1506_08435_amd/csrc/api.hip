@@ -383,15 +383,42 @@ nn_status ensure_val32(nn_ctx *ctx, nn_matrix *K, const float **v32)
     return settle(ctx, K, st, formed);
 }
 
-// `needed`: a refused allocation fails the call; else (the copies that a solve
-// reads for speed only: Galerkin, BLMVM, one workgroup, and patterns without
-// int16 offsets) the solve runs from the sliced-ELL arrays.
-static nn_status ensure_copies(nn_ctx *ctx, nn_matrix *K, bool f64, bool needed, Copies *out)
+// COPY_NEEDED: a refused allocation fails the call.  COPY_WANTED (Galerkin, BLMVM,
+// and patterns without int16 offsets): the solve then runs from the sliced-ELL
+// arrays.  COPY_ONE_RUN (the one-workgroup engine): the same, and a copy only
+// where the diagonal layout has one regular run; no other is read.
+enum CopyUse { COPY_NEEDED, COPY_WANTED, COPY_ONE_RUN };
+
+// Looks for the diagonal layout of K; true if it has one regular run.
+static nn_status look_for_one_run(nn_ctx *ctx, nn_matrix *K, bool &one)
+{
+    one = false;
+    if (K->n == 0) return NN_OK;
+    short *idx = nullptr;
+    if (!K->diag_tried) {
+        if (dev_malloc(K->al, &idx, sizeof(short) * (size_t)std::max<int64_t>(K->nsell, 1)) != hipSuccess)
+            return fail(ctx, NN_EOOM, "index copy allocation");
+        const nn_status st = diag_find(ctx, K, idx);
+        if (st != NN_OK) {
+            dev_free(K->al, idx);
+            return st;
+        }
+    }
+    DiagReg reg;
+    one = diag_one_run(K, &reg);
+    if (one && !K->d16p) K->d16p = idx;   // (filled with the copy)
+    else dev_free(K->al, idx);
+    return NN_OK;
+}
+
+static nn_status ensure_copies(nn_ctx *ctx, nn_matrix *K, bool f64, CopyUse use, Copies *out)
 {
     std::lock_guard<std::mutex> lock(K->copies);
-    bool formed = false;
-    nn_status st = ensure_paired(ctx, K, f64, formed);
-    if (!needed) st = without_copy(ctx, st);
+    bool formed = false, form = true;
+    nn_status st = NN_OK;
+    if (use == COPY_ONE_RUN) st = look_for_one_run(ctx, K, form);
+    if (st == NN_OK && form) st = ensure_paired(ctx, K, f64, formed);
+    if (use != COPY_NEEDED) st = without_copy(ctx, st);
     st = settle(ctx, K, st, formed);
     *out = Copies{K->val32, K->val32q, K->val64p};
     return st;
@@ -825,12 +852,13 @@ nn_status nn_solve_nonneg(nn_ctx *ctx, nn_matrix *K, const double *f_dev,
     if (st != NN_OK) return st;
     Copies C;
     if (opts->method == NN_BLMVM) {
-        if ((st = ensure_copies(ctx, K, true, false, &C)) != NN_OK) return st;
+        if ((st = ensure_copies(ctx, K, true, COPY_WANTED, &C)) != NN_OK) return st;
         return blmvm_impl(ctx, K, K->val, C.v64p, f_dev, opts, c_dev, active_dev, stats);
     }
     if ((st = choose_solo(ctx, K, opts)) == NN_OK) {
         // (the copy is read up to kSoloMaxRows rows)
-        if (K->n <= kSoloMaxRows && (st = ensure_copies(ctx, K, true, false, &C)) != NN_OK) return st;
+        if (K->n <= kSoloMaxRows && (st = ensure_copies(ctx, K, true, COPY_ONE_RUN, &C)) != NN_OK)
+            return st;
         return solo_solve_impl(ctx, K, K->val, C.v64p, K->diag, f_dev, opts, c_dev, active_dev,
                                stats);
     }
@@ -839,7 +867,8 @@ nn_status nn_solve_nonneg(nn_ctx *ctx, nn_matrix *K, const double *f_dev,
     if (opts->precision == NN_MIXED && K->n > 0 && (st = ensure_val32(ctx, K, &v32)) != NN_OK) return st;
     // the copies the CG and search passes read
     const bool pair64 = NNQP_PAIR_F64 && v32 == nullptr;
-    if ((v32 || pair64) && (st = ensure_copies(ctx, K, pair64, K->sl_d16 != nullptr, &C)) != NN_OK)
+    if ((v32 || pair64) &&
+        (st = ensure_copies(ctx, K, pair64, K->sl_d16 ? COPY_NEEDED : COPY_WANTED, &C)) != NN_OK)
         return st;
     return solve_impl(ctx, K, K->val, v32, v32 ? C.v32q : nullptr, v32 ? nullptr : C.v64p, K->diag,
                       f_dev, opts, c_dev, active_dev, stats);
@@ -855,7 +884,7 @@ nn_status nn_solve_galerkin(nn_ctx *ctx, nn_matrix *K, const double *f_dev, cons
     if (opts->precision != NN_FP64)
         return fail(ctx, NN_EINVAL, "the Galerkin solve runs in float64 only");
     Copies C;
-    if ((st = ensure_copies(ctx, K, true, false, &C)) != NN_OK) return st;
+    if ((st = ensure_copies(ctx, K, true, COPY_WANTED, &C)) != NN_OK) return st;
     return galerkin_impl(ctx, K, C.v64p, f_dev, opts, c_dev, stats);
 }
 

@@ -139,3 +139,27 @@ def test_float64_solves_make_no_float32_copy(what):
     assert K.bytes() - before == 10 * _entries(c, K)
     K.free()
     c.close()
+
+
+def test_one_workgroup_engine_copies_what_it_reads():
+    """A small matrix without the diagonal layout (explicit zeros at random
+    columns) is solved from its sliced-ELL arrays and takes no further memory;
+    a multi-block solve adds the pairs, and the engine's result stays."""
+    from paper_1506_08435_amd import nnqp
+    from test_gpu_paths import _with_zeros
+    c = nnqp.Context(0)
+    K, F, _ = c.assemble(W.cube3d(12))
+    rp, col, val, _ = c.matrix_export(K)
+    rpz, colz, (valz,) = _with_zeros(rp, col, [val], 3, extra=3)
+    Z = c.matrix_from_csr(rpz, colz, valz)
+    before = Z.bytes()
+    a = c.solve_nonneg(Z, F, tol=1e-10, engine=2)[0].cpu().numpy().copy()
+    assert Z.bytes() == before
+    c.solve_nonneg(Z, F, tol=1e-10, engine=1)
+    assert Z.bytes() - before == 10 * _entries(c, Z)
+    b = c.solve_nonneg(Z, F, tol=1e-10, engine=2)[0].cpu().numpy().copy()
+    k = c.solve_nonneg(K, F, tol=1e-10, engine=2)[0].cpu().numpy().copy()
+    assert np.array_equal(a, b) and np.array_equal(a, k)
+    K.free()
+    Z.free()
+    c.close()
