@@ -164,7 +164,9 @@ typedef struct {
     double norm_f;        /* ||f||_2 */
     int32_t outer_its;
     int32_t cg_its;
-    int32_t spmvs;        /* sparse matrix-vector products of every kind */
+    int32_t spmvs;        /* sparse matrix-vector products of every kind (the Cauchy
+                             trials formed beside the gradient that ends a solve are
+                             left out) */
     int32_t n_active;     /* #{i : c_i == lower or c_i == upper} (#{c_i == 0} by default) */
     int32_t cauchy_trials;
     int32_t search_trials;

@@ -492,11 +492,14 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
         // ---- 4. projected search along w: first crossing, g.w, w.w, and,
         // where the last search needed one, the first trial (t = 1) in the
         // same launch, so that one wait covers both (a trial that turns out
-        // not to be needed costs one matrix pass and is not counted)
+        // not to be needed costs one matrix pass; its product is counted, the
+        // trial is not)
         auto trial_w = [&](double t, bool brk) {
             prof_begin(ctx, KC_TRIAL, spmv_s + 16.0 * n, spmv_csr + 16.0 * n);
             launch_trial(ctx, A, VS, c, dir_w, t, W.g, W.mask, nullptr, box, brk);
             prof_end(ctx);
+            S.spmvs++;
+            S.bytes_moved += spmv_s + 16.0 * n;
         };
         const Part Pn = make_part(n);
         const Publish p_brk(ctx->partials + (size_t)SLOT_Q * kMaxRed * kMaxBlocks, 3, Pn.nb, kBrkOps);
@@ -524,9 +527,7 @@ nn_status solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals, const 
             crossed = bmin < tmax;
             if (crossed) {
                 for (int k = 0; k < kMaxTrials; k++) {
-                    S.spmvs++;
                     S.search_trials++;
-                    S.bytes_moved += spmv_s + 16.0 * n;
                     // (without a trust region tmax = 1, the trial made above)
                     if (k > 0 || !early) {
                         trial_w(ts, false);
