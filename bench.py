@@ -534,7 +534,7 @@ def main():
                     help="TRON's subspace loop (1) or a Cauchy step every iteration (0, the "
                          "library default); the minimiser is the same")
     ap.add_argument("--cg-chunk", type=int, default=16,
-                    help="CG iterations enqueued ahead at most; steps of a batched chunk (0: no limit; 16)")
+                    help="CG iterations enqueued ahead (0, 16: as many as pay); steps of a batched chunk (0: 16)")
     ap.add_argument("--engine", type=int, choices=[0, 1, 2], default=0,
                     help="single-problem solves: 0 = by size (one workgroup up to 4,096 rows), "
                          "1 = multi-block passes, 2 = one workgroup")

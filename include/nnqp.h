@@ -108,11 +108,10 @@ typedef struct {
                              radius only ever grows (x4 when a step reaches it).
                              The batched entry points scale the CG step back into
                              the radius instead. */
-    int32_t cg_chunk;     /* CG iterations the host enqueues ahead of the last one that has
-                             begun on the device: k > 0 at most k (default 16), 0 no limit
-                             of the caller's; the library goes no further than pays (2).  In
-                             a batched solve, the steps of a chunk (0: 16).  Iterates do not
-                             depend on it. */
+    int32_t cg_chunk;     /* CG iterations the host keeps enqueued ahead of the last one that
+                             has begun on the device: 0 or 16 (the default) as many as pay
+                             (2), any other k > 0 that many.  In a batched solve, the steps
+                             of a chunk (0: 16).  Iterates do not depend on it. */
     int32_t verbose;      /* 1: one line per outer iteration on stderr; default 0 */
     double lower;         /* bounds lower <= c <= upper of the constrained solves
                              (Sec. 2.2.2, eq. Eq:non-negative: c_min 1 <= c <= c_max 1).

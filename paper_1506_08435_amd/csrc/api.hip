@@ -7,6 +7,7 @@
 #include <string>
 #include <thread>
 
+#include "ahead.hpp"
 #include "nnqp_internal.hpp"
 
 namespace nnqp {
@@ -631,7 +632,7 @@ nn_status nn_default_opts(nn_opts *o)
     o->c0_mode = 0;
     o->c0_value = 1e-8;
     o->delta0 = 0.0;
-    o->cg_chunk = 16;
+    o->cg_chunk = kCgChunkDefault;
     o->lower = 0.0;
     o->upper = INFINITY;
     o->method = NN_TRON;

@@ -43,6 +43,7 @@
 #include <cstdio>
 #include <cstring>
 
+#include "ahead.hpp"
 #include "nnqp_internal.hpp"
 
 namespace nnqp {
@@ -130,18 +131,11 @@ static nn_status read_grad_and_ladder(nn_ctx *ctx, int64_t n, double *grad, doub
 
 // Runs one CG solve behind its set-up: enqueue(j) launches iteration j.  The
 // device reports each iteration that begins, and the end; the host keeps
-// `ahead` iterations enqueued beyond the last one begun.  A launch after the
-// end returns at once, but costs 2 us, so it is two: the iteration that covers
-// the host's way to a launch and one behind it (250 k rows float64: 2, 3, 4, 6
-// ahead 12.1, 12.4, 12.7, 13.1 ms; 90 k rows with float32 values, whose
-// iterations take 8 us, 26.7 +- 0.3 ms at any of them).  With a synchronisation
-// each 16 iterations instead the two took 18.6 and 38.5 ms.
-constexpr int kAhead = 2;
-
+// cg_ahead iterations enqueued beyond the last one begun.
 template <class Enqueue>
 static nn_status run_cg(nn_ctx *ctx, const nn_opts *o, Enqueue enqueue)
 {
-    const int ahead = o->cg_chunk > 0 ? std::min(o->cg_chunk, kAhead) : kAhead;
+    const int ahead = cg_ahead(o->cg_chunk);
     const unsigned long long epoch = ctx->flow_cg;
     const HostFlow *F = ctx->flow;
     for (int j = 0;;) {

@@ -35,3 +35,16 @@ def test_every_search_pass_is_counted():
         K.free()
     assert surplus > 0
     c.close()
+
+
+def test_more_iterations_enqueued_ahead_than_a_solve_has():
+    """cg_chunk far beyond the iterations of any CG solve, and the launches past
+    its end: the same bits and counts."""
+    from paper_1506_08435_amd import nnqp
+    c = nnqp.Context(0)
+    K, F, _ = c.assemble(W.cube3d(19))
+    for kw in ({}, {"delta0": 1e-3}, {"precision": nnqp.NN_MIXED}, {"precond_degree": 3}):
+        a, b = (c.solve_nonneg(K, F, tol=1e-10, engine=1, cg_chunk=k, **kw) for k in (2, 300))
+        assert (a[0] == b[0]).all() and all(a[2][k] == b[2][k] for k in ("cg_its", "spmvs", "outer_its"))
+    K.free()
+    c.close()
