@@ -240,7 +240,7 @@ __device__ __forceinline__ void for_bslices(const BDev &B, const int (&ops)[NV],
 // every member's offsets fit int16, quads of float32 values or pairs of
 // float64 values; else int32 columns.  Float64 values load with the non-temporal
 // hint, float32 values normally (as in the single-problem kernels).
-enum { CM_I32 = 0, CM_D16 = 2, CM_Q4 = 3, CM_P2 = 4, CM_DIAG = 5 };
+enum { CM_I32, CM_Q4, CM_P2, CM_DIAG };
 
 // Position of entry k of lane l in a slice of width w of the quad layout
 // (CM_Q4), relative to the slice's first entry: entries 4j .. 4j+3 of a row
@@ -305,20 +305,14 @@ __device__ __forceinline__ float bld_val(const float *p) { return *p; }
 // Row sums of slice s of member p: sum_k val(k) x(col(k)), with the same
 // wave-uniform load phases (eight entries each) and column order as the
 // single-problem kernels.  Padding and rows past the end hold valid columns.
-template <int WMAX, int CM, class VT, class X>
+template <int WMAX, class VT, class X>
 __device__ __forceinline__ double bsell_row(const BDev &B, const VT *__restrict__ sv, int p, int s,
                                             X x)
 {
     const int lane = threadIdx.x & 63;
     const int ls = s - B.s0[p];
-    const int lrow = ls * kSlice + lane;
     const int *__restrict__ so = B.so[p];
     const int *__restrict__ sc = B.sc[p];
-    const short *__restrict__ sd = B.sd[p];
-    auto col = [&](int e) {
-        if (CM == CM_D16) return lrow + (int)sd[e];
-        return sc[e];
-    };
     const int off = so[ls];
     const int w = (so[ls + 1] - off) >> 6;
     double acc = 0.0;
@@ -330,7 +324,7 @@ __device__ __forceinline__ double bsell_row(const BDev &B, const VT *__restrict_
 #pragma unroll
         for (int k = 0; k < H; k++) {
             if (h0 + k < w) {
-                cc[k] = col(off + (h0 + k) * kSlice + lane);
+                cc[k] = sc[off + (h0 + k) * kSlice + lane];
                 vv[k] = bld_val(sv + off + (h0 + k) * kSlice + lane);
             } else {
                 cc[k] = 0;
@@ -343,7 +337,7 @@ __device__ __forceinline__ double bsell_row(const BDev &B, const VT *__restrict_
     }
     for (int k = WMAX; k < w; k++) {
         const int e = off + k * kSlice + lane;
-        acc += (double)bld_val(sv + e) * x(col(e));
+        acc += (double)bld_val(sv + e) * x(sc[e]);
     }
     return acc;
 }
@@ -467,7 +461,7 @@ __device__ __forceinline__ double gsell_row8(const BDev &B, const VT *__restrict
         acc = (w & 1) ? y8 : acc;
         return acc;
     } else {
-        // column-major entries 0-7 (int32 global columns or int16 offsets)
+        // column-major entries 0-7 (int32 global columns)
         const int *__restrict__ gc = B.gcol;
         VT v[8];
         int cc[8];
@@ -476,15 +470,15 @@ __device__ __forceinline__ double gsell_row8(const BDev &B, const VT *__restrict
             if (k < w) {
                 const int e = off + k * kSlice + lane;
                 v[k] = bld_val(sv + e);
-                cc[k] = CM == CM_D16 ? (int)gd[e] : gc[e];
+                cc[k] = gc[e];
             } else {
                 v[k] = VT(0);
-                cc[k] = CM == CM_D16 ? 0 : i;
+                cc[k] = i;
             }
         }
         double xv[8];
 #pragma unroll
-        for (int k = 0; k < 8; k++) xv[k] = x(CM == CM_D16 ? i + cc[k] : cc[k]);
+        for (int k = 0; k < 8; k++) xv[k] = x(cc[k]);
 #pragma unroll
         for (int k = 0; k < 8; k++) {
             const double y = __builtin_fma((double)v[k], xv[k], acc);
@@ -495,8 +489,7 @@ __device__ __forceinline__ double gsell_row8(const BDev &B, const VT *__restrict
 }
 
 // Row sums over the concatenated matrix for global row i = s*64 + lane of a
-// slice whose first entry (off) and width (w) are known; global columns
-// (int16 offsets from the row in CM_D16 mode).
+// slice whose first entry (off) and width (w) are known; global columns.
 template <int WMAX, int CM, class VT, class X>
 __device__ __forceinline__ double gsell_row_at(const BDev &B, const VT *__restrict__ sv, int i,
                                                int off, int w, X x)
@@ -506,7 +499,7 @@ __device__ __forceinline__ double gsell_row_at(const BDev &B, const VT *__restri
     const int *__restrict__ gc = B.gcol;
     const short *__restrict__ gd = B.gd16;
     auto col = [&](int e) {
-        if (CM == CM_D16 || CM == CM_Q4 || CM == CM_P2) return i + (int)gd[e];
+        if (CM == CM_Q4 || CM == CM_P2) return i + (int)gd[e];
         return gc[e];
     };
     double acc = 0.0;
@@ -810,7 +803,7 @@ __global__ void kb_transient_rhs(BDev B, double dt, double *__restrict__ ft)
                    [&](int p, int s, int i, int il, bool row, double (&)[1]) {
                        const double *c = B.c[p];
                        const double mc =
-                           bsell_row<WMAX, CM_I32>(B, B.mv[p], p, s, [&](int j) { return c[j]; });
+                           bsell_row<WMAX>(B, B.mv[p], p, s, [&](int j) { return c[j]; });
                        if (row) ft[i] = B.f0[p][il] + mc / dt;
                        else ft[i] = 0.0;
                    });

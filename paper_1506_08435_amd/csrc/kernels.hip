@@ -11,10 +11,10 @@
 //  - vector updates and dot products are fused into the passes that already
 //    touch the same rows;
 //  - reductions leave one partial per block and are never combined with
-//    atomics or fences: the host combines what it reads, and the CG scalars
-//    are combined by every block of the next kernel in the same fixed order,
-//    so results are bitwise reproducible and no cross-XCD synchronisation is
-//    needed inside a kernel.
+//    atomics: what the host reads is combined by a launch that publishes it
+//    (k_publish), and the CG scalars by every block of the next kernel, in the
+//    same fixed order, so results are bitwise reproducible and no cross-XCD
+//    synchronisation is needed inside a kernel.
 #include <cmath>
 
 #include "nnqp_internal.hpp"
@@ -193,7 +193,9 @@ struct Ladder {
 };
 
 #ifndef NNQP_LADDER_PHASE
-#define NNQP_LADDER_PHASE 4   // entries per load phase of the Cauchy ladder pass
+// entries per load phase of the Cauchy ladder pass (the diagonal layout's walk
+// takes five)
+#define NNQP_LADDER_PHASE 4
 #endif
 
 template <int WMAX, class VT, class Cols>

@@ -160,7 +160,7 @@ struct ProfEntry {
     int cls;
     hipEvent_t a, b;                 // markers recorded before and after the launch
     hipEvent_t ka = nullptr, kb = nullptr;   // or the kernel's own begin and end
-    int seq = -1;                    // CG launches: index within their chunk
+    int seq = -1;                    // CG launches: iteration of their CG solve
     double bytes;       // algorithmic bytes of the layout the kernel reads
     double bytes_csr;   // the same launch under the paper's CSR byte model
     int valid;
@@ -255,7 +255,7 @@ struct nn_ctx {
     bool prof_open = false;    // a begin event was recorded and awaits its end
     bool prof_attach = false;  // the next row-kernel launch takes the open entry's kernel events
     int prof_every = 1;        // time one CG-class launch in prof_every
-    int prof_seq = -1;         // chunk index the next CG-class entry is tagged with
+    int prof_seq = -1;         // iteration the next CG-class entry is tagged with
     int64_t prof_calls[NN_KCLASSES] = {0};   // CG-class launches seen (sampling)
     std::vector<nnqp::ProfEntry> prof_live;
     std::vector<hipEvent_t> ev_pool;
@@ -431,10 +431,10 @@ void launch_pair_f64(nn_ctx *ctx, const nn_matrix *A, const double *src, double 
 // quad copies (layout of nn_matrix::d16q)
 void launch_quad_f32(nn_ctx *ctx, const nn_matrix *A, const float *src, float *dst);
 void launch_quad_d16(nn_ctx *ctx, const nn_matrix *A, const short *src, short *dst);
-// Diagonal layout (diag.hip).  diag_find looks the pattern over once (scratch
-// holds at least 136 bytes per slice); diag_upload writes the tables into an
-// index copy, diag_fill a value array's diagonals; diag_symmetric tells
-// whether every entry read through the opposite triangle has its bits there.
+// Diagonal layout (diag.hip).  diag_find looks the pattern and the values over
+// once (scratch: the size of an index copy, two bytes per stored entry);
+// diag_upload writes the tables into an index copy, diag_fill a value array's
+// diagonals.
 nn_status diag_find(nn_ctx *ctx, nn_matrix *A, void *scratch);
 nn_status diag_upload(nn_ctx *ctx, const nn_matrix *A, void *index);
 nn_status diag_fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const double *src,

@@ -220,13 +220,6 @@ __device__ __forceinline__ void combine_loaded(double (&a)[NV])
         a[k] = lanes_in_order<kPartWaves>(op_of<OPS>(k), sh[k][lane & (kPartWaves - 1)]);
 }
 
-template <uint32_t OPS, int NV>
-__device__ __forceinline__ void combine_partials(const double *slot, int nb, double (&a)[NV])
-{
-    load_partials<OPS, NV>(slot, nb, a);
-    combine_loaded<OPS, NV>(a);
-}
-
 // ---------------------------------------------------------------- slice walkers
 // Calls body(i, act) for the row i = 64 s + lane of every slice s this
 // wavefront owns; act = i < n.  The loop trip count is uniform in a wavefront.
