@@ -47,9 +47,10 @@ CSRC = os.path.join(ROOT, "paper_1506_08435_amd", "csrc")
 # sources that decide what a kernel reads and writes: its code, the slice
 # walkers, the constants and the host code that chooses layouts and launches
 KERNEL_SOURCES = {
-    "single": ("kernels.hip", "rows.hpp", "diag.hpp", "diag.hip", "nnqp_internal.hpp", "solver.hip",
-               "api.hip"),
-    "batch": ("batch.hip", "rows.hpp", "diag.hpp", "diag.hip", "nnqp_internal.hpp", "api.hip"),
+    "single": ("kernels.hip", "rows.hpp", "diag.hpp", "diag.hip", "diag_plan.hpp", "ahead.hpp",
+               "nnqp_internal.hpp", "solver.hip", "api.hip"),
+    "batch": ("batch.hip", "rows.hpp", "diag.hpp", "diag.hip", "diag_plan.hpp", "nnqp_internal.hpp",
+              "api.hip"),
 }
 
 

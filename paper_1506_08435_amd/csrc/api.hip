@@ -70,9 +70,10 @@ nn_status ensure_workspace(nn_ctx *ctx, int64_t n)
 
 // One block per value combines its partials, in block order, and stores the
 // result where the host polls for it.  One lane adds them out of LDS, eight
-// reads ahead: 1 us for 245 blocks.  With the partials copied out instead the
-// host read up to 57 KB that had just arrived and added 14 dependent chains
-// (63^3 unknowns 11.5 -> 11.05 ms, 96 x 96 x 24 step 3.44 -> 3.22).
+// reads ahead, a chain of as many additions as there are blocks: the launch takes
+// 3.6 us for 24 blocks, 4.2 for 245 and 6.8 for 512.  With the partials copied out
+// instead the host read up to 57 KB that had just arrived and added 14 dependent
+// chains (63^3 unknowns 11.5 -> 11.05 ms, 96 x 96 x 24 step 3.44 -> 3.22).
 __global__ __launch_bounds__(256) void k_publish(Publish A, Publish B, HostFlow *F,
                                                  unsigned long long seq)
 {

@@ -26,9 +26,10 @@ namespace nnqp {
 // one slice per wavefront at most (up to 524,288 rows: solves of 63^3, 71^3 and
 // the holed cube of k = 9 12.0 -> 11.5, 21.4 -> 19.9, 26.1 -> 24.5 ms, 79^3 Galerkin
 // 12.2 -> 10.7), and float32 passes of any size (100^3, 127^3: 26.4 -> 23.9,
-// 79.8 -> 78.7 ms).  Larger float64 passes stream from HBM, and it costs them
-// more than the reuse gives (81^3, 89^3, 99^3, 127^3 rows: 32.7 -> 31.4,
-// 31.5 -> 32.7, 40.0 -> 38.9, 130.6 -> 138.9 ms).
+// 79.8 -> 78.7 ms).  Larger float64 passes stream from HBM, where it costs some
+// sizes more than the reuse gives others (81^3, 89^3, 99^3, 127^3 rows:
+// 32.7 -> 31.4, 31.5 -> 32.7, 40.0 -> 38.9, 130.6 -> 138.9 ms); no rule in the
+// size parts them, so they keep the order whose worst case is the smaller loss.
 Part make_part(int64_t n, int max_blocks, bool f32)
 {
     Part p;

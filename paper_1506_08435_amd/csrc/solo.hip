@@ -79,9 +79,12 @@ __host__ __device__ constexpr int solo_lds_rows(int nv) { return nv == 5 ? kSolo
 // alternating between calls (parity, the same in every thread since every
 // thread makes the same calls), and every wavefront combines them itself, so a
 // half is written again only two reductions later, after the next barrier.
-// One or two sums read the totals as broadcast vector loads; more would hold
-// 16 registers each, so they go lane by lane through scalar registers.
-template <uint32_t OPS, int NV>
+// Up to DIRECT values read the totals as broadcast vector loads; more go lane by
+// lane through scalar registers, as their totals would hold 16 registers each:
+// the engine with the matrix in registers has none left for them (64^2 square
+// 2.49 -> 1.93 ms), the other one has (5.98 -> 5.69).
+constexpr int kDirectFew = 2, kDirectAll = kMaxRed;
+template <uint32_t OPS, int DIRECT, int NV>
 __device__ __forceinline__ void wg_reduce(double (&a)[NV], double *sh, int &parity)
 {
     const int lane = threadIdx.x & 63, wid = wave_id();
@@ -94,7 +97,7 @@ __device__ __forceinline__ void wg_reduce(double (&a)[NV], double *sh, int &pari
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < NV; k++) {
-        if constexpr (NV <= 2) {
+        if constexpr (NV <= DIRECT) {
             double v = buf[k * kSoloWaves];
 #pragma unroll
             for (int w = 1; w < kSoloWaves; w++)
@@ -309,7 +312,7 @@ __device__ void solo_solve(const SoloProb &P, const SoloOpts &O, Box B, double *
                 C[i] = proj_box(cv, B);
             }
         }
-        wg_reduce<OPS4(OP_SUM, OP_MAX, OP_SUM, OP_SUM), 4>(a, shbuf, par);
+        wg_reduce<OPS4(OP_SUM, OP_MAX, OP_SUM, OP_SUM), kDirectAll>(a, shbuf, par);
         bytes += 16.0 * dn;
         S.norm_f = sqrt(a[0]);
         if (a[2] != 0.0 || a[3] != 0.0) {
@@ -342,7 +345,7 @@ __device__ void solo_solve(const SoloProb &P, const SoloOpts &O, Box B, double *
                 a5[3] = fmin(a5[3], cv);
                 a5[4] += (cv == B.lo || cv == B.hi) ? 1.0 : 0.0;
             });
-            wg_reduce<OPS5(OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM), 5>(a5, shbuf, par);
+            wg_reduce<OPS5(OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM), kDirectAll>(a5, shbuf, par);
             S.spmvs++;
             bytes += spmv_b + 16.0 * dn;
             if (a5[1] != 0.0) {
@@ -373,7 +376,7 @@ __device__ void solo_solve(const SoloProb &P, const SoloOpts &O, Box B, double *
                                   a3[0] += sg.b * sg.a;
                                   a3[1] += sg.a * s;
                               });
-                wg_reduce<OPS2(OP_SUM, OP_SUM), 2>(a3, shbuf, par);
+                wg_reduce<OPS2(OP_SUM, OP_SUM), kDirectAll>(a3, shbuf, par);
                 gs = a3[0];
                 sks = a3[1];
                 S.spmvs++;
@@ -440,7 +443,7 @@ __device__ void solo_solve(const SoloProb &P, const SoloOpts &O, Box B, double *
                             u[2] += fr ? 1.0 : 0.0;
                             u[3] += fr ? (double)v.len : 0.0;
                         });
-            wg_reduce<0u, 4>(u, shbuf, par);
+            wg_reduce<0u, kDirectAll>(u, shbuf, par);
             bytes += 88.0 * dn;
             double rz = u[0], rr = u[1], rz_prev = 0.0;
             const double nf = u[2], nzf = u[3], rr_stop = O.rtol2 * u[1];
@@ -466,7 +469,7 @@ __device__ void solo_solve(const SoloProb &P, const SoloOpts &O, Box B, double *
                                   Q[i] = qi;
                                   pq[0] += pi * qi;
                               });
-                wg_reduce<0u, 1>(pq, shbuf, par);
+                wg_reduce<0u, kDirectAll>(pq, shbuf, par);
                 if (!(pq[0] > 0.0 && isfinite(pq[0]))) {
                     status = isfinite(pq[0]) ? NN_ENOTSPD : NN_ENONFINITE;
                     cg_fail = true;
@@ -489,7 +492,7 @@ __device__ void solo_solve(const SoloProb &P, const SoloOpts &O, Box B, double *
                                 a2[0] += ri * zi;
                                 a2[1] += ri * ri;
                             });
-                wg_reduce<0u, 2>(a2, shbuf, par);
+                wg_reduce<0u, kDirectAll>(a2, shbuf, par);
                 rz_prev = rz;
                 rz = a2[0];
                 rr = a2[1];
@@ -511,7 +514,7 @@ __device__ void solo_solve(const SoloProb &P, const SoloOpts &O, Box B, double *
                 b3[1] += G[i] * wi;
                 b3[2] += wi * wi;
             });
-            wg_reduce<OPS3(OP_MIN, OP_SUM, OP_SUM), 3>(b3, shbuf, par);
+            wg_reduce<OPS3(OP_MIN, OP_SUM, OP_SUM), kDirectAll>(b3, shbuf, par);
             bytes += 24.0 * dn;
             const double bmin = b3[0], gw = b3[1], wn = sqrt(b3[2]);
             if (it > 0 && gw < 0.0 && wn > 0.0) {
@@ -528,7 +531,7 @@ __device__ void solo_solve(const SoloProb &P, const SoloOpts &O, Box B, double *
                                           a3[0] += sg.b * sg.a;
                                           a3[1] += sg.a * s;
                                       });
-                        wg_reduce<OPS2(OP_SUM, OP_SUM), 2>(a3, shbuf, par);
+                        wg_reduce<OPS2(OP_SUM, OP_SUM), kDirectAll>(a3, shbuf, par);
                         S.spmvs++;
                         S.search_trials++;
                         bytes += spmv_b + 16.0 * dn;
@@ -581,10 +584,13 @@ finish:
 // instructions per wavefront, two wavefronts per SIMD) and its LDS reads (63
 // slices x 7 x 512 B at 128 B per cycle, 1,770 cycles); passes outside the CG
 // also fetch their entries (224 KB).  Measured: 2.45 us per CG iteration and
-// 7 us per other pass on the 64^2 square, the solve 5.5-6.1 -> 1.9-2.0 ms
-// against the kernel above; 13^3 rows 1.48 -> 0.81 ms.  The entries are loaded
-// again at each CG: kept in registers for the whole solve they were spilled
-// inside the CG loop (7.8 us per iteration).
+// 7 us per other pass on the 64^2 square, the solve 5.7 -> 1.9 ms against the
+// kernel above; 13^3 rows 1.55 -> 0.86 ms.  The entries are loaded again at each
+// CG: kept in registers for the whole solve they were spilled inside the CG
+// loop (7.8 us per iteration).  The large variants still spill some of what
+// lives across the passes: 16 VGPRs of <7, 8, 7>, 42 of <15, 5, 15> and 127 of
+// <15, 8, 8> (none of <7, 2, 7>, <7, 4, 7> and <15, 2, 15>), and all of them
+// scalar registers (94 to 395) into lanes of vector registers.
 constexpr int kSoloPad = 512;                               // offsets reach at most this far
 constexpr int kSoloSpan = kSoloLdsRows + 2 * kSoloPad;      // a gathered vector in LDS
 
@@ -714,7 +720,7 @@ __device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpt
             C[t * T] = m ? cv : 0.0;
             __builtin_amdgcn_sched_barrier(0);
         }
-        wg_reduce<OPS4(OP_SUM, OP_MAX, OP_SUM, OP_SUM), 4>(a, shbuf, par);
+        wg_reduce<OPS4(OP_SUM, OP_MAX, OP_SUM, OP_SUM), kDirectFew>(a, shbuf, par);
         bytes += 16.0 * dn;
         normf = sqrt(a[0]);
         if (a[2] != 0.0 || a[3] != 0.0) {
@@ -762,7 +768,7 @@ __device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpt
                     a5[4] += m && (cv == B.lo || cv == B.hi) ? 1.0 : 0.0;
                 });
             }
-            wg_reduce<OPS5(OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM), 5>(a5, shbuf, par);
+            wg_reduce<OPS5(OP_SUM, OP_SUM, OP_MAX, OP_MIN, OP_SUM), kDirectFew>(a5, shbuf, par);
             spmvs++;
             bytes += spmv_b + 16.0 * dn;
             if (a5[1] != 0.0) {
@@ -797,7 +803,7 @@ __device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpt
                     a3[0] += G[t * T] * si;
                     a3[1] += si * s;
                 });
-                wg_reduce<OPS2(OP_SUM, OP_SUM), 2>(a3, shbuf, par);
+                wg_reduce<OPS2(OP_SUM, OP_SUM), kDirectFew>(a3, shbuf, par);
                 gs = a3[0];
                 sks = a3[1];
                 spmvs++;
@@ -869,7 +875,7 @@ __device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpt
                 if (__ballot(fr) != 0) live |= 1u << t2;
                 __builtin_amdgcn_sched_barrier(0);
             }
-            wg_reduce<0u, 4>(u, shbuf, par);
+            wg_reduce<0u, kDirectFew>(u, shbuf, par);
             bytes += 88.0 * dn;
             // the CG's entries in registers
             double v[NS][RK];
@@ -914,7 +920,7 @@ __device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpt
                     pq[0] += pi * qi;
                     __builtin_amdgcn_sched_barrier(0);   // one slice's gathers in registers at a time
                 }
-                wg_reduce<0u, 1>(pq, shbuf, par);
+                wg_reduce<0u, kDirectFew>(pq, shbuf, par);
                 if (!(pq[0] > 0.0 && isfinite(pq[0]))) {
                     status = isfinite(pq[0]) ? NN_ENOTSPD : NN_ENONFINITE;
                     cg_fail = true;
@@ -933,7 +939,7 @@ __device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpt
                     a2[0] += ri * zi;
                     a2[1] += ri * ri;
                 }
-                wg_reduce<0u, 2>(a2, shbuf, par);
+                wg_reduce<0u, kDirectFew>(a2, shbuf, par);
                 rz_prev = rz;
                 rz = a2[0];
                 rr = a2[1];
@@ -957,7 +963,7 @@ __device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpt
                 b3[1] += G[t2 * T] * wi;
                 b3[2] += wi * wi;
             }
-            wg_reduce<OPS3(OP_MIN, OP_SUM, OP_SUM), 3>(b3, shbuf, par);
+            wg_reduce<OPS3(OP_MIN, OP_SUM, OP_SUM), kDirectFew>(b3, shbuf, par);
             bytes += 24.0 * dn;
             const double bmin = b3[0], gw = b3[1], wn = sqrt(b3[2]);
             if (it > 0 && gw < 0.0 && wn > 0.0) {
@@ -979,7 +985,7 @@ __device__ __forceinline__ void solo_solve_diag(const SoloDiag &P, const SoloOpt
                             a3[0] += G[t2 * T] * sf;
                             a3[1] += sf * s;
                         });
-                        wg_reduce<OPS2(OP_SUM, OP_SUM), 2>(a3, shbuf, par);
+                        wg_reduce<OPS2(OP_SUM, OP_SUM), kDirectFew>(a3, shbuf, par);
                         spmvs++;
                         strl++;
                         bytes += spmv_b + 16.0 * dn;
@@ -1117,9 +1123,14 @@ nn_status solo_solve_impl(nn_ctx *ctx, const nn_matrix *A, const double *vals,
                                O, box);                                                          \
     } while (0)
     // The matrix in registers: one regular run over all slices, offsets inside
-    // the LDS padding, at most eight slices per wavefront.  Above five slices
-    // a thread's 15-point rows leave no room for their first seven entries.
-    // 63^2 and 13^3 rows: 2.01 and 0.81 ms, k_solo 6.11 and 1.48.
+    // the LDS padding, at most eight slices per wavefront.  63^2 and 13^3 rows:
+    // 1.93 and 0.86 ms, k_solo 5.69 and 1.55.
+    // NS, the slices a thread has room for, is the smallest that fits, as every
+    // pass works through all of them: 16 slices in all 0.58 ms at NS = 2, 0.78 at
+    // 4, 1.31 at 8 (15-point rows: 0.39 at 2, 0.80 at 5, 1.19 at 8), 32 slices
+    // 0.92 at 4, 1.50 at 8 (15-point, 35 slices: 0.86 at 5, 1.34 at 8).  Above
+    // five slices a thread's 15-point rows leave no room for their first seven
+    // entries.
     DiagReg reg{};
     const bool one_run = vals64p && n <= kSoloLdsRows && diag_one_run(A, &reg) &&
                          reg.h[A->wmax <= 8 ? 2 : 6] <= kSoloPad;

@@ -191,8 +191,9 @@ class Context:
         self.torch = torch
         self.device = torch.device("cuda", device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._raw_stream = self.stream.cuda_stream
         h = ctypes.c_void_p()
-        sp = ctypes.c_void_p(self.stream.cuda_stream)
+        sp = ctypes.c_void_p(self._raw_stream)
         self._hooks = None
         if allocator is None:
             st = self.lib.nn_create(ctypes.byref(h), device, sp)
@@ -305,9 +306,9 @@ class Context:
         """The caller's tensors (and those made here) live on torch's current
         stream: a context on another stream starts behind the work queued there.
         Returns the current stream when it is another one."""
-        cur = self.torch.cuda.current_stream(self.device)
-        if cur.cuda_stream == self.stream.cuda_stream:
+        if self.torch._C._cuda_getCurrentRawStream(self.device.index) == self._raw_stream:
             return None
+        cur = self.torch.cuda.current_stream(self.device)
         self.stream.wait_stream(cur)
         return cur
 
