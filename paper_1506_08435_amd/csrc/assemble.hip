@@ -8,10 +8,10 @@
 // row lengths and slice widths (scans), and a row-gather numeric phase.  The host waits twice before
 // it, for the flags of the validation with the number of free nodes and for
 // the sizes of the matrix.  A mesh with a row of more than kRowMax columns
-// or kIncMax elements takes the host's symbolic phase and k_assemble instead
-// (behind the device's, which finds that row: a square of 500^2 cells beside a hub
-// of 200 triangles 16.0 ms, 1,000^2 38.3; with the host's alone 16.7 and 47.0, the
-// layout pass behind it then being the host's too).
+// or kIncMax elements takes the host's symbolic phase and k_assemble instead,
+// behind the device's, which finds that row (a square of 500^2 cells beside a hub
+// of 200 triangles 16.0 ms, one of 1,000^2 38.3; 16.7 and 47.0 before there was a
+// device phase to run first).
 //
 // Numeric phase: one thread owns one free row i and walks the elements
 // incident to its node in increasing element order; for each it forms the P1
