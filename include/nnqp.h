@@ -274,6 +274,11 @@ nn_status nn_matrix_export(nn_ctx *ctx, const nn_matrix *A, int64_t *rowptr, int
 nn_status nn_matrix_bytes(const nn_matrix *A, int precision, size_t *bytes);
 void nn_matrix_free(nn_ctx *ctx, nn_matrix *A);
 
+/* A matrix may be solved with by several contexts at the same time, each on its
+ * own thread and stream of the matrix's device: what solves add to it is formed
+ * once, under a lock, and other streams wait for it (transient steps: all with
+ * the same dt).  A context belongs to one thread at a time. */
+
 /* y = A x on the stream (device vectors of length n); which = 0: K, 1: M. */
 nn_status nn_matvec(nn_ctx *ctx, const nn_matrix *A, int which, const double *x_dev,
                     double *y_dev);
