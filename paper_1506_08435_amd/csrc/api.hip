@@ -341,22 +341,31 @@ static nn_status ensure_paired(nn_ctx *ctx, nn_matrix *K, bool f64, bool &formed
     return NN_OK;
 }
 
-// The end of a call's work on K's copies (its lock is held): contexts on other
-// streams wait for what it enqueued, and it for what they did.
-static nn_status settle(nn_ctx *ctx, nn_matrix *K, nn_status st, bool formed)
+// What other contexts enqueued for K's copies on their streams comes before what
+// this one does with them (K's lock is held).
+static nn_status behind_others(nn_ctx *ctx, nn_matrix *K)
+{
+    if (!K->pending || K->form_stream == ctx->stream) return NN_OK;
+    hipError_t e = hipEventQuery(K->form_done);
+    if (e == hipSuccess) {
+        K->pending = false;
+        return NN_OK;
+    }
+    if (e == hipErrorNotReady) {
+        (void)hipGetLastError();
+        e = hipStreamWaitEvent(ctx->stream, K->form_done, 0);
+    }
+    return e == hipSuccess ? NN_OK : fail(ctx, NN_EHIP, hipGetErrorString(e));
+}
+
+// This context has enqueued work that forms copies of K: others wait for it.
+static nn_status formed_here(nn_ctx *ctx, nn_matrix *K, nn_status st)
 {
     hipError_t e = hipSuccess;
-    if (K->pending && K->form_stream != ctx->stream) {
-        e = hipEventQuery(K->form_done);
-        if (e == hipSuccess) K->pending = false;
-        else if (e == hipErrorNotReady) (void)hipGetLastError(), e = hipStreamWaitEvent(ctx->stream, K->form_done, 0);
-    }
-    if (formed && e == hipSuccess) {
-        if (!K->form_done) e = hipEventCreateWithFlags(&K->form_done, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventRecord(K->form_done, ctx->stream);
-        K->form_stream = ctx->stream;
-        K->pending = e == hipSuccess;
-    }
+    if (!K->form_done) e = hipEventCreateWithFlags(&K->form_done, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(K->form_done, ctx->stream);
+    K->form_stream = ctx->stream;
+    K->pending = e == hipSuccess;
     if (st == NN_OK && e != hipSuccess) return fail(ctx, NN_EHIP, hipGetErrorString(e));
     return st;
 }
@@ -365,24 +374,23 @@ nn_status present_copies(nn_ctx *ctx, nn_matrix *K, Copies *out)
 {
     std::lock_guard<std::mutex> lock(K->copies);
     *out = Copies{K->val32, K->val32q, K->val64p};
-    return settle(ctx, K, NN_OK, false);
+    return behind_others(ctx, K);
 }
 
 nn_status ensure_val32(nn_ctx *ctx, nn_matrix *K, const float **v32)
 {
     std::lock_guard<std::mutex> lock(K->copies);
-    bool formed = false;
-    nn_status st = NN_OK;
-    if (K->n > 0 && !K->val32) {
+    nn_status st = behind_others(ctx, K);
+    if (st == NN_OK && K->n > 0 && !K->val32) {
         if (dev_malloc(K->al, &K->val32, sizeof(float) * std::max<int64_t>(K->nsell, 1)) != hipSuccess)
             return fail(ctx, NN_EOOM, "float32 value allocation");
         launch_to_f32(ctx, K->nsell, K->val, K->val32);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) st = fail(ctx, NN_EHIP, hipGetErrorString(e));
-        formed = true;
+        st = formed_here(ctx, K, st);
     }
     *v32 = K->val32;
-    return settle(ctx, K, st, formed);
+    return st;
 }
 
 // COPY_NEEDED: a refused allocation fails the call.  COPY_WANTED (Galerkin, BLMVM,
@@ -417,11 +425,11 @@ static nn_status ensure_copies(nn_ctx *ctx, nn_matrix *K, bool f64, CopyUse use,
 {
     std::lock_guard<std::mutex> lock(K->copies);
     bool formed = false, form = true;
-    nn_status st = NN_OK;
-    if (use == COPY_ONE_RUN) st = look_for_one_run(ctx, K, form);
+    nn_status st = behind_others(ctx, K);
+    if (st == NN_OK && use == COPY_ONE_RUN) st = look_for_one_run(ctx, K, form);
     if (st == NN_OK && form) st = ensure_paired(ctx, K, f64, formed);
     if (use != COPY_NEEDED) st = without_copy(ctx, st);
-    st = settle(ctx, K, st, formed);
+    if (formed) st = formed_here(ctx, K, st);
     *out = Copies{K->val32, K->val32q, K->val64p};
     return st;
 }
@@ -448,12 +456,13 @@ static nn_status form_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed
     want32q = want32q && K->d16q;
     want64p = want64p && K->d16p;
     const bool fresh = K->kt && K->kt_dt == dt;
-    if (fresh && (!mixed || K->kt32) && (!want32q || K->kt32q) && (!want64p || K->kt64p))
+    if (fresh && (!mixed || K->kt32_dt == dt) && (!want32q || K->kt32q_dt == dt) &&
+        (!want64p || K->kt64p_dt == dt))
         return NN_OK;
     formed = true;
     // each buffer is guarded on its own: a call that got one of them and was
     // refused the other leaves the first in place, and a later call takes
-    // only the missing one (the values are formed below whenever kt_dt != dt)
+    // only the missing one
     if (!K->kt && dev_malloc(K->al, &K->kt, sizeof(double) * m) != hipSuccess)
         return fail(ctx, NN_EOOM, "transient matrix allocation");
     if (!K->kt_diag && dev_malloc(K->al, &K->kt_diag, sizeof(double) * n) != hipSuccess)
@@ -466,13 +475,32 @@ static nn_status form_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed
         st = fail(ctx, NN_EOOM, "transient float64 copy allocation");
     if (!K->sl_d16) st = without_copy(ctx, st);
     if (st != NN_OK) return st;
-    launch_axpby_vals(ctx, K->nsell, K->mval, dt, K->val, K->kt);
-    launch_diag(ctx, K, K->kt, K->kt_diag);
-    if (K->kt32) launch_to_f32(ctx, K->nsell, K->kt, K->kt32);
-    if (K->kt32 && K->kt32q && (st = fill_copy(ctx, K, K->kt32, K->kt32q)) != NN_OK) return st;
-    if (K->kt64p && (st = fill_copy(ctx, K, K->kt, K->kt64p)) != NN_OK) return st;
+    // Only what does not hold this dt's values is formed (the marks are set when
+    // it is enqueued): another context may be reading the rest.
+    if (!fresh) {
+        K->kt_dt = 0.0;
+        launch_axpby_vals(ctx, K->nsell, K->mval, dt, K->val, K->kt);
+        launch_diag(ctx, K, K->kt, K->kt_diag);
+        NN_HIP_TRY(ctx, hipGetLastError());
+        K->kt_dt = dt;
+    }
+    if (K->kt32 && K->kt32_dt != dt) {
+        K->kt32_dt = 0.0;
+        launch_to_f32(ctx, K->nsell, K->kt, K->kt32);
+        NN_HIP_TRY(ctx, hipGetLastError());
+        K->kt32_dt = dt;
+    }
+    if (K->kt32 && K->kt32q && K->kt32q_dt != dt) {
+        K->kt32q_dt = 0.0;
+        if ((st = fill_copy(ctx, K, K->kt32, K->kt32q)) != NN_OK) return st;
+        K->kt32q_dt = dt;
+    }
+    if (K->kt64p && K->kt64p_dt != dt) {
+        K->kt64p_dt = 0.0;
+        if ((st = fill_copy(ctx, K, K->kt, K->kt64p)) != NN_OK) return st;
+        K->kt64p_dt = dt;
+    }
     NN_HIP_TRY(ctx, hipGetLastError());
-    K->kt_dt = dt;
     return NN_OK;
 }
 
@@ -481,7 +509,9 @@ nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, boo
 {
     std::lock_guard<std::mutex> lock(K->copies);
     bool formed = false;
-    const nn_status st = settle(ctx, K, form_transient(ctx, K, dt, mixed, paired, formed), formed);
+    nn_status st = behind_others(ctx, K);
+    if (st == NN_OK) st = form_transient(ctx, K, dt, mixed, paired, formed);
+    if (formed) st = formed_here(ctx, K, st);
     *out = Copies{K->kt32, K->kt32q, K->kt64p};
     return st;
 }

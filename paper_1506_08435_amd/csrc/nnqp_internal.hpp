@@ -229,7 +229,7 @@ struct nn_matrix {
     double *diag = nullptr;    // diag(K)
     double *kt = nullptr;      // M/dt + K values (transient), lazily formed
     double *kt_diag = nullptr;
-    double kt_dt = 0.0;
+    double kt_dt = 0.0, kt32_dt = 0.0, kt32q_dt = 0.0, kt64p_dt = 0.0;   // dt each was formed for
     float *val32 = nullptr;    // float32 K values (mixed precision), lazily formed
     float *kt32 = nullptr;     // float32 M/dt + K values, formed with kt
     int wmax = 0;              // widest slice

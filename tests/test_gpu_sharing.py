@@ -163,3 +163,79 @@ def test_one_workgroup_engine_copies_what_it_reads():
     K.free()
     Z.free()
     c.close()
+
+
+def test_float64_and_mixed_steps_of_one_matrix_at_the_same_time():
+    """Steps at the same dt in both precisions: whichever precision comes second
+    forms only what is missing while the first is reading."""
+    import torch
+    from paper_1506_08435_amd import nnqp
+    p = W.cube3d(24)
+    precs = [nnqp.NN_FP64, nnqp.NN_MIXED, nnqp.NN_FP64, nnqp.NN_MIXED]
+    home = nnqp.Context(0)
+    streams = [torch.cuda.Stream(0) for _ in precs]
+    ctxs = [nnqp.Context(0, stream=s) for s in streams]
+
+    def steps(c, K, F, prec, n):
+        u = torch.zeros(K.n, dtype=torch.float64, device=c.device)
+        for _ in range(n):
+            c.step_transient(K, 1e-3, F, u, tol=1e-9, precision=prec)
+        return u.cpu().numpy().copy()
+
+    K, F, _ = home.assemble(p, with_mass=True)
+    alone = {prec: steps(home, K, F, prec, 6) for prec in set(precs)}
+    K.free()
+    for _ in range(3):
+        K, F, _ = home.assemble(p, with_mass=True)
+        torch.cuda.synchronize()
+        gate, got, errors = threading.Barrier(len(precs)), {}, []
+
+        def work(i):
+            try:
+                with torch.cuda.stream(streams[i]):
+                    gate.wait()
+                    got[i] = steps(ctxs[i], K, F, precs[i], 6)
+            except Exception as e:   # noqa: BLE001 (reported by the main thread)
+                errors.append(e)
+
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(len(precs))]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not errors, errors
+        assert all(np.array_equal(got[i], alone[precs[i]]) for i in range(len(precs)))
+        K.free()
+    for c in ctxs:
+        c.close()
+    home.close()
+
+
+def test_transient_copies_of_several_time_steps():
+    """Single, mixed and batched steps that change dt between them: every copy is
+    formed anew for the dt it is read at (the bits of a fresh matrix)."""
+    import torch
+    from paper_1506_08435_amd import nnqp
+    c = nnqp.Context(0)
+    p = W.cube3d(12)
+    K, F, _ = c.assemble(p, with_mass=True)
+    plan = [("fp64", 1e-3), ("mixed", 1e-3), ("fp64", 2e-3), ("mixed", 1e-3), ("batch", 4e-3), ("fp64", 4e-3),
+            ("mixed", 4e-3), ("batch_mixed", 1e-3), ("blmvm", 1e-3), ("mixed", 2e-3), ("fp64", 2e-3)]
+
+    def step(A, what, dt):
+        u = torch.zeros(A.n, dtype=torch.float64, device=c.device)
+        kw = dict(tol=1e-8, precision=nnqp.NN_MIXED if "mixed" in what else nnqp.NN_FP64, engine=1)
+        if what == "blmvm":
+            kw.update(method=nnqp.NN_BLMVM)
+        if "batch" in what:
+            c.step_transient_batch([A], dt, [F], [u], **kw)
+        else:
+            c.step_transient(A, dt, F, u, **kw)
+        return u.cpu().numpy().copy()
+
+    for what, dt in plan:
+        fresh, _, _ = c.assemble(p, with_mass=True)
+        assert np.array_equal(step(K, what, dt), step(fresh, what, dt)), (what, dt)
+        fresh.free()
+    K.free()
+    c.close()
