@@ -372,21 +372,25 @@ static nn_status formed_here(nn_ctx *ctx, nn_matrix *K, nn_status st)
 
 nn_status present_copies(nn_ctx *ctx, nn_matrix *K, Copies *out)
 {
-    std::lock_guard<std::mutex> lock(K->copies);
+    std::lock_guard<std::recursive_mutex> lock(K->copies);
     *out = Copies{K->val32, K->val32q, K->val64p};
     return behind_others(ctx, K);
 }
 
 nn_status ensure_val32(nn_ctx *ctx, nn_matrix *K, const float **v32)
 {
-    std::lock_guard<std::mutex> lock(K->copies);
+    std::lock_guard<std::recursive_mutex> lock(K->copies);
     nn_status st = behind_others(ctx, K);
     if (st == NN_OK && K->n > 0 && !K->val32) {
         if (dev_malloc(K->al, &K->val32, sizeof(float) * std::max<int64_t>(K->nsell, 1)) != hipSuccess)
             return fail(ctx, NN_EOOM, "float32 value allocation");
         launch_to_f32(ctx, K->nsell, K->val, K->val32);
         const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) st = fail(ctx, NN_EHIP, hipGetErrorString(e));
+        if (e != hipSuccess) {
+            dev_free(K->al, K->val32);
+            K->val32 = nullptr;
+            return fail(ctx, NN_EHIP, hipGetErrorString(e));
+        }
         st = formed_here(ctx, K, st);
     }
     *v32 = K->val32;
@@ -423,7 +427,7 @@ static nn_status look_for_one_run(nn_ctx *ctx, nn_matrix *K, bool &one)
 
 static nn_status ensure_copies(nn_ctx *ctx, nn_matrix *K, bool f64, CopyUse use, Copies *out)
 {
-    std::lock_guard<std::mutex> lock(K->copies);
+    std::lock_guard<std::recursive_mutex> lock(K->copies);
     bool formed = false, form = true;
     nn_status st = behind_others(ctx, K);
     if (st == NN_OK && use == COPY_ONE_RUN) st = look_for_one_run(ctx, K, form);
@@ -507,7 +511,7 @@ static nn_status form_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed
 nn_status ensure_transient(nn_ctx *ctx, nn_matrix *K, double dt, bool mixed, bool paired,
                            Copies *out)
 {
-    std::lock_guard<std::mutex> lock(K->copies);
+    std::lock_guard<std::recursive_mutex> lock(K->copies);
     bool formed = false;
     nn_status st = behind_others(ctx, K);
     if (st == NN_OK) st = form_transient(ctx, K, dt, mixed, paired, formed);
@@ -806,7 +810,7 @@ nn_status nn_matrix_export(nn_ctx *ctx, const nn_matrix *A, int64_t *rowptr, int
 nn_status nn_matrix_bytes(const nn_matrix *A, int precision, size_t *bytes)
 {
     if (!A || !bytes) return NN_EINVAL;
-    std::lock_guard<std::mutex> lock(A->copies);
+    std::lock_guard<std::recursive_mutex> lock(A->copies);
     const double n = (double)A->n, nnz = (double)A->nnz, ns = (double)A->nsell;
     double b = 4.0 * (n + 1) + 4.0 * nnz;                   // CSR pattern
     b += 4.0 * (A->nslices + 1) + 12.0 * ns + 8.0 * n;      // sliced-ELL columns, values, diag

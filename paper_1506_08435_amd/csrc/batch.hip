@@ -1681,7 +1681,7 @@ nn_status solve_batch_impl(nn_ctx *ctx, int P, nn_matrix *const *K, const double
             if (K[p]->n > 0) all.push_back(K[p]);
         std::sort(all.begin(), all.end());
         all.erase(std::unique(all.begin(), all.end()), all.end());
-        std::vector<std::unique_lock<std::mutex>> locks;
+        std::vector<std::unique_lock<std::recursive_mutex>> locks;
         locks.reserve(all.size());
         for (nn_matrix *A : all) {
             locks.emplace_back(A->copies);

@@ -199,8 +199,9 @@ struct nn_matrix {
     // A matrix may be read by several contexts, each on its thread and stream.
     // What solves add to it below (copies, the diagonal layout, the transient
     // values) is formed under this lock, and a context on another stream waits
-    // for the event of what was formed last.
-    mutable std::mutex copies;
+    // for the event of what was formed last.  (The caller's memory hooks run under
+    // it and may ask for the matrix's size.)
+    mutable std::recursive_mutex copies;
     hipEvent_t form_done = nullptr;
     hipStream_t form_stream = nullptr;
     bool pending = false;      // form_done has not been seen to have passed

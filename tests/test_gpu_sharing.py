@@ -239,3 +239,27 @@ def test_transient_copies_of_several_time_steps():
         fresh.free()
     K.free()
     c.close()
+
+
+def test_memory_hooks_may_ask_for_the_matrix_size():
+    """The hooks run while the library forms a copy: a hook that looks at the
+    matrix's reported bytes (to account for them) gets an answer."""
+    import torch
+    from paper_1506_08435_amd import nnqp
+    at, seen = [None], []
+
+    def alloc(nbytes):
+        if at[0] is not None:
+            seen.append(at[0].bytes())
+        return torch.cuda.caching_allocator_alloc(nbytes, 0, torch.cuda.current_stream(0))
+
+    c = nnqp.Context(0, allocator=(alloc, torch.cuda.caching_allocator_delete))
+    K, F, _ = c.assemble(W.cube3d(18))
+    at[0] = K
+    c.solve_nonneg(K, F, tol=1e-8)
+    c.solve_batch([K], [F], tol=1e-8, precision=nnqp.NN_MIXED)
+    c.solve_nonneg(K, F, tol=1e-8, precision=nnqp.NN_MIXED)
+    at[0] = None
+    assert seen and seen[-1] > seen[0]
+    K.free()
+    c.close()
